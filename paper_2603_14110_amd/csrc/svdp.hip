@@ -480,214 +480,7 @@ void *static_scratch()
     return p;
 }
 
-// ---- offline build with whitening (Alg. 1): fp64 work buffers and the Jacobi driver ----
-struct WhitenWs {
-    double *W64, *M, *Mt;       // [D][d], [D][d], [d][D]
-    double *Xt;                 // [d][T]
-    double *A0, *A1;            // [d][d] symmetric matrix, ping-pong
-    double *V0, *V1;            // [d][d] eigenvectors as rows, ping-pong
-    double *St;                 // [d][d]  S^T, S = the lower Cholesky factor of X^T X
-    double *S;                  // [d][d]  S
-    double *lamG;               // [d] eigenvalues by place
-    double *invL, *invLt;       // [64][64] scratch; [d/64][64][64] transposed inverses of S's diagonal blocks
-    int32_t *fail;              // set by the factorisation if X^T X is not positive definite
-    double *Vr;                 // [r][d]
-    double *out64;              // [max(D, d)][r]
-    double *Uall, *rowsums, *sums;     // [d/64][64][64] strip transforms; norms
-    int32_t *sel;               // [r]
-    size_t bytes;
-};
-
-WhitenWs carve_whiten(void *base, int d, int D, int T, int r)
-{
-    WhitenWs w;
-    char *p = static_cast<char *>(base);
-    size_t off = 0;
-    auto take = [&](size_t n_doubles) {
-        double *q = reinterpret_cast<double *>(p + off);
-        off += align_up(n_doubles * 8);
-        return q;
-    };
-    const size_t dd = (size_t)d * d, Dd = (size_t)D * d;
-    w.W64 = take(Dd);
-    w.M = take(Dd);
-    w.Mt = take(Dd);
-    w.Xt = take((size_t)d * T);
-    w.A0 = take(dd);
-    w.A1 = take(dd);
-    w.V0 = take(dd);
-    w.V1 = take(dd);
-    w.St = take(dd);
-    w.S = take(dd);
-    w.lamG = take(d);
-    w.invL = take(64 * 64);
-    w.invLt = take((size_t)d * 64);
-    w.fail = reinterpret_cast<int32_t *>(take(32));
-    w.Vr = take((size_t)r * d);
-    w.out64 = take((size_t)(D > d ? D : d) * r);
-    w.Uall = take((size_t)d * 64);
-    w.rowsums = take((size_t)2 * d);
-    w.sums = take(2);
-    w.sel = reinterpret_cast<int32_t *>(p + off);
-    off += align_up((size_t)r * 4);
-    w.bytes = off;
-    return w;
-}
-
-inline dim3 grid1(size_t n) { return dim3((unsigned)((n + 255) / 256)); }
-
-// C = A B^T, or with Cin: C = Cin - A B^T (C and Cin different memory)
-void dgemm_nt(const double *A, int lda, const double *Bm, int ldb, double *C, int ldc, int M, int N, int K, hipStream_t st,
-              const double *Cin = nullptr, int ldcin = 0)
-{
-    if (M <= 0 || N <= 0) return;
-    hipLaunchKernelGGL(k_dgemm_nt, dim3((N + DG_BN - 1) / DG_BN, (M + DG_BM - 1) / DG_BM), dim3(256), 0, st, A, lda, Bm, ldb,
-                       C, ldc, M, N, K, Cin, ldcin);
-}
-
-// L (lower, [n][n], zero above the diagonal) with L L^T = C; T: scratch [n][n]; invLt: [n/64][64][64], the
-// transposed inverses of L's diagonal blocks; invL: scratch [64][64]; scale: device double; fail: device int,
-// set to 1 if C is not positive definite to working precision (then L is not to be used).
-void cholesky_blocked(const double *C, double *L, double *T, int n, double *invL, double *invLt, double *scale, int *fail,
-                      hipStream_t st)
-{
-    const int nb = n / CH_B;
-    hipLaunchKernelGGL(k_max_diag, dim3(1), dim3(256), 0, st, C, n, scale);
-    for (int k = 0; k < nb; ++k) {
-        const size_t row0 = (size_t)k * CH_B * n, diag = row0 + (size_t)k * CH_B;
-        // T[k:, k] = C[k:, k] - L[k:, :k] L[k, :k]^T   (K = 0 for the first block column: a copy)
-        dgemm_nt(L + row0, n, L + row0, n, T + diag, n, n - k * CH_B, CH_B, k * CH_B, st, C + diag, n);
-        hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, T, L, n, diag, scale, 1e-13, invL,
-                           invLt + (size_t)k * CH_B * CH_B, fail);
-        // L[k+1:, k] = T[k+1:, k] Lkk^-T
-        dgemm_nt(T + diag + (size_t)CH_B * n, n, invL, CH_B, L + diag + (size_t)CH_B * n, n, n - (k + 1) * CH_B, CH_B, CH_B,
-                 st);
-    }
-    hipLaunchKernelGGL(k_zero_upper_blocks, grid1((size_t)n * n), dim3(256), 0, st, L, n);
-}
-
-// Bout [r][n] = Bin [r][n] L^-1 for the lower-triangular L given as Lt = L^T [n][n] and the transposed inverses of
-// its diagonal blocks: block back-substitution from the last block column to the first.  tmp: scratch [r][64].
-void solve_right_lower(const double *Bin, double *Bout, int r, int n, const double *Lt, const double *invLt, double *tmp,
-                       hipStream_t st)
-{
-    const int nb = n / CH_B;
-    for (int i = nb - 1; i >= 0; --i) {
-        const int c0 = i * CH_B, rest = n - (i + 1) * CH_B;
-        // tmp = Bin[:, i] - Bout[:, i+1:] L[i+1:, i]      (L[k][c0 + a] = Lt[c0 + a][k])
-        dgemm_nt(Bout + c0 + CH_B, n, Lt + (size_t)c0 * n + c0 + CH_B, n, tmp, CH_B, r, CH_B, rest, st, Bin + c0, n);
-        // Bout[:, i] = tmp Lii^-1
-        dgemm_nt(tmp, CH_B, invLt + (size_t)i * CH_B * CH_B, CH_B, Bout + c0, n, r, CH_B, CH_B, st);
-    }
-}
-
-// Eigen-decomposition of the symmetric matrix in *A (n x n, n % 64 == 0) by block Jacobi sweeps.  On return
-// *A / *V point at the buffers holding the (numerically) diagonal matrix and the eigenvectors as rows, lam[i]
-// (device) = (*A)[i][i].  Uall: n/64 matrices of 64 x 64.  Synchronises the stream once per sweep (the
-// convergence figure is read on the host).
-svdp_status jacobi_eigh(double **A, double **Aalt, double **V, double **Valt, int n, double *Uall, double *rowsums,
-                        double *sums, double *lam, double tol, int max_sweeps, int *sweeps_out, hipStream_t st)
-{
-    const size_t lds_solve = (size_t)2 * BJ_S * BJ_LD * 8, lds_two = (size_t)2 * BJ_S * BJ_LD * 8,
-                 lds_one = lds_two;
-    if (!grant_lds<k_bjacobi_solve>(lds_solve) || !grant_lds<k_bjacobi_apply<true>>(lds_two) ||
-        !grant_lds<k_bjacobi_apply<false>>(lds_one))
-        return SVDP_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(k_identity, grid1((size_t)n * n), dim3(256), 0, st, *V, n);
-    const int strips = n / BJ_S, rounds = n / BJ_B > 2 ? n / BJ_B - 1 : 1;
-    const int ct = strips >= 32 ? 4 : 1, cgrid = (strips + ct - 1) / ct;      // column tiles per block
-    int sweep = 0;
-    for (;; ++sweep) {
-        hipLaunchKernelGGL(k_jacobi_norms, dim3(n), dim3(256), 0, st, *A, n, rowsums);
-        hipLaunchKernelGGL(k_jacobi_norms_finish, dim3(1), dim3(256), 0, st, rowsums, n, *A, sums, lam);
-        double h[2] = {0.0, 0.0};
-        if (hipMemcpyAsync(h, sums, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess) {
-            (void)hipGetLastError();
-            return SVDP_ERR_HIP;
-        }
-        if (!(h[1] == h[1]) || h[0] <= tol * tol * h[1] || sweep >= max_sweeps) break;
-        for (int round = 0; round < rounds; ++round) {
-            hipLaunchKernelGGL(k_bjacobi_solve, dim3(strips), dim3(BJ_SOLVE_THREADS), lds_solve, st, *A, n, Uall);
-            hipLaunchKernelGGL(k_bjacobi_apply<true>, dim3(cgrid, strips), dim3(256), lds_two, st, *A, Uall, n, ct, *Aalt);
-            hipLaunchKernelGGL(k_bjacobi_apply<false>, dim3(cgrid, strips), dim3(256), lds_one, st, *V, Uall, n, ct, *Valt);
-            std::swap(*A, *Aalt);
-            std::swap(*V, *Valt);
-        }
-    }
-    if (sweeps_out != nullptr) *sweeps_out = sweep;
-    return hip_status(hipSuccess);
-}
-
-template <typename W>
-svdp_status whiten_impl(const void *W_gate, const void *X, int d, int D, int T, int r, float *P, float *Q, float *sigma,
-                        int32_t *sweeps, const WhitenWs &w, hipStream_t st)
-{
-    const W *Wg = static_cast<const W *>(W_gate), *Xs = static_cast<const W *>(X);
-    const double tol = 1e-11;          // off-diagonal Frobenius norm relative to the matrix's
-    const int max_sweeps = 24;
-    std::vector<double> lam(d);
-    std::vector<int32_t> order(d);
-
-    // second moments C = X^T X  (d x d) and its Cholesky factor S (lower, S S^T = C)
-    hipLaunchKernelGGL((k_transpose_to_f64<W>), dim3((d + 31) / 32, (T + 31) / 32), dim3(256), 0, st, Xs, T, d, w.Xt);
-    dgemm_nt(w.Xt, T, w.Xt, T, w.A0, d, d, d, T, st);
-    if (hipMemsetAsync(w.fail, 0, 4, st) != hipSuccess) {
-        (void)hipGetLastError();
-        return SVDP_ERR_HIP;
-    }
-    cholesky_blocked(w.A0, w.S, w.A1, d, w.invL, w.invLt, w.sums, w.fail, st);
-    int32_t failed = 0;
-    if (hipMemcpyAsync(&failed, w.fail, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess) {
-        (void)hipGetLastError();
-        return SVDP_ERR_HIP;
-    }
-    // S needs C positive definite (more independent tokens than dimensions)
-    if (failed != 0) return SVDP_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((k_transpose_to_f64<double>), dim3((d + 31) / 32, (d + 31) / 32), dim3(256), 0, st, w.S, d, d, w.St);
-
-    // M = W_gate S, G = M^T M
-    hipLaunchKernelGGL((k_to_f64<W>), grid1((size_t)D * d), dim3(256), 0, st, Wg, (size_t)D * d, w.W64);
-    dgemm_nt(w.W64, d, w.St, d, w.M, d, D, d, d, st);
-    hipLaunchKernelGGL((k_transpose_to_f64<double>), dim3((d + 31) / 32, (D + 31) / 32), dim3(256), 0, st, w.M, D, d, w.Mt);
-    double *A = w.A0, *Aalt = w.A1, *V = w.V0, *Valt = w.V1;
-    dgemm_nt(w.Mt, D, w.Mt, D, A, d, d, d, D, st);
-    int sw2 = 0;
-    svdp_status e = jacobi_eigh(&A, &Aalt, &V, &Valt, d, w.Uall, w.rowsums, w.sums, w.lamG, tol, max_sweeps, &sw2, st);
-    if (e != SVDP_OK) return e;
-    if (hipMemcpyAsync(lam.data(), w.lamG, (size_t)d * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess) {
-        (void)hipGetLastError();
-        return SVDP_ERR_HIP;
-    }
-    // the r largest eigenvalues (= squared singular values of W S), largest first; ties by place
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return lam[a] > lam[b]; });
-    if (hipMemcpyAsync(w.sel, order.data(), (size_t)r * 4, hipMemcpyHostToDevice, st) != hipSuccess) {
-        (void)hipGetLastError();
-        return SVDP_ERR_HIP;
-    }
-    // Q = A = M V_r
-    hipLaunchKernelGGL(k_gather_rows, grid1((size_t)r * d), dim3(256), 0, st, V, w.sel, r, d, w.Vr);
-    dgemm_nt(w.M, d, w.Vr, d, w.out64, r, D, r, d, st);
-    hipLaunchKernelGGL(k_f64_to_f32, grid1((size_t)D * r), dim3(256), 0, st, w.out64, (size_t)D * r, Q);
-    // B = V_r^T S^-1 (block back-substitution; V_r^T is w.Vr, rows = the chosen eigenvectors), P = B^T
-    solve_right_lower(w.Vr, w.out64, r, d, w.St, w.invLt, w.Uall, st);
-    hipLaunchKernelGGL((k_transpose_to_f64<double>), dim3((d + 31) / 32, (r + 31) / 32), dim3(256), 0, st, w.out64, r, d, w.M);
-    hipLaunchKernelGGL(k_f64_to_f32, grid1((size_t)d * r), dim3(256), 0, st, w.M, (size_t)d * r, P);
-    if (hipStreamSynchronize(st) != hipSuccess) {                 // order[] leaves scope: the copy above must be done
-        (void)hipGetLastError();
-        return SVDP_ERR_HIP;
-    }
-    if (sigma != nullptr)
-        for (int k = 0; k < r; ++k) sigma[k] = (float)std::sqrt(std::max(lam[order[k]], 0.0));
-    if (sweeps != nullptr) {
-        sweeps[0] = 0;              // the factor of the second moments is a Cholesky factor: no sweeps
-        sweeps[1] = sw2;
-    }
-    return hip_status(hipSuccess);
-}
+#include "svdp_whiten_run.h"
 
 }  // namespace
 

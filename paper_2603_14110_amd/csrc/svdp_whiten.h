@@ -5,7 +5,7 @@
 // W_gate S = U Sigma V^T, and returns A = U_r Sigma_r, B = V_r^T S^-1, the rank-r pair
 // minimising ||(W_gate - A B) X^T||_F.  In the library's letters Q = A [D][r], P = B^T [d][r].
 //
-// Everything that is a dense contraction runs on the matrix cores (k_dgemm_nt, fp64 MFMA),
+// Everything that is a dense contraction runs on the matrix cores (k_dgemm, fp64 MFMA),
 // including the bulk of the blocked Cholesky factorisation that gives S and of the block
 // back-substitution that applies S^-1; the symmetric d x d eigen-decomposition (of (W S)^T (W S), whose
 // eigenvectors are V and eigenvalues Sigma^2) is a two-sided BLOCK Jacobi method in which a round
@@ -15,27 +15,13 @@
 // written to the places the round-robin pairing wants its blocks in for the next round.
 #pragma once
 
-#include "svdp_device.h"
+#include "svdp_dgemm.h"
 
 namespace svdp {
 
-typedef double f64x4_t __attribute__((ext_vector_type(4)));
-
 // ---- element-wise helpers ----
 
-// dst[i] = (double) src[i]
-template <typename W>
-__global__ __launch_bounds__(256) void k_to_f64(const W *__restrict__ src, size_t n, double *__restrict__ dst)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) dst[i] = (double)to_f32(src[i]);
-}
-
 // dst [cols][rows] (fp64) = src [rows][cols]^T, 32 x 32 tiles through LDS.
-template <typename T>
-__device__ __forceinline__ double as_f64(T v) { return (double)to_f32(v); }
-__device__ __forceinline__ double as_f64(double v) { return v; }
-
 template <typename T>
 __global__ __launch_bounds__(256) void k_transpose_to_f64(const T *__restrict__ src, int rows, int cols,
                                                           double *__restrict__ dst)
@@ -66,86 +52,10 @@ __global__ __launch_bounds__(256) void k_f64_to_f32(const double *__restrict__ s
 }
 
 // ---------------------------------------------------------------------------
-// C [M][ldc] = A [M][lda] * B [N][ldb]^T over K (both operands K-contiguous), fp64, on
-// v_mfma_f64_16x16x4_f64.  Block tile 64 x 64 x 16, four waves of 32 x 32 (2 x 2 MFMA tiles);
-// the next K step's global loads are in flight while the current one is multiplied.
-// Operand lanes: A[row = lane%16][k = lane/16], B[k = lane/16][col = lane%16]; the result
-// register v of a lane is C[row = 4*v + lane/16][col = lane%16].
-// ---------------------------------------------------------------------------
-constexpr int DG_BM = 64, DG_BN = 64, DG_BK = 16;
-constexpr int DG_LD = DG_BK + 1;            // LDS row stride in doubles (odd: spreads the banks)
-
-// With Cin the result is Cin - A B^T (Cin [M][ldcin], not the same memory as C).
-__global__ __launch_bounds__(256) void k_dgemm_nt(const double *__restrict__ A, int lda, const double *__restrict__ Bm,
-                                                  int ldb, double *__restrict__ C, int ldc, int M, int N, int K,
-                                                  const double *__restrict__ Cin, int ldcin)
-{
-    __shared__ double sA[DG_BM * DG_LD];
-    __shared__ double sB[DG_BN * DG_LD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lm = lane & 15, lq = lane >> 4;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int m0 = blockIdx.y * DG_BM, n0 = blockIdx.x * DG_BN;
-    // a thread moves four consecutive k of one row of each operand per K step
-    const int lrow = tid >> 2, lk = (tid & 3) * 4;
-
-    f64x4_t acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-
-    double ra[4], rb[4];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int k = k0 + lk + e;
-            ra[e] = (m0 + lrow < M && k < K) ? A[(size_t)(m0 + lrow) * lda + k] : 0.0;
-            rb[e] = (n0 + lrow < N && k < K) ? Bm[(size_t)(n0 + lrow) * ldb + k] : 0.0;
-        }
-    };
-    fetch(0);
-    for (int k0 = 0; k0 < K; k0 += DG_BK) {
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            sA[lrow * DG_LD + lk + e] = ra[e];
-            sB[lrow * DG_LD + lk + e] = rb[e];
-        }
-        __syncthreads();
-        if (k0 + DG_BK < K) fetch(k0 + DG_BK);
-#pragma unroll
-        for (int kk = 0; kk < DG_BK; kk += 4) {
-            double fa[2], fb[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) fa[i] = sA[(wm * 32 + i * 16 + lm) * DG_LD + kk + lq];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) fb[j] = sB[(wn * 32 + j * 16 + lm) * DG_LD + kk + lq];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i], fb[j], acc[i][j], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int m = m0 + wm * 32 + i * 16 + 4 * v + lq;
-                const int n = n0 + wn * 32 + j * 16 + lm;
-                if (m < M && n < N)
-                    C[(size_t)m * ldc + n] = Cin != nullptr ? Cin[(size_t)m * ldcin + n] - acc[i][j][v] : acc[i][j][v];
-            }
-}
-
-// ---------------------------------------------------------------------------
 // Blocked Cholesky factorisation C = L L^T (Alg. 1's S), block size 64, left-looking.  Per block column k:
-//   T[k:, k] = C[k:, k] - L[k:, :k] L[k, :k]^T         k_dgemm_nt with Cin (T is a scratch matrix)
+//   T[k:, k] = C[k:, k] - L[k:, :k] L[k, :k]^T         k_dgemm with C as C1 (T is a scratch matrix)
 //   L[k, k]  = chol(T[k, k]), and its inverse           k_chol_diag (one block, in LDS)
-//   L[k+1:, k] = T[k+1:, k] L[k, k]^-T                  k_dgemm_nt against the inverse
+//   L[k+1:, k] = T[k+1:, k] L[k, k]^-T                  k_dgemm against the inverse
 // The inverses of the diagonal blocks are kept (transposed) for the block back-substitution that applies
 // L^-1 to the chosen singular vectors at the end.
 // ---------------------------------------------------------------------------

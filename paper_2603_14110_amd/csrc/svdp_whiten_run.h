@@ -1,0 +1,306 @@
+// Host side of the offline build with whitening (Alg. 1): fp64 work buffers, the launches of the contraction kernel
+// and the drivers of the factorisations.  Included by svdp.hip inside its unnamed namespace.
+
+inline dim3 grid1(size_t n) { return dim3((unsigned)((n + 255) / 256)); }
+
+// ---- C = alpha A B^T + beta C1 + gamma C2 (k_dgemm): operands and the choice of the tile ----
+
+template <typename T>
+struct DgOperand {
+    const T *p;
+    int ld;
+};
+template <typename T>
+DgOperand<T> op(const T *p, int ld) { return DgOperand<T>{p, ld}; }
+
+struct DgScratch {          // where parts of a split K range meet
+    double *p;
+    size_t n;               // doubles
+};
+
+template <typename TA, DgLayout LA, typename TB, DgLayout LB, int WM, int WN, int TM, int TN, int BK>
+bool dgemm_tile(DgOperand<TA> A, DgOperand<TB> B, double *C, int ldc, int M, int N, int K, int flags, const DgEpilogue &ep,
+                int nz, const DgScratch &scr, hipStream_t st)
+{
+    constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
+    constexpr auto kernel = &k_dgemm<TA, LA, TB, LB, WM, WN, TM, TN, BK>;
+    constexpr size_t lds = (size_t)2 * (DgStage<BM, BK, LA>::SIZE + DgStage<BN, BK, LB>::SIZE) * 8;
+    if (!grant_lds<kernel>(lds)) return false;
+    const int tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
+    int kpart = K;
+    if (nz > 1) {
+        kpart = round_up((K + nz - 1) / nz, BK);
+        nz = (K + kpart - 1) / kpart;
+    }
+    const dim3 grid = (flags & DG_LOWER) ? dim3(tm * (tm + 1) / 2, 1, nz)
+                                         : (flags & DG_K_FROM_N) ? dim3(tm, tn, nz) : dim3(tn, tm, nz);
+    if (nz > 1) {
+        hipLaunchKernelGGL(kernel, grid, dim3(DG_THREADS), lds, st, A.p, A.ld, B.p, B.ld, scr.p, N, M, N, K, kpart, flags,
+                           DgEpilogue{});
+        hipLaunchKernelGGL(k_dgemm_sum, grid1((size_t)M * N), dim3(256), 0, st, scr.p, nz, C, ldc, M, N, flags, ep);
+    } else {
+        hipLaunchKernelGGL(kernel, grid, dim3(DG_THREADS), lds, st, A.p, A.ld, B.p, B.ld, C, ldc, M, N, K, kpart, flags, ep);
+    }
+    return true;
+}
+
+// Tile and split of a product.  DG_LOWER needs M == N.  `one_tile_wide` (N <= 64): every block covers all columns of
+// its rows, so that C may be A itself.
+//  - large products: 128 x 128, 96 x 96 or 64 x 64 tiles, whichever leaves the least idle in the last round (the lower
+//    half of a 4096 x 4096 product is 528 tiles of 128 x 128, i.e. 2.06 rounds of the 256 compute units that take the
+//    time of three, but 946 of 96 x 96, 3.7 rounds of 9/16 of the work each); a smaller tile reads more from L2 per
+//    product, which the weights stand for;
+//  - 80 x 64 tiles (four waves side by side) likewise: 320 rows by 4096 columns are exactly 256 of them;
+//  - small products: 32 x 32 tiles and parts of K (k_dgemm_sum adds them in order).
+template <DgLayout LA, DgLayout LB, typename TA, typename TB>
+bool dgemm(DgOperand<TA> A, DgOperand<TB> B, double *C, int ldc, int M, int N, int K, hipStream_t st, int flags = 0,
+           const DgEpilogue &ep = DgEpilogue{}, const DgScratch &scr = DgScratch{nullptr, 0}, bool one_tile_wide = false)
+{
+    if (M <= 0 || N <= 0) return true;
+    if (!aligned16(A.p)) flags |= DG_LOOSE_A;       // possible for the caller's own matrices only
+    if (!aligned16(B.p)) flags |= DG_LOOSE_B;
+    auto tiles = [&](int bm, int bn) {
+        const long long tm = (M + bm - 1) / bm, tn = (N + bn - 1) / bn;
+        return (flags & DG_LOWER) ? tm * (tm + 1) / 2 : tm * tn;
+    };
+    constexpr long long CUS = 256;
+    if (one_tile_wide) return dgemm_tile<TA, LA, TB, LB, 2, 2, 2, 2, 16>(A, B, C, ldc, M, N, K, flags, ep, 1, scr, st);
+    if (tiles(64, 64) >= 200) {
+        auto cost = [&](int bm, int bn, double weight) {
+            return (double)((tiles(bm, bn) + CUS - 1) / CUS) * bm * bn * weight;
+        };
+        const bool lower = (flags & DG_LOWER) != 0;
+        const double c128 = cost(128, 128, 1.0), c96 = cost(96, 96, 1.05), c64 = cost(64, 64, 1.25),
+                     c80 = lower ? 1e300 : cost(80, 64, 1.2);
+        const double best = std::min(std::min(c128, c96), std::min(c64, c80));
+        if (best == c128) return dgemm_tile<TA, LA, TB, LB, 2, 2, 4, 4, 16>(A, B, C, ldc, M, N, K, flags, ep, 1, scr, st);
+        if (best == c96) return dgemm_tile<TA, LA, TB, LB, 2, 2, 3, 3, 16>(A, B, C, ldc, M, N, K, flags, ep, 1, scr, st);
+        if (best == c80) return dgemm_tile<TA, LA, TB, LB, 1, 4, 5, 1, 32>(A, B, C, ldc, M, N, K, flags, ep, 1, scr, st);
+        return dgemm_tile<TA, LA, TB, LB, 2, 2, 2, 2, 16>(A, B, C, ldc, M, N, K, flags, ep, 1, scr, st);
+    }
+    const long long t32 = tiles(32, 32);
+    int nz = (int)std::max<long long>(1, std::min<long long>(2 * CUS / t32, K / 256));
+    while (nz > 1 && (size_t)nz * M * N > scr.n) --nz;
+    return dgemm_tile<TA, LA, TB, LB, 2, 2, 1, 1, 32>(A, B, C, ldc, M, N, K, flags, ep, nz, scr, st);
+}
+
+// C = Cin - (product)
+inline DgEpilogue minus_from(const double *Cin, int ld)
+{
+    DgEpilogue e;
+    e.alpha = -1.0;
+    e.c1 = Cin;
+    e.ld1 = ld;
+    e.beta = 1.0;
+    return e;
+}
+
+// ---- work buffers ----
+struct WhitenWs {
+    double *S;                  // [d][d]  the lower Cholesky factor of C = X^T X
+    double *St;                 // [d][d]  S^T
+    double *G;                  // [d][d]  (W S)^T (W S)
+    double *T0, *T1, *T2;       // [d][d]  C, W^T W and the like; later the work matrices of the eigen-decomposition
+    double *lamG;               // [d] eigenvalues by place
+    double *invL, *invLt;       // [64][64] scratch; [d/64][64][64] transposed inverses of S's diagonal blocks
+    int32_t *fail;              // set by the factorisation if X^T X is not positive definite
+    double *Vr, *Zr;            // [r][d]
+    double *out64;              // [max(D, d)][r]
+    double *part;               // parts of split products
+    size_t n_part;
+    double *Uall, *rowsums, *sums;     // [d/64][64][64] strip transforms; norms
+    int32_t *sel;               // [r]
+    size_t bytes;
+};
+
+WhitenWs carve_whiten(void *base, int d, int D, int T, int r)
+{
+    (void)T;
+    WhitenWs w;
+    char *p = static_cast<char *>(base);
+    size_t off = 0;
+    auto take = [&](size_t n_doubles) {
+        double *q = reinterpret_cast<double *>(p + off);
+        off += align_up(n_doubles * 8);
+        return q;
+    };
+    const size_t dd = (size_t)d * d;
+    w.S = take(dd);
+    w.St = take(dd);
+    w.G = take(dd);
+    w.T0 = take(dd);
+    w.T1 = take(dd);
+    w.T2 = take(dd);
+    w.lamG = take(d);
+    w.invL = take(64 * 64);
+    w.invLt = take((size_t)d * 64);
+    w.fail = reinterpret_cast<int32_t *>(take(32));
+    w.Vr = take((size_t)r * d);
+    w.Zr = take((size_t)r * d);
+    w.out64 = take((size_t)(D > d ? D : d) * r);
+    w.n_part = (size_t)16 * 512 * 512;
+    w.part = take(w.n_part);
+    w.Uall = take((size_t)d * 64);
+    w.rowsums = take((size_t)2 * d);
+    w.sums = take(2);
+    w.sel = reinterpret_cast<int32_t *>(p + off);
+    off += align_up((size_t)r * 4);
+    w.bytes = off;
+    return w;
+}
+
+// L (lower, [n][n], zero above the diagonal) with L L^T = C; T: scratch [n][n]; invLt: [n/64][64][64], the
+// transposed inverses of L's diagonal blocks; invL: scratch [64][64]; scale: device double; fail: device int,
+// set to 1 if C is not positive definite to working precision (then L is not to be used).
+void cholesky_blocked(const double *C, double *L, double *T, int n, double *invL, double *invLt, double *scale, int *fail,
+                      const DgScratch &scr, hipStream_t st)
+{
+    const int nb = n / CH_B;
+    hipLaunchKernelGGL(k_max_diag, dim3(1), dim3(256), 0, st, C, n, scale);
+    for (int k = 0; k < nb; ++k) {
+        const size_t row0 = (size_t)k * CH_B * n, diag = row0 + (size_t)k * CH_B;
+        // T[k:, k] = C[k:, k] - L[k:, :k] L[k, :k]^T   (K = 0 for the first block column: a copy)
+        dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)L + row0, n), op((const double *)L + row0, n), T + diag, n, n - k * CH_B, CH_B, k * CH_B, st, 0,
+                                    minus_from(C + diag, n), scr);
+        hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, T, L, n, diag, scale, 1e-13, invL,
+                           invLt + (size_t)k * CH_B * CH_B, fail);
+        // L[k+1:, k] = T[k+1:, k] Lkk^-T
+        dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)T + diag + (size_t)CH_B * n, n), op((const double *)invL, CH_B), L + diag + (size_t)CH_B * n, n,
+                                    n - (k + 1) * CH_B, CH_B, CH_B, st);
+    }
+    hipLaunchKernelGGL(k_zero_upper_blocks, grid1((size_t)n * n), dim3(256), 0, st, L, n);
+}
+
+// Bout [r][n] = Bin [r][n] L^-1 for the lower-triangular L given as Lt = L^T [n][n] and the transposed inverses of
+// its diagonal blocks: block back-substitution from the last block column to the first.  tmp: scratch [r][64].
+void solve_right_lower(const double *Bin, double *Bout, int r, int n, const double *Lt, const double *invLt, double *tmp,
+                       const DgScratch &scr, hipStream_t st)
+{
+    const int nb = n / CH_B;
+    for (int i = nb - 1; i >= 0; --i) {
+        const int c0 = i * CH_B, rest = n - (i + 1) * CH_B;
+        // tmp = Bin[:, i] - Bout[:, i+1:] L[i+1:, i]      (L[k][c0 + a] = Lt[c0 + a][k])
+        dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)Bout + c0 + CH_B, n), op(Lt + (size_t)c0 * n + c0 + CH_B, n), tmp, CH_B, r, CH_B, rest,
+                                    st, 0, minus_from(Bin + c0, n), scr);
+        // Bout[:, i] = tmp Lii^-1
+        dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)tmp, CH_B), op(invLt + (size_t)i * CH_B * CH_B, CH_B), Bout + c0, n, r, CH_B, CH_B, st);
+    }
+}
+
+// Eigen-decomposition of the symmetric matrix in *A (n x n, n % 64 == 0) by block Jacobi sweeps.  On return
+// *A / *V point at the buffers holding the (numerically) diagonal matrix and the eigenvectors as rows, lam[i]
+// (device) = (*A)[i][i].  Uall: n/64 matrices of 64 x 64.  Synchronises the stream once per sweep (the
+// convergence figure is read on the host).
+svdp_status jacobi_eigh(double **A, double **Aalt, double **V, double **Valt, int n, double *Uall, double *rowsums,
+                        double *sums, double *lam, double tol, int max_sweeps, int *sweeps_out, hipStream_t st)
+{
+    const size_t lds_solve = (size_t)2 * BJ_S * BJ_LD * 8, lds_two = (size_t)2 * BJ_S * BJ_LD * 8,
+                 lds_one = lds_two;
+    if (!grant_lds<k_bjacobi_solve>(lds_solve) || !grant_lds<k_bjacobi_apply<true>>(lds_two) ||
+        !grant_lds<k_bjacobi_apply<false>>(lds_one))
+        return SVDP_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(k_identity, grid1((size_t)n * n), dim3(256), 0, st, *V, n);
+    const int strips = n / BJ_S, rounds = n / BJ_B > 2 ? n / BJ_B - 1 : 1;
+    const int ct = strips >= 32 ? 4 : 1, cgrid = (strips + ct - 1) / ct;      // column tiles per block
+    int sweep = 0;
+    for (;; ++sweep) {
+        hipLaunchKernelGGL(k_jacobi_norms, dim3(n), dim3(256), 0, st, *A, n, rowsums);
+        hipLaunchKernelGGL(k_jacobi_norms_finish, dim3(1), dim3(256), 0, st, rowsums, n, *A, sums, lam);
+        double h[2] = {0.0, 0.0};
+        if (hipMemcpyAsync(h, sums, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess) {
+            (void)hipGetLastError();
+            return SVDP_ERR_HIP;
+        }
+        if (!(h[1] == h[1]) || h[0] <= tol * tol * h[1] || sweep >= max_sweeps) break;
+        for (int round = 0; round < rounds; ++round) {
+            hipLaunchKernelGGL(k_bjacobi_solve, dim3(strips), dim3(BJ_SOLVE_THREADS), lds_solve, st, *A, n, Uall);
+            hipLaunchKernelGGL(k_bjacobi_apply<true>, dim3(cgrid, strips), dim3(256), lds_two, st, *A, Uall, n, ct, *Aalt);
+            hipLaunchKernelGGL(k_bjacobi_apply<false>, dim3(cgrid, strips), dim3(256), lds_one, st, *V, Uall, n, ct, *Valt);
+            std::swap(*A, *Aalt);
+            std::swap(*V, *Valt);
+        }
+    }
+    if (sweeps_out != nullptr) *sweeps_out = sweep;
+    return hip_status(hipSuccess);
+}
+
+template <typename W>
+svdp_status whiten_impl(const void *W_gate, const void *X, int d, int D, int T, int r, float *P, float *Q, float *sigma,
+                        int32_t *sweeps, const WhitenWs &w, hipStream_t st)
+{
+    const W *Wg = static_cast<const W *>(W_gate), *Xs = static_cast<const W *>(X);
+    const double tol = 1e-11;          // off-diagonal Frobenius norm relative to the matrix's
+    const int max_sweeps = 24;
+    std::vector<double> lam(d);
+    std::vector<int32_t> order(d);
+
+    const DgScratch scr{w.part, w.n_part};
+    constexpr int SYM = DG_LOWER | DG_MIRROR;
+
+    // second moments C = X^T X  (d x d) and its Cholesky factor S (lower, S S^T = C)
+    if (!dgemm<DG_K_ROWS, DG_K_ROWS>(op(Xs, d), op(Xs, d), w.T0, d, d, d, T, st, SYM, DgEpilogue{}, scr))
+        return SVDP_ERR_UNSUPPORTED;
+    if (hipMemsetAsync(w.fail, 0, 4, st) != hipSuccess) {
+        (void)hipGetLastError();
+        return SVDP_ERR_HIP;
+    }
+    cholesky_blocked(w.T0, w.S, w.T1, d, w.invL, w.invLt, w.sums, w.fail, scr, st);
+    int32_t failed = 0;
+    if (hipMemcpyAsync(&failed, w.fail, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess) {
+        (void)hipGetLastError();
+        return SVDP_ERR_HIP;
+    }
+    // S needs C positive definite (more independent tokens than dimensions)
+    if (failed != 0) return SVDP_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((k_transpose_to_f64<double>), dim3((d + 31) / 32, (d + 31) / 32), dim3(256), 0, st, w.S, d, d, w.St);
+
+    // G = (W S)^T (W S) = S^T ((W^T W) S): 2/3 of the products that W S and its Gram matrix would take (S is
+    // triangular and both Gram matrices are symmetric), and no D x d matrix in 64 bits is ever stored
+    bool ok = dgemm<DG_K_ROWS, DG_K_ROWS>(op(Wg, d), op(Wg, d), w.T0, d, d, d, D, st, SYM, DgEpilogue{}, scr) &&
+              dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.T0, d), op((const double *)w.S, d), w.T1, d, d, d, d, st,
+                                          DG_K_FROM_N, DgEpilogue{}, scr) &&
+              dgemm<DG_K_ROWS, DG_K_ROWS>(op((const double *)w.S, d), op((const double *)w.T1, d), w.G, d, d, d, d, st,
+                                          SYM | DG_K_FROM_M, DgEpilogue{}, scr);
+    if (!ok) return SVDP_ERR_UNSUPPORTED;
+    double *A = w.G, *Aalt = w.T0, *V = w.T1, *Valt = w.T2;
+    int sw2 = 0;
+    svdp_status e = jacobi_eigh(&A, &Aalt, &V, &Valt, d, w.Uall, w.rowsums, w.sums, w.lamG, tol, max_sweeps, &sw2, st);
+    if (e != SVDP_OK) return e;
+    if (hipMemcpyAsync(lam.data(), w.lamG, (size_t)d * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess) {
+        (void)hipGetLastError();
+        return SVDP_ERR_HIP;
+    }
+    // the r largest eigenvalues (= squared singular values of W S), largest first; ties by place
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return lam[a] > lam[b]; });
+    if (hipMemcpyAsync(w.sel, order.data(), (size_t)r * 4, hipMemcpyHostToDevice, st) != hipSuccess) {
+        (void)hipGetLastError();
+        return SVDP_ERR_HIP;
+    }
+    // Q = A = W (S V_r)
+    hipLaunchKernelGGL(k_gather_rows, grid1((size_t)r * d), dim3(256), 0, st, V, w.sel, r, d, w.Vr);
+    ok = dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)w.Vr, d), op((const double *)w.S, d), w.Zr, d, r, d, d, st, DG_K_UPTO_N,
+                                     DgEpilogue{}, scr) &&
+         dgemm<DG_ROWS_K, DG_ROWS_K>(op(Wg, d), op((const double *)w.Zr, d), w.out64, r, D, r, d, st, 0, DgEpilogue{}, scr);
+    if (!ok) return SVDP_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(k_f64_to_f32, grid1((size_t)D * r), dim3(256), 0, st, w.out64, (size_t)D * r, Q);
+    // B = V_r^T S^-1 (block back-substitution; V_r^T is w.Vr, rows = the chosen eigenvectors), P = B^T
+    solve_right_lower(w.Vr, w.out64, r, d, w.St, w.invLt, w.Zr, scr, st);
+    hipLaunchKernelGGL((k_transpose_to_f64<double>), dim3((d + 31) / 32, (r + 31) / 32), dim3(256), 0, st, w.out64, r, d, w.Vr);
+    hipLaunchKernelGGL(k_f64_to_f32, grid1((size_t)d * r), dim3(256), 0, st, w.Vr, (size_t)d * r, P);
+    if (hipStreamSynchronize(st) != hipSuccess) {                 // order[] leaves scope: the copy above must be done
+        (void)hipGetLastError();
+        return SVDP_ERR_HIP;
+    }
+    if (sigma != nullptr)
+        for (int k = 0; k < r; ++k) sigma[k] = (float)std::sqrt(std::max(lam[order[k]], 0.0));
+    if (sweeps != nullptr) {
+        sweeps[0] = 0;              // the factor of the second moments is a Cholesky factor: no sweeps
+        sweeps[1] = sw2;
+    }
+    return hip_status(hipSuccess);
+}
+

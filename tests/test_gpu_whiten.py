@@ -109,3 +109,33 @@ def test_whiten_rejects_what_it_cannot_take(env):
     X = torch.ones(512, 128, device="cuda")
     with pytest.raises(binding.SvdpError, match="unsupported"):
         binding.whiten_factors(W, X, 8)
+
+
+@pytest.mark.parametrize("d,D,T,r,dt", [
+    (64, 1, 77, 1, "f32"),                    # one neuron; T and r on no tile edge
+    (192, 200, 193, 3, "bf16"),               # T barely above d, not a multiple of anything
+    (1088, 1100, 1200, 70, "bf16"),           # 128-wide tiles with a ragged last tile
+])
+def test_contractions_at_ragged_sizes_and_unaligned_inputs(env, d, D, T, r, dt):
+    """The fp64 contraction kernel at the edges of its tiles, and inputs that start on no 16-byte boundary: the
+    product of the factors against the oracle with the tolerance of the test above, and the same bits from the
+    aligned and the unaligned copy."""
+    binding, torch, calib = env
+    rng = np.random.default_rng(31 * d + r)
+    W_st = synth.to_storage(rng.standard_normal((D, d)) / np.sqrt(d), dt)
+    X_st = synth.to_storage(rng.standard_normal((T, d)) * (0.998 ** np.arange(d))[None, :], dt)
+    W, X = synth.storage_to_f32(W_st, dt).astype(np.float64), synth.storage_to_f32(X_st, dt).astype(np.float64)
+    Wd, Xd = binding.to_device(W_st, dt), binding.to_device(X_st, dt)
+
+    def shifted(t):
+        flat = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")
+        flat[1:] = t.flatten()
+        return flat[1:].view(t.shape)
+
+    P, Q, _, _ = binding.whiten_factors(Wd, Xd, r)
+    P2, Q2, _, _ = binding.whiten_factors(shifted(Wd), shifted(Xd), r)
+    assert torch.equal(P, P2) and torch.equal(Q, Q2)
+    A, B = calib.whitened_factors(W, X, r)
+    QP, AB = Q.cpu().numpy().astype(np.float64) @ P.cpu().numpy().astype(np.float64).T, A @ B
+    err, best, scale = np.linalg.norm((W - QP) @ X.T), np.linalg.norm((W - AB) @ X.T), np.linalg.norm(W @ X.T)
+    assert abs(err - best) <= 2e-5 * scale
