@@ -52,14 +52,18 @@ __global__ __launch_bounds__(256) void k_f64_to_f32(const double *__restrict__ s
 }
 
 // ---------------------------------------------------------------------------
-// Blocked Cholesky factorisation C = L L^T (Alg. 1's S), block size 64, left-looking.  Per block column k:
-//   T[k:, k] = C[k:, k] - L[k:, :k] L[k, :k]^T         k_dgemm with C as C1 (T is a scratch matrix)
-//   L[k, k]  = chol(T[k, k]), and its inverse           k_chol_diag (one block, in LDS)
-//   L[k+1:, k] = T[k+1:, k] L[k, k]^-T                  k_dgemm against the inverse
-// The inverses of the diagonal blocks are kept (transposed) for the block back-substitution that applies
-// L^-1 to the chosen singular vectors at the end.
+// Blocked Cholesky factorisation C = L L^T (Alg. 1's S) in place, block size 64, right-looking inside panels of
+// CH_PANEL columns and between panels.  Per block column k:
+//   L[k, k]    = chol(C[k, k]), and its inverse                              k_chol_diag (one block)
+//   L[k+1:, k] = C[k+1:, k] L[k, k]^-T                                       k_dgemm against the inverse
+//   C[k+1:, rest of the panel] -= L[k+1:, k] L[rest of the panel, k]^T       k_dgemm, K = 64
+// and after a panel its whole update of the lower triangle behind it, K = CH_PANEL.  A left-looking order would sum
+// over all earlier columns for 64 columns at a time: at most n / 64 blocks with K up to n, which leaves the chip idle
+// (up to 0.24 ms per block column at n = 4096); this way the bulk is one wide product per panel.
+// Measured at n = 4096: 25 -> 3.4 ms (192 launches; k_chol_diag 189 -> 28 us a block).
 // ---------------------------------------------------------------------------
 constexpr int CH_B = 64;
+constexpr int CH_PANEL = 256;
 
 // out[0] = largest diagonal element of A [n][n] (one block)
 __global__ __launch_bounds__(256) void k_max_diag(const double *__restrict__ A, int n, double *__restrict__ out)
@@ -76,56 +80,83 @@ __global__ __launch_bounds__(256) void k_max_diag(const double *__restrict__ A, 
     if (threadIdx.x == 0) out[0] = sm[0];
 }
 
-// Lkk (lower, the part above the diagonal zero) = Cholesky factor of the 64 x 64 block at T + toff (row stride n),
-// written to L + toff; invL [64][64] = Lkk^-1 and invLt its transpose.  A pivot that is not above tiny * scale[0]
-// (the matrix is not positive definite to working precision) sets fail[0] = 1 and is replaced by that bound, so
-// that the rest of the run stays finite.
-__global__ __launch_bounds__(256) void k_chol_diag(const double *__restrict__ T, double *__restrict__ L, int n,
-                                                   size_t toff, const double *__restrict__ scale, double tiny,
-                                                   double *__restrict__ invL, double *__restrict__ invLt,
-                                                   int *__restrict__ fail)
+// The value lane `src` (uniform) holds.
+__device__ __forceinline__ double lane_value(double v, int src)
 {
-    __shared__ double S[CH_B][CH_B + 1], X[CH_B][CH_B + 1];
-    const int tid = threadIdx.x;
-    for (int e = tid; e < CH_B * CH_B; e += 256) S[e >> 6][e & 63] = T[toff + (size_t)(e >> 6) * n + (e & 63)];
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src), __builtin_amdgcn_readlane(__double2loint(v), src));
+}
+
+// The 64 x 64 block at A + off (row stride n, lower part) becomes its Cholesky factor (zero above the diagonal);
+// invL [64][64] = the factor's inverse.  A pivot that is not above tiny * scale[0] (the matrix is not positive definite
+// to working precision) sets fail[0] = 1 and is replaced by that bound, so that the rest of the run stays finite.
+// Bound: 64 dependent steps.  A thread keeps 16 columns of one row of the block and of the inverse in registers
+// (lane = row, wave = column group).  A wave factors its 16 columns by itself (the multipliers of a step are other
+// lanes' values, no LDS and no barrier in the chain); then, once per group, the waves to its right take the 16 columns
+// out of theirs through LDS and the others apply the 16 row operations to the inverse while the next group is factored.
+// A block: 189 us in LDS element by element with three barriers a step and a serial substitution for the inverse,
+// 39 us with one barrier per step, 28 us so.
+__global__ __launch_bounds__(256) void k_chol_diag(double *__restrict__ A, int n, size_t off,
+                                                   const double *__restrict__ scale, double tiny,
+                                                   double *__restrict__ invL, int *__restrict__ fail)
+{
+    constexpr int CPT = CH_B / 4;
+    __shared__ double col[2][CPT][CH_B];        // the group's finished columns
+    __shared__ double inv_sh[2][CPT];
+    const int row = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const double bound = tiny * scale[0];
-    __syncthreads();
-    for (int j = 0; j < CH_B; ++j) {
-        if (tid == 0) {
-            double p = S[j][j];
-            if (!(p > bound)) {
-                fail[0] = 1;
-                p = bound > 0.0 ? bound : 1.0;
-            }
-            S[j][j] = sqrt(p);
-        }
-        __syncthreads();
-        if (tid > j && tid < CH_B) S[tid][j] /= S[j][j];
-        __syncthreads();
-        for (int e = tid; e < CH_B * CH_B; e += 256) {
-            const int i = e >> 6, c = e & 63;
-            if (c > j && i >= c) S[i][c] -= S[i][j] * S[c][j];
-        }
-        __syncthreads();
+    double s[CPT], x[CPT];
+    double *mine = A + off + (size_t)row * n + wave * CPT;
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+        s[k] = mine[k];
+        x[k] = row == wave * CPT + k ? 1.0 : 0.0;
     }
-    if (tid < CH_B) {                         // column tid of the inverse, by forward substitution
-        const int c = tid;
-        for (int i = 0; i < CH_B; ++i) {
-            double v = 0.0;
-            if (i >= c) {
-                v = i == c ? 1.0 : 0.0;
-                for (int k = c; k < i; ++k) v -= S[i][k] * X[k][c];
-                v /= S[i][i];
+    for (int jb = 0; jb < 4; ++jb) {
+        const int buf = jb & 1;
+        if (wave == jb) {
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) {
+                const int j = jb * CPT + k;
+                double p = lane_value(s[k], j);
+                if (!(p > bound)) {
+                    if (row == 0) fail[0] = 1;
+                    p = bound > 0.0 ? bound : 1.0;
+                }
+                double inv = __builtin_amdgcn_rsq(p);                 // 1 / sqrt(p), two Newton steps
+#pragma unroll
+                for (int it = 0; it < 2; ++it) inv = __builtin_fma(0.5 * inv, __builtin_fma(-p * inv, inv, 1.0), inv);
+                s[k] = row > j ? s[k] * inv : row == j ? p * inv : 0.0;
+                col[buf][k][row] = s[k];
+                if (row == 0) inv_sh[buf][k] = inv;
+#pragma unroll
+                for (int c = k + 1; c < CPT; ++c) s[c] = __builtin_fma(-s[k], lane_value(s[k], jb * CPT + c), s[c]);
             }
-            X[i][c] = v;
+        }
+        __syncthreads();
+        if (wave > jb) {
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) {
+                const double l = col[buf][k][row];
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) s[c] = __builtin_fma(-l, col[buf][k][wave * CPT + c], s[c]);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) {
+                const int j = jb * CPT + k;
+                const double inv = inv_sh[buf][k], l = row > j ? col[buf][k][row] : 0.0;
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) {
+                    const double xj = lane_value(x[c], j) * inv;
+                    x[c] = row == j ? xj : __builtin_fma(-l, xj, x[c]);
+                }
+            }
         }
     }
-    __syncthreads();
-    for (int e = tid; e < CH_B * CH_B; e += 256) {
-        const int i = e >> 6, c = e & 63;
-        L[toff + (size_t)i * n + c] = c <= i ? S[i][c] : 0.0;
-        invL[e] = X[i][c];
-        invLt[c * CH_B + i] = X[i][c];
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+        mine[k] = row >= wave * CPT + k ? s[k] : 0.0;
+        invL[row * CH_B + wave * CPT + k] = x[k];
     }
 }
 

@@ -97,12 +97,11 @@ inline DgEpilogue minus_from(const double *Cin, int ld)
 
 // ---- work buffers ----
 struct WhitenWs {
-    double *S;                  // [d][d]  the lower Cholesky factor of C = X^T X
-    double *St;                 // [d][d]  S^T
+    double *S;                  // [d][d]  C = X^T X, then its lower Cholesky factor
     double *G;                  // [d][d]  (W S)^T (W S)
-    double *T0, *T1, *T2;       // [d][d]  C, W^T W and the like; later the work matrices of the eigen-decomposition
+    double *T0, *T1, *T2;       // [d][d]  W^T W, (W^T W) S; then the work matrices of the eigen-decomposition
     double *lamG;               // [d] eigenvalues by place
-    double *invL, *invLt;       // [64][64] scratch; [d/64][64][64] transposed inverses of S's diagonal blocks
+    double *invL;               // [d/64][64][64] inverses of S's diagonal blocks
     int32_t *fail;              // set by the factorisation if X^T X is not positive definite
     double *Vr, *Zr;            // [r][d]
     double *out64;              // [max(D, d)][r]
@@ -126,14 +125,12 @@ WhitenWs carve_whiten(void *base, int d, int D, int T, int r)
     };
     const size_t dd = (size_t)d * d;
     w.S = take(dd);
-    w.St = take(dd);
     w.G = take(dd);
     w.T0 = take(dd);
     w.T1 = take(dd);
     w.T2 = take(dd);
     w.lamG = take(d);
-    w.invL = take(64 * 64);
-    w.invLt = take((size_t)d * 64);
+    w.invL = take((size_t)d * 64);
     w.fail = reinterpret_cast<int32_t *>(take(32));
     w.Vr = take((size_t)r * d);
     w.Zr = take((size_t)r * d);
@@ -149,41 +146,41 @@ WhitenWs carve_whiten(void *base, int d, int D, int T, int r)
     return w;
 }
 
-// L (lower, [n][n], zero above the diagonal) with L L^T = C; T: scratch [n][n]; invLt: [n/64][64][64], the
-// transposed inverses of L's diagonal blocks; invL: scratch [64][64]; scale: device double; fail: device int,
-// set to 1 if C is not positive definite to working precision (then L is not to be used).
-void cholesky_blocked(const double *C, double *L, double *T, int n, double *invL, double *invLt, double *scale, int *fail,
-                      const DgScratch &scr, hipStream_t st)
+// The lower triangle of A [n][n] (n a multiple of 64) becomes L with L L^T = A, zero above the diagonal; invL:
+// [n/64][64][64], the inverses of L's diagonal blocks; scale: device double; fail: device int, set to 1 if A is not
+// positive definite to working precision (then L is not to be used).
+void cholesky_blocked(double *A, int n, double *invL, double *scale, int *fail, hipStream_t st)
 {
-    const int nb = n / CH_B;
-    hipLaunchKernelGGL(k_max_diag, dim3(1), dim3(256), 0, st, C, n, scale);
-    for (int k = 0; k < nb; ++k) {
-        const size_t row0 = (size_t)k * CH_B * n, diag = row0 + (size_t)k * CH_B;
-        // T[k:, k] = C[k:, k] - L[k:, :k] L[k, :k]^T   (K = 0 for the first block column: a copy)
-        dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)L + row0, n), op((const double *)L + row0, n), T + diag, n, n - k * CH_B, CH_B, k * CH_B, st, 0,
-                                    minus_from(C + diag, n), scr);
-        hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, T, L, n, diag, scale, 1e-13, invL,
-                           invLt + (size_t)k * CH_B * CH_B, fail);
-        // L[k+1:, k] = T[k+1:, k] Lkk^-T
-        dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)T + diag + (size_t)CH_B * n, n), op((const double *)invL, CH_B), L + diag + (size_t)CH_B * n, n,
-                                    n - (k + 1) * CH_B, CH_B, CH_B, st);
+    hipLaunchKernelGGL(k_max_diag, dim3(1), dim3(256), 0, st, A, n, scale);
+    for (int k = 0; k < n; k += CH_B) {
+        const int p1 = std::min(n, k / CH_PANEL * CH_PANEL + CH_PANEL);       // end of the panel
+        const int k1 = k + CH_B, rest = n - k1;
+        double *inv = invL + (size_t)k * CH_B;
+        hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, A, n, (size_t)k * n + k, scale, 1e-13, inv, fail);
+        const double *below = A + (size_t)k1 * n + k;
+        // in place: a block of the product covers all 64 columns of its rows
+        dgemm<DG_ROWS_K, DG_ROWS_K>(op(below, n), op((const double *)inv, CH_B), A + (size_t)k1 * n + k, n, rest, CH_B, CH_B, st,
+                                    0, DgEpilogue{}, DgScratch{nullptr, 0}, true);
+        double *upd = A + (size_t)k1 * n + k1;
+        dgemm<DG_ROWS_K, DG_ROWS_K>(op(below, n), op(below, n), upd, n, rest, p1 - k1, CH_B, st, 0, minus_from(upd, n));
+        if (k1 == p1 && rest > 0) {
+            const double *pan = A + (size_t)k1 * n + (k1 / CH_PANEL - 1) * CH_PANEL;
+            dgemm<DG_ROWS_K, DG_ROWS_K>(op(pan, n), op(pan, n), upd, n, rest, rest, CH_PANEL, st, DG_LOWER, minus_from(upd, n));
+        }
     }
-    hipLaunchKernelGGL(k_zero_upper_blocks, grid1((size_t)n * n), dim3(256), 0, st, L, n);
+    hipLaunchKernelGGL(k_zero_upper_blocks, grid1((size_t)n * n), dim3(256), 0, st, A, n);
 }
 
-// Bout [r][n] = Bin [r][n] L^-1 for the lower-triangular L given as Lt = L^T [n][n] and the transposed inverses of
-// its diagonal blocks: block back-substitution from the last block column to the first.  tmp: scratch [r][64].
-void solve_right_lower(const double *Bin, double *Bout, int r, int n, const double *Lt, const double *invLt, double *tmp,
-                       const DgScratch &scr, hipStream_t st)
+// Bout [r][n] = Bin [r][n] L^-1 for the lower-triangular L [n][n] and the inverses of its diagonal blocks: block
+// back-substitution from the last block column to the first.  A finished block column is taken out of all columns to
+// its left at once (a wide product with K = 64).  Bin is destroyed.
+void solve_right_lower(double *Bin, double *Bout, int r, int n, const double *L, const double *invL, hipStream_t st)
 {
-    const int nb = n / CH_B;
-    for (int i = nb - 1; i >= 0; --i) {
-        const int c0 = i * CH_B, rest = n - (i + 1) * CH_B;
-        // tmp = Bin[:, i] - Bout[:, i+1:] L[i+1:, i]      (L[k][c0 + a] = Lt[c0 + a][k])
-        dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)Bout + c0 + CH_B, n), op(Lt + (size_t)c0 * n + c0 + CH_B, n), tmp, CH_B, r, CH_B, rest,
-                                    st, 0, minus_from(Bin + c0, n), scr);
-        // Bout[:, i] = tmp Lii^-1
-        dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)tmp, CH_B), op(invLt + (size_t)i * CH_B * CH_B, CH_B), Bout + c0, n, r, CH_B, CH_B, st);
+    for (int c0 = n - CH_B; c0 >= 0; c0 -= CH_B) {
+        dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)Bin + c0, n), op(invL + (size_t)c0 * CH_B, CH_B), Bout + c0, n, r, CH_B,
+                                    CH_B, st);
+        dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)Bout + c0, n), op(L + (size_t)c0 * n, n), Bin, n, r, c0, CH_B, st, 0,
+                                    minus_from(Bin, n));
     }
 }
 
@@ -239,13 +236,13 @@ svdp_status whiten_impl(const void *W_gate, const void *X, int d, int D, int T, 
     constexpr int SYM = DG_LOWER | DG_MIRROR;
 
     // second moments C = X^T X  (d x d) and its Cholesky factor S (lower, S S^T = C)
-    if (!dgemm<DG_K_ROWS, DG_K_ROWS>(op(Xs, d), op(Xs, d), w.T0, d, d, d, T, st, SYM, DgEpilogue{}, scr))
+    if (!dgemm<DG_K_ROWS, DG_K_ROWS>(op(Xs, d), op(Xs, d), w.S, d, d, d, T, st, SYM, DgEpilogue{}, scr))
         return SVDP_ERR_UNSUPPORTED;
     if (hipMemsetAsync(w.fail, 0, 4, st) != hipSuccess) {
         (void)hipGetLastError();
         return SVDP_ERR_HIP;
     }
-    cholesky_blocked(w.T0, w.S, w.T1, d, w.invL, w.invLt, w.sums, w.fail, scr, st);
+    cholesky_blocked(w.S, d, w.invL, w.sums, w.fail, st);
     int32_t failed = 0;
     if (hipMemcpyAsync(&failed, w.fail, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess) {
@@ -254,7 +251,6 @@ svdp_status whiten_impl(const void *W_gate, const void *X, int d, int D, int T, 
     }
     // S needs C positive definite (more independent tokens than dimensions)
     if (failed != 0) return SVDP_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((k_transpose_to_f64<double>), dim3((d + 31) / 32, (d + 31) / 32), dim3(256), 0, st, w.S, d, d, w.St);
 
     // G = (W S)^T (W S) = S^T ((W^T W) S): 2/3 of the products that W S and its Gram matrix would take (S is
     // triangular and both Gram matrices are symmetric), and no D x d matrix in 64 bits is ever stored
@@ -288,7 +284,7 @@ svdp_status whiten_impl(const void *W_gate, const void *X, int d, int D, int T, 
     if (!ok) return SVDP_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(k_f64_to_f32, grid1((size_t)D * r), dim3(256), 0, st, w.out64, (size_t)D * r, Q);
     // B = V_r^T S^-1 (block back-substitution; V_r^T is w.Vr, rows = the chosen eigenvectors), P = B^T
-    solve_right_lower(w.Vr, w.out64, r, d, w.St, w.invLt, w.Zr, scr, st);
+    solve_right_lower(w.Vr, w.out64, r, d, w.S, w.invL, st);
     hipLaunchKernelGGL((k_transpose_to_f64<double>), dim3((d + 31) / 32, (r + 31) / 32), dim3(256), 0, st, w.out64, r, d, w.Vr);
     hipLaunchKernelGGL(k_f64_to_f32, grid1((size_t)d * r), dim3(256), 0, st, w.Vr, (size_t)d * r, P);
     if (hipStreamSynchronize(st) != hipSuccess) {                 // order[] leaves scope: the copy above must be done
