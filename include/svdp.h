@@ -239,10 +239,11 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
  * Outputs in the library's letters, fp32, device: Q = A [D][r], P = B^T [d][r], so that the predictor's
  * scores are (x P) Q^T; the caller rounds them to the layer's storage type.  sigma [r] (host, nullable):
  * the r leading singular values of W_gate S, descending.  sweeps [2] (host, nullable): sweeps[0] = 0,
- * sweeps[1] = block-Jacobi sweeps the eigen-decomposition took.
+ * sweeps[1] = block-Jacobi sweeps that the (last projected) eigen-decomposition took.
  * S is the lower Cholesky factor of X^T X, as Alg. 1 prints it (blocked factorisation, 64-wide blocks);
- * V and Sigma^2 come from the symmetric eigen-decomposition of (W_gate S)^T (W_gate S) by block Jacobi
- * sweeps, and S^-1 is applied to the r chosen vectors by block back-substitution.  All arithmetic is
+ * V and Sigma^2 are the r leading eigenpairs of (W_gate S)^T (W_gate S), by subspace iteration with Chebyshev
+ * filters to residuals of 2e-13 of its norm (block Jacobi sweeps on the projections; on the whole matrix where r is
+ * more than about 0.4 d or no gap follows the r-th value), and S^-1 is applied to the r chosen vectors by block back-substitution.  All arithmetic is
  * fp64, the contractions on the matrix cores.
  * Needs d a multiple of 64, T >= d and X^T X positive definite to working precision (every pivot of
  * the factorisation above 1e-13 of the largest diagonal element), r <= d; otherwise

@@ -11,11 +11,11 @@
 #include "svdp_calib.h"
 #include "svdp_calib_stats.h"
 #include "svdp_whiten.h"
+#include "svdp_eigtop.h"
 
 #include <algorithm>
 #include <atomic>
 #include <cmath>
-#include <numeric>
 #include <mutex>
 #include <type_traits>
 #include <vector>
@@ -481,6 +481,8 @@ void *static_scratch()
 }
 
 #include "svdp_whiten_run.h"
+#include "svdp_eigtop_run.h"
+#include "svdp_whiten_call.h"
 
 }  // namespace
 

@@ -95,57 +95,6 @@ inline DgEpilogue minus_from(const double *Cin, int ld)
     return e;
 }
 
-// ---- work buffers ----
-struct WhitenWs {
-    double *S;                  // [d][d]  C = X^T X, then its lower Cholesky factor
-    double *G;                  // [d][d]  (W S)^T (W S)
-    double *T0, *T1, *T2;       // [d][d]  W^T W, (W^T W) S; then the work matrices of the eigen-decomposition
-    double *lamG;               // [d] eigenvalues by place
-    double *invL;               // [d/64][64][64] inverses of S's diagonal blocks
-    int32_t *fail;              // set by the factorisation if X^T X is not positive definite
-    double *Vr, *Zr;            // [r][d]
-    double *out64;              // [max(D, d)][r]
-    double *part;               // parts of split products
-    size_t n_part;
-    double *Uall, *rowsums, *sums;     // [d/64][64][64] strip transforms; norms
-    int32_t *sel;               // [r]
-    size_t bytes;
-};
-
-WhitenWs carve_whiten(void *base, int d, int D, int T, int r)
-{
-    (void)T;
-    WhitenWs w;
-    char *p = static_cast<char *>(base);
-    size_t off = 0;
-    auto take = [&](size_t n_doubles) {
-        double *q = reinterpret_cast<double *>(p + off);
-        off += align_up(n_doubles * 8);
-        return q;
-    };
-    const size_t dd = (size_t)d * d;
-    w.S = take(dd);
-    w.G = take(dd);
-    w.T0 = take(dd);
-    w.T1 = take(dd);
-    w.T2 = take(dd);
-    w.lamG = take(d);
-    w.invL = take((size_t)d * 64);
-    w.fail = reinterpret_cast<int32_t *>(take(32));
-    w.Vr = take((size_t)r * d);
-    w.Zr = take((size_t)r * d);
-    w.out64 = take((size_t)(D > d ? D : d) * r);
-    w.n_part = (size_t)16 * 512 * 512;
-    w.part = take(w.n_part);
-    w.Uall = take((size_t)d * 64);
-    w.rowsums = take((size_t)2 * d);
-    w.sums = take(2);
-    w.sel = reinterpret_cast<int32_t *>(p + off);
-    off += align_up((size_t)r * 4);
-    w.bytes = off;
-    return w;
-}
-
 // The lower triangle of A [n][n] (n a multiple of 64) becomes L with L L^T = A, zero above the diagonal; invL:
 // [n/64][64][64], the inverses of L's diagonal blocks; scale: device double; fail: device int, set to 1 if A is not
 // positive definite to working precision (then L is not to be used).
@@ -221,82 +170,3 @@ svdp_status jacobi_eigh(double **A, double **Aalt, double **V, double **Valt, in
     if (sweeps_out != nullptr) *sweeps_out = sweep;
     return hip_status(hipSuccess);
 }
-
-template <typename W>
-svdp_status whiten_impl(const void *W_gate, const void *X, int d, int D, int T, int r, float *P, float *Q, float *sigma,
-                        int32_t *sweeps, const WhitenWs &w, hipStream_t st)
-{
-    const W *Wg = static_cast<const W *>(W_gate), *Xs = static_cast<const W *>(X);
-    const double tol = 1e-11;          // off-diagonal Frobenius norm relative to the matrix's
-    const int max_sweeps = 24;
-    std::vector<double> lam(d);
-    std::vector<int32_t> order(d);
-
-    const DgScratch scr{w.part, w.n_part};
-    constexpr int SYM = DG_LOWER | DG_MIRROR;
-
-    // second moments C = X^T X  (d x d) and its Cholesky factor S (lower, S S^T = C)
-    if (!dgemm<DG_K_ROWS, DG_K_ROWS>(op(Xs, d), op(Xs, d), w.S, d, d, d, T, st, SYM, DgEpilogue{}, scr))
-        return SVDP_ERR_UNSUPPORTED;
-    if (hipMemsetAsync(w.fail, 0, 4, st) != hipSuccess) {
-        (void)hipGetLastError();
-        return SVDP_ERR_HIP;
-    }
-    cholesky_blocked(w.S, d, w.invL, w.sums, w.fail, st);
-    int32_t failed = 0;
-    if (hipMemcpyAsync(&failed, w.fail, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess) {
-        (void)hipGetLastError();
-        return SVDP_ERR_HIP;
-    }
-    // S needs C positive definite (more independent tokens than dimensions)
-    if (failed != 0) return SVDP_ERR_UNSUPPORTED;
-
-    // G = (W S)^T (W S) = S^T ((W^T W) S): 2/3 of the products that W S and its Gram matrix would take (S is
-    // triangular and both Gram matrices are symmetric), and no D x d matrix in 64 bits is ever stored
-    bool ok = dgemm<DG_K_ROWS, DG_K_ROWS>(op(Wg, d), op(Wg, d), w.T0, d, d, d, D, st, SYM, DgEpilogue{}, scr) &&
-              dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.T0, d), op((const double *)w.S, d), w.T1, d, d, d, d, st,
-                                          DG_K_FROM_N, DgEpilogue{}, scr) &&
-              dgemm<DG_K_ROWS, DG_K_ROWS>(op((const double *)w.S, d), op((const double *)w.T1, d), w.G, d, d, d, d, st,
-                                          SYM | DG_K_FROM_M, DgEpilogue{}, scr);
-    if (!ok) return SVDP_ERR_UNSUPPORTED;
-    double *A = w.G, *Aalt = w.T0, *V = w.T1, *Valt = w.T2;
-    int sw2 = 0;
-    svdp_status e = jacobi_eigh(&A, &Aalt, &V, &Valt, d, w.Uall, w.rowsums, w.sums, w.lamG, tol, max_sweeps, &sw2, st);
-    if (e != SVDP_OK) return e;
-    if (hipMemcpyAsync(lam.data(), w.lamG, (size_t)d * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess) {
-        (void)hipGetLastError();
-        return SVDP_ERR_HIP;
-    }
-    // the r largest eigenvalues (= squared singular values of W S), largest first; ties by place
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return lam[a] > lam[b]; });
-    if (hipMemcpyAsync(w.sel, order.data(), (size_t)r * 4, hipMemcpyHostToDevice, st) != hipSuccess) {
-        (void)hipGetLastError();
-        return SVDP_ERR_HIP;
-    }
-    // Q = A = W (S V_r)
-    hipLaunchKernelGGL(k_gather_rows, grid1((size_t)r * d), dim3(256), 0, st, V, w.sel, r, d, w.Vr);
-    ok = dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)w.Vr, d), op((const double *)w.S, d), w.Zr, d, r, d, d, st, DG_K_UPTO_N,
-                                     DgEpilogue{}, scr) &&
-         dgemm<DG_ROWS_K, DG_ROWS_K>(op(Wg, d), op((const double *)w.Zr, d), w.out64, r, D, r, d, st, 0, DgEpilogue{}, scr);
-    if (!ok) return SVDP_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(k_f64_to_f32, grid1((size_t)D * r), dim3(256), 0, st, w.out64, (size_t)D * r, Q);
-    // B = V_r^T S^-1 (block back-substitution; V_r^T is w.Vr, rows = the chosen eigenvectors), P = B^T
-    solve_right_lower(w.Vr, w.out64, r, d, w.S, w.invL, st);
-    hipLaunchKernelGGL((k_transpose_to_f64<double>), dim3((d + 31) / 32, (r + 31) / 32), dim3(256), 0, st, w.out64, r, d, w.Vr);
-    hipLaunchKernelGGL(k_f64_to_f32, grid1((size_t)d * r), dim3(256), 0, st, w.Vr, (size_t)d * r, P);
-    if (hipStreamSynchronize(st) != hipSuccess) {                 // order[] leaves scope: the copy above must be done
-        (void)hipGetLastError();
-        return SVDP_ERR_HIP;
-    }
-    if (sigma != nullptr)
-        for (int k = 0; k < r; ++k) sigma[k] = (float)std::sqrt(std::max(lam[order[k]], 0.0));
-    if (sweeps != nullptr) {
-        sweeps[0] = 0;              // the factor of the second moments is a Cholesky factor: no sweeps
-        sweeps[1] = sw2;
-    }
-    return hip_status(hipSuccess);
-}
-

@@ -139,3 +139,42 @@ def test_contractions_at_ragged_sizes_and_unaligned_inputs(env, d, D, T, r, dt):
     QP, AB = Q.cpu().numpy().astype(np.float64) @ P.cpu().numpy().astype(np.float64).T, A @ B
     err, best, scale = np.linalg.norm((W - QP) @ X.T), np.linalg.norm((W - AB) @ X.T), np.linalg.norm(W @ X.T)
     assert abs(err - best) <= 2e-5 * scale
+
+
+@pytest.mark.parametrize("kind,d,r", [
+    ("mean", 512, 128),       # one direction with 1e6 times the energy: leaves the block, which is refilled
+    ("flat", 320, 96),        # no gap behind the wanted vectors; block of 128 rows
+    ("flat", 384, 128),       # block of 192 rows = d / 2, the largest that is iterated
+    ("flat", 384, 161),       # one rank above it: the full decomposition
+    ("ties", 256, 40),        # all eigenvalues equal: nothing to iterate on, the full decomposition takes over
+    ("rank", 256, 40),        # rank 20 < r
+    ("zero", 128, 8),         # nothing at all
+])
+def test_leading_eigenvectors_over_spectra(env, kind, d, r):
+    """The leading-eigenvector iteration and its hand-over to the full decomposition: the minimised error and the
+    singular values against the oracle.  Tolerance: the factors are rounded to fp32 (2^-24 each), so the product moves by
+    at most 2 * 2^-24 * sum_k |Q_ik||P_jk| <= 2 * 2^-24 * sqrt(r) * |W| on the tokens, 1.5e-6 at r = 161."""
+    binding, torch, calib = env
+    rng = np.random.default_rng(d + r)
+    D, T = 2 * d + 64, 2 * d
+    W, X = rng.standard_normal((D, d)) / np.sqrt(d), rng.standard_normal((T, d))
+    if kind == "mean":
+        u = rng.standard_normal(d)
+        W, X = W - 40.0 * u / np.linalg.norm(u), X + 3.0 * u
+    elif kind == "ties":
+        W, X = np.linalg.qr(W)[0], np.linalg.qr(X)[0]
+    elif kind == "rank":
+        W = W[:, :20] @ rng.standard_normal((20, d))
+    elif kind == "zero":
+        W = np.zeros_like(W)
+    W, X = W.astype(np.float32), X.astype(np.float32)
+    P, Q, sigma, sweeps = binding.whiten_factors(torch.from_numpy(W).cuda(), torch.from_numpy(X).cuda(), r)
+    W, X = W.astype(np.float64), X.astype(np.float64)
+    A, B = calib.whitened_factors(W, X, r)
+    QP = Q.cpu().numpy().astype(np.float64) @ P.cpu().numpy().astype(np.float64).T
+    scale = np.linalg.norm(W @ X.T)
+    assert abs(np.linalg.norm((W - QP) @ X.T) - np.linalg.norm((W - A @ B) @ X.T)) <= 2e-6 * scale
+    sv = np.linalg.norm(A, axis=0)
+    # fp32, and eigenvalues of a Gram matrix: an error of 1e-13 of the largest is 3e-7 of its root where sigma is zero
+    assert np.all(np.abs(sigma - sv) <= 1e-6 * sv[0])
+    assert np.all(np.diff(sigma) <= 0) and 0 <= sweeps[1] <= 24
