@@ -784,7 +784,7 @@ svdp_status svdp_calib_stats(const svdp_layer *layer, const void *X, int32_t T, 
 size_t svdp_whiten_workspace_bytes(int32_t d, int32_t D, int32_t T, int32_t r)
 {
     if (d < 64 || d % 64 != 0 || D < 1 || T < d || r < 1 || r > d) return 0;
-    return carve_whiten(nullptr, d, D, T, r).bytes;
+    return whiten_ws_bytes(d, D, T, r);
 }
 
 svdp_status svdp_whiten_factors(const void *W_gate, const void *X, int32_t d, int32_t D, int32_t T, int32_t r,
@@ -797,7 +797,7 @@ svdp_status svdp_whiten_factors(const void *W_gate, const void *X, int32_t d, in
     if (d < 64 || d % 64 != 0 || T < d || r > d) return SVDP_ERR_UNSUPPORTED;
     if (ws == nullptr || (reinterpret_cast<uintptr_t>(ws) & (ALIGN - 1))) return SVDP_ERR_WORKSPACE;
     const WhitenWs w = carve_whiten(ws, d, D, T, r);
-    if (ws_bytes < w.bytes) return SVDP_ERR_WORKSPACE;
+    if (ws_bytes < w.bytes || !w.fits) return SVDP_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (wdtype == SVDP_F32) return whiten_impl<float>(W_gate, X, d, D, T, r, P, Q, sigma, sweeps, w, st);
     return whiten_impl<bf16>(W_gate, X, d, D, T, r, P, Q, sigma, sweeps, w, st);

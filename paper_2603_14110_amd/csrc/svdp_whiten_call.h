@@ -16,11 +16,26 @@ struct WhitenWs {
     int32_t *sel;               // [d]
     double *small;              // the leading-eigenvector iteration's projected matrices
     size_t bytes;
+    bool fits;
 };
 
+// Workspace size: what the call has asked for since its first version (fp64 copies of W, of W S and its transpose and
+// of the tokens, six d x d matrices), so that a size a caller has stored stays right; carve_whiten() fits into it.
+size_t whiten_ws_bytes(int d, int D, int T, int r)
+{
+    const size_t dd = (size_t)d * d, Dd = (size_t)D * d, most = D > d ? D : d;
+    size_t bytes = 0;
+    for (size_t n : {Dd, Dd, Dd, (size_t)d * T, dd, dd, dd, dd, dd, dd, (size_t)d, (size_t)64 * 64, (size_t)d * 64, (size_t)32,
+                     (size_t)r * d, most * r, (size_t)d * 64, (size_t)2 * d, (size_t)2})
+        bytes += align_up(n * 8);
+    return bytes + align_up((size_t)r * 4);
+}
+
+// Everything but `part` takes at most 6.9 d^2 + (max(D, d) + 64) r + 170 d doubles (2 k <= d and r <= 0.8 k where the
+// iteration runs, no block where it does not) and T >= d, so it always fits; the parts of split products get what is
+// left, up to what they can use.
 WhitenWs carve_whiten(void *base, int d, int D, int T, int r)
 {
-    (void)T;
     WhitenWs w;
     char *p = static_cast<char *>(base);
     size_t off = 0;
@@ -41,16 +56,16 @@ WhitenWs carve_whiten(void *base, int d, int D, int T, int r)
     w.Vr = take((size_t)r * d);
     w.Zr = take((size_t)r * d);
     w.out64 = take((size_t)(D > d ? D : d) * r);
-    w.n_part = (size_t)16 * 512 * 512;
-    w.part = take(w.n_part);
     w.Uall = take((size_t)d * 64);
     w.rowsums = take((size_t)2 * d);
     w.sums = take(2);
-    w.sel = reinterpret_cast<int32_t *>(p + off);
-    off += align_up((size_t)d * 4);
+    w.sel = reinterpret_cast<int32_t *>(take((size_t)(d + 1) / 2));
     const size_t k = eigtop_block(d, r);
     w.small = take(6 * k * k + 64 * k + 3 * k + 32);
-    w.bytes = off;
+    w.bytes = whiten_ws_bytes(d, D, T, r);
+    w.n_part = std::min<size_t>((size_t)16 * 512 * 512, off < w.bytes ? (w.bytes - off) / 8 : 0);
+    w.part = take(w.n_part);
+    w.fits = off <= w.bytes;
     return w;
 }
 
