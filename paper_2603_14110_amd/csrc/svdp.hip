@@ -764,20 +764,30 @@ svdp_status svdp_calib_stats(const svdp_layer *layer, const void *X, int32_t T, 
     const bf16 *Xb = static_cast<const bf16 *>(X);
     auto tiles = [](int n, int b) { return (n + b - 1) / b; };
 
+    if (!grant_lds<k_gemm_wide>(GW_LDS)) return SVDP_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(k_row_norm2, dim3(tiles(D, 4)), dim3(256), 0, st, static_cast<const bf16 *>(layer->W_downT), D, d,
                        cn);
     hipLaunchKernelGGL(k_transpose16, dim3(tiles(r, 32), tiles(d, 32)), dim3(256), 0, st,
                        static_cast<const uint16_t *>(layer->P), d, r, reinterpret_cast<uint16_t *>(Pt));
-    // w = (ReLU(W_gate X^T) * (W_up X^T))^2 * cn
-    hipLaunchKernelGGL((k_gemm_nt<2, EPI_DAMAGE>), dim3(tiles(T, GM_BN), tiles(D, GM_BM)), dim3(GM_THREADS), 0, st, Wg,
-                       Wu, d, d, Xb, d, D, T, d, cn, w, nullptr, T);
-    // t = X P, split
-    hipLaunchKernelGGL((k_gemm_nt<1, EPI_SPLIT3>), dim3(tiles(r, GM_BN), tiles(T, GM_BM)), dim3(GM_THREADS), 0, st, Xb,
-                       nullptr, d, d, Pt, d, T, r, d, nullptr, nullptr, tp, 3 * r);
-    // s = Q t^T over the three terms
-    hipLaunchKernelGGL((k_gemm_nt<1, EPI_PLAIN>), dim3(tiles(T, GM_BN), tiles(D, GM_BM)), dim3(GM_THREADS), 0, st,
-                       static_cast<const bf16 *>(layer->Q), nullptr, r, r, reinterpret_cast<const bf16 *>(tp), 3 * r, D,
-                       T, 3 * r, nullptr, s, nullptr, T);
+    // t = X P, split into three terms.  Its tiles alone are few (32 at r = 256, T = 2048: 90 us on an eighth of the chip,
+    // 16 + 5 us in eight parts), so they are cut along K into as many parts as fill it; the parts meet in s, which the
+    // last launch overwrites.
+    const int t_tiles = tiles(r, GM_BN) * tiles(T, GM_BM);
+    const int parts = std::max(1, std::min({256 / t_tiles, d / 256, D / r, 16}));
+    const int kpart = round_up(tiles(d, parts), GM_BK), nz = tiles(d, kpart);
+    if (nz > 1) {
+        hipLaunchKernelGGL((k_gemm_nt<EPI_PLAIN>), dim3(tiles(r, GM_BN), tiles(T, GM_BM), nz), dim3(GM_THREADS), 0, st, Xb,
+                           d, Pt, d, T, r, d, s, nullptr, r, kpart);
+        hipLaunchKernelGGL(k_sum_split3, dim3(tiles(T * r, 256)), dim3(256), 0, st, s, nz, T, r, tp);
+    } else {
+        hipLaunchKernelGGL((k_gemm_nt<EPI_SPLIT3>), dim3(tiles(r, GM_BN), tiles(T, GM_BM)), dim3(GM_THREADS), 0, st, Xb,
+                           d, Pt, d, T, r, d, nullptr, tp, 3 * r, d);
+    }
+    // w = (ReLU(W_gate X^T) * (W_up X^T))^2 * cn and s = Q t^T over the three terms
+    const bf16 *Qb = static_cast<const bf16 *>(layer->Q), *tb = reinterpret_cast<const bf16 *>(tp);
+    const WideJob jw = wide_job(Wg, Wu, d, d, Xb, d, D, T, d, cn, w, T), js = wide_job(Qb, nullptr, r, r, tb, 3 * r, D, T, 3 * r,
+                                                                                      nullptr, s, T);
+    hipLaunchKernelGGL(k_gemm_wide, dim3(jw.tiles + js.tiles), dim3(GW_THREADS), GW_LDS, st, jw, js);
     return hip_status(hipSuccess);
 }
 

@@ -158,6 +158,24 @@ def test_stats_against_the_oracle(env, shape):
     assert np.all(w >= 0) and np.all((w == 0) | (g > -eg))
 
 
+@pytest.mark.parametrize("d,D,r,T", [(96, 704, 16, 513), (520, 1216, 88, 300), (32, 64, 8, 3)])
+def test_stats_of_tokens_on_any_boundary(env, d, D, r, T):
+    """Tokens that start on no 16-byte boundary take another way into local memory: the same bits.  Sizes: ragged last
+    tiles in both directions, K steps that end in 8 and in none, fewer K steps than stages."""
+    binding, torch, calib = env
+    f, dev, Xd = _bf16_layer(env, 900 + d, d, D, r, T)
+    flat = torch.empty(T * d + 1, dtype=Xd.dtype, device="cuda")
+    flat[1:] = Xd.flatten()
+    w, s = binding.calib_stats(dev, Xd)
+    w2, s2 = binding.calib_stats(dev, flat[1:].view(T, d))
+    assert torch.equal(w, w2) and torch.equal(s, s2)
+    s_or = calib.proxy_scores(f["Q"], f["P"].T, f["X"])
+    assert np.all(np.abs(s.cpu().numpy() - s_or) <= 2e-5 * np.abs(s_or).max(axis=0, keepdims=True))
+    w_or = calib.damage_weights(f["W_gate"], f["W_up"], f["W_downT"], f["X"])
+    # fp32 sums of d exact products, twice, squared: 4 d 2^-24 of a typical weight
+    assert np.linalg.norm(w.cpu().numpy() - w_or) <= 4 * d * 2.0 ** -24 * np.linalg.norm(w_or)
+
+
 def test_statistics_then_calibration_end_to_end(env):
     """The two GPU calls chained, against the oracle's pipeline on its own fp64 statistics: the pointers may
     differ where costs agree to rounding, the achieved sparsity and the loss may not."""
