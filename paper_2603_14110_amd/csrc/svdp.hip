@@ -703,21 +703,32 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
     float *tauc = reinterpret_cast<float *>(p);
     p += align_up((size_t)D * (MS + 1) * 4);
     int32_t *k0 = reinterpret_cast<int32_t *>(p);
-    int n2 = 1;
-    while (n2 < T) n2 <<= 1;
-    const size_t lds = (size_t)n2 * 8 + (size_t)T * 8 + (size_t)(MS + 1) * 8;
-    if (!grant_lds<k_calib_sort>(lds)) return SVDP_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(k_calib_sort, dim3(D), dim3(CAL_THREADS), lds, st, w, s, T, n2, eta, MS, key, drop, tauc, k0,
-                       kendall);
-    svdp_status e = hip_status(hipSuccess);
-    if (e != SVDP_OK) return e;
     p += align_up((size_t)D * 4);
     SelectState *state = reinterpret_cast<SelectState *>(p);
     p += align_up(sizeof(SelectState));
     long long *hist = reinterpret_cast<long long *>(p);
+    p += align_up((size_t)SEL_BINS * 8);
+    int32_t *lo = reinterpret_cast<int32_t *>(p);                // before the selection: dropped pairs at the start
+    p += align_up((size_t)D * 4);
+    int32_t *up = reinterpret_cast<int32_t *>(p);
+    int n2 = 1;
+    while (n2 < T) n2 <<= 1;
+    auto sort = [&](auto per) {
+        constexpr int PER = decltype(per)::value;
+        const size_t lds = calib_sort_lds<PER>(n2, MS);
+        if (!grant_lds<k_calib_sort<PER>>(lds)) return SVDP_ERR_UNSUPPORTED;
+        hipLaunchKernelGGL(k_calib_sort<PER>, dim3(D), dim3(CAL_THREADS), lds, st, w, s, T, n2, eta, MS, key, drop, tauc, k0,
+                           lo, kendall);
+        return hip_status(hipSuccess);
+    };
+    svdp_status e = T <= 2 * CAL_THREADS ? sort(std::integral_constant<int, 2>{})
+                    : T <= 4 * CAL_THREADS ? sort(std::integral_constant<int, 4>{})
+                    : T <= 8 * CAL_THREADS ? sort(std::integral_constant<int, 8>{})
+                                           : sort(std::integral_constant<int, 16>{});
+    if (e != SVDP_OK) return e;
     const size_t items = (size_t)D * MS;
-    const int hb = (int)((items + 256 * 8 - 1) / (256 * 8) < 2048 ? (items + 256 * 8 - 1) / (256 * 8) : 2048);
-    hipLaunchKernelGGL(k_select_init, dim3(1), dim3(SEL_THREADS), 0, st, drop, D, MS, (long long)need, state, hist);
+    const int hb = (int)std::min<size_t>((items + 256 * SEL_RUN - 1) / (256 * SEL_RUN), 256);       // more of them only meet at the counters
+    hipLaunchKernelGGL(k_select_init, dim3(1), dim3(SEL_THREADS), 0, st, lo, D, (long long)need, state, hist, steps);
     hipLaunchKernelGGL((k_select_hist<23, 8>), dim3(hb), dim3(256), 0, st, key, drop, D, MS, state, hist);
     hipLaunchKernelGGL((k_select_pick<23, true>), dim3(1), dim3(64), 0, st, state, hist);
     hipLaunchKernelGGL((k_select_hist<15, 8>), dim3(hb), dim3(256), 0, st, key, drop, D, MS, state, hist);
@@ -726,13 +737,11 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
     hipLaunchKernelGGL((k_select_pick<7, false>), dim3(1), dim3(64), 0, st, state, hist);
     hipLaunchKernelGGL((k_select_hist<0, 7>), dim3(hb), dim3(256), 0, st, key, drop, D, MS, state, hist);
     hipLaunchKernelGGL((k_select_pick<0, false>), dim3(1), dim3(64), 0, st, state, hist);
-    p += align_up((size_t)SEL_BINS * 8);
-    int32_t *lo = reinterpret_cast<int32_t *>(p);
-    p += align_up((size_t)D * 4);
-    int32_t *up = reinterpret_cast<int32_t *>(p);
-    hipLaunchKernelGGL(k_select_bounds, dim3((D + 255) / 256), dim3(256), 0, st, key, D, MS, state, lo, up);
-    hipLaunchKernelGGL(k_select_finish, dim3(1), dim3(SEL_THREADS), 0, st, lo, up, drop, tauc, k0, D, T, eta, MS, state, b,
-                       k, steps);
+    // the digit counts are done with: their place holds the blocks' gains, so there are at most SEL_BINS blocks
+    const int chunk = (int)(((long long)D + 256 * SEL_BINS - 1) / (256 * SEL_BINS)) * 256, blocks = (D + chunk - 1) / chunk;
+    hipLaunchKernelGGL(k_select_bounds, dim3(blocks), dim3(256), 0, st, key, drop, D, MS, chunk, state, lo, up, hist);
+    hipLaunchKernelGGL(k_select_finish, dim3(blocks), dim3(256), 0, st, lo, up, drop, tauc, k0, D, T, eta, MS, chunk, state, hist,
+                       b, k, steps);
     return hip_status(hipSuccess);
 }
 

@@ -11,15 +11,15 @@
 // kernels follow from it:
 //   k_calib_sort   one block per neuron: the samples from the first positive weight
 //                  on (in the order by score, ties by sample index) are sorted
-//                  in LDS, the ones below only counted; step costs (fp32, left
+//                  in LDS by buckets, the ones below only counted; step costs (fp32, left
 //                  to right), their running maxima, and for every step the
 //                  number of dropped samples and the threshold it would set;
 //                  optionally the Kendall check of App. A.
 //   k_select_*     the cost level at which the required number of pairs is first
 //                  reached, by a radix select over the keys' bit patterns
-//                  (four digit passes, integer atomics); then one block takes
-//                  the steps at exactly that level in neuron order and writes
-//                  b = -tau and the pointers.
+//                  (four digit passes, integer atomics); then the steps at
+//                  exactly that level are taken in neuron order, and b = -tau
+//                  and the pointers written.
 // Integer results equal the sequential algorithm's bit for bit.
 #pragma once
 
@@ -27,7 +27,7 @@
 
 namespace svdp {
 
-constexpr int CAL_THREADS = 512;
+constexpr int CAL_THREADS = 256;
 constexpr int CAL_MAX_T = 4096;
 constexpr int SEL_THREADS = 1024;
 
@@ -38,93 +38,217 @@ __device__ __forceinline__ uint32_t ordered_bits(float v)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+__device__ __forceinline__ float from_ordered_bits(uint32_t u)
+{
+    return __uint_as_float((u & 0x80000000u) ? u ^ 0x80000000u : ~u);
+}
+
 // Per-neuron tables written by k_calib_sort, MS = ceil(T / eta) steps at most:
 //   key  [D][MS]     running maximum of the step costs, +inf beyond the neuron's last step
 //   drop [D][MS + 1] number of samples with s <= tau after 0, 1, 2, ... steps
 //   tauc [D][MS + 1] the threshold after 0, 1, 2, ... steps
 //   k0   [D]         the starting pointer (1-based count)
+//   drop0[D]         drop[.][0] once more, side by side
 // Only the part of the order that the algorithm walks is sorted: everything below the first sample
 // with a positive weight (in the order by score, then sample index) is merely counted -- those
 // samples have zero weight and are dropped from the start -- and the rest, the "tail", typically a
-// tenth of the samples of a sparse layer, goes through a bitonic sort sized to it.
-// Dynamic LDS: n2*8 (sort keys) + 2*T*4 (sorted tail: s, w) + 2*(MS+1)*4 bytes, n2 = T rounded up to a power of two.
+// tenth to a third of the samples of a sparse layer, is sorted by score, then sample index.
+// Bound: the dependent phases of a block (barriers, LDS round trips, two trips to memory), not the 16 KB a neuron reads.
+// A bitonic network takes 55 steps with a barrier each at 1024 keys.  Instead a sample's bucket is a linear function of its
+// score between the tail's ends (monotone in fp32 too), a counting pass gives the buckets' places, and inside a bucket (one
+// to three samples on the scores of a layer) a sample's rank is the number of smaller keys: the number of barriers does not
+// depend on the length.  A bucket of more than CAL_BUCKET_MAX samples (many equal scores, an outlier that leaves everybody
+// else in one bucket, an infinite score) sends the neuron to the network.
+// Measured at D = 11008, T = 2048, eta = 16: network 450 us, buckets 131 us (512 threads, 64-bit reductions), 117 us with
+// the sorted tail in the keys' place (four blocks a compute unit instead of three), 91 us with 256 threads, reductions on
+// the scores alone and the ranks taken by tail position (660 -> 370 vector instructions a wave, half the waves).
+// Scores and weights are read once and stay in registers, PER of each per thread (T <= PER * CAL_THREADS).
+// Dynamic LDS: calib_sort_lds().
+constexpr int CAL_BUCKET_MAX = 32;
+template <int PER>
+constexpr int cal_buckets() { return PER <= 8 ? 1024 : 2048; }
+
+// sort keys (n2 = T rounded up to a power of two), later the sorted tail (s, w) in their place; costs and their running
+// maxima; buckets.  26 KB at T = 2048, eta = 16: six blocks a compute unit.
+template <int PER>
+size_t calib_sort_lds(int n2, int MS)
+{
+    return (size_t)n2 * 8 + (size_t)(MS + 1) * 8 + (size_t)cal_buckets<PER>() * 8;
+}
+
+template <int PER>
 __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restrict__ w, const float *__restrict__ s,
                                                             int T, int n2max, int eta, int MS,
                                                             float *__restrict__ key, int32_t *__restrict__ drop,
                                                             float *__restrict__ tauc, int32_t *__restrict__ k0_out,
-                                                            float *__restrict__ kendall)
+                                                            int32_t *__restrict__ drop0, float *__restrict__ kendall)
 {
+    constexpr int NBK = cal_buckets<PER>(), BPT = NBK / CAL_THREADS, WAVES = CAL_THREADS / 64;
     extern __shared__ unsigned long long smem64[];
-    unsigned long long *sk = smem64;                               // [n2max]
-    float *ss = reinterpret_cast<float *>(sk + n2max);             // [T] scores of the tail, sorted
-    float *ww = ss + T;                                            // [T] weights in that order
-    float *cost = ww + T;                                          // [MS + 1]
+    unsigned long long *sk = smem64;                               // [n2max] (score, sample) of the tail
+    float *ss = reinterpret_cast<float *>(sk);                     // [n2max] scores of the tail, sorted
+    float *ww = ss + n2max;                                        // [n2max] weights in that order
+    float *cost = ww + n2max;                                      // [MS + 1]
     float *scan = cost + (MS + 1);                                 // [MS + 1]
-    __shared__ unsigned long long kmin_sh;                         // smallest (score, sample) key with a positive weight
-    __shared__ unsigned long long kmax_sh;                         // largest (score, sample) key: the last sample in sorted order
-    __shared__ int below_sh, fill_sh, kd_total;
-    const int i = blockIdx.x, tid = threadIdx.x;
+    uint32_t *hist = reinterpret_cast<uint32_t *>(scan + (MS + 1));        // [NBK] samples of a bucket
+    uint32_t *start = hist + NBK;                                  // [NBK] samples in front of it
+    __shared__ float lo_w[WAVES], hi_w[WAVES];
+    __shared__ int wave_tot[WAVES], first_sh, big_sh, kd_total;
+    __shared__ unsigned long long last_sh;
+    const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float *si = s + (size_t)i * T, *wi = w + (size_t)i * T;
-    auto key_of = [&](int t) { return ((unsigned long long)ordered_bits(si[t]) << 32) | (unsigned)t; };
+    auto key_of = [&](float v, int t) { return ((unsigned long long)ordered_bits(v) << 32) | (unsigned)t; };
 
+    // samples beyond the last: a score below all, no weight
+    float sv[PER], wv[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int t = tid + q * CAL_THREADS;
+        sv[q] = t < T ? si[t] : -__builtin_inff();
+        wv[q] = t < T ? wi[t] : 0.f;
+    }
     if (tid == 0) {
-        kmin_sh = ~0ull;
-        kmax_sh = 0ull;
-        below_sh = 0;
-        fill_sh = 0;
+        first_sh = T;
+        big_sh = 0;
         kd_total = 0;
+        last_sh = 0ull;
+    }
+#pragma unroll
+    for (int q = 0; q < BPT; ++q) hist[tid + q * CAL_THREADS] = 0u;
+    // the smallest score with a positive weight (+inf if there is none), the largest score
+    float s_lo = __builtin_inff(), s_hi = -__builtin_inff();
+    bool some = false;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        s_lo = wv[q] > 0.f ? fminf(s_lo, sv[q]) : s_lo;
+        some = some || wv[q] > 0.f;
+        s_hi = fmaxf(s_hi, sv[q]);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        s_lo = fminf(s_lo, __shfl_xor(s_lo, off));
+        s_hi = fmaxf(s_hi, __shfl_xor(s_hi, off));
+    }
+    if (lane == 0) {
+        lo_w[wave] = s_lo;
+        hi_w[wave] = s_hi;
+    }
+    const bool any = __syncthreads_or(some ? 1 : 0) != 0;
+#pragma unroll
+    for (int v = 0; v < WAVES; ++v) {
+        s_lo = fminf(s_lo, lo_w[v]);
+        s_hi = fmaxf(s_hi, hi_w[v]);
+    }
+    // where the tail begins among equal scores: the first sample with that score and a positive weight
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (wv[q] > 0.f && sv[q] == s_lo) atomicMin(&first_sh, tid + q * CAL_THREADS);
+    __syncthreads();
+    const int first = first_sh;
+    // the tail: samples at or above the first positive one, into buckets; the rest is counted
+    const float range = s_hi - s_lo, scale = range > 0.f && range <= 3.4e38f && NBK / range <= 3.4e38f ? NBK / range : 0.f;
+    auto bucket_of = [&](float v) { return scale > 0.f ? max(0, min((int)((v - s_lo) * scale), NBK - 1)) : 0; };
+    int pos[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int t = tid + q * CAL_THREADS;
+        pos[q] = -1;
+        if (any && t < T && (sv[q] > s_lo || (sv[q] == s_lo && t >= first))) pos[q] = (int)atomicAdd(&hist[bucket_of(sv[q])], 1u);
     }
     __syncthreads();
+    int ntail = 0;
     {
-        unsigned long long kmin = ~0ull;
-        unsigned long long kmax = 0ull;
-        for (int t = tid; t < T; t += CAL_THREADS) {
-            const unsigned long long k = key_of(t);
-            if (wi[t] > 0.f && k < kmin) kmin = k;
-            if (k > kmax) kmax = k;
+        uint32_t h[BPT], most = 0u;
+        int sum = 0;
+#pragma unroll
+        for (int q = 0; q < BPT; ++q) {
+            h[q] = hist[tid * BPT + q];
+            most = h[q] > most ? h[q] : most;
+            sum += (int)h[q];
         }
-        if (kmin != ~0ull) atomicMin(&kmin_sh, kmin);
-        atomicMax(&kmax_sh, kmax);
-    }
-    __syncthreads();
-    const unsigned long long kmin = kmin_sh;
-    // the tail: samples at or above the first positive one; the rest is counted
-    {
-        int below = 0;
-        for (int t = tid; t < T; t += CAL_THREADS) {
-            const unsigned long long k = key_of(t);
-            if (k < kmin) ++below;
-            else sk[atomicAdd(&fill_sh, 1)] = k;                   // any order: sorted next
+        if (most > CAL_BUCKET_MAX) big_sh = 1;
+        int inc = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(inc, off);
+            if (lane >= off) inc += o;
         }
-        if (below) atomicAdd(&below_sh, below);
+        if (lane == 63) wave_tot[wave] = inc;
+        __syncthreads();
+        int before = inc - sum;
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) {
+            if (v < wave) before += wave_tot[v];
+            ntail += wave_tot[v];
+        }
+#pragma unroll
+        for (int q = 0; q < BPT; ++q) {
+            start[tid * BPT + q] = (uint32_t)before;
+            before += (int)h[q];
+        }
     }
+    const int nb = T - ntail;                                      // samples below the tail (T if no weight is positive)
     __syncthreads();
-    const int nb = below_sh;                                       // samples below the tail (T if no weight is positive)
-    const int ntail = T - nb;
-    int n2 = 1;
-    while (n2 < ntail) n2 <<= 1;
-    for (int t = ntail + tid; t < n2; t += CAL_THREADS) sk[t] = ~0ull;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (pos[q] >= 0) sk[start[bucket_of(sv[q])] + pos[q]] = key_of(sv[q], tid + q * CAL_THREADS);
     __syncthreads();
-    for (int k = 2; k <= n2; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int t = tid; t < n2; t += CAL_THREADS) {
-                const int p = t ^ j;
-                if (p > t) {
-                    const unsigned long long a = sk[t], b = sk[p];
-                    const bool up = (t & k) == 0;
-                    if ((a > b) == up) {
-                        sk[t] = b;
-                        sk[p] = a;
+    if (big_sh != 0) {
+        int n2 = 1;
+        while (n2 < ntail) n2 <<= 1;
+        for (int t = ntail + tid; t < n2; t += CAL_THREADS) sk[t] = ~0ull;
+        __syncthreads();
+        for (int k = 2; k <= n2; k <<= 1) {
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                for (int t = tid; t < n2; t += CAL_THREADS) {
+                    const int p = t ^ j;
+                    if (p > t) {
+                        const unsigned long long a = sk[t], b = sk[p];
+                        const bool up = (t & k) == 0;
+                        if ((a > b) == up) {
+                            sk[t] = b;
+                            sk[p] = a;
+                        }
                     }
                 }
+                __syncthreads();
             }
-            __syncthreads();
         }
     }
-    for (int p = tid; p < ntail; p += CAL_THREADS) {
-        const int t = (int)(sk[p] & 0xffffffffu);
-        ss[p] = si[t];
-        ww[p] = wi[t];
+    // tail sample p (by bucket, or sorted already): its score, weight and place; then the keys make room
+    float tw[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int p = tid + q * CAL_THREADS;
+        pos[q] = -1;
+        if (p < ntail) {
+            const unsigned long long k = sk[p];
+            const int t = (int)(k & 0xffffffffu);
+            tw[q] = wi[t];
+            sv[q] = si[t];                                         // not from the key: -0 keeps its sign
+            pos[q] = p;
+            if (big_sh == 0) {
+                const int b = bucket_of(from_ordered_bits((uint32_t)(k >> 32))), b0 = (int)start[b], b1 = b0 + (int)hist[b];
+                int rank = b0;
+                for (int e = b0; e < b1; ++e) rank += sk[e] < k ? 1 : 0;
+                pos[q] = rank;
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        if (pos[q] < 0) continue;
+        ss[pos[q]] = sv[q];
+        ww[pos[q]] = tw[q];
+    }
+    if (ntail == 0) {                                              // nothing ever active: the last sample in sorted order
+        unsigned long long last = 0ull;
+        for (int t = tid; t < T; t += CAL_THREADS) {
+            const unsigned long long k = key_of(si[t], t);
+            last = k > last ? k : last;
+        }
+        atomicMax(&last_sh, last);
     }
     __syncthreads();
     // sorted position q of the whole sample = tail position q - nb; the first positive weight is tail position 0
@@ -135,20 +259,37 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
     for (int j = tid; j < M; j += CAL_THREADS) {
         const int lo = k0 - nb + j * eta, hi = min(lo + eta, ntail);
         float c = 0.f;
-        for (int p = lo; p < hi; ++p) c += ww[p];
+        int p = lo;
+        for (; p + 4 <= hi; p += 4) {                               // four reads on their way, added in order
+            const float a0 = ww[p], a1 = ww[p + 1], a2 = ww[p + 2], a3 = ww[p + 3];
+            c += a0;
+            c += a1;
+            c += a2;
+            c += a3;
+        }
+        for (; p < hi; ++p) c += ww[p];
         cost[j] = c;
     }
     __syncthreads();
-    // running maximum (inclusive), Hillis-Steele over M entries
-    float *src = cost, *dst = scan;
-    for (int off = 1; off < M; off <<= 1) {
-        for (int j = tid; j < M; j += CAL_THREADS) dst[j] = j >= off ? fmaxf(src[j], src[j - off]) : src[j];
-        __syncthreads();
-        float *tmp = src;
-        src = dst;
-        dst = tmp;
+    // running maximum (inclusive): one wave, consecutive steps per lane, then across the lanes
+    if (wave == 0) {
+        const int per = (M + 63) >> 6, j0 = min(lane * per, M), j1 = min(j0 + per, M);
+        float m = -__builtin_inff();
+        for (int j = j0; j < j1; ++j) m = fmaxf(m, cost[j]);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const float o = __shfl_up(m, off);
+            if (lane >= off) m = fmaxf(m, o);
+        }
+        float run = __shfl_up(m, 1);
+        if (lane == 0) run = -__builtin_inff();
+        for (int j = j0; j < j1; ++j) {
+            run = fmaxf(run, cost[j]);
+            scan[j] = run > -__builtin_inff() ? run : cost[j];      // nothing but NaN so far stays that
+        }
     }
-    for (int j = tid; j < MS; j += CAL_THREADS) key[(size_t)i * MS + j] = j < M ? src[j] : __builtin_inff();
+    __syncthreads();
+    for (int j = tid; j < MS; j += CAL_THREADS) key[(size_t)i * MS + j] = j < M ? scan[j] : __builtin_inff();
     // thresholds and dropped counts after j steps: k = min(k0 + j*eta, T), tau = s_(k), #{s <= tau};
     // every sample below the tail has a score <= tau
     for (int j = tid; j <= MS; j += CAL_THREADS) {
@@ -156,12 +297,13 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
         float tj = 0.f;
         if (j <= M) {
             if (ntail == 0) {                                       // nothing ever active: all dropped, tau = the last score
-                tj = si[(int)(kmax_sh & 0xffffffffu)];
+                tj = si[(int)(last_sh & 0xffffffffu)];
                 dj = T;
             } else {
                 const int k = min(k0 + j * eta, T) - nb;            // tail count, >= 1
                 tj = ss[k - 1];
                 int lo = k, hi = ntail;                             // first tail position whose score exceeds tau
+                if (lo < hi && !(ss[lo] <= tj)) hi = lo;            // mostly the next one
                 while (lo < hi) {
                     const int mid = (lo + hi) >> 1;
                     if (ss[mid] <= tj) lo = mid + 1;
@@ -172,6 +314,7 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
         }
         drop[(size_t)i * (MS + 1) + j] = dj;
         tauc[(size_t)i * (MS + 1) + j] = tj;
+        if (j == 0) drop0[i] = dj;
     }
     if (tid == 0) k0_out[i] = k0;
 
@@ -241,13 +384,13 @@ struct SelectState {
 constexpr int SEL_BINS = 256;
 constexpr uint32_t SEL_TOP = 0x7f7fffffu;      // largest finite float: keys above it are padding
 
-__global__ __launch_bounds__(SEL_THREADS) void k_select_init(const int32_t *__restrict__ drop, int D, int MS,
-                                                             long long need, SelectState *__restrict__ st,
-                                                             long long *__restrict__ hist)
+__global__ __launch_bounds__(SEL_THREADS) void k_select_init(const int32_t *__restrict__ drop0, int D, long long need,
+                                                             SelectState *__restrict__ st, long long *__restrict__ hist,
+                                                             int32_t *__restrict__ steps)
 {
     __shared__ long long red[SEL_THREADS / 64];
     long long c0 = 0;
-    for (int i = threadIdx.x; i < D; i += SEL_THREADS) c0 += drop[(size_t)i * (MS + 1)];
+    for (int i = threadIdx.x; i < D; i += SEL_THREADS) c0 += drop0[i];
     c0 = block_sum_i64(c0, red);
     if (threadIdx.x < SEL_BINS) hist[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
@@ -256,10 +399,14 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_init(const int32_t *__re
         st->prefix = 0u;
         st->reachable = c0 < need ? 1 : 0;
         st->at_start = c0 < need ? 0 : 1;
+        if (steps != nullptr) *steps = 0;
     }
 }
 
-// hist[digit] += gain over the steps whose key matches the prefix above this digit.
+// hist[digit] += gain over the steps whose key matches the prefix above this digit.  A thread takes SEL_RUN steps in a
+// row: a neuron's keys do not decrease, so they share few digits and most gains are added before they reach the (then
+// contended) counters.
+constexpr int SEL_RUN = 8;
 template <int SHIFT, int BITS>
 __global__ __launch_bounds__(256) void k_select_hist(const float *__restrict__ key, const int32_t *__restrict__ drop,
                                                      int D, int MS, const SelectState *__restrict__ st,
@@ -271,15 +418,32 @@ __global__ __launch_bounds__(256) void k_select_hist(const float *__restrict__ k
     for (int q = threadIdx.x; q < SEL_BINS; q += 256) lh[q] = 0;
     __syncthreads();
     const size_t total = (size_t)D * MS;
-    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256) {
-        const int i = (int)(e / MS), j = (int)(e % MS);
-        const uint32_t kb = __float_as_uint(key[e]);
-        if (kb > SEL_TOP) continue;
-        if (SHIFT + BITS < 31 && (kb >> (SHIFT + BITS)) != (prefix >> (SHIFT + BITS))) continue;
-        const int32_t *di = drop + (size_t)i * (MS + 1);
-        const long long gain = (long long)di[j + 1] - di[j];
-        if (gain != 0) atomicAdd(reinterpret_cast<unsigned long long *>(&lh[(kb >> SHIFT) & ((1u << BITS) - 1u)]),
-                                 (unsigned long long)gain);
+    for (size_t e0 = ((size_t)blockIdx.x * 256 + threadIdx.x) * SEL_RUN; e0 < total; e0 += (size_t)gridDim.x * 256 * SEL_RUN) {
+        uint32_t kb[SEL_RUN];
+#pragma unroll
+        for (int q = 0; q < SEL_RUN; ++q) kb[q] = e0 + q < total ? __float_as_uint(key[e0 + q]) : ~0u;
+        int i = (int)(e0 / MS), j = (int)(e0 % MS);
+        long long gain = 0;
+        int digit = -1;
+#pragma unroll
+        for (int q = 0; q < SEL_RUN; ++q) {
+            if (kb[q] <= SEL_TOP &&
+                !(SHIFT + BITS < 31 && (kb[q] >> (SHIFT + BITS)) != (prefix >> (SHIFT + BITS)))) {
+                const int dg = (int)((kb[q] >> SHIFT) & ((1u << BITS) - 1u));
+                if (dg != digit) {
+                    if (gain != 0) atomicAdd(reinterpret_cast<unsigned long long *>(&lh[digit]), (unsigned long long)gain);
+                    gain = 0;
+                    digit = dg;
+                }
+                const int32_t *di = drop + (size_t)i * (MS + 1);
+                gain += (long long)di[j + 1] - di[j];
+            }
+            if (++j == MS) {
+                j = 0;
+                ++i;
+            }
+        }
+        if (gain != 0) atomicAdd(reinterpret_cast<unsigned long long *>(&lh[digit]), (unsigned long long)gain);
     }
     __syncthreads();
     for (int q = threadIdx.x; q < SEL_BINS; q += 256)
@@ -329,100 +493,94 @@ __global__ __launch_bounds__(64) void k_select_pick(SelectState *__restrict__ st
     }
 }
 
-// With the level known, per neuron: the number of its steps strictly below the level and up to it.
-__global__ __launch_bounds__(256) void k_select_bounds(const float *__restrict__ key, int D, int MS,
-                                                       const SelectState *__restrict__ st,
-                                                       int32_t *__restrict__ lo_out, int32_t *__restrict__ up_out)
+// With the level known, per neuron: the number of its steps strictly below the level and up to it, and (reachable target)
+// how many pairs the latter add; per block the sum of those.  A block has `chunk` neurons, a multiple of 256.
+__global__ __launch_bounds__(256) void k_select_bounds(const float *__restrict__ key, const int32_t *__restrict__ drop, int D,
+                                                       int MS, int chunk, const SelectState *__restrict__ st,
+                                                       int32_t *__restrict__ lo_out, int32_t *__restrict__ up_out,
+                                                       long long *__restrict__ block_gain)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= D) return;
+    __shared__ long long red[4];
     const float lv = __uint_as_float(st->reachable != 0 ? st->prefix : SEL_TOP);
-    const float *ki = key + (size_t)i * MS;
-    lo_out[i] = steps_below<false>(ki, MS, lv);
-    up_out[i] = steps_below<true>(ki, MS, lv);
+    long long gain = 0;
+    for (int i = blockIdx.x * chunk + threadIdx.x; i < min(D, (int)(blockIdx.x + 1) * chunk); i += 256) {
+        const float *ki = key + (size_t)i * MS;
+        const int32_t *di = drop + (size_t)i * (MS + 1);
+        const int lo = steps_below<false>(ki, MS, lv), up = steps_below<true>(ki, MS, lv);
+        lo_out[i] = lo;
+        up_out[i] = up;
+        gain += (long long)di[up] - di[lo];
+    }
+    gain = block_sum_i64(gain, red);
+    if (threadIdx.x == 0) block_gain[blockIdx.x] = gain;
 }
 
 // Steps strictly below the level are all taken; those at the level in neuron order until the
-// missing pairs are found; writes b = -tau, the pointers and the number of steps.  One block.
-__global__ __launch_bounds__(SEL_THREADS) void k_select_finish(const int32_t *__restrict__ lo_in,
-                                                               const int32_t *__restrict__ up_in,
-                                                               const int32_t *__restrict__ drop,
-                                                               const float *__restrict__ tauc,
-                                                               const int32_t *__restrict__ k0, int D, int T, int eta,
-                                                               int MS, const SelectState *__restrict__ st,
-                                                               float *__restrict__ b, int32_t *__restrict__ k_out,
-                                                               int32_t *__restrict__ steps)
+// missing pairs are found; writes b = -tau, the pointers and the number of steps.  Every block adds up the gains in front
+// of its own 256 neurons, so that no block waits for another (in one block, neuron by neuron behind two dependent loads,
+// this took 30 us at D = 11008).
+__global__ __launch_bounds__(256) void k_select_finish(const int32_t *__restrict__ lo_in, const int32_t *__restrict__ up_in,
+                                                       const int32_t *__restrict__ drop, const float *__restrict__ tauc,
+                                                       const int32_t *__restrict__ k0, int D, int T, int eta, int MS,
+                                                       int chunk, const SelectState *__restrict__ st,
+                                                       const long long *__restrict__ block_gain, float *__restrict__ b,
+                                                       int32_t *__restrict__ k_out, int32_t *__restrict__ steps)
 {
-    __shared__ long long red[SEL_THREADS / 64];
-    __shared__ long long wave_tot[SEL_THREADS / 64];
-    __shared__ int star;                                            // neuron at which the target is reached
-    __shared__ long long star_before;                               // pairs found before its steps at the level
+    __shared__ long long red[4], wave_tot[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool at_start = st->at_start != 0;
-    const bool reachable = st->reachable != 0;
+    const bool at_start = st->at_start != 0, reachable = st->reachable != 0;
     const long long missing = st->missing;                          // among the steps at the level
-    if (tid == 0) {
-        star = D;
-        star_before = 0;
-    }
-    __syncthreads();
     long long carried = 0;
-    for (int i0 = 0; i0 < D && reachable; i0 += SEL_THREADS) {
+    for (int q = tid; q < (int)blockIdx.x; q += 256) carried += block_gain[q];
+    carried = block_sum_i64(carried, red);
+    long long taken = 0;
+    for (int i0 = blockIdx.x * chunk; i0 < min(D, (int)(blockIdx.x + 1) * chunk); i0 += 256) {
         const int i = i0 + tid;
+        int lo = 0, up = 0;
+        const int32_t *di = drop + (size_t)(i < D ? i : 0) * (MS + 1);
         long long gain = 0;
         if (i < D) {
-            const int32_t *di = drop + (size_t)i * (MS + 1);
-            gain = (long long)di[up_in[i]] - di[lo_in[i]];
+            lo = lo_in[i];
+            up = up_in[i];
+            gain = (long long)di[up] - di[lo];
         }
-        long long inc = gain;                                       // inclusive scan inside the wave
+        long long inc = gain;                                       // inclusive scan inside the wave, then over the waves
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const long long o = __shfl_up(inc, off);
             if (lane >= off) inc += o;
         }
+        __syncthreads();                                            // the previous round's readers are done
         if (lane == 63) wave_tot[wave] = inc;
         __syncthreads();
         long long before = carried;
-        for (int q = 0; q < wave; ++q) before += wave_tot[q];
-        long long chunk_total = 0;
-        for (int q = 0; q < SEL_THREADS / 64; ++q) chunk_total += wave_tot[q];
-        const long long excl = before + inc - gain;                 // found before this neuron's steps at the level
-        if (i < D && excl < missing && excl + gain >= missing) {
-            star = i;                                               // exactly one neuron satisfies this
-            star_before = excl;
+        for (int q = 0; q < 4; ++q) {
+            if (q < wave) before += wave_tot[q];
+            carried += wave_tot[q];
         }
-        __syncthreads();
-        carried += chunk_total;
-        if (star < D) break;
-    }
-    __syncthreads();
-    const int istar = star;
-    const long long sb = star_before;
-    long long taken = 0;
-    for (int i = tid; i < D; i += SEL_THREADS) {
-        const int32_t *di = drop + (size_t)i * (MS + 1);
-        int J;
-        if (at_start) {
-            J = 0;
-        } else if (!reachable || i < istar) {
-            J = up_in[i];                                           // unreachable target: every finite step
-        } else {
-            J = lo_in[i];
-            if (i == istar) {
-                long long c = sb;
-                while (c < missing) {                               // its steps at the level, one at a time
-                    c += di[J + 1] - di[J];
+        const long long found = before + inc;                       // with this neuron's steps at the level
+        long long c = found - gain;                                 // and without
+        if (i < D) {
+            int J;
+            if (at_start) {
+                J = 0;
+            } else if (!reachable || found < missing) {
+                J = up;                                             // unreachable target: every finite step
+            } else {
+                J = lo;
+                while (c < missing) {                               // the neuron that reaches the target: its steps at
+                    c += di[J + 1] - di[J];                         // the level, one at a time
                     ++J;
                 }
             }
+            taken += J;
+            b[i] = -tauc[(size_t)i * (MS + 1) + J];
+            if (k_out != nullptr) k_out[i] = min(k0[i] + J * eta, T);
         }
-        taken += J;
-        b[i] = -tauc[(size_t)i * (MS + 1) + J];
-        if (k_out != nullptr) k_out[i] = min(k0[i] + J * eta, T);
     }
     if (steps != nullptr) {
-        const long long tot = block_sum_i64(taken, red);
-        if (tid == 0) *steps = (int32_t)tot;
+        taken = block_sum_i64(taken, red);
+        if (tid == 0 && taken != 0) atomicAdd(steps, (int32_t)taken);
     }
 }
 

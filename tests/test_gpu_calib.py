@@ -102,6 +102,35 @@ def test_non_monotone_costs(env):
             _check(env, w, s, eta, binding.calib_need(sp, D, T))
 
 
+@pytest.mark.parametrize("D,T,eta,kind", [
+    (5, 512, 3, "spread"), (5, 513, 3, "spread"), (4, 1024, 1, "spread"), (4, 1025, 7, "spread"), (3, 2049, 16, "spread"),
+    (6, 700, 4, "levels"),        # few score values: buckets far above the limit, equal scores in sample order
+    (6, 300, 4, "outlier"),       # one huge score per neuron: everybody else shares a bucket
+    (6, 300, 2, "infinite"),      # no finite range
+    (6, 2100, 5, "equal"),        # one score value
+    (6, 900, 4, "mixed"),         # neurons of all kinds side by side
+    (65537, 3, 2, "spread"),      # more neurons than one round of the selection's blocks
+])
+def test_sort_by_buckets_and_selection(env, D, T, eta, kind):
+    """The bucket sort of a neuron's samples and its hand-over to the sorting network, at the limits of a thread's
+    share of the samples; whole numbers and thresholds bit for bit."""
+    binding, torch, calib = env
+    rng = np.random.default_rng(D + T)
+    w, s = _stats(rng, D, T, dead=(1,))
+    kinds = [kind] * D if kind != "mixed" else ["spread", "levels", "outlier", "infinite", "equal", "spread"]
+    for i in range(D):
+        if kinds[i] == "levels":
+            s[i] = np.round(s[i])
+        elif kinds[i] == "outlier":
+            s[i, T // 3] = 1e30
+        elif kinds[i] == "infinite":
+            s[i, T // 2], s[i, 0] = np.inf, -np.inf
+        elif kinds[i] == "equal":
+            s[i] = -0.25
+    for sp in (0.3, 0.9, 0.99) if D < 1000 else (0.7,):
+        _check(env, w, s, eta, binding.calib_need(sp, D, T))
+
+
 def test_validation(env):
     binding, torch, calib = env
     L = binding.lib()
