@@ -88,6 +88,31 @@ __global__ __launch_bounds__(256) void k_ritz_residual(const double *__restrict_
     if (threadIdx.x == 0) res[blockIdx.x] = s;
 }
 
+// out[i] = X[i] . Y[i] / X[i] . X[i] (one block per row)
+__global__ __launch_bounds__(256) void k_rayleigh(const double *__restrict__ X, const double *__restrict__ Y, int n,
+                                                  double *__restrict__ out)
+{
+    __shared__ double sm[256];
+    const size_t at = (size_t)blockIdx.x * n;
+    double xy = 0.0, xx = 0.0;
+    for (int j = threadIdx.x; j < n; j += 256) {
+        const double x = X[at + j];
+        xy += x * Y[at + j];
+        xx += x * x;
+    }
+    xy = block_sum_256(xy, sm);
+    xx = block_sum_256(xx, sm);
+    if (threadIdx.x == 0) out[blockIdx.x] = xy / xx;
+}
+
+// y = alpha y + beta x
+__global__ __launch_bounds__(256) void k_combine(double *__restrict__ y, const double *__restrict__ x, double alpha, double beta,
+                                                 size_t n)
+{
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) y[i] = alpha * y[i] + beta * x[i];
+}
+
 // dst[i] = theta[i] * src[i], rows of n
 __global__ __launch_bounds__(256) void k_scale_rows(const double *__restrict__ src, const double *__restrict__ theta, int rows,
                                                     int n, double *__restrict__ dst)

@@ -1,27 +1,31 @@
 // The r leading eigenvectors of a symmetric positive semi-definite matrix G [n][n] without its other n - r: a block of
 // k > r vectors is filtered by Chebyshev polynomials of G that are small on [0, b], b = the block's smallest Ritz value,
 // and large above (subspace iteration with Rayleigh-Ritz).  Almost all of it is k x n x n products on the fp64 matrix
-// cores, about 25 of them; block Jacobi runs on the k x k projections only.  Included by svdp.hip after
+// cores, 4 to 35 of them; block Jacobi runs on the k x k projections only.  Included by svdp.hip after
 // svdp_whiten_run.h's helpers, inside its unnamed namespace.
 //
 //   start    k pseudo-random rows, three times X <- orth(X G)
 //   repeat   Rayleigh-Ritz: H = X G X^T, its eigenvectors rotate X; residuals of the wanted vectors; done if small
-//            vectors that are already exact leave the block: G <- G - v theta v^T, so that a few dominant directions
+//            vectors that have settled leave the block: G <- G - v theta v^T, so that a few dominant directions
 //            (the mean of the tokens carries 1e8 times the energy of the rest) do not limit the filter's degree
-//            X <- orth(p(G) X), as many degrees as the Ritz values say are missing, in pieces that keep X's condition
-//            number below EIG_AMPLIFY
+//            X <- orth(p(G) X), as many degrees as the Ritz values say are missing, in pieces of at most EIG_PIECE that
+//            also keep X's condition number below EIG_AMPLIFY
 //
-// Accuracy: a vector counts as found when all residuals together are below 2e-13 of ||G||_F; the Jacobi path stops at an
-// off-diagonal norm of 1e-11 of it.  Rounding leaves about 1e-15.
-// Measured (bf16, whole call): d = 4096, r = 256: 401 -> 50 ms (39 products of 320 x 4096 x 4096 at 0.27 ms, three
-// projections of 18 Jacobi sweeps together); d = 1024, r = 64: 43.6 -> 3.8 ms; d = 2560, r = 640 (k = 832): 74 ms.
+// Accuracy: the residuals of the block's wanted vectors together end below 2e-13 of ||G||_F, those of the r that left it
+// below 3e-14 sqrt(r); the Jacobi path stops at an off-diagonal norm of 1e-11 of it.
+// Measured (bf16, whole call), full Jacobi -> this: d = 4096, r = 256: 401 -> 33 ms (33 products of 256 to 320 x 4096 x
+// 4096 at 0.16 to 0.22 ms, two projections of 11 Jacobi sweeps together); d = 1024, r = 64: 43.6 -> 3.3 ms; d = 2560,
+// r = 640: 183 -> 49 ms.  With b fixed between projections and pieces as long as the condition number allowed, the first
+// took three projections and 50 ms: b starts at 0.65 of where it ends, which costs three quarters of the filter's rate.
 // Where it does not apply (block of more than half the dimension; no gap in reach behind the wanted vectors; X loses
 // rank, e.g. G of rank below r) the full Jacobi decomposition runs instead, on the untouched G.
 
 constexpr double EIG_TOL = 2e-13;           // sqrt(sum of squared residuals of the wanted vectors) / ||G||_F
 constexpr double EIG_TOL_JACOBI = 1e-13;    // of the projected problems (off-diagonal / total Frobenius norm)
-constexpr double EIG_EXACT = 2e-15;         // residual / ||G||_F below which a vector is as good as rounding allows
+constexpr double EIG_TOL_FIRST = 1e-12;     // of the first one, which only has to separate what dominates
+constexpr double EIG_SETTLED = 3e-14;       // residual / ||G||_F of one vector that may leave the block
 constexpr double EIG_AMPLIFY = 1e5;         // largest over smallest filter value between two orthogonalisations
+constexpr double EIG_PIECE = 8.0;           // largest degree of a piece of the filter
 constexpr double EIG_SHIFT = 4e-13;         // of the first Cholesky QR pass (above k_chol_diag's bound of 1e-13)
 
 // Rows of the block for r wanted vectors: a quarter more (at least 32), so that the filter has a gap to work with, in
@@ -101,11 +105,11 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
     for (int p = 0; p < 3; ++p) {
         times_g(G, X, tmp, k, n, st, w.scr);
         std::swap(X, tmp);
-        orthonormalize(X, tmp, k, n, p < 2 ? 2 : 3, w, st);
+        orthonormalize(X, tmp, k, n, p < 2 ? 1 : 3, w, st);
     }
     const double *Gc = G;
     double norm = 0.0, last_err = 1e300;
-    int l = 0, ka = k, products = 4;             // vectors that left the block; rows of the block
+    int l = 0, ka = k, products = 4, piece = 0;             // vectors that left the block; rows of the block
     for (int cycle = 0; cycle < 12; ++cycle) {
         // Rayleigh-Ritz
         double *Y = nullptr, *Xr = nullptr, *Yr = nullptr;
@@ -117,7 +121,7 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
         double *A = w.H, *Aa = w.Ha, *V = w.V, *Va = w.Va;
         int sw = 0;
         const svdp_status e =
-            jacobi_eigh(&A, &Aa, &V, &Va, ka, w.Uall, w.rowsums, w.sums, w.lam, EIG_TOL_JACOBI, 24, &sw, st);
+            jacobi_eigh(&A, &Aa, &V, &Va, ka, w.Uall, w.rowsums, w.sums, w.lam, cycle == 0 ? EIG_TOL_FIRST : EIG_TOL_JACOBI, 24, &sw, st);
         if (e != SVDP_OK) return e;
         *sweeps = std::max(1, sw);
         hipLaunchKernelGGL(k_rank_descending, grid1(ka), dim3(256), 0, st, w.lam, ka, w.sel, w.theta);
@@ -151,14 +155,14 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             return hip_status(hipSuccess);
         }
         last_err = err;
-        // degree that the Ritz values call for, with a margin for those that have not settled yet
-        const double b = std::max(theta[ka - 1], 1e-15 * norm), margin = cycle == 0 ? 1e3 : 30.0;
-        const double reach = std::acosh(std::max(2.0 * theta[need - 1] / b - 1.0, 1.0));
-        const double degrees = std::acosh(std::max(err / EIG_TOL * margin, 2.0)) / reach;
-        if (!(degrees * ka < 16.0 * n - (double)products * ka)) return SVDP_OK;       // Jacobi would be done sooner
-        // exact vectors leave the block
+        const double b = std::max(theta[ka - 1], 1e-15 * norm), margin = 10.0;
+        // no gap in reach: the full decomposition would be done sooner
+        const double apart = std::acosh(std::max(2.0 * theta[need - 1] / b - 1.0, 1.0));
+        if (!(std::log(std::max(err / EIG_TOL, 2.0)) / apart * ka < 16.0 * n - (double)products * ka)) return SVDP_OK;
+        // Settled vectors leave the block.  What is left of their residual couples them to the rest of G by as little, far
+        // below the filter's edge, so it does not grow.
         int out = 0;
-        while (out < need && std::sqrt(res[out]) < EIG_EXACT * norm && theta[out] > 2.0 * theta[need - 1]) ++out;
+        while (out < need && std::sqrt(res[out]) < EIG_SETTLED * norm && theta[out] > 2.0 * theta[need - 1]) ++out;
         double top = theta[0];
         if (out > 0) {
             double *Vl = Vr + (size_t)l * n;
@@ -186,23 +190,45 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
                 orthonormalize(X, tmp, ka, n, 1, w, st);
             }
         }
-        // filter
-        const double wide = std::acosh(std::max(2.0 * top / b - 1.0, 1.0));
-        const int piece = (int)std::max(1.0, std::min(1000.0, std::acosh(EIG_AMPLIFY) / std::max(wide, 1e-3)));
-        for (int left = (int)std::ceil(std::max(1.0, degrees)); left > 0;) {
-            const int m = std::min(piece, left);
-            left -= m;
-            products += m;
-            const double half = 0.5 * b, s0 = half / (top - half);
-            double s1 = s0;
+        // Filter, in pieces.  Before each but the first, b follows the smallest Rayleigh quotient of the block, which is
+        // near its smallest Ritz value (the rows stay in the order of the Ritz values): it rises while the block's last rows
+        // settle, and the rate hangs on it, because what lies outside the block is only damped as far as b reaches.
+        double bound = b, todo = std::log(std::max(err / EIG_TOL * margin, 2.0));
+        double wanted = theta[need - 1];
+        auto growth = [](double value, double edge) { return std::acosh(std::max(2.0 * value / edge - 1.0, 1.0)); };
+        int single = 0;
+        for (bool first = true, last = false; !last; first = false) {
             double *prev = X, *cur = X == w.X ? w.Xa : w.X;
+            if (!first) {
+                times_g(Gc, X, cur, ka, n, st, w.scr);
+                hipLaunchKernelGGL(k_rayleigh, dim3(ka), dim3(256), 0, st, X, cur, n, w.res);
+                if (hipMemcpyAsync(res, w.res, (size_t)ka * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+                    hipStreamSynchronize(st) != hipSuccess)
+                    return hip_failed();
+                std::sort(res, res + ka, std::greater<double>());
+                const double lowest = res[ka - 1];
+                wanted = std::max(wanted, res[r - l - 1]);         // has risen, too
+                if (!(lowest < wanted)) break;                     // (also NaN) the next projection tells more
+                // what the last piece gained where the new bound now is
+                todo += piece * growth(lowest, bound);
+                bound = std::max(bound, lowest);
+            }
+            const double rate = growth(wanted, bound), left = std::ceil(todo / rate);
+            if (!(left * ka < 16.0 * n - (double)products * ka)) return SVDP_OK;
+            piece = (int)std::max(1.0, std::min({EIG_PIECE, std::floor(std::acosh(EIG_AMPLIFY) / std::max(growth(top, bound), 1e-3)), left}));
+            last = piece >= left || (piece == 1 && ++single == 3);  // a dominant direction keeps the pieces short: project, it may have settled
+            todo -= piece * rate;
+            products += piece;
+            const double half = 0.5 * bound, s0 = half / (top - half);
+            double s1 = s0;
             DgEpilogue ep;
             ep.alpha = s1 / half;
             ep.c1 = prev;
             ep.ld1 = n;
             ep.beta = -s1;
-            times_g(Gc, prev, cur, ka, n, st, w.scr, ep);
-            for (int i = 2; i <= m; ++i) {
+            if (first) times_g(Gc, prev, cur, ka, n, st, w.scr, ep);
+            else hipLaunchKernelGGL(k_combine, grid1((size_t)ka * n), dim3(256), 0, st, cur, prev, ep.alpha, ep.beta, (size_t)ka * n);
+            for (int i = 2; i <= piece; ++i) {
                 const double s2 = 1.0 / (2.0 / s0 - s1);
                 DgEpilogue e2;
                 e2.alpha = 2.0 * s2 / half;
@@ -219,7 +245,7 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             X = cur;
             tmp = prev;
             project_out(X, ka, n, Vr, l, w, st);
-            orthonormalize(X, tmp, ka, n, 2, w, st);
+            orthonormalize(X, tmp, ka, n, last ? 2 : 1, w, st);
         }
         products += 1;
     }
