@@ -7,6 +7,7 @@
 
 #include "svdp_kernels.h"
 #include "svdp_rows_mfma.h"
+#include "svdp_predict_small.h"
 #include "svdp_rows_seq.h"
 #include "svdp_calib.h"
 #include "svdp_calib_stats.h"
@@ -418,10 +419,35 @@ bool tsum_needed(const svdp_layer *L)
     return NB >= 4 && L->d > XP_ROWS && !scores_on_matrix<W, NB>(L);
 }
 
+// One token and a P of at most PS_TILES tiles: both predictor stages in one launch (k_predict_small).
+template <typename W>
+bool predict_small(const svdp_layer *L)
+{
+    const int tiles = ((L->d + XP_ROWS - 1) / XP_ROWS) * ((L->r + XP_COLS - 1) / XP_COLS);
+    return tiles <= PS_TILES && !scores_on_matrix<W, 1>(L);
+}
+
+template <typename W>
+svdp_status launch_predict_small(const svdp_layer *L, const void *x, float *s, uint64_t *mask, hipStream_t st)
+{
+    auto go = [&](auto lpr) {
+        hipLaunchKernelGGL((k_predict_small<W, decltype(lpr)::value>), dim3(L->D / SC_SLAB), dim3(PS_THREADS),
+                           ps_lds<W>(L->d, L->r), st, static_cast<const W *>(L->P), static_cast<const W *>(L->Q), L->b,
+                           static_cast<const W *>(x), L->d, L->r, s, mask);
+        return hip_status(hipSuccess);
+    };
+    switch (scores_lpr_log2<W>(L)) {                  // r <= 32 PS_TILES: at most 32 column groups
+    case 3: return go(std::integral_constant<int, 3>{});
+    case 4: return go(std::integral_constant<int, 4>{});
+    default: return go(std::integral_constant<int, 5>{});
+    }
+}
+
 template <typename W, int NB>
 svdp_status run_predict(const svdp_layer *L, const void *x, int B, float *s, uint64_t *mask, const Workspace &w,
                         hipStream_t st, const GlueArgs *glue)
 {
+    if (NB == 1 && glue == nullptr && predict_small<W>(L)) return launch_predict_small<W>(L, x, s, mask, st);
     int nt = 0;
     svdp_status e = launch_xP<W, NB>(L, x, B, w.tpart, &nt, st, glue);
     if (e != SVDP_OK) return e;
