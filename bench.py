@@ -610,7 +610,7 @@ def calibrate(a):
                                f"sparsity level {a.calib_sparsity}"},
         "stats_ms": ms_stats, "bias_ms": ms_bias, "bias_with_kendall_ms": ms_bias_k, "greedy_steps": int(steps.item()),
         "roofline": {"bound": "mfma", "achieved": tflops, "peak": 2500.0, "unit": "TFLOP/s", "frac": tflops / 2500.0,
-                     "traffic": None, "kernel": "svdp_calib_stats (k_gemm_nt x3 + row norms + transpose), bf16 MFMA"},
+                     "traffic": None, "kernel": "svdp_calib_stats (k_gemm_wide, k_gemm_nt, row norms, transpose), bf16 MFMA"},
         "on_256_decode_tokens": {"calibrated_bias": summ(on_new), "generator_bias": summ(on_old)},
         "cpu_baseline": cpu}))
 

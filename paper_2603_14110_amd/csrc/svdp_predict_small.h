@@ -3,6 +3,9 @@
 // Bound of the two launches there: the launches.  Every block of the scores forms t = x P by itself from at most
 // PS_TILES tiles of P (16 or 32 KB each, from L2 after the first block) while its rows of Q are on their way.  All sums are
 // formed in the order of k_xP and k_scores, so that the scores have the same bits (svdp_ffn_step_glued keeps those two).
+// Measured, one step, two launches -> one (us, issued one by one / in a graph with 24 layers in turn): d = 256, r = 32, fp32
+// (one tile) 18.5 -> 14.4 / 12.3 -> 9.2; d = 1024, r = 32, bf16 (four tiles) 19.3 -> 14.8 / 14.3 -> 13.3; with eight tiles
+// (d = 2048, r = 32) a graph is slower, 15.6 -> 18.2, hence the limit.
 #pragma once
 
 #include "svdp_kernels.h"
