@@ -148,7 +148,8 @@ def test_contractions_at_ragged_sizes_and_unaligned_inputs(env, d, D, T, r, dt):
     ("flat", 384, 161),       # one rank above it: the full decomposition
     ("ties", 256, 40),        # all eigenvalues equal: nothing to iterate on, the full decomposition takes over
     ("rank", 256, 40),        # rank 20 < r
-    ("zero", 128, 8),         # nothing at all
+    ("flat", 256, 32),        # the smallest matrix that is iterated, block of 64 rows
+    ("zero", 256, 8),         # nothing at all
 ])
 def test_leading_eigenvectors_over_spectra(env, kind, d, r):
     """The leading-eigenvector iteration and its hand-over to the full decomposition: the minimised error and the
