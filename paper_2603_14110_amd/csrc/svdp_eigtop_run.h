@@ -13,9 +13,9 @@
 //
 // Accuracy: the residuals of the block's wanted vectors together end below 2e-13 of ||G||_F, those of the r that left it
 // below 3e-14 sqrt(r); the Jacobi path stops at an off-diagonal norm of 1e-11 of it.
-// Measured (bf16, whole call), full Jacobi -> this: d = 4096, r = 256: 401 -> 33 ms (33 products of 256 to 320 x 4096 x
-// 4096 at 0.16 to 0.22 ms, two projections of 11 Jacobi sweeps together); d = 1024, r = 64: 43.6 -> 3.3 ms; d = 2560,
-// r = 640: 183 -> 49 ms.  With b fixed between projections and pieces as long as the condition number allowed, the first
+// Measured (bf16, whole call), full Jacobi -> this: d = 4096, r = 256: 401 -> 31 ms (33 products of 256 to 320 x 4096 x
+// 4096 at 0.16 to 0.22 ms, two projections of 11 Jacobi sweeps together); d = 1024, r = 64: 43.6 -> 3.2 ms; d = 2560,
+// r = 640: 183 -> 45 ms.  With b fixed between projections and pieces as long as the condition number allowed, the first
 // took three projections and 50 ms: b starts at 0.65 of where it ends, which costs three quarters of the filter's rate.
 // Where it does not apply (block of more than half the dimension; no gap in reach behind the wanted vectors; X loses
 // rank, e.g. G of rank below r) the full Jacobi decomposition runs instead, on the untouched G.
@@ -30,8 +30,8 @@ constexpr double EIG_SHIFT = 4e-13;         // of the first Cholesky QR pass (ab
 
 // Rows of the block for r wanted vectors: a quarter more (at least 32), so that the filter has a gap to work with, in
 // whole Jacobi strips; 0 where the Jacobi decomposition of all of G is the better way: from n = 256 on the block wins on
-// every spectrum tried (whole call 4.2 to 4.7 against 5.0 to 8.1 ms there), at n = 128 it loses on decaying ones (2.2
-// against 2.1 ms).
+// every spectrum tried (whole call 3.9 to 4.4 against 5.0 to 8.1 ms at r = 64), at n = 128 it loses on decaying ones (2.2
+// against 1.6 ms).
 inline int eigtop_block(int n, int r)
 {
     const int k = round_up(r + std::max(32, r / 4), BJ_S);

@@ -254,24 +254,29 @@ __device__ __forceinline__ double bj_neighbour(double v)
 // and written by exactly one lane, and a wave's 64 lanes always touch 64 different columns of one row, so the
 // accesses spread over all LDS banks.  U <- U J is the same column rotation; the angles of the next step are
 // computed (32 lanes) while the other waves are in it.
+// The rows of U are independent of each other and of S, so BJ_U_PARTS blocks per strip sweep the same S and take a part of
+// the rows each: a round has far fewer strips than the chip has compute units (64 -> 50 us a launch; bound by the LDS traffic
+// and the two barriers of the 63 dependent steps; with eight waves instead of sixteen the call is 2 % slower).
 constexpr int BJ_SOLVE_THREADS = 1024;
+constexpr int BJ_U_PARTS = 4;
+constexpr size_t BJ_SOLVE_LDS = (size_t)(BJ_S + BJ_S / BJ_U_PARTS) * BJ_LD * 8;
 __global__ __launch_bounds__(BJ_SOLVE_THREADS) void k_bjacobi_solve(const double *__restrict__ A, int n,
                                                                     double *__restrict__ Uall)
 {
     extern __shared__ double bj_smem[];
     double *S = bj_smem;                       // [64][65]
-    double *U = S + BJ_S * BJ_LD;              // [64][65]
+    double *U = S + BJ_S * BJ_LD;              // [64 / BJ_U_PARTS][65]
     __shared__ double csv[2][BJ_B][2];
     __shared__ double red[2][BJ_SOLVE_THREADS / 64];
     __shared__ int done;
-    constexpr int WAVES = BJ_SOLVE_THREADS / 64, PAIRS = BJ_B / WAVES, ROWS = BJ_S / WAVES;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k = blockIdx.x;
+    constexpr int WAVES = BJ_SOLVE_THREADS / 64, PAIRS = BJ_B / WAVES, UR = BJ_S / BJ_U_PARTS, ROWS = UR / WAVES;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k = blockIdx.x, u0 = blockIdx.y * UR;
     const int pb = lane >> 1, second = lane & 1;
     const size_t base = (size_t)(k * BJ_S) * n + (size_t)k * BJ_S;
     for (int e = tid; e < BJ_S * BJ_S; e += BJ_SOLVE_THREADS) {
         const int i = e >> 6, j = e & 63;
         S[i * BJ_LD + j] = A[base + (size_t)i * n + j];
-        U[i * BJ_LD + j] = i == j ? 1.0 : 0.0;
+        if (i < UR) U[i * BJ_LD + j] = u0 + i == j ? 1.0 : 0.0;
     }
     __syncthreads();
     for (int sweep = 0; sweep < BJ_INNER_SWEEPS; ++sweep) {
@@ -363,9 +368,9 @@ __global__ __launch_bounds__(BJ_SOLVE_THREADS) void k_bjacobi_solve(const double
             __syncthreads();
         }
     }
-    for (int e = tid; e < BJ_S * BJ_S; e += BJ_SOLVE_THREADS) {
+    for (int e = tid; e < UR * BJ_S; e += BJ_SOLVE_THREADS) {
         const int i = e >> 6, j = e & 63;
-        Uall[(size_t)k * BJ_S * BJ_S + e] = U[i * BJ_LD + j];
+        Uall[((size_t)k * BJ_S + u0) * BJ_S + e] = U[i * BJ_LD + j];
     }
 }
 

@@ -144,7 +144,7 @@ void solve_right_lower(double *Bin, double *Bout, int r, int n, const double *L,
 svdp_status jacobi_eigh(double **A, double **Aalt, double **V, double **Valt, int n, double *Uall, double *rowsums,
                         double *sums, double *lam, double tol, int max_sweeps, int *sweeps_out, hipStream_t st)
 {
-    const size_t lds_solve = (size_t)2 * BJ_S * BJ_LD * 8, lds_two = (size_t)2 * BJ_S * BJ_LD * 8,
+    const size_t lds_solve = BJ_SOLVE_LDS, lds_two = (size_t)2 * BJ_S * BJ_LD * 8,
                  lds_one = lds_two;
     if (!grant_lds<k_bjacobi_solve>(lds_solve) || !grant_lds<k_bjacobi_apply<true>>(lds_two) ||
         !grant_lds<k_bjacobi_apply<false>>(lds_one))
@@ -169,7 +169,7 @@ svdp_status jacobi_eigh(double **A, double **Aalt, double **V, double **Valt, in
         if (!(h[1] == h[1]) || h[0] <= tol * tol * h[1] || stalled || sweep >= max_sweeps) break;
         previous = h[0];
         for (int round = 0; round < rounds; ++round) {
-            hipLaunchKernelGGL(k_bjacobi_solve, dim3(strips), dim3(BJ_SOLVE_THREADS), lds_solve, st, *A, n, Uall);
+            hipLaunchKernelGGL(k_bjacobi_solve, dim3(strips, BJ_U_PARTS), dim3(BJ_SOLVE_THREADS), lds_solve, st, *A, n, Uall);
             hipLaunchKernelGGL(k_bjacobi_apply<true>, dim3(cgrid, strips), dim3(256), lds_two, st, *A, Uall, n, ct, *Aalt);
             hipLaunchKernelGGL(k_bjacobi_apply<false>, dim3(cgrid, strips), dim3(256), lds_one, st, *V, Uall, n, ct, *Valt);
             std::swap(*A, *Aalt);
