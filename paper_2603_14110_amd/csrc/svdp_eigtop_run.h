@@ -39,6 +39,7 @@ inline int eigtop_block(int n, int r)
 }
 
 struct EigTopWs {
+    int k;                              // eigtop_block(n, r)
     double *X, *Y, *Xa, *Xb;            // [k][n]
     double *Gd;                         // [n][n] deflated G
     double *H, *Ha, *V, *Va, *Vs, *L;   // [k][k]
@@ -73,12 +74,15 @@ void orthonormalize(double *&X, double *&tmp, int k, int n, int passes, const Ei
     }
 }
 
-// X <- X - (X Vl^T) Vl for the l rows of Vl
-void project_out(double *X, int k, int n, const double *Vl, int l, const EigTopWs &w, hipStream_t st)
+// X <- X - (X Vl^T) Vl for the l rows of Vl and the ka of X.  The coefficients lie in Vs with the full block's stride: as
+// vectors leave the block, l outgrows ka, but never w.k (l < r < w.k).  false: it would not fit, nothing was done.
+bool project_out(double *X, int ka, int n, const double *Vl, int l, const EigTopWs &w, hipStream_t st)
 {
-    if (l == 0) return;
-    dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)X, n), op(Vl, n), w.Vs, k, k, l, n, st, 0, DgEpilogue{}, w.scr);
-    dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.Vs, k), op(Vl, n), X, n, k, n, l, st, 0, minus_from(X, n));
+    if (l == 0) return true;
+    if (l > w.k || ka > w.k) return false;
+    dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)X, n), op(Vl, n), w.Vs, w.k, ka, l, n, st, 0, DgEpilogue{}, w.scr);
+    dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.Vs, w.k), op(Vl, n), X, n, ka, n, l, st, 0, minus_from(X, n));
+    return true;
 }
 
 // X <- G X (rows)
@@ -188,7 +192,7 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             tmp = Xr;
             for (int p = 0; p < 2; ++p) {
                 hipLaunchKernelGGL(k_normalize_rows, dim3(ka), dim3(256), 0, st, X, n);
-                project_out(X, ka, n, Vr, l, w, st);
+                if (!project_out(X, ka, n, Vr, l, w, st)) return SVDP_OK;
                 orthonormalize(X, tmp, ka, n, 1, w, st);
             }
         }
@@ -246,7 +250,7 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             }
             X = cur;
             tmp = prev;
-            project_out(X, ka, n, Vr, l, w, st);
+            if (!project_out(X, ka, n, Vr, l, w, st)) return SVDP_OK;
             orthonormalize(X, tmp, ka, n, last ? 2 : 1, w, st);
         }
         products += 1;

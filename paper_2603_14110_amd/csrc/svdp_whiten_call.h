@@ -73,6 +73,7 @@ EigTopWs carve_eigtop(const WhitenWs &w, int d, int r)
 {
     EigTopWs e;
     const size_t k = eigtop_block(d, r), kn = k * d, kk = k * k;      // 2 k <= d: two blocks of vectors fit a d x d matrix
+    e.k = (int)k;
     e.X = w.T0;
     e.Y = w.T0 + kn;
     e.Xa = w.T1;

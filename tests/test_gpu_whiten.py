@@ -179,3 +179,40 @@ def test_leading_eigenvectors_over_spectra(env, kind, d, r):
     # fp32, and eigenvalues of a Gram matrix: an error of 1e-13 of the largest is 3e-7 of its root where sigma is zero
     assert np.all(np.abs(sigma - sv) <= 1e-6 * sv[0])
     assert np.all(np.diff(sigma) <= 0) and 0 <= sweeps[1] <= 24
+
+
+def _with_spectrum(rng, D, T, d, sv):
+    """W [D][d], X [T][d] (fp32 values) with the given singular values of W S, S S^T = X^T X."""
+    X = rng.standard_normal((T, d)).astype(np.float32)
+    S = np.linalg.cholesky(X.astype(np.float64).T @ X.astype(np.float64))
+    U, V = np.linalg.qr(rng.standard_normal((D, d)))[0], np.linalg.qr(rng.standard_normal((d, d)))[0]
+    return np.linalg.solve(S.T, ((U * sv) @ V.T).T).T.astype(np.float32, order="C"), X
+
+
+@pytest.mark.parametrize("d,r,kind", [
+    (512, 128, "10^(-6i/r)"),          # most vectors leave the block at once: more than stay in it
+    (1024, 256, "10^(-6.5i/r)"),
+    (1024, 256, "ramp and drop"),      # and the block is filled up with new rows behind a gap
+])
+def test_more_vectors_leave_the_block_than_stay(env, d, r, kind):
+    """Decaying spectra, where the vectors that have left the block soon outnumber its rows: the same bits from two calls,
+    and every singular value, the product and its columns against the oracle.  The weights are rounded to fp32, so the
+    matrix moves by at most 2^-24 of its largest singular value; both sides are given the rounded ones.  Tolerances: fp32
+    results (2^-24 per element), sigma relative to itself."""
+    binding, torch, calib = env
+    rng = np.random.default_rng(d + r)
+    i = np.arange(d)
+    energy = {"10^(-6i/r)": lambda: 10.0 ** (-6.0 * i / r), "10^(-6.5i/r)": lambda: 10.0 ** (-6.5 * i / r),
+              "ramp and drop": lambda: np.where(i < 0.75 * r, 10.0 ** (-4.0 * i / r), 1e-5 * np.exp(-i / d))}[kind]()
+    W, X = _with_spectrum(rng, d + 64, 2 * d, d, np.sqrt(energy))
+    Wd, Xd = torch.from_numpy(W).cuda(), torch.from_numpy(X).cuda()
+    P, Q, sigma, _ = binding.whiten_factors(Wd, Xd, r)
+    P2, Q2, sigma2, _ = binding.whiten_factors(Wd, Xd, r)
+    assert torch.equal(P, P2) and torch.equal(Q, Q2) and np.array_equal(sigma, sigma2)
+    A, B = calib.whitened_factors(W.astype(np.float64), X.astype(np.float64), r)
+    AB, QP = A @ B, Q.cpu().numpy().astype(np.float64) @ P.cpu().numpy().astype(np.float64).T
+    assert np.linalg.norm(QP - AB) <= 2e-6 * np.linalg.norm(AB)
+    sv = np.linalg.norm(A, axis=0)
+    assert np.all(np.abs(sigma - sv) <= 1e-6 * sv)
+    col = np.linalg.norm(Q.cpu().numpy().astype(np.float64), axis=0)
+    assert np.all(np.abs(col - sv) <= 1e-6 * sv)
