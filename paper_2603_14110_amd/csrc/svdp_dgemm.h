@@ -6,7 +6,7 @@
 // tile as a template parameter, two LDS stages and ONE barrier per K step (the next step's global loads are in
 // flight during the products, and are stored to the other stage after them).  Operands are taken as they lie in
 // memory: either [rows][K] or [K][rows], and in the storage type (bf16 and fp32 are widened on the way into LDS),
-// so that neither X^T X nor W^T W needs a transposed or a widened copy.
+// so that neither X^T X nor (W S)^T (W S) needs a transposed or a widened copy.
 // Measured at d = 4096, D = 11008, T = 8192 (bf16 inputs), before = 64 x 64 tiles, two barriers per step, 8-byte
 // loads, fp64 copies of the inputs:  X^T X 7.6 -> 2.8 ms and W^T W 4.0 ms (lower halves: 50 and 48 TFLOP/s of 78.6),
 // product with a triangular 4096 x 4096 factor 1.35 ms (53 TFLOP/s); second moments and Gram matrix of the call
@@ -32,10 +32,9 @@ enum DgFlags : int {
     DG_LOWER = 1,        // only tiles that touch the lower triangle of C are formed (square tiles) ...
     DG_MIRROR = 2,       // ... and written to the upper triangle too
     DG_K_FROM_N = 4,     // B's column n is zero for k < n (a lower-triangular B given as [K][N])
-    DG_K_FROM_M = 8,     // A's row m is zero for k < m
-    DG_K_UPTO_N = 16,    // B's row n is zero for k > n
-    DG_LOOSE_A = 32,     // A (B) does not start on a 16-byte boundary: element by element
-    DG_LOOSE_B = 64
+    DG_K_UPTO_N = 8,     // B's row n is zero for k > n
+    DG_LOOSE_A = 16,     // A (B) does not start on a 16-byte boundary: element by element
+    DG_LOOSE_B = 32
 };
 
 struct DgEpilogue {
@@ -154,7 +153,6 @@ __global__ __launch_bounds__(DG_THREADS, 2) void k_dgemm(const TA *__restrict__ 
     const int m0 = bm * BM, n0 = bn * BN;
     int k_begin = blockIdx.z * kpart, k_end = min(K, k_begin + kpart);
     if (flags & DG_K_FROM_N) k_begin = max(k_begin, n0 / BK * BK);
-    if (flags & DG_K_FROM_M) k_begin = max(k_begin, m0 / BK * BK);
     if (flags & DG_K_UPTO_N) k_end = min(k_end, n0 + BN);
 
     f64x4_t acc[TM][TN];

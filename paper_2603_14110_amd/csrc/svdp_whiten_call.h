@@ -3,8 +3,9 @@
 // ---- work buffers ----
 struct WhitenWs {
     double *S;                  // [d][d]  C = X^T X, then its lower Cholesky factor
-    double *G;                  // [d][d]  (W S)^T (W S)
-    double *T0, *T1, *T2;       // [d][d]  W^T W, (W^T W) S; then the work matrices of the eigen-decomposition
+    double *M;                  // [D][d]  W S
+    double *G;                  // [d][d]  M^T M
+    double *T0, *T1, *T2;       // [d][d]  work matrices of the eigen-decomposition
     double *lamG;               // [d] eigenvalues by place
     double *invL;               // [d/64][64][64] inverses of S's diagonal blocks
     int32_t *fail;              // set by the factorisation if X^T X is not positive definite
@@ -31,9 +32,11 @@ size_t whiten_ws_bytes(int d, int D, int T, int r)
     return bytes + align_up((size_t)r * 4);
 }
 
-// Everything but `part` takes at most 6.9 d^2 + (max(D, d) + 64) r + 170 d doubles (2 k <= d and r <= 0.8 k where the
-// iteration runs, no block where it does not) and T >= d, so it always fits; the parts of split products get what is
-// left, up to what they can use.
+// That size holds 3 D d + d T + 6 d^2 + r d + max(D, d) r + 131 d + 4096 doubles; what follows takes, without `part`,
+// D d + 5 d^2 + 2 r d + 6 k^2 + max(D, d) r + 131.5 d + 67 k and at most 24 roundings to 32 doubles more.  T >= d leaves
+// 2 D d + 2 d^2 - r d - 6 k^2 - 67 k - d / 2 + 4096 at least: more than d^2 where the iteration does not run (k = 0, r <= d),
+// and 0.1 d^2 + 2 D d - 34 d + 4096 where it does (2 k <= d, r <= 0.8 k), at no d below 2400.
+// The parts of split products get what is left, up to what they can use.
 WhitenWs carve_whiten(void *base, int d, int D, int T, int r)
 {
     WhitenWs w;
@@ -46,6 +49,7 @@ WhitenWs carve_whiten(void *base, int d, int D, int T, int r)
     };
     const size_t dd = (size_t)d * d;
     w.S = take(dd);
+    w.M = take((size_t)D * d);
     w.G = take(dd);
     w.T0 = take(dd);
     w.T1 = take(dd);
@@ -133,13 +137,13 @@ svdp_status whiten_impl(const void *W_gate, const void *X, int d, int D, int T, 
     // S needs C positive definite (more independent tokens than dimensions)
     if (failed != 0) return SVDP_ERR_UNSUPPORTED;
 
-    // G = (W S)^T (W S) = S^T ((W^T W) S): 2/3 of the products that W S and its Gram matrix would take (S is
-    // triangular and both Gram matrices are symmetric), and no D x d matrix in 64 bits is ever stored
-    bool ok = dgemm<DG_K_ROWS, DG_K_ROWS>(op(Wg, d), op(Wg, d), w.T0, d, d, d, D, st, SYM, DgEpilogue{}, scr) &&
-              dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.T0, d), op((const double *)w.S, d), w.T1, d, d, d, d, st,
-                                          DG_K_FROM_N, DgEpilogue{}, scr) &&
-              dgemm<DG_K_ROWS, DG_K_ROWS>(op((const double *)w.S, d), op((const double *)w.T1, d), w.G, d, d, d, d, st,
-                                          SYM | DG_K_FROM_M, DgEpilogue{}, scr);
+    // M = W S and G = M^T M.  Not S^T ((W^T W) S), a quarter of the operations less at D = 2.7 d: where W hardly
+    // responds to the direction that dominates the tokens, W^T W and S S^T cancel, and G would be off by
+    // 2^-53 (||W|| ||S|| / ||W S||)^2 of itself (at tokens with a mean 1e6 times their spread 1e-6 of every singular value)
+    bool ok = dgemm<DG_ROWS_K, DG_K_ROWS>(op(Wg, d), op((const double *)w.S, d), w.M, d, D, d, d, st, DG_K_FROM_N, DgEpilogue{},
+                                          scr) &&
+              dgemm<DG_K_ROWS, DG_K_ROWS>(op((const double *)w.M, d), op((const double *)w.M, d), w.G, d, d, d, D, st, SYM,
+                                          DgEpilogue{}, scr);
     if (!ok) return SVDP_ERR_UNSUPPORTED;
     bool found = false;
     int sw2 = 0;

@@ -216,3 +216,33 @@ def test_more_vectors_leave_the_block_than_stay(env, d, r, kind):
     assert np.all(np.abs(sigma - sv) <= 1e-6 * sv)
     col = np.linalg.norm(Q.cpu().numpy().astype(np.float64), axis=0)
     assert np.all(np.abs(col - sv) <= 1e-6 * sv)
+
+
+def _dominated(rng, d, D, T, mean, blind):
+    """Weights and tokens whose mean is `mean` times their spread, in a direction on no axis; `blind`: the weights do not
+    respond to it (they are still rounded to fp32 afterwards)."""
+    W, X = rng.standard_normal((D, d)) / np.sqrt(d), rng.standard_normal((T, d))
+    u = rng.standard_normal(d)
+    u /= np.linalg.norm(u)
+    if blind:
+        W -= np.outer(W @ u, u)
+    return W.astype(np.float32), (X + mean * u).astype(np.float32)
+
+
+@pytest.mark.parametrize("mean", [1e2, 1e4, 1e5, 1e6])
+@pytest.mark.parametrize("d,r", [(256, 40), (128, 24)])       # the iteration; the full decomposition
+def test_gate_that_does_not_respond_to_the_dominant_direction(env, d, r, mean):
+    """W S is small beside ||W|| ||S|| here, and its Gram matrix has to be formed so that it is accurate all the same.  The
+    factor S itself is only known to 2^-53 mean^2 in 64 bits, so what is compared is what holds for any S: the columns of
+    Q = U Sigma have sigma's lengths and are orthogonal.  Tolerance: fp32 rounding of Q's elements and of sigma (6e-8 each)."""
+    binding, torch, calib = env
+    rng = np.random.default_rng(d)
+    W, X = _dominated(rng, d, d + 64, 2 * d, mean, True)
+    P, Q, sigma, _ = binding.whiten_factors(torch.from_numpy(W).cuda(), torch.from_numpy(X).cuda(), r)
+    Q = Q.cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(np.linalg.norm(Q, axis=0) - sigma) <= 2e-7 * sigma)
+    C = (Q / sigma).T @ (Q / sigma)
+    assert np.abs(C - np.eye(r)).max() <= 4e-7
+    A, B = calib.whitened_factors(W.astype(np.float64), X.astype(np.float64), r)
+    AB = A @ B
+    assert np.linalg.norm(Q @ P.cpu().numpy().astype(np.float64).T - AB) <= (2e-6 + 2.0 ** -52 * mean ** 2) * np.linalg.norm(AB)
