@@ -242,9 +242,11 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
  * sweeps[1] = block-Jacobi sweeps that the (last projected) eigen-decomposition took.
  * S is the lower Cholesky factor of X^T X, as Alg. 1 prints it (blocked factorisation, 64-wide blocks);
  * V and Sigma^2 are the r leading eigenpairs of (W_gate S)^T (W_gate S), by subspace iteration with Chebyshev
- * filters to residuals of 2e-13 of its norm (block Jacobi sweeps on the projections; on the whole matrix where r is
- * more than about 0.4 d or no gap follows the r-th value), and S^-1 is applied to the r chosen vectors by block back-substitution.  All arithmetic is
- * fp64, the contractions on the matrix cores.
+ * filters; directions that dominate are taken out of W_gate S, so that the others are accurate relative to themselves
+ * (residuals of the wanted vectors together at most 1e-10 of the smallest wanted eigenvalue, as a rule below 2e-11).
+ * Block Jacobi sweeps decompose the projections, and the whole matrix where d < 256, r is more than about 0.4 d, no gap
+ * follows the r-th value or fewer than r are above rounding (off-diagonal norm of 1e-11 of the whole).  S^-1 is applied
+ * to the r chosen vectors by block back-substitution.  All arithmetic is fp64, the contractions on the matrix cores.
  * Needs d a multiple of 64, T >= d and X^T X positive definite to working precision (every pivot of
  * the factorisation above 1e-13 of the largest diagonal element), r <= d; otherwise
  * SVDP_ERR_UNSUPPORTED.

@@ -113,12 +113,4 @@ __global__ __launch_bounds__(256) void k_combine(double *__restrict__ y, const d
     if (i < n) y[i] = alpha * y[i] + beta * x[i];
 }
 
-// dst[i] = theta[i] * src[i], rows of n
-__global__ __launch_bounds__(256) void k_scale_rows(const double *__restrict__ src, const double *__restrict__ theta, int rows,
-                                                    int n, double *__restrict__ dst)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < (size_t)rows * n) dst[i] = theta[i / n] * src[i];
-}
-
 }   // namespace svdp

@@ -1,29 +1,39 @@
-// The r leading eigenvectors of a symmetric positive semi-definite matrix G [n][n] without its other n - r: a block of
-// k > r vectors is filtered by Chebyshev polynomials of G that are small on [0, b], b = the block's smallest Ritz value,
-// and large above (subspace iteration with Rayleigh-Ritz).  Almost all of it is k x n x n products on the fp64 matrix
-// cores, 4 to 35 of them; block Jacobi runs on the k x k projections only.  Included by svdp.hip after
-// svdp_whiten_run.h's helpers, inside its unnamed namespace.
+// The r leading eigenvectors of G = M^T M [n][n] without its other n - r: a block of k > r vectors is filtered by Chebyshev
+// polynomials of G that are small on [0, b], b = the block's smallest Ritz value, and large above (subspace iteration with
+// Rayleigh-Ritz).  Almost all of it is k x n x n products on the fp64 matrix cores, 4 to 50 of them; block Jacobi runs on the
+// k x k projections only.  Included by svdp.hip after svdp_whiten_run.h's helpers, inside its unnamed namespace.
 //
 //   start    k pseudo-random rows, three times X <- orth(X G)
 //   repeat   Rayleigh-Ritz: H = X G X^T, its eigenvectors rotate X; residuals of the wanted vectors; done if small
-//            vectors that have settled leave the block: G <- G - v theta v^T, so that a few dominant directions
-//            (the mean of the tokens carries 1e8 times the energy of the rest) do not limit the filter's degree
+//            dominant vectors that have settled leave the block: M <- M - (M v) v^T and G is formed again
 //            X <- orth(p(G) X), as many degrees as the Ritz values say are missing, in pieces of at most EIG_PIECE that
 //            also keep X's condition number below EIG_AMPLIFY
 //
-// Accuracy: the residuals of the block's wanted vectors together end below 2e-13 of ||G||_F, those of the r that left it
-// below 3e-14 sqrt(r); the Jacobi path stops at an off-diagonal norm of 1e-11 of it.
-// Measured (bf16, whole call), full Jacobi -> this: d = 4096, r = 256: 401 -> 31 ms (33 products of 256 to 320 x 4096 x
-// 4096 at 0.16 to 0.22 ms, two projections of 11 Jacobi sweeps together); d = 1024, r = 64: 43.6 -> 3.2 ms; d = 2560,
-// r = 640: 183 -> 45 ms.  With b fixed between projections and pieces as long as the condition number allowed, the first
-// took three projections and 50 ms: b starts at 0.65 of where it ends, which costs three quarters of the filter's rate.
-// Where it does not apply (block of more than half the dimension; no gap in reach behind the wanted vectors; X loses
-// rank, e.g. G of rank below r) the full Jacobi decomposition runs instead, on the untouched G.
+// Accuracy: a stored G, and every product with it, carries an error of a few 2^-53 of its LARGEST eigenvalue.  The mean of the
+// tokens alone often has 1e8 times the energy of the wanted directions behind it, so that error and a residual measured
+// against ||G|| say nothing about those.  Hence what dominates is taken out of the factor M, whose elements only carry 2^-53
+// of the largest singular value, until the block's eigenvalues are within EIG_SPREAD of each other; and the residuals of
+// the wanted vectors together end below EIG_TOL (where they stop falling first: 5 EIG_TOL) of the SMALLEST wanted eigenvalue.
+// Against singular values worked out with 64-bit mantissas (d = 256, r = 40, tokens with a mean of 10 to 3e6 times their
+// spread; geometric spectra over up to twelve decades): within 4e-12 each, the product within 2e-9 of sigma_r.
+// Measured (bf16, whole call), full Jacobi -> this: d = 4096, r = 256: 467 -> 42 ms (56 products of 256 to 320 x 4096 x 4096 at
+// 0.16 to 0.22 ms, two projections of 11 Jacobi sweeps together, G once more); d = 1024, r = 64: 47 -> 4.3 ms;
+// d = 2560, r = 640: 183 -> 53 ms.  With b fixed between projections and pieces as long as the condition number allowed, the
+// first took three projections: b starts at 0.65 of where it ends, which costs three quarters of the filter's rate.  With
+// EIG_SETTLED = 1e-13 a projection more was needed at d = 512, r = 128 (9.1 against 6.2 ms): vectors that share a strip of the
+// projected matrix with the largest are left with that much.
+// Where it does not apply (block of more than half the dimension; no gap in reach behind the wanted vectors; fewer than r
+// singular values above rounding) the full Jacobi decomposition runs instead, on the untouched G.
 
-constexpr double EIG_TOL = 2e-13;           // sqrt(sum of squared residuals of the wanted vectors) / ||G||_F
-constexpr double EIG_TOL_JACOBI = 1e-13;    // of the projected problems (off-diagonal / total Frobenius norm)
-constexpr double EIG_TOL_FIRST = 1e-12;     // of the first one, which only has to separate what dominates
-constexpr double EIG_SETTLED = 3e-14;       // residual / ||G||_F of one vector that may leave the block
+// sqrt(sum of squared residuals of the wanted vectors) / smallest wanted eigenvalue: a vector whose eigenvalue is a
+// thousandth away from the first unwanted one is then off by 2e-8, which fp32 results do not show
+constexpr double EIG_TOL = 2e-11;
+constexpr double EIG_TOL_JACOBI = 1e-12;    // of the projected problems (off-diagonal / total Frobenius norm), or less where
+                                            // the wanted eigenvalues are small in them
+// Largest over smallest eigenvalue of one block.  Up to here the error of G, 1e-16 of the largest, is 1e-13 of the smallest.
+constexpr double EIG_SPREAD = 1e3;
+constexpr double EIG_SETTLED = 5e-13;       // residual of a vector that may leave, of sqrt(its eigenvalue * the largest)
+constexpr double EIG_NOISE = 2e-28;         // eigenvalues below this part of the largest are rounding errors of M
 constexpr double EIG_AMPLIFY = 1e5;         // largest over smallest filter value between two orthogonalisations
 constexpr double EIG_PIECE = 8.0;           // largest degree of a piece of the filter
 constexpr double EIG_SHIFT = 4e-13;         // of the first Cholesky QR pass (above k_chol_diag's bound of 1e-13)
@@ -41,13 +51,15 @@ inline int eigtop_block(int n, int r)
 struct EigTopWs {
     int k;                              // eigtop_block(n, r)
     double *X, *Y, *Xa, *Xb;            // [k][n]
-    double *Gd;                         // [n][n] deflated G
+    double *M;                          // [D][n], G = M^T M; what leaves the block is taken out of it
+    int D;
+    double *MV;                         // [D][<= r]
+    double *Gd;                         // [n][n] G formed again
     double *H, *Ha, *V, *Va, *Vs, *L;   // [k][k]
     double *invL;                       // [k][64]
     double *lam, *theta, *res;          // [k]
     double *scale;                      // [1]
     double *Uall, *rowsums, *sums;      // as in WhitenWs
-    double *scaled;                     // [r][n]
     int32_t *sel, *fail;
     DgScratch scr;
 };
@@ -92,8 +104,17 @@ inline void times_g(const double *G, const double *X, double *out, int k, int n,
     dgemm<DG_ROWS_K, DG_ROWS_K>(op(X, n), op(G, n), out, n, k, n, n, st, 0, ep, scr);
 }
 
-// Vr [r][n] = the r leading eigenvectors of G as rows, largest eigenvalue first; lam [r] (host).  `found` = false: the
-// caller takes the Jacobi decomposition (G is untouched).  sweeps: of the last projected problem.
+// M <- M - (M Vl^T) Vl for the l rows of Vl, l < r
+bool take_out_of_factor(const double *Vl, int l, int n, const EigTopWs &w, hipStream_t st)
+{
+    const int ld = l + (l & 1);                                // 16-byte aligned rows
+    dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)w.M, n), op(Vl, n), w.MV, ld, w.D, l, n, st, 0, DgEpilogue{}, w.scr);
+    dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.MV, ld), op(Vl, n), w.M, n, w.D, n, l, st, 0, minus_from(w.M, n));
+    return true;
+}
+
+// Vr [r][n] = the r leading eigenvectors of G = M^T M as rows, largest eigenvalue first; lam [r] (host).  M is destroyed.
+// `found` = false: the caller takes the Jacobi decomposition (G is untouched).  sweeps: of the last projected problem.
 svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, double *lam, bool &found, int *sweeps,
                                  EigTopWs &w, hipStream_t st)
 {
@@ -114,20 +135,22 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
         orthonormalize(X, tmp, k, n, p < 2 ? 1 : 3, w, st);
     }
     const double *Gc = G;
-    double norm = 0.0, last_err = 1e300;
-    int l = 0, ka = k, products = 4, piece = 0;             // vectors that left the block; rows of the block
-    for (int cycle = 0; cycle < 12; ++cycle) {
+    double largest = 0.0, last_err = 1e300, jacobi_tol = EIG_TOL_JACOBI;
+    double spent = 3.0 * k;                                 // n x n products of one row each; the limit is 16 n of them
+    int l = 0, ka = k, piece = 0;                           // vectors that left the block; rows of the block
+    for (int cycle = 0; cycle < 24; ++cycle) {
         // Rayleigh-Ritz
         double *Y = nullptr, *Xr = nullptr, *Yr = nullptr;
         for (double *p : {w.X, w.Xa, w.Xb, w.Y})
             if (p != X) (Y == nullptr ? Y : Xr == nullptr ? Xr : Yr) = p;
         times_g(Gc, X, Y, ka, n, st, w.scr);
+        spent += ka;
         dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)X, n), op((const double *)Y, n), w.H, ka, ka, ka, n, st,
                                     DG_LOWER | DG_MIRROR, DgEpilogue{}, w.scr);
         double *A = w.H, *Aa = w.Ha, *V = w.V, *Va = w.Va;
         int sw = 0;
         const svdp_status e =
-            jacobi_eigh(&A, &Aa, &V, &Va, ka, w.Uall, w.rowsums, w.sums, w.lam, cycle == 0 ? EIG_TOL_FIRST : EIG_TOL_JACOBI, 24, &sw, st);
+            jacobi_eigh(&A, &Aa, &V, &Va, ka, w.Uall, w.rowsums, w.sums, w.lam, jacobi_tol, 24, &sw, st);
         if (e != SVDP_OK) return e;
         *sweeps = std::max(1, sw);
         hipLaunchKernelGGL(k_rank_descending, grid1(ka), dim3(256), 0, st, w.lam, ka, w.sel, w.theta);
@@ -143,17 +166,14 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             hipStreamSynchronize(st) != hipSuccess)
             return hip_failed();
         X = Xr;
-        if (cycle == 0) {
-            // ||G||_F up to what is outside the block (which is small or else nothing here converges)
-            for (int i = 0; i < ka; ++i) norm += theta[i] * theta[i];
-            norm = std::sqrt(norm);
-        }
+        if (cycle == 0) largest = theta[0];
         const int need = r - l;
+        const double smallest = theta[ka - 1], tol = EIG_TOL * theta[need - 1];
         double err = 0.0;
         for (int i = 0; i < need; ++i) err += res[i];
-        err = std::sqrt(err) / norm;
-        if (failed != 0 || !(err < 1e300) || !(norm > 0.0)) return SVDP_OK;
-        if (err <= EIG_TOL || (err <= 1e-12 && err > 0.5 * last_err)) {
+        err = std::sqrt(err);
+        if (failed != 0 || !(err < 1e300) || !(theta[0] > EIG_NOISE * largest)) return SVDP_OK;
+        if (theta[0] <= EIG_SPREAD * theta[need - 1] && (err <= tol || (err <= 5.0 * tol && err > 0.5 * last_err))) {
             for (int i = 0; i < need; ++i) lam[l + i] = theta[i];
             if (hipMemcpyAsync(Vr + (size_t)l * n, X, (size_t)need * n * 8, hipMemcpyDeviceToDevice, st) != hipSuccess)
                 return hip_failed();
@@ -161,25 +181,28 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             return hip_status(hipSuccess);
         }
         last_err = err;
-        const double b = std::max(theta[ka - 1], 1e-15 * norm), margin = 10.0;
-        // no gap in reach: the full decomposition would be done sooner
-        const double apart = std::acosh(std::max(2.0 * theta[need - 1] / b - 1.0, 1.0));
-        if (!(std::log(std::max(err / EIG_TOL, 2.0)) / apart * ka < 16.0 * n - (double)products * ka)) return SVDP_OK;
-        // Settled vectors leave the block.  What is left of their residual couples them to the rest of G by as little, far
-        // below the filter's edge, so it does not grow.
+        // Settled vectors leave the block, the largest first and not beyond EIG_SPREAD.  What is left of their residual couples
+        // them to the rest of G by as little, far below the filter's edge, so it does not grow.
+        double wanted = theta[need - 1], margin = 10.0;
         int out = 0;
-        while (out < need && std::sqrt(res[out]) < EIG_SETTLED * norm && theta[out] > 2.0 * theta[need - 1]) ++out;
-        double top = theta[0];
+        while (out + 1 < need && theta[out] > 2.0 * wanted && theta[out] * EIG_SPREAD >= theta[0] &&
+               std::sqrt(res[out]) < EIG_SETTLED * std::sqrt(theta[0] * theta[out]))
+            ++out;
+        double rest = 0.0;
+        for (int i = out; i < ka; ++i) rest += theta[i] * theta[i];
+        jacobi_tol = std::max(1e-15, std::min(EIG_TOL_JACOBI, 0.25 * tol / std::sqrt(rest)));
         if (out > 0) {
             double *Vl = Vr + (size_t)l * n;
             if (hipMemcpyAsync(Vl, X, (size_t)out * n * 8, hipMemcpyDeviceToDevice, st) != hipSuccess) return hip_failed();
-            hipLaunchKernelGGL(k_scale_rows, grid1((size_t)out * n), dim3(256), 0, st, Vl, w.theta, out, n, w.scaled);
-            dgemm<DG_K_ROWS, DG_K_ROWS>(op((const double *)w.scaled, n), op((const double *)Vl, n), w.Gd, n, n, n, out, st,
-                                        DG_LOWER | DG_MIRROR, minus_from(Gc, n));
-            Gc = w.Gd;
             for (int i = 0; i < out; ++i) lam[l + i] = theta[i];
-            top = theta[out];
             l += out;
+            // the second time all of them: the first leaves 2^-53 of what was taken out, which may be more than the rest
+            take_out_of_factor(Vl, out, n, w, st);
+            take_out_of_factor(Vr, l, n, w, st);
+            dgemm<DG_K_ROWS, DG_K_ROWS>(op((const double *)w.M, n), op((const double *)w.M, n), w.Gd, n, n, n, w.D, st,
+                                        DG_LOWER | DG_MIRROR, DgEpilogue{}, w.scr);
+            Gc = w.Gd;
+            spent += 0.5 * w.D;
             const int left = ka - out, want = std::min(k, round_up(r - l + std::max(32, r / 4), BJ_S));
             X += (size_t)out * n;                // moved to the front of a buffer by the orthonormalisation below
             double *front = Y;
@@ -193,14 +216,18 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             for (int p = 0; p < 2; ++p) {
                 hipLaunchKernelGGL(k_normalize_rows, dim3(ka), dim3(256), 0, st, X, n);
                 if (!project_out(X, ka, n, Vr, l, w, st)) return SVDP_OK;
-                orthonormalize(X, tmp, ka, n, 1, w, st);
+                orthonormalize(X, tmp, ka, n, p + 1, w, st);
             }
+            last_err = 1e300;
+            margin = 100.0;                      // the residuals were those of the old G; another projection costs more
+            if (!(wanted > 1e-14 * theta[0])) continue;        // the Ritz values behind them were rounding errors
         }
+        if (!(wanted > 0.0)) return SVDP_OK;
+        const double top = theta[out];
         // Filter, in pieces.  Before each but the first, b follows the smallest Rayleigh quotient of the block, which is
         // near its smallest Ritz value (the rows stay in the order of the Ritz values): it rises while the block's last rows
         // settle, and the rate hangs on it, because what lies outside the block is only damped as far as b reaches.
-        double bound = b, todo = std::log(std::max(err / EIG_TOL * margin, 2.0));
-        double wanted = theta[need - 1];
+        double bound = std::max(smallest, 1e-15 * top), todo = std::log(std::max(err / tol * margin, 2.0));
         auto growth = [](double value, double edge) { return std::acosh(std::max(2.0 * value / edge - 1.0, 1.0)); };
         int single = 0;
         for (bool first = true, last = false; !last; first = false) {
@@ -214,17 +241,18 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
                 std::sort(res, res + ka, std::greater<double>());
                 const double lowest = res[ka - 1];
                 wanted = std::max(wanted, res[r - l - 1]);         // has risen, too
-                if (!(lowest < wanted)) break;                     // (also NaN) the next projection tells more
+                if (!(lowest < wanted)) return SVDP_OK;            // no gap at all (also NaN)
                 // what the last piece gained where the new bound now is
                 todo += piece * growth(lowest, bound);
                 bound = std::max(bound, lowest);
             }
             const double rate = growth(wanted, bound), left = std::ceil(todo / rate);
-            if (!(left * ka < 16.0 * n - (double)products * ka)) return SVDP_OK;
+            // no gap in reach: the full decomposition would be done sooner
+            if (!(left * ka < 16.0 * n - spent)) return SVDP_OK;
             piece = (int)std::max(1.0, std::min({EIG_PIECE, std::floor(std::acosh(EIG_AMPLIFY) / std::max(growth(top, bound), 1e-3)), left}));
             last = piece >= left || (piece == 1 && ++single == 3);  // a dominant direction keeps the pieces short: project, it may have settled
             todo -= piece * rate;
-            products += piece;
+            spent += (double)piece * ka;
             const double half = 0.5 * bound, s0 = half / (top - half);
             double s1 = s0;
             DgEpilogue ep;
@@ -253,7 +281,6 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             if (!project_out(X, ka, n, Vr, l, w, st)) return SVDP_OK;
             orthonormalize(X, tmp, ka, n, last ? 2 : 1, w, st);
         }
-        products += 1;
     }
     return SVDP_OK;
 }

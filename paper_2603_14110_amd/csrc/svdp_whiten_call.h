@@ -3,7 +3,7 @@
 // ---- work buffers ----
 struct WhitenWs {
     double *S;                  // [d][d]  C = X^T X, then its lower Cholesky factor
-    double *M;                  // [D][d]  W S
+    double *M;                  // [D][d]  W S; the iteration takes what dominates out of it
     double *G;                  // [d][d]  M^T M
     double *T0, *T1, *T2;       // [d][d]  work matrices of the eigen-decomposition
     double *lamG;               // [d] eigenvalues by place
@@ -73,7 +73,7 @@ WhitenWs carve_whiten(void *base, int d, int D, int T, int r)
     return w;
 }
 
-EigTopWs carve_eigtop(const WhitenWs &w, int d, int r)
+EigTopWs carve_eigtop(const WhitenWs &w, int d, int D, int r)
 {
     EigTopWs e;
     const size_t k = eigtop_block(d, r), kn = k * d, kk = k * k;      // 2 k <= d: two blocks of vectors fit a d x d matrix
@@ -82,6 +82,9 @@ EigTopWs carve_eigtop(const WhitenWs &w, int d, int r)
     e.Y = w.T0 + kn;
     e.Xa = w.T1;
     e.Xb = w.T1 + kn;
+    e.M = w.M;
+    e.D = D;
+    e.MV = w.out64;
     e.Gd = w.T2;
     double *p = w.small;
     auto take = [&](size_t n) {
@@ -103,7 +106,6 @@ EigTopWs carve_eigtop(const WhitenWs &w, int d, int r)
     e.Uall = w.Uall;
     e.rowsums = w.rowsums;
     e.sums = w.sums;
-    e.scaled = w.out64;
     e.sel = w.sel;
     e.fail = w.fail;
     e.scr = DgScratch{w.part, w.n_part};
@@ -147,7 +149,7 @@ svdp_status whiten_impl(const void *W_gate, const void *X, int d, int D, int T, 
     if (!ok) return SVDP_ERR_UNSUPPORTED;
     bool found = false;
     int sw2 = 0;
-    EigTopWs ew = carve_eigtop(w, d, r);
+    EigTopWs ew = carve_eigtop(w, d, D, r);
     svdp_status e = leading_eigenvectors(w.G, d, r, w.Vr, lam.data(), found, &sw2, ew, st);
     if (e != SVDP_OK) return e;
     if (!found) {

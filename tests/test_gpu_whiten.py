@@ -246,3 +246,47 @@ def test_gate_that_does_not_respond_to_the_dominant_direction(env, d, r, mean):
     A, B = calib.whitened_factors(W.astype(np.float64), X.astype(np.float64), r)
     AB = A @ B
     assert np.linalg.norm(Q @ P.cpu().numpy().astype(np.float64).T - AB) <= (2e-6 + 2.0 ** -52 * mean ** 2) * np.linalg.norm(AB)
+
+
+@pytest.mark.parametrize("mean", [1e1, 1e3, 1e4, 1e5, 1e6, 3e6])
+@pytest.mark.parametrize("d,r", [(256, 40), (512, 64), (128, 24)])       # the iteration twice; the full decomposition
+def test_wanted_directions_behind_a_dominant_mean(env, d, r, mean):
+    """Tokens whose mean has up to 1e13 times the energy of everything else: the directions behind it are still accurate
+    relative to themselves.  Tolerance: fp32 results, and the second moments and their factor, which 64 bits hold to
+    2^-53 mean^2 of what is left beside the mean (the oracle's own as well: twice that, and as much again for the sum)."""
+    binding, torch, calib = env
+    rng = np.random.default_rng(d + 1)
+    W, X = _dominated(rng, d, d + 64, 2 * d, mean, False)
+    P, Q, sigma, _ = binding.whiten_factors(torch.from_numpy(W).cuda(), torch.from_numpy(X).cuda(), r)
+    A, B = calib.whitened_factors(W.astype(np.float64), X.astype(np.float64), r)
+    AB, moments = A @ B, 2.0 ** -51 * mean ** 2
+    QP = Q.cpu().numpy().astype(np.float64) @ P.cpu().numpy().astype(np.float64).T
+    assert np.linalg.norm(QP - AB) <= (2e-6 + moments) * np.linalg.norm(AB)
+    sv = np.linalg.norm(A, axis=0)
+    assert np.all(np.abs(sigma - sv) <= (1e-6 + 0.25 * moments) * sv)
+    col = np.linalg.norm(Q.cpu().numpy().astype(np.float64), axis=0)
+    assert np.all(np.abs(col - sigma) <= 2e-7 * sigma)
+
+
+@pytest.mark.parametrize("kind", ["three levels", "twelve decades", "noise behind"])
+def test_wanted_directions_far_below_the_largest(env, kind):
+    """Spectra over many decades in directions without structure.  W is rounded to fp32, which fills the spectrum up from
+    below at 2^-24 of the largest singular value; the oracle is given the rounded weights.  Its own SVD, and forming W S, are
+    good to 2^-53 d of the largest singular value, 1e-10 of the smallest wanted one here."""
+    binding, torch, calib = env
+    rng = np.random.default_rng(5)
+    d, D, T, r = 512, 640, 1024, 64
+    i = np.arange(d)
+    energy = {"three levels": lambda: np.where(i < 1, 1e9, np.where(i < 2, 1e8, np.where(i < 3, 1e5, np.exp(-i / 100.0)))),
+              "twelve decades": lambda: 10.0 ** (-12.0 * i / r),
+              "noise behind": lambda: np.where(i < 40, 1e4 * 0.9 ** i, 0.0)}[kind]()
+    W, X = _with_spectrum(rng, D, T, d, np.sqrt(energy))
+    P, Q, sigma, _ = binding.whiten_factors(torch.from_numpy(W).cuda(), torch.from_numpy(X).cuda(), r)
+    A, B = calib.whitened_factors(W.astype(np.float64), X.astype(np.float64), r)
+    AB, Q = A @ B, Q.cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(Q @ P.cpu().numpy().astype(np.float64).T - AB) <= 2e-6 * np.linalg.norm(AB)
+    sv, col = np.linalg.norm(A, axis=0), np.linalg.norm(Q, axis=0)
+    assert np.all(np.abs(sigma - sv) <= 1e-6 * sv)
+    assert np.all(np.abs(col - sv) <= 1e-6 * sv)
+    C = (Q / sv).T @ (Q / sv)
+    assert np.abs(C - np.eye(r)).max() <= 1e-6
