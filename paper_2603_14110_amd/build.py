@@ -11,6 +11,8 @@ SRC = os.path.join(HERE, "csrc", "svdp.hip")
 # every file the translation unit includes: the library is rebuilt when any of them is newer
 DEPS = [SRC, os.path.join(os.path.dirname(HERE), "include", "svdp.h")] + sorted(glob.glob(os.path.join(HERE, "csrc", "*.h")))
 LIB = os.path.join(HERE, "libsvdp.so")
+# a matrix product that the device refused must not go unnoticed ([[nodiscard]])
+WARNINGS = ["-Wall", "-Wno-unused-function", "-Werror=unused-result"]
 PROBE_SRC = os.path.join(HERE, "csrc", "svdp_probe.hip")
 PROBE_LIB = os.path.join(HERE, "libsvdp_probe.so")
 
@@ -21,8 +23,7 @@ def hipcc_path() -> str:
 
 def _hipcc(src: str, out: str, verbose: bool) -> None:
     cmd = [hipcc_path(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Wall", "-Wno-unused-function", "-o", out, src]
+           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", *WARNINGS, "-o", out, src]
     if verbose:
         print(" ".join(cmd))
     subprocess.run(cmd, check=True)

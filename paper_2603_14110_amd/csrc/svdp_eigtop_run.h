@@ -67,50 +67,51 @@ struct EigTopWs {
 // X [k][n] becomes orthonormal by passes of Cholesky QR (Gram matrix, factor, forward substitution by blocks); the first
 // pass adds EIG_SHIFT to the unit diagonal, which lets it take any condition number and leaves one that the next pass can.
 // The columns' order is kept: row i stays in the span of the rows up to i.  Swaps X and tmp once per pass.
-void orthonormalize(double *&X, double *&tmp, int k, int n, int passes, const EigTopWs &w, hipStream_t st)
+[[nodiscard]] bool orthonormalize(double *&X, double *&tmp, int k, int n, int passes, const EigTopWs &w, hipStream_t st)
 {
+    bool ok = true;
     for (int p = 0; p < passes; ++p) {
         hipLaunchKernelGGL(k_normalize_rows, dim3(k), dim3(256), 0, st, X, n);
-        dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)X, n), op((const double *)X, n), w.L, k, k, k, n, st, DG_LOWER | DG_MIRROR,
-                                    DgEpilogue{}, w.scr);
+        ok &= dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)X, n), op((const double *)X, n), w.L, k, k, k, n, st,
+                                          DG_LOWER | DG_MIRROR, DgEpilogue{}, w.scr);
         if (p == 0) hipLaunchKernelGGL(k_add_diagonal, grid1(k), dim3(256), 0, st, w.L, k, EIG_SHIFT);
-        cholesky_blocked(w.L, k, w.invL, w.scale, w.fail, st);
+        ok &= cholesky_blocked(w.L, k, w.invL, w.scale, w.fail, st);
         for (int c0 = 0; c0 < k; c0 += CH_B) {
             double *done = tmp + (size_t)c0 * n, *below = X + (size_t)(c0 + CH_B) * n;
-            dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.invL + (size_t)c0 * CH_B, CH_B),
-                                        op((const double *)X + (size_t)c0 * n, n), done, n, CH_B, n, CH_B, st);
-            dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.L + (size_t)(c0 + CH_B) * k + c0, k), op((const double *)done, n),
-                                        below, n, k - c0 - CH_B, n, CH_B, st, 0, minus_from(below, n));
+            ok &= dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.invL + (size_t)c0 * CH_B, CH_B),
+                                              op((const double *)X + (size_t)c0 * n, n), done, n, CH_B, n, CH_B, st);
+            ok &= dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.L + (size_t)(c0 + CH_B) * k + c0, k),
+                                              op((const double *)done, n), below, n, k - c0 - CH_B, n, CH_B, st, 0,
+                                              minus_from(below, n));
         }
         std::swap(X, tmp);
     }
+    return ok;
 }
 
 // X <- X - (X Vl^T) Vl for the l rows of Vl and the ka of X.  The coefficients lie in Vs with the full block's stride: as
-// vectors leave the block, l outgrows ka, but never w.k (l < r < w.k).  false: it would not fit, nothing was done.
-bool project_out(double *X, int ka, int n, const double *Vl, int l, const EigTopWs &w, hipStream_t st)
+// vectors leave the block, l outgrows ka, but never w.k (l < r < w.k).
+[[nodiscard]] bool project_out(double *X, int ka, int n, const double *Vl, int l, const EigTopWs &w, hipStream_t st)
 {
     if (l == 0) return true;
     if (l > w.k || ka > w.k) return false;
-    dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)X, n), op(Vl, n), w.Vs, w.k, ka, l, n, st, 0, DgEpilogue{}, w.scr);
-    dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.Vs, w.k), op(Vl, n), X, n, ka, n, l, st, 0, minus_from(X, n));
-    return true;
+    return dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)X, n), op(Vl, n), w.Vs, w.k, ka, l, n, st, 0, DgEpilogue{}, w.scr) &&
+           dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.Vs, w.k), op(Vl, n), X, n, ka, n, l, st, 0, minus_from(X, n));
 }
 
 // X <- G X (rows)
-inline void times_g(const double *G, const double *X, double *out, int k, int n, hipStream_t st, const DgScratch &scr,
-                    const DgEpilogue &ep = DgEpilogue{})
+[[nodiscard]] inline bool times_g(const double *G, const double *X, double *out, int k, int n, hipStream_t st,
+                                  const DgScratch &scr, const DgEpilogue &ep = DgEpilogue{})
 {
-    dgemm<DG_ROWS_K, DG_ROWS_K>(op(X, n), op(G, n), out, n, k, n, n, st, 0, ep, scr);
+    return dgemm<DG_ROWS_K, DG_ROWS_K>(op(X, n), op(G, n), out, n, k, n, n, st, 0, ep, scr);
 }
 
 // M <- M - (M Vl^T) Vl for the l rows of Vl, l < r
-bool take_out_of_factor(const double *Vl, int l, int n, const EigTopWs &w, hipStream_t st)
+[[nodiscard]] bool take_out_of_factor(const double *Vl, int l, int n, const EigTopWs &w, hipStream_t st)
 {
     const int ld = l + (l & 1);                                // 16-byte aligned rows
-    dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)w.M, n), op(Vl, n), w.MV, ld, w.D, l, n, st, 0, DgEpilogue{}, w.scr);
-    dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.MV, ld), op(Vl, n), w.M, n, w.D, n, l, st, 0, minus_from(w.M, n));
-    return true;
+    return dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)w.M, n), op(Vl, n), w.MV, ld, w.D, l, n, st, 0, DgEpilogue{}, w.scr) &&
+           dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.MV, ld), op(Vl, n), w.M, n, w.D, n, l, st, 0, minus_from(w.M, n));
 }
 
 // Vr [r][n] = the r leading eigenvectors of G = M^T M as rows, largest eigenvalue first; lam [r] (host).  M is destroyed.
@@ -127,12 +128,13 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
     };
     if (hipMemsetAsync(w.fail, 0, 4, st) != hipSuccess) return hip_failed();
     std::vector<double> h(2 * (size_t)k + 2);
+    bool ok = true;                                         // every product so far was enqueued
     double *X = w.X, *tmp = w.Xa;
     hipLaunchKernelGGL(k_random_rows, grid1((size_t)k * n), dim3(256), 0, st, X, 0, k, n);
     for (int p = 0; p < 3; ++p) {
-        times_g(G, X, tmp, k, n, st, w.scr);
+        ok &= times_g(G, X, tmp, k, n, st, w.scr);
         std::swap(X, tmp);
-        orthonormalize(X, tmp, k, n, p < 2 ? 1 : 3, w, st);
+        ok &= orthonormalize(X, tmp, k, n, p < 2 ? 1 : 3, w, st);
     }
     const double *Gc = G;
     double largest = 0.0, last_err = 1e300, jacobi_tol = EIG_TOL_JACOBI;
@@ -143,9 +145,9 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
         double *Y = nullptr, *Xr = nullptr, *Yr = nullptr;
         for (double *p : {w.X, w.Xa, w.Xb, w.Y})
             if (p != X) (Y == nullptr ? Y : Xr == nullptr ? Xr : Yr) = p;
-        times_g(Gc, X, Y, ka, n, st, w.scr);
+        ok &= times_g(Gc, X, Y, ka, n, st, w.scr);
         spent += ka;
-        dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)X, n), op((const double *)Y, n), w.H, ka, ka, ka, n, st,
+        ok &= dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)X, n), op((const double *)Y, n), w.H, ka, ka, ka, n, st,
                                     DG_LOWER | DG_MIRROR, DgEpilogue{}, w.scr);
         double *A = w.H, *Aa = w.Ha, *V = w.V, *Va = w.Va;
         int sw = 0;
@@ -155,9 +157,10 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
         *sweeps = std::max(1, sw);
         hipLaunchKernelGGL(k_rank_descending, grid1(ka), dim3(256), 0, st, w.lam, ka, w.sel, w.theta);
         hipLaunchKernelGGL(k_gather_rows, grid1((size_t)ka * ka), dim3(256), 0, st, V, w.sel, ka, ka, w.Vs);
-        dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.Vs, ka), op((const double *)X, n), Xr, n, ka, n, ka, st);
-        dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.Vs, ka), op((const double *)Y, n), Yr, n, ka, n, ka, st);
+        ok &= dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.Vs, ka), op((const double *)X, n), Xr, n, ka, n, ka, st);
+        ok &= dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.Vs, ka), op((const double *)Y, n), Yr, n, ka, n, ka, st);
         hipLaunchKernelGGL(k_ritz_residual, dim3(ka), dim3(256), 0, st, Xr, Yr, w.theta, n, w.res);
+        if (!ok) return SVDP_ERR_UNSUPPORTED;
         double *theta = h.data(), *res = theta + k;
         int32_t failed = 0;
         if (hipMemcpyAsync(theta, w.theta, (size_t)ka * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -197,9 +200,9 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             for (int i = 0; i < out; ++i) lam[l + i] = theta[i];
             l += out;
             // the second time all of them: the first leaves 2^-53 of what was taken out, which may be more than the rest
-            take_out_of_factor(Vl, out, n, w, st);
-            take_out_of_factor(Vr, l, n, w, st);
-            dgemm<DG_K_ROWS, DG_K_ROWS>(op((const double *)w.M, n), op((const double *)w.M, n), w.Gd, n, n, n, w.D, st,
+            ok &= take_out_of_factor(Vl, out, n, w, st);
+            ok &= take_out_of_factor(Vr, l, n, w, st);
+            ok &= dgemm<DG_K_ROWS, DG_K_ROWS>(op((const double *)w.M, n), op((const double *)w.M, n), w.Gd, n, n, n, w.D, st,
                                         DG_LOWER | DG_MIRROR, DgEpilogue{}, w.scr);
             Gc = w.Gd;
             spent += 0.5 * w.D;
@@ -215,8 +218,8 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             tmp = Xr;
             for (int p = 0; p < 2; ++p) {
                 hipLaunchKernelGGL(k_normalize_rows, dim3(ka), dim3(256), 0, st, X, n);
-                if (!project_out(X, ka, n, Vr, l, w, st)) return SVDP_OK;
-                orthonormalize(X, tmp, ka, n, p + 1, w, st);
+                ok &= project_out(X, ka, n, Vr, l, w, st);
+                ok &= orthonormalize(X, tmp, ka, n, p + 1, w, st);
             }
             last_err = 1e300;
             margin = 100.0;                      // the residuals were those of the old G; another projection costs more
@@ -233,7 +236,8 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
         for (bool first = true, last = false; !last; first = false) {
             double *prev = X, *cur = X == w.X ? w.Xa : w.X;
             if (!first) {
-                times_g(Gc, X, cur, ka, n, st, w.scr);
+                ok &= times_g(Gc, X, cur, ka, n, st, w.scr);
+                if (!ok) return SVDP_ERR_UNSUPPORTED;
                 hipLaunchKernelGGL(k_rayleigh, dim3(ka), dim3(256), 0, st, X, cur, n, w.res);
                 if (hipMemcpyAsync(res, w.res, (size_t)ka * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
                     hipStreamSynchronize(st) != hipSuccess)
@@ -260,7 +264,7 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             ep.c1 = prev;
             ep.ld1 = n;
             ep.beta = -s1;
-            if (first) times_g(Gc, prev, cur, ka, n, st, w.scr, ep);
+            if (first) ok &= times_g(Gc, prev, cur, ka, n, st, w.scr, ep);
             else hipLaunchKernelGGL(k_combine, grid1((size_t)ka * n), dim3(256), 0, st, cur, prev, ep.alpha, ep.beta, (size_t)ka * n);
             for (int i = 2; i <= piece; ++i) {
                 const double s2 = 1.0 / (2.0 / s0 - s1);
@@ -272,14 +276,14 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
                 e2.c2 = prev;
                 e2.ld2 = n;
                 e2.gamma = -s1 * s2;
-                times_g(Gc, cur, prev, ka, n, st, w.scr, e2);      // the new term takes the place of the one before last
+                ok &= times_g(Gc, cur, prev, ka, n, st, w.scr, e2);      // the new term takes the place of the one before last
                 std::swap(prev, cur);
                 s1 = s2;
             }
             X = cur;
             tmp = prev;
-            if (!project_out(X, ka, n, Vr, l, w, st)) return SVDP_OK;
-            orthonormalize(X, tmp, ka, n, last ? 2 : 1, w, st);
+            ok &= project_out(X, ka, n, Vr, l, w, st);
+            ok &= orthonormalize(X, tmp, ka, n, last ? 2 : 1, w, st);
         }
     }
     return SVDP_OK;

@@ -129,7 +129,7 @@ svdp_status whiten_impl(const void *W_gate, const void *X, int d, int D, int T, 
         (void)hipGetLastError();
         return SVDP_ERR_HIP;
     }
-    cholesky_blocked(w.S, d, w.invL, w.sums, w.fail, st);
+    if (!cholesky_blocked(w.S, d, w.invL, w.sums, w.fail, st)) return SVDP_ERR_UNSUPPORTED;
     int32_t failed = 0;
     if (hipMemcpyAsync(&failed, w.fail, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess) {
@@ -164,14 +164,18 @@ svdp_status whiten_impl(const void *W_gate, const void *X, int d, int D, int T, 
             return SVDP_ERR_HIP;
         }
     }
+    auto refused = [&] {                                          // the copies into lam must be done
+        (void)hipStreamSynchronize(st);
+        return SVDP_ERR_UNSUPPORTED;
+    };
     // Q = A = W (S V_r)
     ok = dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)w.Vr, d), op((const double *)w.S, d), w.Zr, d, r, d, d, st, DG_K_UPTO_N,
                                      DgEpilogue{}, scr) &&
          dgemm<DG_ROWS_K, DG_ROWS_K>(op(Wg, d), op((const double *)w.Zr, d), w.out64, r, D, r, d, st, 0, DgEpilogue{}, scr);
-    if (!ok) return SVDP_ERR_UNSUPPORTED;
+    if (!ok) return refused();
     hipLaunchKernelGGL(k_f64_to_f32, grid1((size_t)D * r), dim3(256), 0, st, w.out64, (size_t)D * r, Q);
     // B = V_r^T S^-1 (block back-substitution; V_r^T is w.Vr, rows = the chosen eigenvectors), P = B^T
-    solve_right_lower(w.Vr, w.out64, r, d, w.S, w.invL, st);
+    if (!solve_right_lower(w.Vr, w.out64, r, d, w.S, w.invL, st)) return refused();
     hipLaunchKernelGGL((k_transpose_to_f64<double>), dim3((d + 31) / 32, (r + 31) / 32), dim3(256), 0, st, w.out64, r, d, w.Vr);
     hipLaunchKernelGGL(k_f64_to_f32, grid1((size_t)d * r), dim3(256), 0, st, w.Vr, (size_t)d * r, P);
     if (hipStreamSynchronize(st) != hipSuccess) {                 // the copies into lam must be done

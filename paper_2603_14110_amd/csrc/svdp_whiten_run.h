@@ -19,7 +19,7 @@ struct DgScratch {          // where parts of a split K range meet
 };
 
 template <typename TA, DgLayout LA, typename TB, DgLayout LB, int WM, int WN, int TM, int TN, int BK>
-bool dgemm_tile(DgOperand<TA> A, DgOperand<TB> B, double *C, int ldc, int M, int N, int K, int flags, const DgEpilogue &ep,
+[[nodiscard]] bool dgemm_tile(DgOperand<TA> A, DgOperand<TB> B, double *C, int ldc, int M, int N, int K, int flags, const DgEpilogue &ep,
                 int nz, const DgScratch &scr, hipStream_t st)
 {
     constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
@@ -44,7 +44,8 @@ bool dgemm_tile(DgOperand<TA> A, DgOperand<TB> B, double *C, int ldc, int M, int
     return true;
 }
 
-// Tile and split of a product.  DG_LOWER needs M == N.  `one_tile_wide` (N <= 64): every block covers all columns of
+// Tile and split of a product.  false: the device does not grant the LDS a tile needs, nothing was enqueued (every function
+// that forms products hands this on, and the call answers SVDP_ERR_UNSUPPORTED).  DG_LOWER needs M == N.  `one_tile_wide` (N <= 64): every block covers all columns of
 // its rows, so that C may be A itself.
 //  - large products: 128 x 128, 96 x 96 or 64 x 64 tiles, whichever leaves the least idle in the last round (the lower
 //    half of a 4096 x 4096 product is 528 tiles of 128 x 128, i.e. 2.06 rounds of the 256 compute units that take the
@@ -53,7 +54,7 @@ bool dgemm_tile(DgOperand<TA> A, DgOperand<TB> B, double *C, int ldc, int M, int
 //  - 80 x 64 tiles (four waves side by side) likewise: 320 rows by 4096 columns are exactly 256 of them;
 //  - small products: 32 x 32 tiles and parts of K (k_dgemm_sum adds them in order).
 template <DgLayout LA, DgLayout LB, typename TA, typename TB>
-bool dgemm(DgOperand<TA> A, DgOperand<TB> B, double *C, int ldc, int M, int N, int K, hipStream_t st, int flags = 0,
+[[nodiscard]] bool dgemm(DgOperand<TA> A, DgOperand<TB> B, double *C, int ldc, int M, int N, int K, hipStream_t st, int flags = 0,
            const DgEpilogue &ep = DgEpilogue{}, const DgScratch &scr = DgScratch{nullptr, 0}, bool one_tile_wide = false)
 {
     if (M <= 0 || N <= 0) return true;
@@ -102,8 +103,9 @@ inline DgEpilogue minus_from(const double *Cin, int ld)
 // The lower triangle of A [n][n] (n a multiple of 64) becomes L with L L^T = A, zero above the diagonal; invL:
 // [n/64][64][64], the inverses of L's diagonal blocks; scale: device double; fail: device int, set to 1 if A is not
 // positive definite to working precision (then L is not to be used).
-void cholesky_blocked(double *A, int n, double *invL, double *scale, int *fail, hipStream_t st)
+[[nodiscard]] bool cholesky_blocked(double *A, int n, double *invL, double *scale, int *fail, hipStream_t st)
 {
+    bool ok = true;
     hipLaunchKernelGGL(k_max_diag, dim3(1), dim3(256), 0, st, A, n, scale);
     for (int k = 0; k < n; k += CH_B) {
         const int p1 = std::min(n, k / CH_PANEL * CH_PANEL + CH_PANEL);       // end of the panel
@@ -112,29 +114,33 @@ void cholesky_blocked(double *A, int n, double *invL, double *scale, int *fail, 
         hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, A, n, (size_t)k * n + k, scale, 1e-13, inv, fail);
         const double *below = A + (size_t)k1 * n + k;
         // in place: a block of the product covers all 64 columns of its rows
-        dgemm<DG_ROWS_K, DG_ROWS_K>(op(below, n), op((const double *)inv, CH_B), A + (size_t)k1 * n + k, n, rest, CH_B, CH_B, st,
-                                    0, DgEpilogue{}, DgScratch{nullptr, 0}, true);
+        ok &= dgemm<DG_ROWS_K, DG_ROWS_K>(op(below, n), op((const double *)inv, CH_B), A + (size_t)k1 * n + k, n, rest, CH_B,
+                                          CH_B, st, 0, DgEpilogue{}, DgScratch{nullptr, 0}, true);
         double *upd = A + (size_t)k1 * n + k1;
-        dgemm<DG_ROWS_K, DG_ROWS_K>(op(below, n), op(below, n), upd, n, rest, p1 - k1, CH_B, st, 0, minus_from(upd, n));
+        ok &= dgemm<DG_ROWS_K, DG_ROWS_K>(op(below, n), op(below, n), upd, n, rest, p1 - k1, CH_B, st, 0, minus_from(upd, n));
         if (k1 == p1 && rest > 0) {
             const double *pan = A + (size_t)k1 * n + (k1 / CH_PANEL - 1) * CH_PANEL;
-            dgemm<DG_ROWS_K, DG_ROWS_K>(op(pan, n), op(pan, n), upd, n, rest, rest, CH_PANEL, st, DG_LOWER, minus_from(upd, n));
+            ok &= dgemm<DG_ROWS_K, DG_ROWS_K>(op(pan, n), op(pan, n), upd, n, rest, rest, CH_PANEL, st, DG_LOWER,
+                                              minus_from(upd, n));
         }
     }
     hipLaunchKernelGGL(k_zero_upper_blocks, grid1((size_t)n * n), dim3(256), 0, st, A, n);
+    return ok;
 }
 
 // Bout [r][n] = Bin [r][n] L^-1 for the lower-triangular L [n][n] and the inverses of its diagonal blocks: block
 // back-substitution from the last block column to the first.  A finished block column is taken out of all columns to
 // its left at once (a wide product with K = 64).  Bin is destroyed.
-void solve_right_lower(double *Bin, double *Bout, int r, int n, const double *L, const double *invL, hipStream_t st)
+[[nodiscard]] bool solve_right_lower(double *Bin, double *Bout, int r, int n, const double *L, const double *invL, hipStream_t st)
 {
+    bool ok = true;
     for (int c0 = n - CH_B; c0 >= 0; c0 -= CH_B) {
-        dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)Bin + c0, n), op(invL + (size_t)c0 * CH_B, CH_B), Bout + c0, n, r, CH_B,
-                                    CH_B, st);
-        dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)Bout + c0, n), op(L + (size_t)c0 * n, n), Bin, n, r, c0, CH_B, st, 0,
-                                    minus_from(Bin, n));
+        ok &= dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)Bin + c0, n), op(invL + (size_t)c0 * CH_B, CH_B), Bout + c0, n, r,
+                                          CH_B, CH_B, st);
+        ok &= dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)Bout + c0, n), op(L + (size_t)c0 * n, n), Bin, n, r, c0, CH_B, st, 0,
+                                          minus_from(Bin, n));
     }
+    return ok;
 }
 
 // Eigen-decomposition of the symmetric matrix in *A (n x n, n % 64 == 0) by block Jacobi sweeps.  On return

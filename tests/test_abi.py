@@ -4,6 +4,7 @@ status strings) behaves.  No kernel is launched here."""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -272,3 +273,26 @@ def test_bench_refuses_more_than_one_gpu():
     p = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True,
                        timeout=120)
     assert p.returncode != 0 and "ONE GPU" in p.stderr and p.stdout.strip() == ""
+
+
+@pytest.mark.parametrize("call", [
+    "cholesky_blocked(a, 64, a, a, f, st);",
+    "solve_right_lower(a, a, 8, 64, a, a, st);",
+    "dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)a, 64), op((const double *)a, 64), a, 64, 64, 64, 64, st);",
+    "EigTopWs w; double *x = a, *y = a; orthonormalize(x, y, 64, 64, 1, w, st);",
+    "EigTopWs w; project_out(a, 64, 64, a, 1, w, st);",
+    "EigTopWs w; take_out_of_factor(a, 1, 64, w, st);",
+    "times_g(a, a, a, 64, 64, st, DgScratch{nullptr, 0});",
+])
+def test_a_refused_matrix_product_cannot_go_unnoticed(tmp_path, call):
+    """A product whose LDS the device does not grant is not launched and answers false.  Every function of the offline build
+    that forms products is declared so that the build fails where its answer is not looked at."""
+    from paper_2603_14110_amd import build
+
+    flags = [build.hipcc_path(), "--offload-arch=gfx950", "--cuda-host-only", "-fsyntax-only", "-std=c++17", *build.WARNINGS]
+    for body, accepted in (("", True), (call, False)):
+        src = tmp_path / "probe.hip"
+        src.write_text(f'#include "{build.SRC}"\nvoid probe(double *a, int *f, hipStream_t st) {{ {body} }}\n')
+        r = subprocess.run(flags + [str(src)], capture_output=True, text=True)
+        assert (r.returncode == 0) == accepted, r.stderr
+        assert accepted or "unused-result" in r.stderr, r.stderr
