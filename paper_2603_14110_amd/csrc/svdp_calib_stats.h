@@ -146,11 +146,15 @@ constexpr int GW_LDS = GW_STAGES * GW_STAGE_BYTES;
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 // 64 lanes x 16 bytes from `src` (per lane) to LDS bytes [at, at + 1024); `at` uniform.  Not counted by the compiler:
-// the caller waits on vmcnt before a barrier.  (m0 is not used for anything else in a kernel without indirect registers.)
+// the caller waits on vmcnt before a barrier.  m0 is named as written: the compiler does not allocate it, but sets it itself in
+// front of the few instructions that read it, and may only do without where it knows who else writes it.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"        // "reserved register"
 __device__ __forceinline__ void load_to_lds(const void *src, uint32_t at)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 
 // Every wave's LDS reads and all but the newest N of its loads to LDS are done, in all waves of the block.
 template <int N>

@@ -296,3 +296,16 @@ def test_a_refused_matrix_product_cannot_go_unnoticed(tmp_path, call):
         r = subprocess.run(flags + [str(src)], capture_output=True, text=True)
         assert (r.returncode == 0) == accepted, r.stderr
         assert accepted or "unused-result" in r.stderr, r.stderr
+
+
+def test_inline_assembly_names_the_registers_it_writes():
+    """An instruction written by hand that sets m0 says so, or the compiler may keep a value of its own there."""
+    import glob
+
+    found = 0
+    for path in glob.glob(os.path.join(ROOT, "paper_2603_14110_amd", "csrc", "*.h*")):
+        for stmt in re.findall(r"\basm\s+volatile\s*\(.*?\);", open(path).read(), flags=re.S):
+            if re.search(r"s_mov_b32\s+m0\b", stmt):
+                found += 1
+                assert '"m0"' in stmt.rsplit(":", 1)[1], (path, stmt)
+    assert found == 1
