@@ -39,14 +39,29 @@ constexpr double EIG_PIECE = 8.0;           // largest degree of a piece of the 
 constexpr double EIG_SHIFT = 4e-13;         // of the first Cholesky QR pass (above k_chol_diag's bound of 1e-13)
 
 // Rows of the block for r wanted vectors: a quarter more (at least 32), so that the filter has a gap to work with, in
-// whole Jacobi strips; 0 where the Jacobi decomposition of all of G is the better way: from n = 256 on the block wins on
-// every spectrum tried (whole call 3.9 to 4.4 against 5.0 to 8.1 ms at r = 64), at n = 128 it loses on decaying ones (2.2
-// against 1.6 ms).
+// whole Jacobi strips; 0 where the Jacobi decomposition of all of G is the better way.  Whole call in ms, this / full, for a
+// mean of 0, 10, 1e4 times the spread, eigenvalues 10^(-6 i / r), exp(-i / d), all equal (handed over after one projection):
+//   d = 256, r = 64    4.2 / 4.6    7.4 / 4.6    4.4 / 4.6    3.7 / 12    4.7 / 4.7    6.3 / 4.1
+//   d = 512, r = 64    4.9 / 12     7.1 / 12     5.0 / 11     4.3 / 27    5.6 / 11      12 / 9.5
+//   d = 512, r = 200   9.6 / 12      15 / 12      10 / 12     8.4 / 27     11 / 12      14 / 9.6
+//   d = 1024, r = 400   21 / 29      33 / 29      22 / 28      15 / 59     25 / 27      34 / 23
+// so the largest block is the one that no longer wins on most of them, and at n = 128 it loses on decaying ones (2.2 / 1.6).
 inline int eigtop_block(int n, int r)
 {
     const int k = round_up(r + std::max(32, r / 4), BJ_S);
     return n >= 256 && 2 * k <= n ? k : 0;
 }
+
+// Rough times (us) of what the iteration and the full decomposition consist of, fitted to n = 256 .. 4096: a product of k
+// rows with G, one orthonormalisation, `sweeps` Jacobi sweeps over an m x m matrix.  The iteration goes on while what it
+// still needs is below the full decomposition's nine sweeps (it takes 8 to 13), and while it has not spent one and a half
+// times as much.  A limit on products alone (16 n rows) left out that at k = n / 2 the projections and orthonormalisations are
+// most of the time, and gave up blocks that were three products short:
+// whole call at d = 1024, r = 400, tokens with a mean of 10, 100, 1e4 times their spread 52, 46, 44 -> 33, 23, 22 ms (full
+// decomposition 29; eigenvalues exp(-i / d) 40 -> 25).
+inline double eig_product_us(int k, int n) { return 6.0 + 5e-8 * k * (double)n * n; }
+inline double eig_orthonormalize_us(int k) { return 40.0 + 0.8 * k; }
+inline double eig_jacobi_us(int m, int sweeps) { return sweeps * (m / BJ_B - 1) * (64.0 + 9e-6 * m * (double)m); }
 
 struct EigTopWs {
     int k;                              // eigtop_block(n, r)
@@ -138,7 +153,8 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
     }
     const double *Gc = G;
     double largest = 0.0, last_err = 1e300, jacobi_tol = EIG_TOL_JACOBI;
-    double spent = 3.0 * k;                                 // n x n products of one row each; the limit is 16 n of them
+    const double full = eig_jacobi_us(n, 9);
+    double spent = 3.0 * eig_product_us(k, n) + 5.0 * eig_orthonormalize_us(k);        // us so far, roughly
     int l = 0, ka = k, piece = 0;                           // vectors that left the block; rows of the block
     for (int cycle = 0; cycle < 24; ++cycle) {
         // Rayleigh-Ritz
@@ -146,7 +162,6 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
         for (double *p : {w.X, w.Xa, w.Xb, w.Y})
             if (p != X) (Y == nullptr ? Y : Xr == nullptr ? Xr : Yr) = p;
         ok &= times_g(Gc, X, Y, ka, n, st, w.scr);
-        spent += ka;
         ok &= dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)X, n), op((const double *)Y, n), w.H, ka, ka, ka, n, st,
                                     DG_LOWER | DG_MIRROR, DgEpilogue{}, w.scr);
         double *A = w.H, *Aa = w.Ha, *V = w.V, *Va = w.Va;
@@ -155,6 +170,7 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             jacobi_eigh(&A, &Aa, &V, &Va, ka, w.Uall, w.rowsums, w.sums, w.lam, jacobi_tol, 24, &sw, st);
         if (e != SVDP_OK) return e;
         *sweeps = std::max(1, sw);
+        spent += 3.0 * eig_product_us(ka, n) + eig_jacobi_us(ka, sw);
         hipLaunchKernelGGL(k_rank_descending, grid1(ka), dim3(256), 0, st, w.lam, ka, w.sel, w.theta);
         hipLaunchKernelGGL(k_gather_rows, grid1((size_t)ka * ka), dim3(256), 0, st, V, w.sel, ka, ka, w.Vs);
         ok &= dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.Vs, ka), op((const double *)X, n), Xr, n, ka, n, ka, st);
@@ -205,7 +221,7 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             ok &= dgemm<DG_K_ROWS, DG_K_ROWS>(op((const double *)w.M, n), op((const double *)w.M, n), w.Gd, n, n, n, w.D, st,
                                         DG_LOWER | DG_MIRROR, DgEpilogue{}, w.scr);
             Gc = w.Gd;
-            spent += 0.5 * w.D;
+            spent += eig_product_us(w.D / 2, n) + 3.0 * eig_orthonormalize_us(ka);
             const int left = ka - out, want = std::min(k, round_up(r - l + std::max(32, r / 4), BJ_S));
             X += (size_t)out * n;                // moved to the front of a buffer by the orthonormalisation below
             double *front = Y;
@@ -252,11 +268,13 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             }
             const double rate = growth(wanted, bound), left = std::ceil(todo / rate);
             // no gap in reach: the full decomposition would be done sooner
-            if (!(left * ka < 16.0 * n - spent)) return SVDP_OK;
+            const double pass = eig_orthonormalize_us(ka),
+                         missing = left * (eig_product_us(ka, n) + pass / EIG_PIECE) + pass + eig_jacobi_us(ka, 4);
+            if (!(missing < full && spent < 1.5 * full)) return SVDP_OK;
             piece = (int)std::max(1.0, std::min({EIG_PIECE, std::floor(std::acosh(EIG_AMPLIFY) / std::max(growth(top, bound), 1e-3)), left}));
             last = piece >= left || (piece == 1 && ++single == 3);  // a dominant direction keeps the pieces short: project, it may have settled
             todo -= piece * rate;
-            spent += (double)piece * ka;
+            spent += piece * eig_product_us(ka, n) + pass;
             const double half = 0.5 * bound, s0 = half / (top - half);
             double s1 = s0;
             DgEpilogue ep;
