@@ -176,8 +176,9 @@ def test_leading_eigenvectors_over_spectra(env, kind, d, r):
     scale = np.linalg.norm(W @ X.T)
     assert abs(np.linalg.norm((W - QP) @ X.T) - np.linalg.norm((W - A @ B) @ X.T)) <= 2e-6 * scale
     sv = np.linalg.norm(A, axis=0)
-    # fp32, and eigenvalues of a Gram matrix: an error of 1e-13 of the largest is 3e-7 of its root where sigma is zero
-    assert np.all(np.abs(sigma - sv) <= 1e-6 * sv[0])
+    # fp32, each relative to itself; where a singular value is zero, an eigenvalue off by 1e-13 of the largest is 3e-7 of
+    # the root of that
+    assert np.all(np.abs(sigma - sv) <= (1e-6 * sv[0] if kind in ("rank", "zero") else 1e-6 * sv))
     assert np.all(np.diff(sigma) <= 0) and 0 <= sweeps[1] <= 24
 
 
