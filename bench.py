@@ -644,7 +644,9 @@ def whiten(a):
     X64 = Xd.double()
     err = torch.linalg.norm((W64 - Q.double() @ P.double().T) @ X64.T).item()
     ref = torch.linalg.norm(W64 @ X64.T).item()
-    flops = 2.0 * (sp.d * sp.d * T + 2.0 * sp.D * sp.d * sp.d + sp.D * sp.d * r + sp.d * sp.d * r)
+    # contractions: the two symmetric products by half, the one with the triangular factor likewise, the two factor products
+    # and the substitution
+    flops = 1.0 * sp.d * sp.d * T + 2.0 * sp.D * sp.d * sp.d + 2.0 * sp.D * sp.d * r + 2.0 * sp.d * sp.d * r
     # what the eigenpairs cannot do without (reduction of a symmetric d x d matrix 4/3 d^3, r of its eigenvectors) and
     # the Cholesky factor; not what the iteration happens to take
     all_flops = flops + 4.0 / 3.0 * sp.d ** 3 + 2.0 * sp.d * sp.d * r + sp.d ** 3 / 3.0

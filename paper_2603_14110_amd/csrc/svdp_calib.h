@@ -59,6 +59,8 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t u)
 // to three samples on the scores of a layer) a sample's rank is the number of smaller keys: the number of barriers does not
 // depend on the length.  A bucket of more than CAL_BUCKET_MAX samples (many equal scores, an outlier that leaves everybody
 // else in one bucket, an infinite score) sends the neuron to the network.
+// Every neuron through it, whole call at D = 11008, T = 2048, eta = 16: one outlier per neuron 393 us (network alone, 512
+// threads: 535), scores on a grid of quarters 376 (521), one score value 752 (732).
 // Measured at D = 11008, T = 2048, eta = 16: network 450 us, buckets 131 us (512 threads, 64-bit reductions), 117 us with
 // the sorted tail in the keys' place (four blocks a compute unit instead of three), 91 us with 256 threads, reductions on
 // the scores alone and the ranks taken by tail position (660 -> 370 vector instructions a wave, half the waves).

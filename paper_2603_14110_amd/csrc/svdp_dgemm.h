@@ -8,9 +8,8 @@
 // memory: either [rows][K] or [K][rows], and in the storage type (bf16 and fp32 are widened on the way into LDS),
 // so that neither X^T X nor (W S)^T (W S) needs a transposed or a widened copy.
 // Measured at d = 4096, D = 11008, T = 8192 (bf16 inputs), before = 64 x 64 tiles, two barriers per step, 8-byte
-// loads, fp64 copies of the inputs:  X^T X 7.6 -> 2.8 ms and W^T W 4.0 ms (lower halves: 50 and 48 TFLOP/s of 78.6),
-// product with a triangular 4096 x 4096 factor 1.35 ms (53 TFLOP/s); second moments and Gram matrix of the call
-// together 20 -> 8.7 ms.
+// loads, fp64 copies of the inputs:  X^T X 7.6 -> 2.8 ms and M^T M, M [D][d] in fp64, 3.5 to 3.7 ms (lower halves: 49 and 50 to
+// 53 TFLOP/s of 78.6), M = W S with the triangular 4096 x 4096 factor 3.2 ms (58 TFLOP/s); the three together 20 -> 9.6 ms.
 #pragma once
 
 #include "svdp_device.h"

@@ -4,8 +4,9 @@
 // PS_TILES tiles of P (16 or 32 KB each, from L2 after the first block) while its rows of Q are on their way.  All sums are
 // formed in the order of k_xP and k_scores, so that the scores have the same bits (svdp_ffn_step_glued keeps those two).
 // Measured, one step, two launches -> one (us, issued one by one / in a graph with 24 layers in turn): d = 256, r = 32, fp32
-// (one tile) 18.5 -> 14.4 / 12.3 -> 9.2; d = 1024, r = 32, bf16 (four tiles) 19.3 -> 14.8 / 14.3 -> 13.3; with eight tiles
-// (d = 2048, r = 32) a graph is slower, 15.6 -> 18.2, hence the limit.
+// (one tile) 18.2 -> 15.1 / 13.6 -> 10.5 (484 of 1024 rows listed; about 100 listed: 19.1 -> 15.5 one by one); d = 1024, r = 32,
+// bf16 (four tiles) 17.6 -> 14.7 / 15.3 -> 14.2; with eight tiles (d = 2048, r = 32) a graph is slower, 15.6 -> 18.2, hence
+// the limit.  A wide layer does not change that: d = 1024, D = 18944, r = 32, predictor alone 12.9 -> 9.9 / 6.6 -> 4.7.
 #pragma once
 
 #include "svdp_kernels.h"

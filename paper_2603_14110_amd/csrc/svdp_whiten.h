@@ -247,7 +247,8 @@ __device__ __forceinline__ double bj_neighbour(double v)
 }
 
 // U[k] (64 x 64, row-major), the product of the rotations of BJ_INNER_SWEEPS cyclic sweeps over the k-th diagonal
-// tile S of A (the identity if S is already diagonal to rounding).  One block of 1024 threads per strip; S and U live in LDS (dynamic: 2 * 64 * 65 doubles).  A step applies its 32
+// tile S of A (the identity if S is already diagonal to rounding).  BJ_U_PARTS blocks of 1024 threads per strip; all of S and
+// the block's rows of U live in LDS (dynamic: BJ_SOLVE_LDS).  A step applies its 32
 // disjoint rotations J to the whole tile in ONE pass, S <- J^T S J: a lane owns one column (of the pair lane / 2,
 // the first or second index by lane % 2), a wave takes two row pairs, rotates the two rows at its column and
 // gets the neighbour column's values from the neighbouring lane for the column rotation.  Every element is read
@@ -255,7 +256,7 @@ __device__ __forceinline__ double bj_neighbour(double v)
 // accesses spread over all LDS banks.  U <- U J is the same column rotation; the angles of the next step are
 // computed (32 lanes) while the other waves are in it.
 // The rows of U are independent of each other and of S, so BJ_U_PARTS blocks per strip sweep the same S and take a part of
-// the rows each: a round has far fewer strips than the chip has compute units (64 -> 50 us a launch; bound by the LDS traffic
+// the rows each: a round has far fewer strips than the chip has compute units (64 -> 52 us a launch; bound by the LDS traffic
 // and the two barriers of the 63 dependent steps; with eight waves instead of sixteen the call is 2 % slower).
 constexpr int BJ_SOLVE_THREADS = 1024;
 constexpr int BJ_U_PARTS = 4;
