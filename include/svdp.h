@@ -78,16 +78,17 @@ enum {
      * row-at-a-time kernel (Alg. 3) and a gather-then-dense-contraction form (Alg. 4); its
      * Sec. 6 notes that batching lowers the sparsity the first can exploit.
      *  neither flag (default): per kernel and batch capacity, whichever was measured faster on
-     *      MI355X: matrix cores for the scores from 3 tokens and for the rows from 5 tokens,
-     *      vector units below.
+     *      MI355X: matrix cores for the scores from 3 tokens and for the rows from 5 tokens
+     *      (bf16 layers of at least 2 M elements a matrix), vector units below.
      *  SVDP_FLAG_ENGINE_VECTOR: fp32 vector arithmetic everywhere (any dtype, batch, flags).
      *  SVDP_FLAG_ENGINE_MATRIX: matrix cores wherever a kernel for them exists:
      *      - rows (gate, up, down over the list): taken 16 at a time as MFMA tiles straight
      *        from their place in the weight matrices (no gathered copy), bf16 x bf16 -> fp32
      *        for gate and up, fp32 outer products for the down projection; needs bf16 storage,
-     *        d a multiple of 512 and no SVDP_FLAG_REVALIDATE;
-     *      - scores (t Q^T + b): bf16 MFMAs with t split into three bf16 terms (exact to fp32);
-     *        needs bf16 storage, r a multiple of 32, r <= 512.
+     *        d a multiple of 64 and no SVDP_FLAG_REVALIDATE;
+     *      - scores (t Q^T + b): bf16 MFMAs with t split into three bf16 terms (exact to fp32), or
+     *        fp32 MFMAs for fp32 storage; below three tokens bf16 storage with r a multiple of 32,
+     *        r <= 512.
      *      Layers that do not qualify use the vector kernels.
      * Both engines give the same mask and list (up to scores within rounding of zero) and a y
      * that agrees to fp32 rounding (sums are cut differently).  Setting both is an error.     */

@@ -150,21 +150,21 @@ size_t xp_lds(const svdp_layer *)
     return ((size_t)NB * XP_ROWS + nsub * (outs + 1) + parts * outs) * 4;
 }
 
-// Whether the score kernel on the matrix cores takes this layer and batch capacity.
+// Whether the scores run on the matrix cores: from three tokens on unless the caller wants the vector units; for fewer where
+// the caller wants it and the layer is a plain one (bf16, whole column blocks held in registers).
 template <typename W, int NB>
 bool scores_on_matrix(const svdp_layer *L)
 {
-    if (!std::is_same<W, bf16>::value) return false;
     const Engine engine = engine_of(L);
-    const bool want = engine == ENGINE_MATRIX || (engine == ENGINE_AUTO && NB >= 4);
-    return want && L->r % 32 == 0 && L->r <= 32 * SCM_KB;
+    if (NB >= 4) return engine != ENGINE_VECTOR;
+    return engine == ENGINE_MATRIX && std::is_same<W, bf16>::value && L->r % 32 == 0 && L->r <= 512;
 }
 template <int NB>
 constexpr int scores_threads() { return NB <= 2 ? 512 : 256; }
 template <typename W, int NB>
 size_t scores_lds(const svdp_layer *L)
 {
-    if (scores_on_matrix<W, NB>(L)) return (size_t)3 * NB * L->r * 2;
+    if (scores_on_matrix<W, NB>(L)) return scm_lds<W>(NB, L->r);
     const size_t thr = scores_threads<NB>();
     const size_t tsp = (size_t)NB * L->r > thr * 4 ? (size_t)NB * L->r : thr * 4;
     return ((size_t)NB * L->r + (size_t)NB * SC_SLAB + tsp) * 4;
@@ -191,6 +191,7 @@ inline bool split_fits(int d, int D, int NB)
            split_list_offset(d, D, NB) + (size_t)D * 4 <= (size_t)ROWS_BLOCKS * NB * d * 4;
 }
 
+constexpr size_t ROWS_MATRIX_MIN = 2 << 20;          // d * D from which the matrix engine's two row kernels are chosen
 template <typename W, int NB>
 RowsPlan plan_rows(const svdp_layer *L)
 {
@@ -207,9 +208,12 @@ RowsPlan plan_rows(const svdp_layer *L)
     }
     if (std::is_same<W, bf16>::value) {
         const Engine engine = engine_of(L);
-        // measured on the Mistral shape: ahead of the vector kernel only at the largest batch capacity
-        const bool want = engine == ENGINE_MATRIX || (engine == ENGINE_AUTO && NB >= 8);
-        if (want && d % 512 == 0) {
+        // Rows alone, vector -> matrix, at 30 / 60 % of the rows, eight tokens (us): d x D = 512 x 2560 11.4 -> 12.2 / 13.2 ->
+        // 12.6, 768 x 3072 13.4 -> 12.6 / 14.3 -> 13.1, 1024 x 4672 15.8 -> 13.8 / 19.5 -> 15.5, 2432 x 12864 30.1 -> 24.3 /
+        // 43.0 -> 35.6; below 2 M elements the launch more is not earned back.  At four tokens the vector kernel is ahead or
+        // level up to 3584 x 18944 (31.0 -> 31.4).
+        const bool want = engine == ENGINE_MATRIX || (engine == ENGINE_AUTO && NB >= 8 && (size_t)d * D >= ROWS_MATRIX_MIN);
+        if (want && d % 64 == 0) {
             p.kind = ROWS_MATRIX;
             p.min_chunk = MF_ROWS;
             p.max_chunk = round_up(per > p.min_chunk ? per : p.min_chunk, MF_ROWS);
@@ -326,9 +330,7 @@ template <typename W, int NB>
 bool prepare_scores(const svdp_layer *L)
 {
     const size_t lds = scores_lds<W, NB>(L);
-    if constexpr (std::is_same<W, bf16>::value) {
-        if (scores_on_matrix<W, NB>(L)) return grant_lds<k_scores_mfma<NB>>(lds);
-    }
+    if (scores_on_matrix<W, NB>(L)) return grant_lds<k_scores_mfma<W, NB>>(lds);
     return with_scores_kernel<W, NB>(L, [&](auto k) { return grant_lds<decltype(k)::value>(lds); });
 }
 
@@ -337,12 +339,10 @@ svdp_status launch_scores(const svdp_layer *L, const float *tpart, int nt, int B
                           hipStream_t st)
 {
     const size_t lds = scores_lds<W, NB>(L);
-    if constexpr (std::is_same<W, bf16>::value) {
-        if (scores_on_matrix<W, NB>(L)) {
-            hipLaunchKernelGGL((k_scores_mfma<NB>), dim3(L->D / SC_SLAB), dim3(SCM_THREADS), lds, st,
-                               static_cast<const bf16 *>(L->Q), L->b, tpart, nt, B, L->D, L->r, s_out, mask_out);
-            return hip_status(hipSuccess);
-        }
+    if (scores_on_matrix<W, NB>(L)) {
+        hipLaunchKernelGGL((k_scores_mfma<W, NB>), dim3(L->D / SC_SLAB), dim3(SCM_THREADS), lds, st,
+                           static_cast<const W *>(L->Q), L->b, tpart, nt, B, L->D, L->r, s_out, mask_out);
+        return hip_status(hipSuccess);
     }
     // block size: 512 threads for one or two tokens (short critical path), 256 for larger batches
     // (fewer wavefronts repeating the per-wave overhead); measured on the 7B and Mistral shapes

@@ -189,8 +189,8 @@ __global__ __launch_bounds__(XP_THREADS) void k_xP(const W *__restrict__ P, cons
 }
 
 // ---------------------------------------------------------------------------
-// Sum of the nt stage-1 partials into one t (fixed order).  Used for batches of
-// four or more tokens, where re-adding the partials in every score block would
+// Sum of the nt stage-1 partials into one t (fixed order).  Used by the vector engine for batches of
+// three or more tokens, where re-adding the partials in every score block would
 // cost more than this extra launch.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_tsum(const float *__restrict__ tpart, int nt, int count,

@@ -13,7 +13,7 @@
 //   k_down_slices   y[token][col] = sum over the list of h * W_downT[row][col], by blocks that own a
 //            128-byte column slice and one of eight parts of the list (see there).
 // Products of bf16 values are exact in fp32 and every sum has a fixed order.
-// Requirements checked by the host: d % 512 == 0, NB <= 8.
+// Requirements checked by the host: d % 64 == 0 (a row is whole 128-byte lines), NB <= 8.
 // Dynamic LDS of k_gate_up_mfma: NB*d*2 bytes (x) + ROWS_WAVES*max_chunk*2*NB floats (partial tiles) +
 // max_chunk ints (list); max_chunk % 16 == 0.
 #pragma once
@@ -93,19 +93,20 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
     };
     const int ntile = (cnt + MF_ROWS - 1) / MF_ROWS;
 
-    // ---- this wave's share of d is the steps [wave*spw, (wave+1)*spw) ----
-    const int spw = nsteps / ROWS_WAVES;
+    // ---- this wave's share of d is the steps [first, last) ----
+    const int uwave = __builtin_amdgcn_readfirstlane(wave);         // the tests of the loop below stay scalar
+    const int first = uwave * nsteps / ROWS_WAVES, last = (uwave + 1) * nsteps / ROWS_WAVES;
     const int tb = lm & (NB - 1);                                   // token slot read as the x operand
     for (int t = 0; t < ntile; ++t) {
         const size_t row = row_of(t * MF_ROWS + lm);
-        const bf16 *pg = Wg + row * d + (size_t)wave * spw * 64 + lq * 8;
-        const bf16 *pu = Wu + row * d + (size_t)wave * spw * 64 + lq * 8;
+        const bf16 *pg = Wg + row * d + lq * 8;
+        const bf16 *pu = Wu + row * d + lq * 8;
         f32x4_t ag = {0.f, 0.f, 0.f, 0.f}, au = {0.f, 0.f, 0.f, 0.f};
-        for (int s0 = 0; s0 < spw; s0 += MF_UA) {
+        for (int s0 = first; s0 < last; s0 += MF_UA) {
             uint4 g0[MF_UA], g1[MF_UA], u0[MF_UA], u1[MF_UA];
 #pragma unroll
             for (int k = 0; k < MF_UA; ++k) {
-                if (s0 + k < spw) {
+                if (s0 + k < last) {
                     g0[k] = load_raw(pg + (size_t)(s0 + k) * 64);
                     g1[k] = load_raw(pg + (size_t)(s0 + k) * 64 + 32);
                     u0[k] = load_raw(pu + (size_t)(s0 + k) * 64);
@@ -114,8 +115,8 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
             }
 #pragma unroll
             for (int k = 0; k < MF_UA; ++k) {
-                if (s0 + k < spw) {
-                    const int s = wave * spw + s0 + k;
+                if (s0 + k < last) {
+                    const int s = s0 + k;
                     const uint4 xa = xs[((s * 2 + 0) * 4 + lq) * NB + tb];
                     const uint4 xb = xs[((s * 2 + 1) * 4 + lq) * NB + tb];
                     ag = mfma_bf16(g0[k], xa, ag);
@@ -284,16 +285,27 @@ __global__ __launch_bounds__(DS_THREADS) void k_down_slices(const bf16 *__restri
 // ---------------------------------------------------------------------------
 // Predictor stage 2 on the matrix cores: s_i = t . Q[i,:] + b_i for a slab of
 // 64 neurons and up to eight tokens, and the slab's mask word (eq. 2).  One
-// wave per 16 rows of Q; a lane fetches 16 bytes of one row per 32 columns
-// (all requested before t is touched).  t (fp32, the sum of the nt stage-1
-// partials) is split into three bf16 terms hi + mid + lo = t exactly to 24 bits,
-// stored in LDS in operand order, so that bf16 MFMAs give fp32-accurate scores:
-// every product is exact and the accumulation is fp32.
-// Requirements checked by the host: r % 32 == 0, r <= 32 * SCM_KB.
-// Dynamic LDS: 3 * NB * r * 2 bytes.
+// wave per 16 rows of Q; a lane fetches 16 bytes of one row per column block (four lanes: 64
+// contiguous bytes; SCM_KB blocks are requested before t is touched).  t is the sum of the nt
+// stage-1 partials and lies in LDS in operand order:
+//   fp32: as it is, v_mfma_f32_16x16x4_f32;
+//   bf16: split into three bf16 terms hi + mid + lo = t exactly to 24 bits, so that bf16
+//         MFMAs give fp32-accurate scores: every product is exact and the accumulation is fp32.
+// Columns past r are zeros on both sides, so every rank that a layer may have is taken.
+//
+// Bound: the chain launch, partials of t, operands, MFMAs; the bytes of Q are half of it at most.  Taken for fp32 and for
+// ranks that are no multiple of 32 as well: a row's sum over its columns is one accumulator here, where the vector kernel needs
+// six lane exchanges per row and token (and k_tsum before it: 2 to 4.6 us).  Step with three and more tokens, vector kernel
+// -> this one, in us: fp32 d = 464, D = 2176, r = 192, three tokens 22.7 -> 17.7 (scores 10.2 -> 5.1); fp32 d = 1720, D = 8064,
+// r = 464, six tokens 52.4 -> 41.0 (20.7 -> 11.2); bf16 d = 512, D = 2240, r = 24, four tokens 22.0 -> 17.9.
+// Tried on it: two waves per 16 rows with half of the columns each, and sixteen partials requested at once (r = 192: 4.8 ->
+// 5.5; r = 512: 11.5 -> 11.5), the blocks of two slabs in one (the same), column blocks in another order per wave (0.4 slower),
+// the compiler's own unrolling of the partials' loop (eight tokens, r = 256: 6.7 -> 9.2).
+// Dynamic LDS: scm_lds bytes.
 // ---------------------------------------------------------------------------
 constexpr int SCM_THREADS = 256;
-constexpr int SCM_KB = 16;          // 32-column blocks of Q held in registers
+constexpr int SCM_KB = 16;          // column blocks of Q held in registers
+constexpr int SCM_NT = 4;           // partials of t requested together
 
 __device__ __forceinline__ uint32_t bf16_rne_bits(float v)
 {
@@ -302,73 +314,135 @@ __device__ __forceinline__ uint32_t bf16_rne_bits(float v)
     return h.bits;
 }
 
-template <int NB>
-__global__ __launch_bounds__(SCM_THREADS) void k_scores_mfma(const bf16 *__restrict__ Q, const float *__restrict__ bias,
+__device__ __forceinline__ f32x4_t mfma_f32(const uint4 &a, const uint4 &b, f32x4_t c)
+{
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+}
+
+template <typename W>
+constexpr int scm_block() { return 4 * Elem<W>::VEC; }                    // columns of a block
+template <typename W>
+constexpr int scm_terms() { return Elem<W>::BYTES == 2 ? 3 : 1; }         // 16-byte operands per column group and token
+template <typename W>
+size_t scm_lds(int NB, int r)
+{
+    const size_t nkb = (r + scm_block<W>() - 1) / scm_block<W>();
+    return scm_terms<W>() * nkb * 4 * NB * 16;
+}
+
+template <typename W, int NB>
+__global__ __launch_bounds__(SCM_THREADS) void k_scores_mfma(const W *__restrict__ Q, const float *__restrict__ bias,
                                                              const float *__restrict__ tpart, int nt, int B, int D,
                                                              int r, float *__restrict__ s_out,
                                                              uint64_t *__restrict__ mask_out)
 {
     static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8, "token slots are addressed with a mask");
+    constexpr int VEC = Elem<W>::VEC, CB = scm_block<W>(), TERMS = scm_terms<W>();
     extern __shared__ uint4 smem16[];
     __shared__ uint32_t word16[SCM_THREADS / 64];
-    uint4 *planes = smem16;                                         // [3][r/32][4][NB]
+    uint4 *ops = smem16;                                            // [TERMS][nkb * 4 column groups][NB]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lm = lane & 15, lq = lane >> 4;
     const int i0 = blockIdx.x * SC_SLAB + wave * 16;
-    const int nkb = r / 32;
+    const int nkb = (r + CB - 1) / CB;
 
     uint4 q[SCM_KB];
-    const bf16 *qrow = Q + (size_t)(i0 + lm) * r + lq * 8;
+    const W *qrow = Q + (size_t)(i0 + lm) * r + lq * VEC;
+    const int nfull = r / CB;
+    const bool in_tail = nfull * CB + lq * VEC < r;                 // this lane's columns of the last, partial block exist
+    auto request_q = [&](int kb0) {
 #pragma unroll
-    for (int kb = 0; kb < SCM_KB; ++kb)
-        if (kb < nkb) q[kb] = load_raw(qrow + kb * 32);
-    const float4 bs = *reinterpret_cast<const float4 *>(bias + i0 + lq * 4);
+        for (int k = 0; k < SCM_KB; ++k) {
+            const int kb = kb0 + k;
+            if (kb < nfull) {
+                q[k] = load_raw(qrow + (size_t)kb * CB);
+            } else if (kb < nkb) {
+                q[k] = make_uint4(0u, 0u, 0u, 0u);
+                if (in_tail) q[k] = load_raw(qrow + (size_t)kb * CB);
+            }
+        }
+    };
+    request_q(0);
+    float bs[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bs[i] = bias[i0 + lq * 4 + i];
 
-    // t for (token b, columns 8g .. 8g+7): sum of the partials in order, then the three terms
-    const int ngr = r / 8;
-    for (int u = tid; u < NB * ngr; u += SCM_THREADS) {
-        const int b = u / ngr, g = u % ngr;
-        float t[8];
+    // t for (token b, columns VEC g .. VEC g + VEC - 1): sum of the partials in order, then its operands
+    const int ngr = r / VEC, slots = nkb * 4;
+    for (int u = tid; u < NB * slots; u += SCM_THREADS) {
+        const int b = u / slots, g = u % slots;
+        float t[VEC];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) t[e] = 0.f;
-        const float4 *tp = reinterpret_cast<const float4 *>(tpart + (size_t)b * r + (size_t)g * 8);
-        const size_t stride4 = (size_t)NB * r / 4;
-#pragma unroll 4
-        for (int p = 0; p < nt; ++p) {
-            const float4 a = tp[p * stride4], c = tp[p * stride4 + 1];
-            t[0] += a.x; t[1] += a.y; t[2] += a.z; t[3] += a.w;
-            t[4] += c.x; t[5] += c.y; t[6] += c.z; t[7] += c.w;
+        for (int e = 0; e < VEC; ++e) t[e] = 0.f;
+        if (g < ngr) {
+            const float4 *tp = reinterpret_cast<const float4 *>(tpart + (size_t)b * r + (size_t)g * VEC);
+            const size_t stride4 = (size_t)NB * r / 4;
+            int p = 0;
+            for (; p + SCM_NT <= nt; p += SCM_NT) {                 // requested together: one trip for SCM_NT partials
+                float4 v[SCM_NT][VEC / 4];
+#pragma unroll
+                for (int k = 0; k < SCM_NT; ++k)
+#pragma unroll
+                    for (int h = 0; h < VEC / 4; ++h) v[k][h] = tp[(size_t)(p + k) * stride4 + h];
+#pragma unroll
+                for (int k = 0; k < SCM_NT; ++k)
+#pragma unroll
+                    for (int h = 0; h < VEC / 4; ++h) {
+                        t[4 * h] += v[k][h].x; t[4 * h + 1] += v[k][h].y; t[4 * h + 2] += v[k][h].z; t[4 * h + 3] += v[k][h].w;
+                    }
+            }
+            for (; p < nt; ++p) {
+#pragma unroll
+                for (int h = 0; h < VEC / 4; ++h) {
+                    const float4 v = tp[(size_t)p * stride4 + h];
+                    t[4 * h] += v.x; t[4 * h + 1] += v.y; t[4 * h + 2] += v.z; t[4 * h + 3] += v.w;
+                }
+            }
         }
-        uint32_t pl[3][8];
+        uint4 *op = ops + (size_t)g * NB + b;
+        if constexpr (TERMS == 1) {
+            *op = make_uint4(__float_as_uint(t[0]), __float_as_uint(t[1]), __float_as_uint(t[2]), __float_as_uint(t[3]));
+        } else {
+            uint32_t pl[3][VEC];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const uint32_t hi = bf16_rne_bits(t[e]);
-            const float r1 = t[e] - __uint_as_float(hi << 16);
-            const uint32_t mid = bf16_rne_bits(r1);
-            const float r2 = r1 - __uint_as_float(mid << 16);
-            pl[0][e] = hi; pl[1][e] = mid; pl[2][e] = bf16_rne_bits(r2);
+            for (int e = 0; e < VEC; ++e) {
+                const uint32_t hi = bf16_rne_bits(t[e]);
+                const float r1 = t[e] - __uint_as_float(hi << 16);
+                const uint32_t mid = bf16_rne_bits(r1);
+                const float r2 = r1 - __uint_as_float(mid << 16);
+                pl[0][e] = hi; pl[1][e] = mid; pl[2][e] = bf16_rne_bits(r2);
+            }
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                op[(size_t)p * slots * NB] =
+                    make_uint4(pl[p][0] | (pl[p][1] << 16), pl[p][2] | (pl[p][3] << 16), pl[p][4] | (pl[p][5] << 16),
+                               pl[p][6] | (pl[p][7] << 16));
         }
-        const int slot = ((g >> 2) * 4 + (g & 3)) * NB + b;
-#pragma unroll
-        for (int p = 0; p < 3; ++p)
-            planes[(size_t)p * nkb * 4 * NB + slot] =
-                make_uint4(pl[p][0] | (pl[p][1] << 16), pl[p][2] | (pl[p][3] << 16), pl[p][4] | (pl[p][5] << 16),
-                           pl[p][6] | (pl[p][7] << 16));
     }
     __syncthreads();
 
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    const int tb = lm & (NB - 1);
+    const uint4 *op0 = ops + (size_t)lq * NB + (lm & (NB - 1));
+    for (int kb0 = 0; kb0 < nkb; kb0 += SCM_KB) {
+        if (kb0 > 0) request_q(kb0);
 #pragma unroll
-    for (int kb = 0; kb < SCM_KB; ++kb) {
-        if (kb < nkb) {
+        for (int k = 0; k < SCM_KB; ++k) {
+            if (kb0 + k < nkb) {
+                const uint4 *op = op0 + (size_t)(kb0 + k) * 4 * NB;
+                if constexpr (TERMS == 1) {
+                    acc = mfma_f32(q[k], *op, acc);
+                } else {
 #pragma unroll
-            for (int p = 0; p < 3; ++p)
-                acc = mfma_bf16(q[kb], planes[(size_t)p * nkb * 4 * NB + (kb * 4 + lq) * NB + tb], acc);
+                    for (int p = 0; p < 3; ++p) acc = mfma_bf16(q[k], op[(size_t)p * slots * NB], acc);
+                }
+            }
         }
     }
     // the lane holds rows i0 + 4*lq .. +3 for token lm
-    const float sv[4] = {acc[0] + bs.x, acc[1] + bs.y, acc[2] + bs.z, acc[3] + bs.w};
+    const float sv[4] = {acc[0] + bs[0], acc[1] + bs[1], acc[2] + bs[2], acc[3] + bs[3]};
     if (s_out != nullptr && lm < B) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) s_out[(size_t)lm * D + i0 + lq * 4 + i] = sv[i];

@@ -1,0 +1,61 @@
+"""Batches on the matrix cores at the sizes between the plain ones: scores of every rank and storage type, and rows of whole
+128-byte lines that are no multiple of 512 elements, against the CPU oracle."""
+import numpy as np
+import pytest
+
+import parity
+
+pytestmark = pytest.mark.gpu
+
+# d, D, r, B, storage; ranks around a column block (32 bf16 / 16 fp32 columns) and around the blocks held in registers (16)
+RANKS = [(256, 64, 4, 3, "f32"), (264, 448, 12, 8, "f32"), (512, 320, 16, 5, "f32"), (300, 192, 20, 4, "f32"),
+         (260, 640, 252, 8, "f32"), (128, 256, 260, 3, "f32"), (64, 128, 516, 6, "f32"),
+         (256, 64, 8, 3, "bf16"), (264, 448, 40, 8, "bf16"), (1032, 320, 72, 5, "bf16"), (512, 192, 248, 4, "bf16"),
+         (128, 256, 520, 8, "bf16"), (64, 128, 1032, 3, "bf16")]
+
+
+def layer(torch, binding, d, D, r, B, dt, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    dtype = torch.float32 if dt == "f32" else torch.bfloat16
+    mk = lambda *s: (torch.randn(*s, device="cuda", generator=g) / d ** 0.5).to(dtype)
+    L = binding.DeviceLayer(mk(d, r), mk(D, r), torch.randn(D, device="cuda", generator=g) * 0.03, mk(D, d), mk(D, d), mk(D, d))
+    return L, torch.randn(B, d, device="cuda", generator=g).to(dtype)
+
+
+@pytest.mark.parametrize("d,D,r,B,dt", RANKS)
+def test_scores_of_every_rank(d, D, r, B, dt):
+    import torch
+    from paper_2603_14110_amd import binding
+
+    L, x = layer(torch, binding, d, D, r, B, dt, d + D + r)
+    t = L.tensors
+    ref = (x.double() @ t["P"].double()) @ t["Q"].double().T + t["b"].double()
+    s = binding.predict(L, x)
+    # two chains of d and of r fp32 additions: |error| <= (d + r) 2^-24 sum |terms|; far inside the bound used everywhere else
+    assert float((s.double() - ref).abs().max()) <= 2e-5 * float(ref.abs().max())
+    mask = torch.zeros(D // 64, dtype=torch.int64, device="cuda")
+    binding.ffn_step(L, x, mask=mask)
+    m2, _, _ = binding.compact(s)
+    assert torch.equal(mask, m2)
+
+
+@pytest.mark.parametrize("d,D,B", [(64, 64, 8), (192, 640, 5), (576, 4160, 8), (1088, 2112, 3), (1856, 1152, 8)])
+def test_rows_of_whole_lines(d, D, B):
+    import torch
+    import oracle
+    from paper_2603_14110_amd import binding
+
+    L, x = layer(torch, binding, d, D, 16, B, "bf16", d + D)
+    f = {k: L.tensors[k].float().cpu().numpy() for k in ("W_gate", "W_up", "W_downT")}
+    X = x.float().cpu().numpy()
+    L = L.with_flags(binding.FLAG_ENGINE_MATRIX)
+    idx = torch.zeros(D, dtype=torch.int32, device="cuda")
+    nnz = torch.zeros(1, dtype=torch.int32, device="cuda")
+    y = binding.ffn_step(L, x, idx=idx, nnz=nnz).cpu().numpy()
+    lst = idx[: nnz.item()].cpu().numpy()
+    parity.check_y(y, oracle.sparse_ffn(f["W_gate"], f["W_up"], f["W_downT"], X, lst), "bf16",
+                   slack=parity.fp32_forward_bound(f, X, lst))
+    yd = binding.dense_ffn(L, x).cpu().numpy()
+    parity.check_y(yd, oracle.dense_ffn(f["W_gate"], f["W_up"], f["W_downT"], X), "bf16",
+                   slack=parity.fp32_forward_bound(f, X, np.arange(D)))
