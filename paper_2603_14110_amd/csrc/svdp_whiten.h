@@ -176,8 +176,9 @@ __global__ __launch_bounds__(256) void k_zero_upper_blocks(double *__restrict__ 
 //
 // The matrix is cut into blocks of 32 rows / columns.  One round pairs the blocks (2k, 2k+1) -
 // always neighbours, so a pair is the contiguous strip of rows 64k .. 64k+63 - and
-//   k_bjacobi_solve  runs a cyclic Jacobi sweep (all 2016 pairs of its 64 indices) over every strip's own
-//                    64 x 64 diagonal tile in LDS and stores the accumulated orthogonal U_k;
+//   k_bjacobi_solve  runs a cyclic Jacobi sweep (all 2016 pairs of its 64 indices, or the 1024 of one index from
+//                    each block) over every strip's own 64 x 64 diagonal tile in LDS and stores the accumulated
+//                    orthogonal U_k;
 //   k_bjacobi_apply  forms A <- U^T A U tile by tile (the tile of strip a and strip c needs only
 //                    itself, U_a and U_c: two 64 x 64 x 64 products on the fp64 matrix cores) and
 //                    Vt <- U^T Vt (one product), and writes every tile straight to the place the
@@ -211,7 +212,16 @@ __device__ __forceinline__ int bjacobi_next_index(int i, int n)
 // the pairs of a step are the seats (m, 63 - m), m = 0 .. 31.  bj_seat gives a seat's index in step 0, bj_advance
 // the index the same seat holds one step later.
 __device__ __forceinline__ int bj_seat(int seat) { return seat; }
-__device__ __forceinline__ int bj_advance(int idx) { return idx == 0 ? 0 : (idx == BJ_S - 1 ? 1 : idx + 1); }
+// CROSS: only pairs of an index of the strip's first block and one of its second, seats m and 32 + m, in 32 steps: the
+// first stays, the second goes round its block.
+template <bool CROSS>
+__device__ __forceinline__ int bj_advance(int idx)
+{
+    if (CROSS) return idx < BJ_B ? idx : (idx == BJ_S - 1 ? BJ_B : idx + 1);
+    return idx == 0 ? 0 : (idx == BJ_S - 1 ? 1 : idx + 1);
+}
+template <bool CROSS>
+__device__ __forceinline__ int bj_partner(int seat) { return CROSS ? BJ_B + seat : BJ_S - 1 - seat; }
 
 // (c, s) of the rotation J = [c s; -s c] that (nearly) zeroes the off-diagonal element of [app apq; apq aqq] in
 // J^T . J.  The tangent is worked out in single precision with the hardware's reciprocal and square root - its
@@ -256,11 +266,12 @@ __device__ __forceinline__ double bj_neighbour(double v)
 // accesses spread over all LDS banks.  U <- U J is the same column rotation; the angles of the next step are
 // computed (32 lanes) while the other waves are in it.
 // The rows of U are independent of each other and of S, so BJ_U_PARTS blocks per strip sweep the same S and take a part of
-// the rows each: a round has far fewer strips than the chip has compute units (64 -> 52 us a launch; bound by the LDS traffic
-// and the two barriers of the 63 dependent steps; with eight waves instead of sixteen the call is 2 % slower).
+// the rows each: a round has far fewer strips than the chip has compute units (64 -> 52 us a launch, 30 across only; bound by the LDS
+// traffic and the two barriers of the 63 or 32 dependent steps; with eight waves instead of sixteen the call is 2 % slower).
 constexpr int BJ_SOLVE_THREADS = 1024;
 constexpr int BJ_U_PARTS = 4;
 constexpr size_t BJ_SOLVE_LDS = (size_t)(BJ_S + BJ_S / BJ_U_PARTS) * BJ_LD * 8;
+template <bool CROSS>
 __global__ __launch_bounds__(BJ_SOLVE_THREADS) void k_bjacobi_solve(const double *__restrict__ A, int n,
                                                                     double *__restrict__ Uall)
 {
@@ -270,6 +281,7 @@ __global__ __launch_bounds__(BJ_SOLVE_THREADS) void k_bjacobi_solve(const double
     __shared__ double csv[2][BJ_B][2];
     __shared__ double red[2][BJ_SOLVE_THREADS / 64];
     __shared__ int done;
+    constexpr int STEPS = CROSS ? BJ_B : BJ_S - 1;
     constexpr int WAVES = BJ_SOLVE_THREADS / 64, PAIRS = BJ_B / WAVES, UR = BJ_S / BJ_U_PARTS, ROWS = UR / WAVES;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k = blockIdx.x, u0 = blockIdx.y * UR;
     const int pb = lane >> 1, second = lane & 1;
@@ -299,14 +311,14 @@ __global__ __launch_bounds__(BJ_SOLVE_THREADS) void k_bjacobi_solve(const double
         }
         // this lane's column, this wave's row pairs and (threads 0 .. 31) the pair whose angle the thread works
         // out, all for step 0; advanced step by step below
-        int col = second ? bj_seat(BJ_S - 1 - pb) : bj_seat(pb);
+        int col = second ? bj_partner<CROSS>(pb) : bj_seat(pb);
         int rp[PAIRS], rq[PAIRS];
 #pragma unroll
         for (int e = 0; e < PAIRS; ++e) {
             rp[e] = bj_seat(wave * PAIRS + e);
-            rq[e] = bj_seat(BJ_S - 1 - (wave * PAIRS + e));
+            rq[e] = bj_partner<CROSS>(wave * PAIRS + e);
         }
-        int ap = bj_seat(tid & (BJ_B - 1)), aq = bj_seat(BJ_S - 1 - (tid & (BJ_B - 1)));
+        int ap = bj_seat(tid & (BJ_B - 1)), aq = bj_partner<CROSS>(tid & (BJ_B - 1));
         __syncthreads();
         if (tid == 0) {
             double o = 0.0, t = 0.0;
@@ -324,7 +336,7 @@ __global__ __launch_bounds__(BJ_SOLVE_THREADS) void k_bjacobi_solve(const double
         }
         __syncthreads();
         if (done) break;
-        for (int step = 0; step < BJ_S - 1; ++step) {
+        for (int step = 0; step < STEPS; ++step) {
             const int cur = step & 1;
             // column rotation of a value v at this lane's column, w the same row's value at the pair's other
             // column:  first column  c v - s w,  second column  c v + s w
@@ -344,9 +356,9 @@ __global__ __launch_bounds__(BJ_SOLVE_THREADS) void k_bjacobi_solve(const double
                 S[rq[e] * BJ_LD + col] = cb * yr + sb * yo;
             }
             __syncthreads();
-            ap = bj_advance(ap);
-            aq = bj_advance(aq);
-            if (tid < BJ_B && step + 1 < BJ_S - 1) {
+            ap = bj_advance<CROSS>(ap);
+            aq = bj_advance<CROSS>(aq);
+            if (tid < BJ_B && step + 1 < STEPS) {
                 double c, s;
                 bj_angle(S[ap * BJ_LD + ap], S[aq * BJ_LD + aq], S[ap * BJ_LD + aq], c, s);
                 csv[cur ^ 1][tid][0] = c;
@@ -360,11 +372,11 @@ __global__ __launch_bounds__(BJ_SOLVE_THREADS) void k_bjacobi_solve(const double
                 const double uo = bj_neighbour(u[e]);
                 U[(wave * ROWS + e) * BJ_LD + col] = cb * u[e] + sb * uo;
             }
-            col = bj_advance(col);
+            col = bj_advance<CROSS>(col);
 #pragma unroll
             for (int e = 0; e < PAIRS; ++e) {
-                rp[e] = bj_advance(rp[e]);
-                rq[e] = bj_advance(rq[e]);
+                rp[e] = bj_advance<CROSS>(rp[e]);
+                rq[e] = bj_advance<CROSS>(rq[e]);
             }
             __syncthreads();
         }
@@ -412,8 +424,8 @@ __device__ __forceinline__ void bj_mma64(const double *Lm, const double *Rm, int
 // two blocks fit a compute unit and one multiplies while the other loads and stores.
 // Dynamic LDS: 2 matrices of 64 x 65 doubles.
 template <bool TWO_SIDED>
-__global__ __launch_bounds__(256, 2) void k_bjacobi_apply(const double *__restrict__ M, const double *__restrict__ Uall,
-                                                          int n, int ct, double *__restrict__ out)
+__device__ __forceinline__ void bj_apply(const double *__restrict__ M, const double *__restrict__ Uall, int n, int ct,
+                                         double *__restrict__ out)
 {
     extern __shared__ double bj_smem[];
     double *Ua = bj_smem, *T = Ua + BJ_S * BJ_LD;
@@ -493,6 +505,15 @@ __global__ __launch_bounds__(256, 2) void k_bjacobi_apply(const double *__restri
                         acc[i][j][v];
                 }
     }
+}
+
+// Both updates of a round in one launch: blockIdx.z 0 the matrix, 1 the eigenvector rows.
+__global__ __launch_bounds__(256, 2) void k_bjacobi_apply(const double *__restrict__ A, const double *__restrict__ Vt,
+                                                          const double *__restrict__ Uall, int n, int ct,
+                                                          double *__restrict__ A_out, double *__restrict__ Vt_out)
+{
+    if (blockIdx.z == 0) bj_apply<true>(A, Uall, n, ct, A_out);
+    else bj_apply<false>(Vt, Uall, n, ct, Vt_out);
 }
 
 __global__ __launch_bounds__(256) void k_identity(double *__restrict__ Vt, int n)

@@ -150,10 +150,9 @@ inline DgEpilogue minus_from(const double *Cin, int ld)
 svdp_status jacobi_eigh(double **A, double **Aalt, double **V, double **Valt, int n, double *Uall, double *rowsums,
                         double *sums, double *lam, double tol, int max_sweeps, int *sweeps_out, hipStream_t st)
 {
-    const size_t lds_solve = BJ_SOLVE_LDS, lds_two = (size_t)2 * BJ_S * BJ_LD * 8,
-                 lds_one = lds_two;
-    if (!grant_lds<k_bjacobi_solve>(lds_solve) || !grant_lds<k_bjacobi_apply<true>>(lds_two) ||
-        !grant_lds<k_bjacobi_apply<false>>(lds_one))
+    const size_t lds_solve = BJ_SOLVE_LDS, lds_apply = (size_t)2 * BJ_S * BJ_LD * 8;
+    if (!grant_lds<k_bjacobi_solve<false>>(lds_solve) || !grant_lds<k_bjacobi_solve<true>>(lds_solve) ||
+        !grant_lds<k_bjacobi_apply>(lds_apply))
         return SVDP_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(k_identity, grid1((size_t)n * n), dim3(256), 0, st, *V, n);
     const int strips = n / BJ_S, rounds = n / BJ_B > 2 ? n / BJ_B - 1 : 1;
@@ -175,9 +174,16 @@ svdp_status jacobi_eigh(double **A, double **Aalt, double **V, double **Valt, in
         if (!(h[1] == h[1]) || h[0] <= tol * tol * h[1] || stalled || sweep >= max_sweeps) break;
         previous = h[0];
         for (int round = 0; round < rounds; ++round) {
-            hipLaunchKernelGGL(k_bjacobi_solve, dim3(strips, BJ_U_PARTS), dim3(BJ_SOLVE_THREADS), lds_solve, st, *A, n, Uall);
-            hipLaunchKernelGGL(k_bjacobi_apply<true>, dim3(cgrid, strips), dim3(256), lds_two, st, *A, Uall, n, ct, *Aalt);
-            hipLaunchKernelGGL(k_bjacobi_apply<false>, dim3(cgrid, strips), dim3(256), lds_one, st, *V, Uall, n, ct, *Valt);
+            // A sweep's first round takes the pairs inside the blocks as well, which all have their turn in it; the others only
+            // those across: half the steps, and a sweep or two more.  With few rounds the first sweep is worth having whole.
+            // Whole call, every round whole / this (ms): n = 512, r = 400 (full decomposition) 11.8 / 7.6, d = 2560, r = 640
+            // 53.3 / 48.9, d = 4096, r = 256 42.5 / 40.3, d = 1024, r = 64 4.2 / 3.1; without the first sweep at d = 320,
+            // r = 80 4.4 / 4.5, with it 4.35.
+            if (round == 0 || (sweep == 0 && rounds <= 5))
+                hipLaunchKernelGGL(k_bjacobi_solve<false>, dim3(strips, BJ_U_PARTS), dim3(BJ_SOLVE_THREADS), lds_solve, st, *A, n, Uall);
+            else
+                hipLaunchKernelGGL(k_bjacobi_solve<true>, dim3(strips, BJ_U_PARTS), dim3(BJ_SOLVE_THREADS), lds_solve, st, *A, n, Uall);
+            hipLaunchKernelGGL(k_bjacobi_apply, dim3(cgrid, strips, 2), dim3(256), lds_apply, st, *A, *V, Uall, n, ct, *Aalt, *Valt);
             std::swap(*A, *Aalt);
             std::swap(*V, *Valt);
         }
