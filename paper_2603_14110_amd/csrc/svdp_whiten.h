@@ -60,7 +60,7 @@ __global__ __launch_bounds__(256) void k_f64_to_f32(const double *__restrict__ s
 // and after a panel its whole update of the lower triangle behind it, K = CH_PANEL.  A left-looking order would sum
 // over all earlier columns for 64 columns at a time: at most n / 64 blocks with K up to n, which leaves the chip idle
 // (up to 0.24 ms per block column at n = 4096); this way the bulk is one wide product per panel.
-// Measured at n = 4096: 25 -> 3.4 ms (192 launches; k_chol_diag 189 -> 28 us a block).
+// Measured at n = 4096: 25 -> 3.4 ms (192 launches; k_chol_diag 189 -> 28 us a block, 20 now).
 // ---------------------------------------------------------------------------
 constexpr int CH_B = 64;
 constexpr int CH_PANEL = 256;
@@ -89,75 +89,150 @@ __device__ __forceinline__ double lane_value(double v, int src)
 // The 64 x 64 block at A + off (row stride n, lower part) becomes its Cholesky factor (zero above the diagonal);
 // invL [64][64] = the factor's inverse.  A pivot that is not above tiny * scale[0] (the matrix is not positive definite
 // to working precision) sets fail[0] = 1 and is replaced by that bound, so that the rest of the run stays finite.
-// Bound: 64 dependent steps.  A thread keeps 16 columns of one row of the block and of the inverse in registers
-// (lane = row, wave = column group).  A wave factors its 16 columns by itself (the multipliers of a step are other
-// lanes' values, no LDS and no barrier in the chain); then, once per group, the waves to its right take the 16 columns
-// out of theirs through LDS and the others apply the 16 row operations to the inverse while the next group is factored.
+// Bound: 64 dependent pivots.  Wave g factors columns 16 g .. 16 g + 15 by itself (lane = row, the multipliers of a step are
+// other lanes' values: no LDS and no barrier in the chain).  Then the waves to its right take those columns out of theirs by
+// fp64 MFMAs (tiles of 16 x 16, result register v of a lane = row 4 v + lane / 16, column lane % 16), while wave g inverts its
+// diagonal 16 x 16 block by substitution (a lane per column) and the waves to its left form a row of blocks of the
+// inverse, X_ij = -X_ii sum_k L_ik X_kj: wave j keeps block column j, whose result registers are the next product's
+// right operand as they are.
 // A block: 189 us in LDS element by element with three barriers a step and a serial substitution for the inverse,
-// 39 us with one barrier per step, 28 us so.
+// 39 us with one barrier per step, 28 us with the trailing columns and the inverse by row operations, 24 us with the
+// compiler's order of the updates (all of a column's in front of its pivot), 20 us so.
 __global__ __launch_bounds__(256) void k_chol_diag(double *__restrict__ A, int n, size_t off,
                                                    const double *__restrict__ scale, double tiny,
                                                    double *__restrict__ invL, int *__restrict__ fail)
 {
-    constexpr int CPT = CH_B / 4;
-    __shared__ double col[2][CPT][CH_B];        // the group's finished columns
-    __shared__ double inv_sh[2][CPT];
-    const int row = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const double bound = tiny * scale[0];
-    double s[CPT], x[CPT];
-    double *mine = A + off + (size_t)row * n + wave * CPT;
+    constexpr int CPT = 16, GROUPS = CH_B / CPT, LDC = CH_B + 2, LDX = CPT + 1;
+    __shared__ double col[GROUPS][CPT][LDC];    // finished columns
+    __shared__ double xd[GROUPS][CPT][LDX];     // inverses of the diagonal blocks
+    __shared__ double turn[CH_B][LDX];          // tiles -> rows of the next group
+    __shared__ double inv_sh[GROUPS][CPT];
+    const int row = threadIdx.x & 63, lm = row & 15, lq = row >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const double bound = tiny * scale[0], floor_p = bound > 0.0 ? bound : 1.0;
+    bool small = false;                         // a pivot was (the same in every lane)
+    double *blk = A + off;
+    double s[CPT];                              // wave 0, later the group's own wave: row `row`, the group's columns
+    f64x4_t acc[GROUPS], xb[GROUPS];            // this group's column of tiles; of the inverse's blocks
 #pragma unroll
-    for (int k = 0; k < CPT; ++k) {
-        s[k] = mine[k];
-        x[k] = row == wave * CPT + k ? 1.0 : 0.0;
+    for (int t = 0; t < GROUPS; ++t) {
+        acc[t] = xb[t] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+        if (wave > 0 && t >= wave) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[t][v] = blk[(size_t)(CPT * t + 4 * v + lq) * n + CPT * wave + lm];
+        }
     }
-    for (int jb = 0; jb < 4; ++jb) {
-        const int buf = jb & 1;
-        if (wave == jb) {
+    if (wave == 0) {
 #pragma unroll
-            for (int k = 0; k < CPT; ++k) {
-                const int j = jb * CPT + k;
-                double p = lane_value(s[k], j);
-                if (!(p > bound)) {
-                    if (row == 0) fail[0] = 1;
-                    p = bound > 0.0 ? bound : 1.0;
-                }
-                double inv = __builtin_amdgcn_rsq(p);                 // 1 / sqrt(p), two Newton steps
+        for (int k = 0; k < CPT; ++k) s[k] = blk[(size_t)row * n + k];
+    }
+    // block (i, wave) of the inverse, wave < i: needs the columns of the groups up to i - 1 and xd[i]
+    auto inverse_block = [&](int i) {
+        f64x4_t t = {0.0, 0.0, 0.0, 0.0}, x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < GROUPS - 1; ++k) {
+            if (k >= wave && k < i) {
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk)
+                    t = __builtin_amdgcn_mfma_f64_16x16x4f64(col[k][4 * kk + lq][CPT * i + lm], xb[k][kk], t, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) x = __builtin_amdgcn_mfma_f64_16x16x4f64(-xd[i][lm][4 * kk + lq], t[kk], x, 0, 0, 0);
+#pragma unroll
+        for (int k = 1; k < GROUPS; ++k)
+            if (k == i) xb[k] = x;
+    };
+#pragma unroll 1
+    for (int g = 0; g < GROUPS; ++g) {
+        if (wave == g) {
+            // The chain from pivot to pivot runs beside the other columns' updates by the column before; nothing else is
+            // in it (no branch; what a row above its diagonal holds is cleared behind it), and the barriers keep the
+            // compiler from gathering a column's updates in front of its pivot.
+            double mine = 0.0, diag = 0.0, inv = 0.0;
+            auto pivot = [&](int k) {                                 // 1 / sqrt of column k's pivot
+                double p = lane_value(s[k], g * CPT + k);
+                const bool good = p > bound;
+                small = small || !good;
+                p = good ? p : floor_p;
+                inv = __builtin_amdgcn_rsq(p);                        // and two Newton steps
 #pragma unroll
                 for (int it = 0; it < 2; ++it) inv = __builtin_fma(0.5 * inv, __builtin_fma(-p * inv, inv, 1.0), inv);
-                s[k] = row > j ? s[k] * inv : row == j ? p * inv : 0.0;
-                col[buf][k][row] = s[k];
-                if (row == 0) inv_sh[buf][k] = inv;
+                mine = row == k ? inv : mine;
+                diag = row == g * CPT + k ? p * inv : diag;
+            };
+            pivot(0);
+            s[0] *= inv;
 #pragma unroll
-                for (int c = k + 1; c < CPT; ++c) s[c] = __builtin_fma(-s[k], lane_value(s[k], jb * CPT + c), s[c]);
+            for (int k = 0; k + 1 < CPT; ++k) {
+                s[k + 1] = __builtin_fma(-s[k], lane_value(s[k], g * CPT + k + 1), s[k + 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                pivot(k + 1);
+#pragma unroll
+                for (int c = k + 2; c < CPT; ++c) s[c] = __builtin_fma(-s[k], lane_value(s[k], g * CPT + c), s[c]);
+                s[k + 1] *= inv;
+                __builtin_amdgcn_sched_barrier(0);
             }
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) {
+                s[k] = row > g * CPT + k ? s[k] : row == g * CPT + k ? diag : 0.0;
+                col[g][k][row] = s[k];
+            }
+            if (row < CPT) inv_sh[g][row] = mine;
         }
         __syncthreads();
-        if (wave > jb) {
+        if (wave > g) {
 #pragma unroll
-            for (int k = 0; k < CPT; ++k) {
-                const double l = col[buf][k][row];
+            for (int kk = 0; kk < 4; ++kk) {
+                const double b = col[g][4 * kk + lq][CPT * wave + lm];
 #pragma unroll
-                for (int c = 0; c < CPT; ++c) s[c] = __builtin_fma(-l, col[buf][k][wave * CPT + c], s[c]);
+                for (int t = 1; t < GROUPS; ++t)
+                    if (t >= wave)
+                        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-col[g][4 * kk + lq][CPT * t + lm], b, acc[t], 0, 0, 0);
             }
-        } else {
+            if (wave == g + 1) {                // its turn next: a wave's LDS accesses stay in order
+#pragma unroll
+                for (int t = 1; t < GROUPS; ++t)
+                    if (t >= wave) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) turn[CPT * t + 4 * v + lq][lm] = acc[t][v];
+                    }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int k = 0; k < CPT; ++k) s[k] = row >= CPT * wave ? turn[row][k] : 0.0;
+            }
+        } else if (wave == g) {
+            double x[CPT];                      // column lm of the diagonal block's inverse
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) x[k] = k == lm ? 1.0 : 0.0;
 #pragma unroll
             for (int k = 0; k < CPT; ++k) {
-                const int j = jb * CPT + k;
-                const double inv = inv_sh[buf][k], l = row > j ? col[buf][k][row] : 0.0;
+                x[k] *= inv_sh[g][k];
 #pragma unroll
-                for (int c = 0; c < CPT; ++c) {
-                    const double xj = lane_value(x[c], j) * inv;
-                    x[c] = row == j ? xj : __builtin_fma(-l, xj, x[c]);
+                for (int c = k + 1; c < CPT; ++c) x[c] = __builtin_fma(-col[g][k][CPT * g + c], x[k], x[c]);
+            }
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) xd[g][k][lm] = x[k];      // the four quarters of the wave hold the same
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int t = 0; t < GROUPS; ++t)
+                if (t == g) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) xb[t][v] = xd[g][4 * v + lq][lm];
                 }
-            }
+        } else if (wave < g - 1) {
+            inverse_block(g - 1);
         }
     }
+    __syncthreads();
+    if (wave < GROUPS - 1) inverse_block(GROUPS - 1);
+    if (small && row == 0) fail[0] = 1;
 #pragma unroll
-    for (int k = 0; k < CPT; ++k) {
-        mine[k] = row >= wave * CPT + k ? s[k] : 0.0;
-        invL[row * CH_B + wave * CPT + k] = x[k];
-    }
+    for (int k = 0; k < CPT; ++k) blk[(size_t)row * n + CPT * wave + k] = row >= CPT * wave + k ? s[k] : 0.0;
+#pragma unroll
+    for (int t = 0; t < GROUPS; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) invL[(CPT * t + 4 * v + lq) * CH_B + CPT * wave + lm] = xb[t][v];
 }
 
 // zero above the diagonal blocks of L [n][n] (the blocks on the diagonal are already lower triangular)
