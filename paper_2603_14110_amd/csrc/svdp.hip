@@ -731,7 +731,8 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
     p += align_up((size_t)D * (MS + 1) * 4);
     int32_t *k0 = reinterpret_cast<int32_t *>(p);
     p += align_up((size_t)D * 4);
-    SelectState *state = reinterpret_cast<SelectState *>(p);
+    SelectWork *work = reinterpret_cast<SelectWork *>(p);
+    static_assert(sizeof(SelectWork) <= ALIGN, "the slot that the workspace keeps for the selection's state");
     p += align_up(sizeof(SelectState));
     long long *hist = reinterpret_cast<long long *>(p);
     p += align_up((size_t)SEL_BINS * 8);
@@ -745,7 +746,7 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
         const size_t lds = calib_sort_lds<PER>(n2, MS);
         if (!grant_lds<k_calib_sort<PER>>(lds)) return SVDP_ERR_UNSUPPORTED;
         hipLaunchKernelGGL(k_calib_sort<PER>, dim3(D), dim3(CAL_THREADS), lds, st, w, s, T, n2, eta, MS, key, drop, tauc, k0,
-                           lo, kendall);
+                           lo, kendall, reinterpret_cast<uint32_t *>(hist), SEL_BINS * 2, &work->readers, steps);
         return hip_status(hipSuccess);
     };
     svdp_status e = T <= 2 * CAL_THREADS ? sort(std::integral_constant<int, 2>{})
@@ -755,15 +756,28 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
     if (e != SVDP_OK) return e;
     const size_t items = (size_t)D * MS;
     const int hb = (int)std::min<size_t>((items + 256 * SEL_RUN - 1) / (256 * SEL_RUN), 256);       // more of them only meet at the counters
-    hipLaunchKernelGGL(k_select_init, dim3(1), dim3(SEL_THREADS), 0, st, lo, D, (long long)need, state, hist, steps);
-    hipLaunchKernelGGL((k_select_hist<23, 8>), dim3(hb), dim3(256), 0, st, key, drop, D, MS, state, hist);
-    hipLaunchKernelGGL((k_select_pick<23, true>), dim3(1), dim3(64), 0, st, state, hist);
-    hipLaunchKernelGGL((k_select_hist<15, 8>), dim3(hb), dim3(256), 0, st, key, drop, D, MS, state, hist);
-    hipLaunchKernelGGL((k_select_pick<15, false>), dim3(1), dim3(64), 0, st, state, hist);
-    hipLaunchKernelGGL((k_select_hist<7, 8>), dim3(hb), dim3(256), 0, st, key, drop, D, MS, state, hist);
-    hipLaunchKernelGGL((k_select_pick<7, false>), dim3(1), dim3(64), 0, st, state, hist);
-    hipLaunchKernelGGL((k_select_hist<0, 7>), dim3(hb), dim3(256), 0, st, key, drop, D, MS, state, hist);
-    hipLaunchKernelGGL((k_select_pick<0, false>), dim3(1), dim3(64), 0, st, state, hist);
+    // Two buffers of counts: `hist` and `up`, which is free until the bounds; where that is too small all pairs together
+    // (D T < 512 * 4096) fit 32 bits, and both lie in `hist`.
+    auto select = [&](auto *first, auto *second) {
+        using Bin = std::remove_pointer_t<decltype(first)>;
+        hipLaunchKernelGGL((k_select_hist<23, 8, -1, Bin>), dim3(hb + 1), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 0,
+                           work, second, first);
+        hipLaunchKernelGGL((k_select_hist<15, 8, 23, Bin>), dim3(hb), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 0, work,
+                           first, second);
+        hipLaunchKernelGGL((k_select_hist<7, 8, 15, Bin>), dim3(hb), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 1, work,
+                           second, first);
+        hipLaunchKernelGGL((k_select_hist<0, 7, 7, Bin>), dim3(hb), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 2, work,
+                           first, second);
+        hipLaunchKernelGGL(k_select_last<Bin>, dim3(1), dim3(64), 0, st, work, second);
+    };
+    static_assert(CAL_MAX_T <= 4096 && SEL_BINS * 8 <= 512 * 4, "see above");
+    if (D >= 512) {
+        select(hist, reinterpret_cast<long long *>(up));
+    } else {
+        uint32_t *h32 = reinterpret_cast<uint32_t *>(hist);
+        select(h32, h32 + SEL_BINS);
+    }
+    const SelectState *state = &work->state[SEL_STATES - 1];
     // the digit counts are done with: their place holds the blocks' gains, so there are at most SEL_BINS blocks
     const int chunk = (int)(((long long)D + 256 * SEL_BINS - 1) / (256 * SEL_BINS)) * 256, blocks = (D + chunk - 1) / chunk;
     hipLaunchKernelGGL(k_select_bounds, dim3(blocks), dim3(256), 0, st, key, drop, D, MS, chunk, state, lo, up, hist);

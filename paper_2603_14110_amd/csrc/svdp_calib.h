@@ -17,7 +17,7 @@
 //                  optionally the Kendall check of App. A.
 //   k_select_*     the cost level at which the required number of pairs is first
 //                  reached, by a radix select over the keys' bit patterns
-//                  (four digit passes, integer atomics); then the steps at
+//                  (four digit launches, integer atomics); then the steps at
 //                  exactly that level are taken in neuron order, and b = -tau
 //                  and the pointers written.
 // Integer results equal the sequential algorithm's bit for bit.
@@ -29,7 +29,6 @@ namespace svdp {
 
 constexpr int CAL_THREADS = 256;
 constexpr int CAL_MAX_T = 4096;
-constexpr int SEL_THREADS = 1024;
 
 // order-preserving map float -> uint32 (-0 and +0 coincide; inputs are not NaN)
 __device__ __forceinline__ uint32_t ordered_bits(float v)
@@ -83,7 +82,9 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
                                                             int T, int n2max, int eta, int MS,
                                                             float *__restrict__ key, int32_t *__restrict__ drop,
                                                             float *__restrict__ tauc, int32_t *__restrict__ k0_out,
-                                                            int32_t *__restrict__ drop0, float *__restrict__ kendall)
+                                                            int32_t *__restrict__ drop0, float *__restrict__ kendall,
+                                                            uint32_t *__restrict__ clear0, int n_clear0,
+                                                            uint32_t *__restrict__ clear1, int32_t *__restrict__ clear2)
 {
     constexpr int NBK = cal_buckets<PER>(), BPT = NBK / CAL_THREADS, WAVES = CAL_THREADS / 64;
     extern __shared__ unsigned long long smem64[];
@@ -319,6 +320,13 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
         if (j == 0) drop0[i] = dj;
     }
     if (tid == 0) k0_out[i] = k0;
+    if (i == 0) {                                                  // what the selection counts in
+        for (int q = tid; q < n_clear0; q += CAL_THREADS) clear0[q] = 0u;
+        if (tid == 0) {
+            *clear1 = 0u;
+            if (clear2 != nullptr) *clear2 = 0;
+        }
+    }
 
     if (kendall != nullptr) {
         // App. A: non-overlapping eta-step sums over the whole sorted sample (zero below the tail),
@@ -376,6 +384,12 @@ __device__ __forceinline__ int steps_below(const float *__restrict__ key_i, int 
 // step adds (its gain) are summed per digit value among the steps that match the digits found so
 // far, and the digit is where the running sum first covers what is still missing.  Integer atomics
 // only, so the result does not depend on the order of arrival.
+//
+// A digit is one launch: every block works out the digit before from that one's counts (a wave, 256 counts) and adds its
+// gains to the other of two count buffers; the block that is last to have read a buffer clears it for the next digit but
+// one.  Bound: the launches.  With a launch for every choice of a digit and one for the start (11 launches behind the sort
+// instead of 7), whole call: D = 1344, T = 1423, eta = 23 50.2 -> 38.0 us, D = 5312, T = 77, eta = 22 51.3 -> 43.8, D = 11008,
+// T = 2048, eta = 16 159.8 -> 157.4 (working a digit out costs a counting launch 3 us of the 4.9 that it saves).
 struct SelectState {
     long long missing;       // pairs still to be found among steps at or above the current prefix
     long long c0;            // pairs dropped before any step
@@ -384,47 +398,129 @@ struct SelectState {
     int32_t at_start;        // 1: the start already meets the target (no step is taken)
 };
 constexpr int SEL_BINS = 256;
+constexpr int SEL_STATES = 5;                  // the start, then the state behind each digit
 constexpr uint32_t SEL_TOP = 0x7f7fffffu;      // largest finite float: keys above it are padding
+// The states and the counter of the blocks that have read a buffer: what the workspace keeps for the selection.
+struct SelectWork {
+    SelectState state[SEL_STATES];
+    uint32_t readers;
+};
 
-__global__ __launch_bounds__(SEL_THREADS) void k_select_init(const int32_t *__restrict__ drop0, int D, long long need,
-                                                             SelectState *__restrict__ st, long long *__restrict__ hist,
-                                                             int32_t *__restrict__ steps)
+// The state behind the digit whose counts are given (all 64 lanes of a wave; lane l owns bins 4l .. 4l+3).
+template <typename Bin>
+__device__ __forceinline__ SelectState select_pick(const SelectState &in, const Bin *__restrict__ counts, int shift)
 {
-    __shared__ long long red[SEL_THREADS / 64];
-    long long c0 = 0;
-    for (int i = threadIdx.x; i < D; i += SEL_THREADS) c0 += drop0[i];
-    c0 = block_sum_i64(c0, red);
-    if (threadIdx.x < SEL_BINS) hist[threadIdx.x] = 0;
-    if (threadIdx.x == 0) {
-        st->c0 = c0;
-        st->missing = need - c0;
-        st->prefix = 0u;
-        st->reachable = c0 < need ? 1 : 0;
-        st->at_start = c0 < need ? 0 : 1;
-        if (steps != nullptr) *steps = 0;
+    SelectState out = in;
+    const int lane = threadIdx.x & 63;
+    long long h[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) h[q] = (long long)counts[4 * lane + q];
+    const long long missing = in.missing;
+    const long long mine = h[0] + h[1] + h[2] + h[3];
+    long long inc = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const long long o = __shfl_up(inc, off);
+        if (lane >= off) inc += o;
     }
+    const long long before = inc - mine;
+    const unsigned long long who = __ballot(before < missing && inc >= missing);      // at most one lane
+    if (in.reachable == 0) return out;
+    if (who == 0ull) {                          // only on the first digit: every finite step together falls short
+        out.reachable = 0;
+        return out;
+    }
+    long long run = before;
+    int digit = 0;
+    for (int q = 0; q < 4; ++q) {
+        if (run + h[q] >= missing) {
+            digit = 4 * lane + q;
+            break;
+        }
+        run += h[q];
+    }
+    const int src = __ffsll(who) - 1;
+    out.missing = __shfl(missing - run, src);   // still to be found among the steps with this digit
+    out.prefix |= (uint32_t)__shfl(digit, src) << shift;
+    return out;
 }
 
-// hist[digit] += gain over the steps whose key matches the prefix above this digit.  A thread takes SEL_RUN steps in a
+__device__ __forceinline__ void select_add(long long *at, long long v)
+{
+    atomicAdd(reinterpret_cast<unsigned long long *>(at), (unsigned long long)v);
+}
+__device__ __forceinline__ void select_add(uint32_t *at, long long v) { atomicAdd(at, (uint32_t)v); }
+
+// counts[digit] += gain over the steps whose key matches the prefix above this digit.  A thread takes SEL_RUN steps in a
 // row: a neuron's keys do not decrease, so they share few digits and most gains are added before they reach the (then
 // contended) counters.
+// FIRST: no digit is known; the launch's last block adds up drop0 instead, sets the start state and clears the other buffer.
+// Otherwise the digit before is worked out from `last` first, while the first keys are on their way.
 constexpr int SEL_RUN = 8;
-template <int SHIFT, int BITS>
+template <int SHIFT, int BITS, int LAST_SHIFT, typename Bin>
 __global__ __launch_bounds__(256) void k_select_hist(const float *__restrict__ key, const int32_t *__restrict__ drop,
-                                                     int D, int MS, const SelectState *__restrict__ st,
-                                                     long long *__restrict__ hist)
+                                                     const int32_t *__restrict__ drop0, int D, int MS, long long need,
+                                                     int which, SelectWork *__restrict__ work, Bin *__restrict__ last,
+                                                     Bin *__restrict__ counts)
 {
-    __shared__ long long lh[SEL_BINS];
-    if (st->reachable == 0) return;
-    const uint32_t prefix = st->prefix;
-    for (int q = threadIdx.x; q < SEL_BINS; q += 256) lh[q] = 0;
-    __syncthreads();
-    const size_t total = (size_t)D * MS;
-    for (size_t e0 = ((size_t)blockIdx.x * 256 + threadIdx.x) * SEL_RUN; e0 < total; e0 += (size_t)gridDim.x * 256 * SEL_RUN) {
-        uint32_t kb[SEL_RUN];
+    constexpr bool FIRST = LAST_SHIFT < 0;
+    __shared__ Bin lh[SEL_BINS];
+    __shared__ long long red[4];
+    __shared__ SelectState now;
+    __shared__ uint32_t arrived;
+    const int tid = threadIdx.x;
+    int blocks = gridDim.x;
+    if (FIRST) {
+        --blocks;
+        if ((int)blockIdx.x == blocks) {
+            long long c0 = 0;
+            constexpr int AHEAD = 16;
+            for (int i0 = tid; i0 < D; i0 += 256 * AHEAD) {
+                int32_t v[AHEAD];
 #pragma unroll
-        for (int q = 0; q < SEL_RUN; ++q) kb[q] = e0 + q < total ? __float_as_uint(key[e0 + q]) : ~0u;
-        int i = (int)(e0 / MS), j = (int)(e0 % MS);
+                for (int q = 0; q < AHEAD; ++q) v[q] = i0 + q * 256 < D ? drop0[i0 + q * 256] : 0;
+#pragma unroll
+                for (int q = 0; q < AHEAD; ++q) c0 += v[q];
+            }
+            c0 = block_sum_i64(c0, red);
+            last[tid] = 0;                      // the buffer of the second digit
+            if (tid == 0) {
+                SelectState st;
+                st.c0 = c0;
+                st.missing = need - c0;
+                st.prefix = 0u;
+                st.reachable = c0 < need ? 1 : 0;
+                st.at_start = c0 < need ? 0 : 1;
+                work->state[0] = st;
+            }
+            return;
+        }
+    }
+    const size_t total = (size_t)D * MS, stride = (size_t)blocks * 256 * SEL_RUN;
+    size_t e0 = ((size_t)blockIdx.x * 256 + tid) * SEL_RUN;
+    uint32_t kb[SEL_RUN];
+    auto request = [&](size_t e) {
+#pragma unroll
+        for (int q = 0; q < SEL_RUN; ++q) kb[q] = e + q < total ? __float_as_uint(key[e + q]) : ~0u;
+    };
+    request(e0);                                // on their way while the digit before is worked out
+    lh[tid] = 0;
+    if (!FIRST && tid < 64) {
+        const SelectState st = select_pick<Bin>(work->state[which], last, LAST_SHIFT);
+        if (tid == 0) {
+            now = st;
+            if (blockIdx.x == 0) work->state[which + 1] = st;
+        }
+    }
+    __syncthreads();
+    const uint32_t prefix = FIRST ? 0u : now.prefix;
+    if (!FIRST && now.reachable == 0) return;   // in every block
+    uint32_t order = 0u;
+    if (!FIRST && tid == 0) order = atomicAdd(&work->readers, 1u);
+    int i0 = (int)(e0 / MS), j0 = (int)(e0 % MS);                     // neuron and step of e0
+    const int di0 = (int)(stride / MS), dj0 = (int)(stride % MS);
+    while (e0 < total) {
+        int i = i0, j = j0;
         long long gain = 0;
         int digit = -1;
 #pragma unroll
@@ -433,7 +529,7 @@ __global__ __launch_bounds__(256) void k_select_hist(const float *__restrict__ k
                 !(SHIFT + BITS < 31 && (kb[q] >> (SHIFT + BITS)) != (prefix >> (SHIFT + BITS)))) {
                 const int dg = (int)((kb[q] >> SHIFT) & ((1u << BITS) - 1u));
                 if (dg != digit) {
-                    if (gain != 0) atomicAdd(reinterpret_cast<unsigned long long *>(&lh[digit]), (unsigned long long)gain);
+                    if (gain != 0) select_add(&lh[digit], gain);
                     gain = 0;
                     digit = dg;
                 }
@@ -445,54 +541,31 @@ __global__ __launch_bounds__(256) void k_select_hist(const float *__restrict__ k
                 ++i;
             }
         }
-        if (gain != 0) atomicAdd(reinterpret_cast<unsigned long long *>(&lh[digit]), (unsigned long long)gain);
+        if (gain != 0) select_add(&lh[digit], gain);
+        e0 += stride;
+        i0 += di0;
+        j0 += dj0;
+        if (j0 >= MS) {
+            j0 -= MS;
+            ++i0;
+        }
+        if (e0 < total) request(e0);
     }
+    if (!FIRST && tid == 0) arrived = order;
     __syncthreads();
-    for (int q = threadIdx.x; q < SEL_BINS; q += 256)
-        if (lh[q] != 0) atomicAdd(reinterpret_cast<unsigned long long *>(&hist[q]), (unsigned long long)lh[q]);
+    if (lh[tid] != 0) select_add(&counts[tid], (long long)lh[tid]);
+    if (!FIRST && arrived == (uint32_t)blocks - 1u) {                 // every block has read `last`
+        last[tid] = 0;
+        if (tid == 0) work->readers = 0u;
+    }
 }
 
-// Picks the digit, updates the state and clears the histogram for the next digit.  One wave:
-// lane l owns bins 4l .. 4l+3, a shuffle scan gives the running sums.
-template <int SHIFT, bool FIRST>
-__global__ __launch_bounds__(64) void k_select_pick(SelectState *__restrict__ st, long long *__restrict__ hist)
+// The last digit.  One wave.
+template <typename Bin>
+__global__ __launch_bounds__(64) void k_select_last(SelectWork *__restrict__ work, const Bin *__restrict__ counts)
 {
-    const int lane = threadIdx.x;
-    long long h[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        h[q] = hist[4 * lane + q];
-        hist[4 * lane + q] = 0;
-    }
-    if (st->reachable == 0) return;
-    const long long missing = st->missing;
-    const long long mine = h[0] + h[1] + h[2] + h[3];
-    long long inc = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const long long o = __shfl_up(inc, off);
-        if (lane >= off) inc += o;
-    }
-    const long long before = inc - mine;
-    const bool here = before < missing && inc >= missing;           // at most one lane
-    const unsigned long long who = __ballot(here);
-    if (who == 0ull) {
-        if (lane == 0) st->reachable = 0;       // only on the first digit: every finite step together falls short
-        return;
-    }
-    if (here) {
-        long long run = before;
-        int digit = 0;
-        for (int q = 0; q < 4; ++q) {
-            if (run + h[q] >= missing) {
-                digit = 4 * lane + q;
-                break;
-            }
-            run += h[q];
-        }
-        st->missing = missing - run;            // still to be found among the steps with this digit
-        st->prefix |= (uint32_t)digit << SHIFT;
-    }
+    const SelectState st = select_pick<Bin>(work->state[SEL_STATES - 2], counts, 0);
+    if (threadIdx.x == 0) work->state[SEL_STATES - 1] = st;
 }
 
 // With the level known, per neuron: the number of its steps strictly below the level and up to it, and (reachable target)

@@ -342,3 +342,15 @@ def test_offline_build_then_decode(env, oracle):
     assert all(0.05 < v < 0.30 for v in dens.values()), dens                       # near 1 - level on held-out tokens
     assert lost["whitened"] < lost["plain"], lost                                  # Sec. 4.1: whitening helps on correlated data
     assert outs["whitened"] < outs["plain"] and outs["whitened"] < 0.5, outs
+
+
+@pytest.mark.parametrize("D,T,eta", [(511, 64, 3), (512, 64, 3), (513, 40, 1), (640, 8, 8), (2049, 24, 2)])
+def test_both_widths_of_the_level_counters(env, D, T, eta):
+    """The selection's counts are 32 bits wide below 512 neurons and 64 from there on; several calls in a row on one
+    allocation, with targets met at the start, inside and beyond the last step."""
+    binding, torch, calib = env
+    rng = np.random.default_rng(D + T)
+    w, s = _stats(rng, D, T, dead=(1,))
+    for sp in (1.0, 0.0, 0.8, 0.5, 0.99):
+        _check(env, w, s, eta, binding.calib_need(sp, D, T))
+    _check(env, w, s, eta, D * T + 1)
