@@ -62,19 +62,21 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t u)
 // threads: 535), scores on a grid of quarters 376 (521), one score value 752 (732).
 // Measured at D = 11008, T = 2048, eta = 16: network 450 us, buckets 131 us (512 threads, 64-bit reductions), 117 us with
 // the sorted tail in the keys' place (four blocks a compute unit instead of three), 91 us with 256 threads, reductions on
-// the scores alone and the ranks taken by tail position (660 -> 370 vector instructions a wave, half the waves).
+// the scores alone and the ranks taken by tail position (660 -> 370 vector instructions a wave, half the waves); with 512
+// instead of 1024 buckets and a bucket's count and place in one word, so that eight blocks share a compute unit instead of
+// six, from memory instead of the cache 101 -> 92 us (D = 18944, T = 4096, eta = 1, whole call: 2915 -> 2144).
 // Scores and weights are read once and stay in registers, PER of each per thread (T <= PER * CAL_THREADS).
 // Dynamic LDS: calib_sort_lds().
 constexpr int CAL_BUCKET_MAX = 32;
 template <int PER>
-constexpr int cal_buckets() { return PER <= 8 ? 1024 : 2048; }
+constexpr int cal_buckets() { return PER <= 8 ? 512 : 1024; }
 
 // sort keys (n2 = T rounded up to a power of two), later the sorted tail (s, w) in their place; costs and their running
-// maxima; buckets.  26 KB at T = 2048, eta = 16: six blocks a compute unit.
+// maxima; buckets.  19.5 KB at T = 2048, eta = 16: eight blocks a compute unit, as many as it has wave slots for.
 template <int PER>
 size_t calib_sort_lds(int n2, int MS)
 {
-    return (size_t)n2 * 8 + (size_t)(MS + 1) * 8 + (size_t)cal_buckets<PER>() * 8;
+    return (size_t)n2 * 8 + (size_t)(MS + 1) * 8 + (size_t)cal_buckets<PER>() * 4;
 }
 
 template <int PER>
@@ -93,8 +95,8 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
     float *ww = ss + n2max;                                        // [n2max] weights in that order
     float *cost = ww + n2max;                                      // [MS + 1]
     float *scan = cost + (MS + 1);                                 // [MS + 1]
-    uint32_t *hist = reinterpret_cast<uint32_t *>(scan + (MS + 1));        // [NBK] samples of a bucket
-    uint32_t *start = hist + NBK;                                  // [NBK] samples in front of it
+    // [NBK] samples of a bucket, and from the scan on, in the upper half, samples in front of it (T <= CAL_MAX_T < 2^16)
+    uint32_t *bucket = reinterpret_cast<uint32_t *>(scan + (MS + 1));
     __shared__ float lo_w[WAVES], hi_w[WAVES];
     __shared__ int wave_tot[WAVES], first_sh, big_sh, kd_total;
     __shared__ unsigned long long last_sh;
@@ -117,7 +119,7 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
         last_sh = 0ull;
     }
 #pragma unroll
-    for (int q = 0; q < BPT; ++q) hist[tid + q * CAL_THREADS] = 0u;
+    for (int q = 0; q < BPT; ++q) bucket[tid + q * CAL_THREADS] = 0u;
     // the smallest score with a positive weight (+inf if there is none), the largest score
     float s_lo = __builtin_inff(), s_hi = -__builtin_inff();
     bool some = false;
@@ -156,7 +158,7 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
     for (int q = 0; q < PER; ++q) {
         const int t = tid + q * CAL_THREADS;
         pos[q] = -1;
-        if (any && t < T && (sv[q] > s_lo || (sv[q] == s_lo && t >= first))) pos[q] = (int)atomicAdd(&hist[bucket_of(sv[q])], 1u);
+        if (any && t < T && (sv[q] > s_lo || (sv[q] == s_lo && t >= first))) pos[q] = (int)atomicAdd(&bucket[bucket_of(sv[q])], 1u);
     }
     __syncthreads();
     int ntail = 0;
@@ -165,7 +167,7 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
         int sum = 0;
 #pragma unroll
         for (int q = 0; q < BPT; ++q) {
-            h[q] = hist[tid * BPT + q];
+            h[q] = bucket[tid * BPT + q];
             most = h[q] > most ? h[q] : most;
             sum += (int)h[q];
         }
@@ -186,7 +188,7 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
         }
 #pragma unroll
         for (int q = 0; q < BPT; ++q) {
-            start[tid * BPT + q] = (uint32_t)before;
+            bucket[tid * BPT + q] = ((uint32_t)before << 16) | h[q];
             before += (int)h[q];
         }
     }
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < PER; ++q)
-        if (pos[q] >= 0) sk[start[bucket_of(sv[q])] + pos[q]] = key_of(sv[q], tid + q * CAL_THREADS);
+        if (pos[q] >= 0) sk[(bucket[bucket_of(sv[q])] >> 16) + pos[q]] = key_of(sv[q], tid + q * CAL_THREADS);
     __syncthreads();
     if (big_sh != 0) {
         int n2 = 1;
@@ -231,7 +233,8 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
             sv[q] = si[t];                                         // not from the key: -0 keeps its sign
             pos[q] = p;
             if (big_sh == 0) {
-                const int b = bucket_of(from_ordered_bits((uint32_t)(k >> 32))), b0 = (int)start[b], b1 = b0 + (int)hist[b];
+                const uint32_t bk = bucket[bucket_of(from_ordered_bits((uint32_t)(k >> 32)))];
+                const int b0 = (int)(bk >> 16), b1 = b0 + (int)(bk & 0xffffu);
                 int rank = b0;
                 for (int e = b0; e < b1; ++e) rank += sk[e] < k ? 1 : 0;
                 pos[q] = rank;
