@@ -815,8 +815,6 @@ svdp_status svdp_calib_stats(const svdp_layer *layer, const void *X, int32_t T, 
     auto tiles = [](int n, int b) { return (n + b - 1) / b; };
 
     if (!grant_lds<k_gemm_wide>(GW_LDS)) return SVDP_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(k_row_norm2, dim3(tiles(D, 4)), dim3(256), 0, st, static_cast<const bf16 *>(layer->W_downT), D, d,
-                       cn);
     hipLaunchKernelGGL(k_transpose16, dim3(tiles(r, 32), tiles(d, 32)), dim3(256), 0, st,
                        static_cast<const uint16_t *>(layer->P), d, r, reinterpret_cast<uint16_t *>(Pt));
     // t = X P, split into three terms.  Its tiles alone are few (32 at r = 256, T = 2048: 90 us on an eighth of the chip,
@@ -825,13 +823,15 @@ svdp_status svdp_calib_stats(const svdp_layer *layer, const void *X, int32_t T, 
     const int t_tiles = tiles(r, GM_BN) * tiles(T, GM_BM);
     const int parts = std::max(1, std::min({256 / t_tiles, d / 256, D / r, 16}));
     const int kpart = round_up(tiles(d, parts), GM_BK), nz = tiles(d, kpart);
+    const NormJob norm{static_cast<const bf16 *>(layer->W_downT), D, d, cn};
+    const int nx = tiles(r, GM_BN), ny = tiles(T, GM_BM), norm_blocks = tiles(D, NORM_ROWS);
     if (nz > 1) {
-        hipLaunchKernelGGL((k_gemm_nt<EPI_PLAIN>), dim3(tiles(r, GM_BN), tiles(T, GM_BM), nz), dim3(GM_THREADS), 0, st, Xb,
-                           d, Pt, d, T, r, d, s, nullptr, r, kpart);
+        hipLaunchKernelGGL((k_gemm_nt<EPI_PLAIN>), dim3(nx * ny * nz + norm_blocks), dim3(GM_THREADS), 0, st, Xb, d, Pt, d, T, r, d,
+                           s, nullptr, r, kpart, nx, ny, nz, norm);
         hipLaunchKernelGGL(k_sum_split3, dim3(tiles(T * r, 256)), dim3(256), 0, st, s, nz, T, r, tp);
     } else {
-        hipLaunchKernelGGL((k_gemm_nt<EPI_SPLIT3>), dim3(tiles(r, GM_BN), tiles(T, GM_BM)), dim3(GM_THREADS), 0, st, Xb,
-                           d, Pt, d, T, r, d, nullptr, tp, 3 * r, d);
+        hipLaunchKernelGGL((k_gemm_nt<EPI_SPLIT3>), dim3(nx * ny + norm_blocks), dim3(GM_THREADS), 0, st, Xb, d, Pt, d, T, r, d,
+                           nullptr, tp, 3 * r, d, nx, ny, 1, norm);
     }
     // w = (ReLU(W_gate X^T) * (W_up X^T))^2 * cn and s = Q t^T over the three terms
     const bf16 *Qb = static_cast<const bf16 *>(layer->Q), *tb = reinterpret_cast<const bf16 *>(tp);
