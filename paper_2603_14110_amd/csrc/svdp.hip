@@ -20,6 +20,7 @@
 #include <functional>
 #include <mutex>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 namespace {
@@ -95,6 +96,19 @@ Workspace carve(void *base, int d, int D, int r, int NB)
     off += align_up((size_t)ROWS_BLOCKS * NB * d * 4);
     w.bytes = off;
     return w;
+}
+
+// Enqueues a kernel.  Straight to hipLaunchKernel: the <<<>>> form goes through a push and a pop of the launch
+// configuration besides (2.4 -> 2.25 us a launch of twenty arguments), and launches are what bounds small calls: a list of two
+// rows 9.7 -> 8.5 us, the step of d = 256, D = 1024 12.7 -> 11.6.  A refused launch is the last error, which
+// hip_status() reports.
+template <typename... P, typename... A>
+inline void launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t st, A &&...args)
+{
+    [&](P... p) {
+        void *at[] = {const_cast<void *>(static_cast<const void *>(&p))...};
+        (void)hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, at, lds, st);
+    }(std::forward<A>(args)...);
 }
 
 inline svdp_status hip_status(hipError_t e)
@@ -294,11 +308,11 @@ svdp_status launch_xP(const svdp_layer *L, const void *x, int B, float *tpart, i
     const int ncs = (r + XP_COLS - 1) / XP_COLS;
     const size_t lds = xp_lds<W, NB>(L);
     if (glue != nullptr) {
-        hipLaunchKernelGGL((k_xP<W, NB, true>), dim3(nt, ncs), dim3(XP_THREADS), lds, st, static_cast<const W *>(L->P),
+        launch((k_xP<W, NB, true>), dim3(nt, ncs), dim3(XP_THREADS), lds, st, static_cast<const W *>(L->P),
                            static_cast<const W *>(x), B, d, r, tpart, glue->y_prev, glue->shift, glue->eps,
                            static_cast<W *>(glue->x_out));
     } else {
-        hipLaunchKernelGGL((k_xP<W, NB, false>), dim3(nt, ncs), dim3(XP_THREADS), lds, st,
+        launch((k_xP<W, NB, false>), dim3(nt, ncs), dim3(XP_THREADS), lds, st,
                            static_cast<const W *>(L->P), static_cast<const W *>(x), B, d, r, tpart, nullptr, nullptr,
                            0.f, nullptr);
     }
@@ -340,14 +354,14 @@ svdp_status launch_scores(const svdp_layer *L, const float *tpart, int nt, int B
 {
     const size_t lds = scores_lds<W, NB>(L);
     if (scores_on_matrix<W, NB>(L)) {
-        hipLaunchKernelGGL((k_scores_mfma<W, NB>), dim3(L->D / SC_SLAB), dim3(SCM_THREADS), lds, st,
+        launch((k_scores_mfma<W, NB>), dim3(L->D / SC_SLAB), dim3(SCM_THREADS), lds, st,
                            static_cast<const W *>(L->Q), L->b, tpart, nt, B, L->D, L->r, s_out, mask_out);
         return hip_status(hipSuccess);
     }
     // block size: 512 threads for one or two tokens (short critical path), 256 for larger batches
     // (fewer wavefronts repeating the per-wave overhead); measured on the 7B and Mistral shapes
     with_scores_kernel<W, NB>(L, [&](auto k) {
-        hipLaunchKernelGGL(decltype(k)::value, dim3(L->D / SC_SLAB), dim3(scores_threads<NB>()), lds, st,
+        launch(decltype(k)::value, dim3(L->D / SC_SLAB), dim3(scores_threads<NB>()), lds, st,
                            static_cast<const W *>(L->Q), L->b, tpart, nt, B, L->D, L->r, s_out, mask_out);
         return 0;
     });
@@ -384,27 +398,27 @@ svdp_status launch_rows(const svdp_layer *L, const void *x, int B, const uint64_
             char *region = reinterpret_cast<char *>(w.ypart);
             float *hbuf = reinterpret_cast<float *>(region + split_h_offset(d, NB));
             int32_t *lst = reinterpret_cast<int32_t *>(region + split_list_offset(d, D, NB));
-            hipLaunchKernelGGL((k_gate_up_mfma<NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, xs, B,
+            launch((k_gate_up_mfma<NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, xs, B,
                                d, D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags,
                                hbuf, lst);
-            hipLaunchKernelGGL((k_down_slices<NB, MODE == ROWS_DENSE>), dim3(d / DS_SW, DOWN_RG), dim3(DS_THREADS), 0, st,
+            launch((k_down_slices<NB, MODE == ROWS_DENSE>), dim3(d / DS_SW, DOWN_RG), dim3(DS_THREADS), 0, st,
                                Wd, lst, MODE == ROWS_DENSE ? nullptr : w.nnz, D, D, d, hbuf, DOWN_MIN_CHUNK, w.ypart);
         }
     }
     if (matrix) {
         // launched above
     } else if (p.kind == ROWS_SEQ) {
-        hipLaunchKernelGGL((k_rows_seq<W, NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, Wd, xs, B,
+        launch((k_rows_seq<W, NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, Wd, xs, B,
                            d, D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags,
                            w.ypart);
     } else {
-        hipLaunchKernelGGL((k_rows<W, NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, Wd, xs, B, d,
+        launch((k_rows<W, NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, Wd, xs, B, d,
                            D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags, w.ypart);
     }
     if (y != nullptr) {
         const int vpt = d / 4;
         const int blocks = B * ((vpt + RED_COLS - 1) / RED_COLS);
-        hipLaunchKernelGGL(k_reduce_y, dim3(blocks), dim3(RED_COLS * RED_SEGS), 0, st, w.ypart,
+        launch(k_reduce_y, dim3(blocks), dim3(RED_COLS * RED_SEGS), 0, st, w.ypart,
                            MODE == ROWS_DENSE ? nullptr : w.nnz, D, D, p.split ? DOWN_RG : ROWS_BLOCKS,
                            p.split ? DOWN_MIN_CHUNK : p.min_chunk, NB, B, d, y);
     }
@@ -431,7 +445,7 @@ template <typename W>
 svdp_status launch_predict_small(const svdp_layer *L, const void *x, float *s, uint64_t *mask, hipStream_t st)
 {
     auto go = [&](auto lpr) {
-        hipLaunchKernelGGL((k_predict_small<W, decltype(lpr)::value>), dim3(L->D / SC_SLAB), dim3(PS_THREADS),
+        launch((k_predict_small<W, decltype(lpr)::value>), dim3(L->D / SC_SLAB), dim3(PS_THREADS),
                            ps_lds<W>(L->d, L->r), st, static_cast<const W *>(L->P), static_cast<const W *>(L->Q), L->b,
                            static_cast<const W *>(x), L->d, L->r, s, mask);
         return hip_status(hipSuccess);
@@ -454,7 +468,7 @@ svdp_status run_predict(const svdp_layer *L, const void *x, int B, float *s, uin
     if (tsum_needed<W, NB>(L)) {
         const int count = NB * L->r;
         float *t = w.tpart + (size_t)XP_MAX_BLOCKS * NB * L->r;
-        hipLaunchKernelGGL(k_tsum, dim3((count + 255) / 256), dim3(256), 0, st, w.tpart, nt, count, t);
+        launch(k_tsum, dim3((count + 255) / 256), dim3(256), 0, st, w.tpart, nt, count, t);
         e = hip_status(hipSuccess);
         if (e != SVDP_OK) return e;
         return launch_scores<W, NB>(L, t, 1, B, s, mask, st);
@@ -551,10 +565,10 @@ svdp_status svdp_compact(const float *s, int32_t B, int32_t D, uint64_t *mask, i
     if (s == nullptr || mask == nullptr || idx == nullptr || nnz == nullptr || bad_batch(B) || D <= 0) return SVDP_ERR_INVALID_ARG;
     if (D % 64 != 0) return SVDP_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(k_mask_from_scores, dim3((D / 64 + 3) / 4), dim3(256), 0, st, s, B, D, mask);
+    launch(k_mask_from_scores, dim3((D / 64 + 3) / 4), dim3(256), 0, st, s, B, D, mask);
     const svdp_status e = hip_status(hipSuccess);
     if (e != SVDP_OK) return e;
-    hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(SCAN_THREADS), 0, st, mask, D / 64, idx, nnz);
+    launch(k_compact_scan, dim3(1), dim3(SCAN_THREADS), 0, st, mask, D / 64, idx, nnz);
     return hip_status(hipSuccess);
 }
 
@@ -671,10 +685,10 @@ svdp_status svdp_stack_glue(const void *x, const float *y, const float *shift, i
     if (!aligned16(x) || !aligned16(y) || !aligned16(shift) || !aligned16(x_next)) return SVDP_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (dtype == SVDP_F32)
-        hipLaunchKernelGGL(k_stack_glue<float>, dim3(1), dim3(256), 0, st, static_cast<const float *>(x), y, shift,
+        launch(k_stack_glue<float>, dim3(1), dim3(256), 0, st, static_cast<const float *>(x), y, shift,
                            d, eps, static_cast<float *>(x_next));
     else
-        hipLaunchKernelGGL(k_stack_glue<bf16>, dim3(1), dim3(256), 0, st, static_cast<const bf16 *>(x), y, shift, d,
+        launch(k_stack_glue<bf16>, dim3(1), dim3(256), 0, st, static_cast<const bf16 *>(x), y, shift, d,
                            eps, static_cast<bf16 *>(x_next));
     return hip_status(hipSuccess);
 }
@@ -745,7 +759,7 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
         constexpr int PER = decltype(per)::value;
         const size_t lds = calib_sort_lds<PER>(n2, MS);
         if (!grant_lds<k_calib_sort<PER>>(lds)) return SVDP_ERR_UNSUPPORTED;
-        hipLaunchKernelGGL(k_calib_sort<PER>, dim3(D), dim3(CAL_THREADS), lds, st, w, s, T, n2, eta, MS, key, drop, tauc, k0,
+        launch(k_calib_sort<PER>, dim3(D), dim3(CAL_THREADS), lds, st, w, s, T, n2, eta, MS, key, drop, tauc, k0,
                            lo, kendall, reinterpret_cast<uint32_t *>(hist), SEL_BINS * 2, &work->readers, steps);
         return hip_status(hipSuccess);
     };
@@ -760,15 +774,15 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
     // (D T < 512 * 4096) fit 32 bits, and both lie in `hist`.
     auto select = [&](auto *first, auto *second) {
         using Bin = std::remove_pointer_t<decltype(first)>;
-        hipLaunchKernelGGL((k_select_hist<23, 8, -1, Bin>), dim3(hb + 1), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 0,
+        launch((k_select_hist<23, 8, -1, Bin>), dim3(hb + 1), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 0,
                            work, second, first);
-        hipLaunchKernelGGL((k_select_hist<15, 8, 23, Bin>), dim3(hb), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 0, work,
+        launch((k_select_hist<15, 8, 23, Bin>), dim3(hb), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 0, work,
                            first, second);
-        hipLaunchKernelGGL((k_select_hist<7, 8, 15, Bin>), dim3(hb), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 1, work,
+        launch((k_select_hist<7, 8, 15, Bin>), dim3(hb), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 1, work,
                            second, first);
-        hipLaunchKernelGGL((k_select_hist<0, 7, 7, Bin>), dim3(hb), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 2, work,
+        launch((k_select_hist<0, 7, 7, Bin>), dim3(hb), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 2, work,
                            first, second);
-        hipLaunchKernelGGL(k_select_last<Bin>, dim3(1), dim3(64), 0, st, work, second);
+        launch(k_select_last<Bin>, dim3(1), dim3(64), 0, st, work, second);
     };
     static_assert(CAL_MAX_T <= 4096 && SEL_BINS * 8 <= 512 * 4, "see above");
     if (D >= 512) {
@@ -780,8 +794,8 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
     const SelectState *state = &work->state[SEL_STATES - 1];
     // the digit counts are done with: their place holds the blocks' gains, so there are at most SEL_BINS blocks
     const int chunk = (int)(((long long)D + 256 * SEL_BINS - 1) / (256 * SEL_BINS)) * 256, blocks = (D + chunk - 1) / chunk;
-    hipLaunchKernelGGL(k_select_bounds, dim3(blocks), dim3(256), 0, st, key, drop, D, MS, chunk, state, lo, up, hist);
-    hipLaunchKernelGGL(k_select_finish, dim3(blocks), dim3(256), 0, st, lo, up, drop, tauc, k0, D, T, eta, MS, chunk, state, hist,
+    launch(k_select_bounds, dim3(blocks), dim3(256), 0, st, key, drop, D, MS, chunk, state, lo, up, hist);
+    launch(k_select_finish, dim3(blocks), dim3(256), 0, st, lo, up, drop, tauc, k0, D, T, eta, MS, chunk, state, hist,
                        b, k, steps);
     return hip_status(hipSuccess);
 }
@@ -815,7 +829,7 @@ svdp_status svdp_calib_stats(const svdp_layer *layer, const void *X, int32_t T, 
     auto tiles = [](int n, int b) { return (n + b - 1) / b; };
 
     if (!grant_lds<k_gemm_wide>(GW_LDS)) return SVDP_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(k_transpose16, dim3(tiles(r, 32), tiles(d, 32)), dim3(256), 0, st,
+    launch(k_transpose16, dim3(tiles(r, 32), tiles(d, 32)), dim3(256), 0, st,
                        static_cast<const uint16_t *>(layer->P), d, r, reinterpret_cast<uint16_t *>(Pt));
     // t = X P, split into three terms.  Its tiles alone are few (32 at r = 256, T = 2048: 90 us on an eighth of the chip,
     // 16 + 5 us in eight parts), so they are cut along K into as many parts as fill it; the parts meet in s, which the
@@ -826,18 +840,18 @@ svdp_status svdp_calib_stats(const svdp_layer *layer, const void *X, int32_t T, 
     const NormJob norm{static_cast<const bf16 *>(layer->W_downT), D, d, cn};
     const int nx = tiles(r, GM_BN), ny = tiles(T, GM_BM), norm_blocks = tiles(D, NORM_ROWS);
     if (nz > 1) {
-        hipLaunchKernelGGL((k_gemm_nt<EPI_PLAIN>), dim3(nx * ny * nz + norm_blocks), dim3(GM_THREADS), 0, st, Xb, d, Pt, d, T, r, d,
+        launch((k_gemm_nt<EPI_PLAIN>), dim3(nx * ny * nz + norm_blocks), dim3(GM_THREADS), 0, st, Xb, d, Pt, d, T, r, d,
                            s, nullptr, r, kpart, nx, ny, nz, norm);
-        hipLaunchKernelGGL(k_sum_split3, dim3(tiles(T * r, 256)), dim3(256), 0, st, s, nz, T, r, tp);
+        launch(k_sum_split3, dim3(tiles(T * r, 256)), dim3(256), 0, st, s, nz, T, r, tp);
     } else {
-        hipLaunchKernelGGL((k_gemm_nt<EPI_SPLIT3>), dim3(nx * ny + norm_blocks), dim3(GM_THREADS), 0, st, Xb, d, Pt, d, T, r, d,
+        launch((k_gemm_nt<EPI_SPLIT3>), dim3(nx * ny + norm_blocks), dim3(GM_THREADS), 0, st, Xb, d, Pt, d, T, r, d,
                            nullptr, tp, 3 * r, d, nx, ny, 1, norm);
     }
     // w = (ReLU(W_gate X^T) * (W_up X^T))^2 * cn and s = Q t^T over the three terms
     const bf16 *Qb = static_cast<const bf16 *>(layer->Q), *tb = reinterpret_cast<const bf16 *>(tp);
     const WideJob jw = wide_job(Wg, Wu, d, d, Xb, d, D, T, d, cn, w, T), js = wide_job(Qb, nullptr, r, r, tb, 3 * r, D, T, 3 * r,
                                                                                       nullptr, s, T);
-    hipLaunchKernelGGL(k_gemm_wide, dim3(jw.tiles + js.tiles), dim3(GW_THREADS), GW_LDS, st, jw, js);
+    launch(k_gemm_wide, dim3(jw.tiles + js.tiles), dim3(GW_THREADS), GW_LDS, st, jw, js);
     return hip_status(hipSuccess);
 }
 

@@ -86,10 +86,10 @@ struct EigTopWs {
 {
     bool ok = true;
     for (int p = 0; p < passes; ++p) {
-        hipLaunchKernelGGL(k_normalize_rows, dim3(k), dim3(256), 0, st, X, n);
+        launch(k_normalize_rows, dim3(k), dim3(256), 0, st, X, n);
         ok &= dgemm<DG_ROWS_K, DG_ROWS_K>(op((const double *)X, n), op((const double *)X, n), w.L, k, k, k, n, st,
                                           DG_LOWER | DG_MIRROR, DgEpilogue{}, w.scr);
-        if (p == 0) hipLaunchKernelGGL(k_add_diagonal, grid1(k), dim3(256), 0, st, w.L, k, EIG_SHIFT);
+        if (p == 0) launch(k_add_diagonal, grid1(k), dim3(256), 0, st, w.L, k, EIG_SHIFT);
         ok &= cholesky_blocked(w.L, k, w.invL, w.scale, w.fail, st);
         for (int c0 = 0; c0 < k; c0 += CH_B) {
             double *done = tmp + (size_t)c0 * n, *below = X + (size_t)(c0 + CH_B) * n;
@@ -145,7 +145,7 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
     std::vector<double> h(2 * (size_t)k + 2);
     bool ok = true;                                         // every product so far was enqueued
     double *X = w.X, *tmp = w.Xa;
-    hipLaunchKernelGGL(k_random_rows, grid1((size_t)k * n), dim3(256), 0, st, X, 0, k, n);
+    launch(k_random_rows, grid1((size_t)k * n), dim3(256), 0, st, X, 0, k, n);
     for (int p = 0; p < 3; ++p) {
         ok &= times_g(G, X, tmp, k, n, st, w.scr);
         std::swap(X, tmp);
@@ -171,11 +171,11 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
         if (e != SVDP_OK) return e;
         *sweeps = std::max(1, sw);
         spent += 3.0 * eig_product_us(ka, n) + eig_jacobi_us(ka, sw);
-        hipLaunchKernelGGL(k_rank_descending, grid1(ka), dim3(256), 0, st, w.lam, ka, w.sel, w.theta);
-        hipLaunchKernelGGL(k_gather_rows, grid1((size_t)ka * ka), dim3(256), 0, st, V, w.sel, ka, ka, w.Vs);
+        launch(k_rank_descending, grid1(ka), dim3(256), 0, st, w.lam, ka, w.sel, w.theta);
+        launch(k_gather_rows, grid1((size_t)ka * ka), dim3(256), 0, st, V, w.sel, ka, ka, w.Vs);
         ok &= dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.Vs, ka), op((const double *)X, n), Xr, n, ka, n, ka, st);
         ok &= dgemm<DG_ROWS_K, DG_K_ROWS>(op((const double *)w.Vs, ka), op((const double *)Y, n), Yr, n, ka, n, ka, st);
-        hipLaunchKernelGGL(k_ritz_residual, dim3(ka), dim3(256), 0, st, Xr, Yr, w.theta, n, w.res);
+        launch(k_ritz_residual, dim3(ka), dim3(256), 0, st, Xr, Yr, w.theta, n, w.res);
         if (!ok) return SVDP_ERR_UNSUPPORTED;
         double *theta = h.data(), *res = theta + k;
         int32_t failed = 0;
@@ -229,11 +229,11 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
                 return hip_failed();
             X = front;
             if (left < want)
-                hipLaunchKernelGGL(k_random_rows, grid1((size_t)(want - left) * n), dim3(256), 0, st, X, left, want - left, n);
+                launch(k_random_rows, grid1((size_t)(want - left) * n), dim3(256), 0, st, X, left, want - left, n);
             ka = want;
             tmp = Xr;
             for (int p = 0; p < 2; ++p) {
-                hipLaunchKernelGGL(k_normalize_rows, dim3(ka), dim3(256), 0, st, X, n);
+                launch(k_normalize_rows, dim3(ka), dim3(256), 0, st, X, n);
                 ok &= project_out(X, ka, n, Vr, l, w, st);
                 ok &= orthonormalize(X, tmp, ka, n, p + 1, w, st);
             }
@@ -254,7 +254,7 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             if (!first) {
                 ok &= times_g(Gc, X, cur, ka, n, st, w.scr);
                 if (!ok) return SVDP_ERR_UNSUPPORTED;
-                hipLaunchKernelGGL(k_rayleigh, dim3(ka), dim3(256), 0, st, X, cur, n, w.res);
+                launch(k_rayleigh, dim3(ka), dim3(256), 0, st, X, cur, n, w.res);
                 if (hipMemcpyAsync(res, w.res, (size_t)ka * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
                     hipStreamSynchronize(st) != hipSuccess)
                     return hip_failed();
@@ -283,7 +283,7 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
             ep.ld1 = n;
             ep.beta = -s1;
             if (first) ok &= times_g(Gc, prev, cur, ka, n, st, w.scr, ep);
-            else hipLaunchKernelGGL(k_combine, grid1((size_t)ka * n), dim3(256), 0, st, cur, prev, ep.alpha, ep.beta, (size_t)ka * n);
+            else launch(k_combine, grid1((size_t)ka * n), dim3(256), 0, st, cur, prev, ep.alpha, ep.beta, (size_t)ka * n);
             for (int i = 2; i <= piece; ++i) {
                 const double s2 = 1.0 / (2.0 / s0 - s1);
                 DgEpilogue e2;

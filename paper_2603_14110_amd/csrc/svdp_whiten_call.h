@@ -157,8 +157,8 @@ svdp_status whiten_impl(const void *W_gate, const void *X, int d, int D, int T, 
         e = jacobi_eigh(&A, &Aalt, &V, &Valt, d, w.Uall, w.rowsums, w.sums, w.lamG, 1e-11, 24, &sw2, st);
         if (e != SVDP_OK) return e;
         // the r largest eigenvalues (= squared singular values of W S), largest first; ties by place
-        hipLaunchKernelGGL(k_rank_descending, grid1(d), dim3(256), 0, st, w.lamG, d, w.sel, w.rowsums);
-        hipLaunchKernelGGL(k_gather_rows, grid1((size_t)r * d), dim3(256), 0, st, V, w.sel, r, d, w.Vr);
+        launch(k_rank_descending, grid1(d), dim3(256), 0, st, w.lamG, d, w.sel, w.rowsums);
+        launch(k_gather_rows, grid1((size_t)r * d), dim3(256), 0, st, V, w.sel, r, d, w.Vr);
         if (hipMemcpyAsync(lam.data(), w.rowsums, (size_t)r * 8, hipMemcpyDeviceToHost, st) != hipSuccess) {
             (void)hipGetLastError();
             return SVDP_ERR_HIP;
@@ -173,11 +173,11 @@ svdp_status whiten_impl(const void *W_gate, const void *X, int d, int D, int T, 
                                      DgEpilogue{}, scr) &&
          dgemm<DG_ROWS_K, DG_ROWS_K>(op(Wg, d), op((const double *)w.Zr, d), w.out64, r, D, r, d, st, 0, DgEpilogue{}, scr);
     if (!ok) return refused();
-    hipLaunchKernelGGL(k_f64_to_f32, grid1((size_t)D * r), dim3(256), 0, st, w.out64, (size_t)D * r, Q);
+    launch(k_f64_to_f32, grid1((size_t)D * r), dim3(256), 0, st, w.out64, (size_t)D * r, Q);
     // B = V_r^T S^-1 (block back-substitution; V_r^T is w.Vr, rows = the chosen eigenvectors), P = B^T
     if (!solve_right_lower(w.Vr, w.out64, r, d, w.S, w.invL, st)) return refused();
-    hipLaunchKernelGGL((k_transpose_to_f64<double>), dim3((d + 31) / 32, (r + 31) / 32), dim3(256), 0, st, w.out64, r, d, w.Vr);
-    hipLaunchKernelGGL(k_f64_to_f32, grid1((size_t)d * r), dim3(256), 0, st, w.Vr, (size_t)d * r, P);
+    launch((k_transpose_to_f64<double>), dim3((d + 31) / 32, (r + 31) / 32), dim3(256), 0, st, w.out64, r, d, w.Vr);
+    launch(k_f64_to_f32, grid1((size_t)d * r), dim3(256), 0, st, w.Vr, (size_t)d * r, P);
     if (hipStreamSynchronize(st) != hipSuccess) {                 // the copies into lam must be done
         (void)hipGetLastError();
         return SVDP_ERR_HIP;

@@ -35,11 +35,11 @@ template <typename TA, DgLayout LA, typename TB, DgLayout LB, int WM, int WN, in
     const dim3 grid = (flags & DG_LOWER) ? dim3(tm * (tm + 1) / 2, 1, nz)
                                          : (flags & DG_K_FROM_N) ? dim3(tm, tn, nz) : dim3(tn, tm, nz);
     if (nz > 1) {
-        hipLaunchKernelGGL(kernel, grid, dim3(DG_THREADS), lds, st, A.p, A.ld, B.p, B.ld, scr.p, N, M, N, K, kpart, flags,
+        launch(kernel, grid, dim3(DG_THREADS), lds, st, A.p, A.ld, B.p, B.ld, scr.p, N, M, N, K, kpart, flags,
                            DgEpilogue{});
-        hipLaunchKernelGGL(k_dgemm_sum, grid1((size_t)M * N), dim3(256), 0, st, scr.p, nz, C, ldc, M, N, flags, ep);
+        launch(k_dgemm_sum, grid1((size_t)M * N), dim3(256), 0, st, scr.p, nz, C, ldc, M, N, flags, ep);
     } else {
-        hipLaunchKernelGGL(kernel, grid, dim3(DG_THREADS), lds, st, A.p, A.ld, B.p, B.ld, C, ldc, M, N, K, kpart, flags, ep);
+        launch(kernel, grid, dim3(DG_THREADS), lds, st, A.p, A.ld, B.p, B.ld, C, ldc, M, N, K, kpart, flags, ep);
     }
     return true;
 }
@@ -106,12 +106,12 @@ inline DgEpilogue minus_from(const double *Cin, int ld)
 [[nodiscard]] bool cholesky_blocked(double *A, int n, double *invL, double *scale, int *fail, hipStream_t st)
 {
     bool ok = true;
-    hipLaunchKernelGGL(k_max_diag, dim3(1), dim3(256), 0, st, A, n, scale);
+    launch(k_max_diag, dim3(1), dim3(256), 0, st, A, n, scale);
     for (int k = 0; k < n; k += CH_B) {
         const int p1 = std::min(n, k / CH_PANEL * CH_PANEL + CH_PANEL);       // end of the panel
         const int k1 = k + CH_B, rest = n - k1;
         double *inv = invL + (size_t)k * CH_B;
-        hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, A, n, (size_t)k * n + k, scale, 1e-13, inv, fail);
+        launch(k_chol_diag, dim3(1), dim3(256), 0, st, A, n, (size_t)k * n + k, scale, 1e-13, inv, fail);
         const double *below = A + (size_t)k1 * n + k;
         // in place: a block of the product covers all 64 columns of its rows
         ok &= dgemm<DG_ROWS_K, DG_ROWS_K>(op(below, n), op((const double *)inv, CH_B), A + (size_t)k1 * n + k, n, rest, CH_B,
@@ -124,7 +124,7 @@ inline DgEpilogue minus_from(const double *Cin, int ld)
                                               minus_from(upd, n));
         }
     }
-    hipLaunchKernelGGL(k_zero_upper_blocks, grid1((size_t)n * n), dim3(256), 0, st, A, n);
+    launch(k_zero_upper_blocks, grid1((size_t)n * n), dim3(256), 0, st, A, n);
     return ok;
 }
 
@@ -154,14 +154,14 @@ svdp_status jacobi_eigh(double **A, double **Aalt, double **V, double **Valt, in
     if (!grant_lds<k_bjacobi_solve<false>>(lds_solve) || !grant_lds<k_bjacobi_solve<true>>(lds_solve) ||
         !grant_lds<k_bjacobi_apply>(lds_apply))
         return SVDP_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(k_identity, grid1((size_t)n * n), dim3(256), 0, st, *V, n);
+    launch(k_identity, grid1((size_t)n * n), dim3(256), 0, st, *V, n);
     const int strips = n / BJ_S, rounds = n / BJ_B > 2 ? n / BJ_B - 1 : 1;
     const int ct = strips >= 32 ? 4 : 1, cgrid = (strips + ct - 1) / ct;      // column tiles per block
     double previous = 1e300;
     int sweep = 0;
     for (;; ++sweep) {
-        hipLaunchKernelGGL(k_jacobi_norms, dim3(n), dim3(256), 0, st, *A, n, rowsums);
-        hipLaunchKernelGGL(k_jacobi_norms_finish, dim3(1), dim3(256), 0, st, rowsums, n, *A, sums, lam);
+        launch(k_jacobi_norms, dim3(n), dim3(256), 0, st, *A, n, rowsums);
+        launch(k_jacobi_norms_finish, dim3(1), dim3(256), 0, st, rowsums, n, *A, sums, lam);
         double h[2] = {0.0, 0.0};
         if (hipMemcpyAsync(h, sums, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess) {
@@ -180,10 +180,10 @@ svdp_status jacobi_eigh(double **A, double **Aalt, double **V, double **Valt, in
             // 53.3 / 48.9, d = 4096, r = 256 42.5 / 40.3, d = 1024, r = 64 4.2 / 3.1; without the first sweep at d = 320,
             // r = 80 4.4 / 4.5, with it 4.35.
             if (round == 0 || (sweep == 0 && rounds <= 5))
-                hipLaunchKernelGGL(k_bjacobi_solve<false>, dim3(strips, BJ_U_PARTS), dim3(BJ_SOLVE_THREADS), lds_solve, st, *A, n, Uall);
+                launch(k_bjacobi_solve<false>, dim3(strips, BJ_U_PARTS), dim3(BJ_SOLVE_THREADS), lds_solve, st, *A, n, Uall);
             else
-                hipLaunchKernelGGL(k_bjacobi_solve<true>, dim3(strips, BJ_U_PARTS), dim3(BJ_SOLVE_THREADS), lds_solve, st, *A, n, Uall);
-            hipLaunchKernelGGL(k_bjacobi_apply, dim3(cgrid, strips, 2), dim3(256), lds_apply, st, *A, *V, Uall, n, ct, *Aalt, *Valt);
+                launch(k_bjacobi_solve<true>, dim3(strips, BJ_U_PARTS), dim3(BJ_SOLVE_THREADS), lds_solve, st, *A, n, Uall);
+            launch(k_bjacobi_apply, dim3(cgrid, strips, 2), dim3(256), lds_apply, st, *A, *V, Uall, n, ct, *Aalt, *Valt);
             std::swap(*A, *Aalt);
             std::swap(*V, *Valt);
         }
