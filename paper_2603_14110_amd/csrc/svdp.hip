@@ -201,7 +201,7 @@ inline size_t split_h_offset(int d, int NB) { return align_up((size_t)DOWN_RG * 
 inline size_t split_list_offset(int d, int D, int NB) { return split_h_offset(d, NB) + align_up((size_t)D * NB * 4); }
 inline bool split_fits(int d, int D, int NB)
 {
-    return (D + DOWN_RG - 1) / DOWN_RG <= DS_MAX_CHUNK && d % DS_SW == 0 &&
+    return (D + DOWN_RG - 1) / DOWN_RG <= DS_MAX_CHUNK &&
            split_list_offset(d, D, NB) + (size_t)D * 4 <= (size_t)ROWS_BLOCKS * NB * d * 4;
 }
 
@@ -225,13 +225,14 @@ RowsPlan plan_rows(const svdp_layer *L)
         // Rows alone, vector -> matrix, at 30 / 60 % of the rows, eight tokens (us): d x D = 512 x 2560 11.4 -> 12.2 / 13.2 ->
         // 12.6, 768 x 3072 13.4 -> 12.6 / 14.3 -> 13.1, 1024 x 4672 15.8 -> 13.8 / 19.5 -> 15.5, 2432 x 12864 30.1 -> 24.3 /
         // 43.0 -> 35.6; below 2 M elements the launch more is not earned back.  At four tokens the vector kernel is ahead or
-        // level up to 3584 x 18944 (31.0 -> 31.4).
+        // level up to 3584 x 18944 (31.0 -> 31.4).  Rows that end inside a 128-byte line, whole step: d x D = 3128 x 12160, B = 8
+        // 78.6 -> 67.8, 2104 x 8064, B = 6 37.5 -> 30.9; asked for by the flag they stay on the vector units as ever.
         const bool want = engine == ENGINE_MATRIX || (engine == ENGINE_AUTO && NB >= 8 && (size_t)d * D >= ROWS_MATRIX_MIN);
-        if (want && d % 64 == 0) {
+        if (want && (d % 64 == 0 || engine == ENGINE_AUTO)) {
             p.kind = ROWS_MATRIX;
             p.min_chunk = MF_ROWS;
             p.max_chunk = round_up(per > p.min_chunk ? per : p.min_chunk, MF_ROWS);
-            p.lds = (size_t)NB * d * 2 + ((size_t)ROWS_WAVES * p.max_chunk * 2 * NB + p.max_chunk) * 4;
+            p.lds = (size_t)NB * round_up(d, 64) * 2 + ((size_t)ROWS_WAVES * p.max_chunk * 2 * NB + p.max_chunk) * 4;
             p.split = true;
             if (p.lds <= LDS_MAX && split_fits(d, D, NB)) return p;
             p.split = false;
@@ -401,7 +402,7 @@ svdp_status launch_rows(const svdp_layer *L, const void *x, int B, const uint64_
             launch((k_gate_up_mfma<NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, xs, B,
                                d, D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags,
                                hbuf, lst);
-            launch((k_down_slices<NB, MODE == ROWS_DENSE>), dim3(d / DS_SW, DOWN_RG), dim3(DS_THREADS), 0, st,
+            launch((k_down_slices<NB, MODE == ROWS_DENSE>), dim3((d + DS_SW - 1) / DS_SW, DOWN_RG), dim3(DS_THREADS), 0, st,
                                Wd, lst, MODE == ROWS_DENSE ? nullptr : w.nnz, D, D, d, hbuf, DOWN_MIN_CHUNK, w.ypart);
         }
     }

@@ -13,8 +13,9 @@
 //   k_down_slices   y[token][col] = sum over the list of h * W_downT[row][col], by blocks that own a
 //            128-byte column slice and one of eight parts of the list (see there).
 // Products of bf16 values are exact in fp32 and every sum has a fixed order.
-// Requirements checked by the host: d % 64 == 0 (a row is whole 128-byte lines), NB <= 8.
-// Dynamic LDS of k_gate_up_mfma: NB*d*2 bytes (x) + ROWS_WAVES*max_chunk*2*NB floats (partial tiles) +
+// A row's last, partial step (d no multiple of 64) is a step of its own, with zeros past the end on both sides.
+// Requirements checked by the host: NB <= 8.
+// Dynamic LDS of k_gate_up_mfma: NB * (d rounded up to 64) * 2 bytes (x) + ROWS_WAVES*max_chunk*2*NB floats (partial tiles) +
 // max_chunk ints (list); max_chunk % 16 == 0.
 #pragma once
 
@@ -43,9 +44,9 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
     static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8, "token slots are addressed with a mask");
     extern __shared__ uint4 smem16[];
     const int nvec = d / 8;                                        // 16-byte vectors per token
-    const int nsteps = d / 64;                                     // 64-element steps per row
+    const int full = d / 64, nsteps = (d + 63) / 64;               // 64-element steps per row: whole ones, all
     uint4 *xs = smem16;                                            // [nsteps][2][4][NB], operand order
-    float *part = reinterpret_cast<float *>(xs + NB * nvec);       // [ROWS_WAVES][tiles][2][16][NB]
+    float *part = reinterpret_cast<float *>(xs + NB * nsteps * 8); // [ROWS_WAVES][tiles][2][16][NB]
     int *lidx = reinterpret_cast<int *>(part + (size_t)ROWS_WAVES * max_chunk * 2 * NB);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lm = lane & 15, lq = lane >> 4;
@@ -67,6 +68,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
         if (tid < nvec) xs[xslot(tid, b)] = xfirst[b];
         for (int c = tid + ROWS_THREADS; c < nvec; c += ROWS_THREADS)
             xs[xslot(c, b)] = b < B ? load_raw(x + (size_t)b * d + (size_t)c * 8) : make_uint4(0u, 0u, 0u, 0u);
+        if (nvec + tid < nsteps * 8) xs[xslot(nvec + tid, b)] = make_uint4(0u, 0u, 0u, 0u);      // at most seven
     }
     const int chunk = chunk_of(n, G, min_chunk);
     const int lo = min(n, (int)blockIdx.x * chunk);
@@ -95,7 +97,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
 
     // ---- this wave's share of d is the steps [first, last) ----
     const int uwave = __builtin_amdgcn_readfirstlane(wave);         // the tests of the loop below stay scalar
-    const int first = uwave * nsteps / ROWS_WAVES, last = (uwave + 1) * nsteps / ROWS_WAVES;
+    const int first = uwave * nsteps / ROWS_WAVES, end = (uwave + 1) * nsteps / ROWS_WAVES, last = min(end, full);
     const int tb = lm & (NB - 1);                                   // token slot read as the x operand
     for (int t = 0; t < ntile; ++t) {
         const size_t row = row_of(t * MF_ROWS + lm);
@@ -125,6 +127,18 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
                     au = mfma_bf16(u1[k], xb, au);
                 }
             }
+        }
+        if (end > full) {                        // the last wave: the partial step
+            const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+            const int col = full * 64 + lq * 8;
+            const uint4 g0 = col < d ? load_raw(pg + (size_t)full * 64) : zero, u0 = col < d ? load_raw(pu + (size_t)full * 64) : zero;
+            const uint4 g1 = col + 32 < d ? load_raw(pg + (size_t)full * 64 + 32) : zero,
+                        u1 = col + 32 < d ? load_raw(pu + (size_t)full * 64 + 32) : zero;
+            const uint4 xa = xs[((full * 2 + 0) * 4 + lq) * NB + tb], xb = xs[((full * 2 + 1) * 4 + lq) * NB + tb];
+            ag = mfma_bf16(g0, xa, ag);
+            au = mfma_bf16(u0, xa, au);
+            ag = mfma_bf16(g1, xb, ag);
+            au = mfma_bf16(u1, xb, au);
         }
         // the lane holds rows 4*lq .. 4*lq+3 of the tile for token lm
         if (lm < NB) {
@@ -167,7 +181,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
 // NB x 8 sums (its eight columns for every token), and h (written by the gate/up kernel, a few hundred KB that stay
 // in L2) is read by position.  The sums over a wave's eight row lanes and then over the waves are taken in a fixed
 // order through LDS.
-// Requirements checked by the host: d a multiple of the slice width, ceil(D / RG) <= DS_MAX_CHUNK.
+// The last slice may have fewer columns.  Requirement checked by the host: ceil(D / RG) <= DS_MAX_CHUNK.
 // ---------------------------------------------------------------------------
 constexpr int DS_THREADS = 256;
 constexpr int DS_WAVES = DS_THREADS / 64;
@@ -202,6 +216,7 @@ __global__ __launch_bounds__(DS_THREADS) void k_down_slices(const bf16 *__restri
     }
     const bf16 *colp = WdT + (size_t)slice * SW + (size_t)cg * 8;
     const int ngroups = (cnt + RPW - 1) / RPW;
+    const bool colok = slice * SW + cg * 8 < d;
 
     // v_mfma_f32_4x4x1_16b: sixteen independent 4 x 4 outer products; the four lanes of a block work on the same
     // row, lane j of the block supplies h of token 4 tg + j and its own column's weight, and keeps the four tokens'
@@ -224,7 +239,7 @@ __global__ __launch_bounds__(DS_THREADS) void k_down_slices(const bf16 *__restri
             if (q < cnt) {
                 const int row = DENSE ? lo + q : lidx[q];
                 if (row >= 0) {                                    // a rejected entry of the caller's list: h is zero
-                    wv[k] = load_raw(colp + (size_t)row * d);
+                    if (colok) wv[k] = load_raw(colp + (size_t)row * d);     // h is read for the lane's neighbours all the same
                     const float *hp = hbuf + (size_t)(lo + q) * NB;
 #pragma unroll
                     for (int g = 0; g < TG; ++g)
@@ -275,6 +290,7 @@ __global__ __launch_bounds__(DS_THREADS) void k_down_slices(const bf16 *__restri
     __syncthreads();
     for (int o = tid; o < NB * SW; o += DS_THREADS) {
         const int b = o / SW, c = o % SW;
+        if (slice * SW + c >= d) continue;
         float t = 0.f;
 #pragma unroll
         for (int p = 0; p < DS_WAVES * RSETS; ++p) t += red[(p * NB + b) * SW + c];

@@ -59,3 +59,24 @@ def test_rows_of_whole_lines(d, D, B):
     yd = binding.dense_ffn(L, x).cpu().numpy()
     parity.check_y(yd, oracle.dense_ffn(f["W_gate"], f["W_up"], f["W_downT"], X), "bf16",
                    slack=parity.fp32_forward_bound(f, X, np.arange(D)))
+
+
+@pytest.mark.parametrize("d,D,B", [(1032, 2112, 8), (1336, 1600, 5), (3128, 704, 8), (2104, 4224, 7), (8184, 320, 5)])
+def test_rows_with_a_partial_line(d, D, B):
+    """Layers of at least 2 M elements a matrix whose rows end inside a line: the default engine's rows."""
+    import torch
+    import oracle
+    from paper_2603_14110_amd import binding
+
+    L, x = layer(torch, binding, d, D, 16, B, "bf16", d + D)
+    f = {k: L.tensors[k].float().cpu().numpy() for k in ("W_gate", "W_up", "W_downT")}
+    X = x.float().cpu().numpy()
+    idx = torch.zeros(D, dtype=torch.int32, device="cuda")
+    nnz = torch.zeros(1, dtype=torch.int32, device="cuda")
+    y = binding.ffn_step(L, x, idx=idx, nnz=nnz).cpu().numpy()
+    lst = idx[: nnz.item()].cpu().numpy()
+    parity.check_y(y, oracle.sparse_ffn(f["W_gate"], f["W_up"], f["W_downT"], X, lst), "bf16",
+                   slack=parity.fp32_forward_bound(f, X, lst))
+    yd = binding.dense_ffn(L, x).cpu().numpy()
+    parity.check_y(yd, oracle.dense_ffn(f["W_gate"], f["W_up"], f["W_downT"], X), "bf16",
+                   slack=parity.fp32_forward_bound(f, X, np.arange(D)))
