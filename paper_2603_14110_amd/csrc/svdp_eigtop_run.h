@@ -41,11 +41,11 @@ constexpr double EIG_SHIFT = 4e-13;         // of the first Cholesky QR pass (ab
 // Rows of the block for r wanted vectors: a quarter more (at least 32), so that the filter has a gap to work with, in
 // whole Jacobi strips; 0 where the Jacobi decomposition of all of G is the better way.  Whole call in ms, this / full, for a
 // mean of 0, 10, 1e4 times the spread, eigenvalues 10^(-6 i / r), exp(-i / d), all equal (handed over after one projection):
-//   d = 256, r = 64    4.2 / 4.6    7.4 / 4.6    4.4 / 4.6    3.7 / 12    4.7 / 4.7    6.3 / 4.1
-//   d = 512, r = 64    4.9 / 12     7.1 / 12     5.0 / 11     4.3 / 27    5.6 / 11      12 / 9.5
-//   d = 512, r = 200   9.6 / 12      15 / 12      10 / 12     8.4 / 27     11 / 12      14 / 9.6
-//   d = 1024, r = 400   21 / 29      33 / 29      22 / 28      15 / 59     25 / 27      34 / 23
-// so the largest block is the one that no longer wins on most of them, and at n = 128 it loses on decaying ones (2.2 / 1.6).
+//   d = 256, r = 64    3.9 / 3.5    6.6 / 3.5    4.1 / 3.2    3.1 / 8.7    4.2 / 3.4    5.0 / 3.1
+//   d = 512, r = 64    4.4 / 7.8    6.4 / 7.5    4.5 / 6.8    3.5 / 17     5.0 / 7.2    8.0 / 6.2
+//   d = 512, r = 200   8.1 / 7.5     13 / 7.4    8.9 / 6.8    7.3 / 17     8.9 / 7.3    9.9 / 6.1
+//   d = 1024, r = 400   17 / 18      28 / 18      19 / 16      14 / 37      19 / 17      21 / 13
+// so the largest block is about level on flat spectra and far ahead on decaying ones, and at n = 128 it loses on decaying ones (2.2 / 1.6).
 inline int eigtop_block(int n, int r)
 {
     const int k = round_up(r + std::max(32, r / 4), BJ_S);
@@ -54,14 +54,15 @@ inline int eigtop_block(int n, int r)
 
 // Rough times (us) of what the iteration and the full decomposition consist of, fitted to n = 256 .. 4096: a product of k
 // rows with G, one orthonormalisation, `sweeps` Jacobi sweeps over an m x m matrix.  The iteration goes on while what it
-// still needs is below the full decomposition's nine sweeps (it takes 8 to 13), and while it has not spent one and a half
+// still needs is below the full decomposition's 14 sweeps (it takes 9 to 14; 9, d = 512, r = 200 and a mean of 10: 13.4 -> 19.1 ms,
+// handed over just before its end), and while it has not spent one and a half
 // times as much.  A limit on products alone (16 n rows) left out that at k = n / 2 the projections and orthonormalisations are
 // most of the time, and gave up blocks that were three products short:
 // whole call at d = 1024, r = 400, tokens with a mean of 10, 100, 1e4 times their spread 52, 46, 44 -> 33, 23, 22 ms (full
 // decomposition 29; eigenvalues exp(-i / d) 40 -> 25).
 inline double eig_product_us(int k, int n) { return 6.0 + 5e-8 * k * (double)n * n; }
 inline double eig_orthonormalize_us(int k) { return 40.0 + 0.8 * k; }
-inline double eig_jacobi_us(int m, int sweeps) { return sweeps * (m / BJ_B - 1) * (64.0 + 9e-6 * m * (double)m); }
+inline double eig_jacobi_us(int m, int sweeps) { return sweeps * (m / BJ_B - 1) * (40.0 + 9e-6 * m * (double)m); }
 
 struct EigTopWs {
     int k;                              // eigtop_block(n, r)
@@ -153,7 +154,7 @@ svdp_status leading_eigenvectors(const double *G, int n, int r, double *Vr, doub
     }
     const double *Gc = G;
     double largest = 0.0, last_err = 1e300, jacobi_tol = EIG_TOL_JACOBI;
-    const double full = eig_jacobi_us(n, 9);
+    const double full = eig_jacobi_us(n, 14);
     double spent = 3.0 * eig_product_us(k, n) + 5.0 * eig_orthonormalize_us(k);        // us so far, roughly
     int l = 0, ka = k, piece = 0;                           // vectors that left the block; rows of the block
     for (int cycle = 0; cycle < 24; ++cycle) {
