@@ -20,6 +20,13 @@ constexpr int GM_CPT = GM_BM * (GM_BK / 8) / GM_THREADS;     // chunks per threa
 
 enum GemmEpilogue { EPI_SPLIT3 = 0, EPI_PLAIN = 1 };
 
+__device__ __forceinline__ uint32_t bf16_rne_bits(float v)
+{
+    bf16 h;
+    from_f32(v, &h);
+    return h.bits;
+}
+
 // c as three bf16 terms, hi + mid + lo = c to 24 bits, at p[0], p[stride], p[2 * stride]
 __device__ __forceinline__ void store_split3(float c, uint16_t *__restrict__ p, int stride)
 {

@@ -306,7 +306,9 @@ __global__ __launch_bounds__(DS_THREADS) void k_down_slices(const bf16 *__restri
 // stage-1 partials and lies in LDS in operand order:
 //   fp32: as it is, v_mfma_f32_16x16x4_f32;
 //   bf16: split into three bf16 terms hi + mid + lo = t exactly to 24 bits, so that bf16
-//         MFMAs give fp32-accurate scores: every product is exact and the accumulation is fp32.
+//         MFMAs give fp32-accurate scores: every product is exact and the accumulation is fp32.  An infinite t or NaN is hi,
+//         with mid = lo = 0.  An infinite Q times a zero mid or lo is NaN, and the terms' products may overflow where t's
+//         does not: a score that is not finite is worked out again from t = (mid + lo) + hi by fp32 arithmetic.
 // Columns past r are zeros on both sides, so every rank that a layer may have is taken.
 //
 // Bound: the chain launch, partials of t, operands, MFMAs; the bytes of Q are half of it at most.  Taken for fp32 and for
@@ -323,11 +325,23 @@ constexpr int SCM_THREADS = 256;
 constexpr int SCM_KB = 16;          // column blocks of Q held in registers
 constexpr int SCM_NT = 4;           // partials of t requested together
 
-__device__ __forceinline__ uint32_t bf16_rne_bits(float v)
+// a and b as hi + mid + lo each, two bf16 to a word.  WIDE: also where an element is infinite or NaN (then hi, with
+// mid = lo = 0) or rounds past the largest bf16 (then hi is that).
+constexpr float BF16_MAX = 0x1.fep127f;
+template <bool WIDE>
+__device__ __forceinline__ void split3(float a, float b, uint32_t &hi, uint32_t &mid, uint32_t &lo)
 {
-    bf16 h;
-    from_f32(v, &h);
-    return h.bits;
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    auto pack = [](float x, float y) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{x, y}), bf16x2_t)); };
+    auto capped = [](float v) { return WIDE && __builtin_isfinite(v) ? fminf(fmaxf(v, -BF16_MAX), BF16_MAX) : v; };
+    hi = pack(capped(a), capped(b));
+    float ra = a - __uint_as_float(hi << 16), rb = b - __uint_as_float(hi & 0xffff0000u);
+    if (WIDE) {
+        ra = __builtin_isfinite(a) ? ra : 0.f;
+        rb = __builtin_isfinite(b) ? rb : 0.f;
+    }
+    mid = pack(ra, rb);
+    lo = pack(ra - __uint_as_float(mid << 16), rb - __uint_as_float(mid & 0xffff0000u));
 }
 
 __device__ __forceinline__ f32x4_t mfma_f32(const uint4 &a, const uint4 &b, f32x4_t c)
@@ -422,20 +436,19 @@ __global__ __launch_bounds__(SCM_THREADS) void k_scores_mfma(const W *__restrict
         if constexpr (TERMS == 1) {
             *op = make_uint4(__float_as_uint(t[0]), __float_as_uint(t[1]), __float_as_uint(t[2]), __float_as_uint(t[3]));
         } else {
-            uint32_t pl[3][VEC];
+            float top = 0.f;
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const uint32_t hi = bf16_rne_bits(t[e]);
-                const float r1 = t[e] - __uint_as_float(hi << 16);
-                const uint32_t mid = bf16_rne_bits(r1);
-                const float r2 = r1 - __uint_as_float(mid << 16);
-                pl[0][e] = hi; pl[1][e] = mid; pl[2][e] = bf16_rne_bits(r2);
+            for (int e = 0; e < VEC; ++e) top = fmaxf(top, fabsf(t[e]));
+            uint32_t pl[3][VEC / 2];
+            if (__builtin_expect(!(top <= BF16_MAX), 0)) {
+#pragma unroll
+                for (int e = 0; e < VEC / 2; ++e) split3<true>(t[2 * e], t[2 * e + 1], pl[0][e], pl[1][e], pl[2][e]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < VEC / 2; ++e) split3<false>(t[2 * e], t[2 * e + 1], pl[0][e], pl[1][e], pl[2][e]);
             }
 #pragma unroll
-            for (int p = 0; p < 3; ++p)
-                op[(size_t)p * slots * NB] =
-                    make_uint4(pl[p][0] | (pl[p][1] << 16), pl[p][2] | (pl[p][3] << 16), pl[p][4] | (pl[p][5] << 16),
-                               pl[p][6] | (pl[p][7] << 16));
+            for (int p = 0; p < 3; ++p) op[(size_t)p * slots * NB] = make_uint4(pl[p][0], pl[p][1], pl[p][2], pl[p][3]);
         }
     }
     __syncthreads();
@@ -454,6 +467,31 @@ __global__ __launch_bounds__(SCM_THREADS) void k_scores_mfma(const W *__restrict
 #pragma unroll
                     for (int p = 0; p < 3; ++p) acc = mfma_bf16(q[k], op[(size_t)p * slots * NB], acc);
                 }
+            }
+        }
+    }
+    if constexpr (TERMS == 3) {
+        const bool plain = __builtin_isfinite(acc[0]) && __builtin_isfinite(acc[1]) && __builtin_isfinite(acc[2]) &&
+                           __builtin_isfinite(acc[3]);
+        if (__builtin_expect(__any(!plain), 0)) {                   // see above: such scores once more, from t itself
+#pragma unroll 1
+            for (int i = 0; i < 4; ++i) {
+                const W *row = Q + (size_t)(i0 + lq * 4 + i) * r;
+                const uint4 *op = ops + (lm & (NB - 1));
+                float v = 0.f;
+#pragma unroll 1
+                for (int g = 0; g < ngr; ++g, op += NB) {
+                    float qv[VEC], hi[VEC], mid[VEC], lo[VEC];
+                    widen(load_raw(row + (size_t)g * VEC), qv, (const W *)nullptr);
+                    widen(op[0], hi, (const W *)nullptr);
+                    widen(op[(size_t)slots * NB], mid, (const W *)nullptr);
+                    widen(op[(size_t)2 * slots * NB], lo, (const W *)nullptr);
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) v = fmaf((mid[e] + lo[e]) + hi[e], qv[e], v);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k == i && !__builtin_isfinite(acc[k])) acc[k] = v;
             }
         }
     }

@@ -40,6 +40,48 @@ def test_scores_of_every_rank(d, D, r, B, dt):
     assert torch.equal(mask, m2)
 
 
+@pytest.mark.parametrize("d,D,r,B,dt", [(256, 64, 8, 5, "bf16"), (64, 128, 40, 6, "bf16"), (128, 192, 544, 8, "bf16"),
+                                         (128, 128, 64, 5, "bf16"), (64, 128, 20, 5, "f32")])
+def test_scores_that_are_not_finite(d, D, r, B, dt):
+    """An infinite or NaN t, a t between the largest bf16 and the largest fp32, and infinite or NaN rows of Q give both
+    engines what the sum of the products is: the same infinities and NaN, everything else finite and right."""
+    import torch
+    from paper_2603_14110_amd import binding
+
+    L, x = layer(torch, binding, d, D, r, B, dt, d + D + r)
+    t = L.tensors
+    P, Q = t["P"].abs(), t["Q"].clone()          # the sign of an infinite t is x's
+    top = torch.finfo(torch.bfloat16).max
+    P[0], P[1], P[2] = 2.0 ** -100, 0.0, 2.0 ** -120
+    P[0, 0] = P[1, 0] = 1.0                      # column 0 of t: x[0] + x[1] + ...
+    P[2, 3] = 4.0                                # column 3: overflows
+    Q[0], Q[1] = Q[0].abs() + 0.25, -Q[1].abs() - 0.25
+    Q[2, 0] = 1.0
+    Q[5, 2], Q[6, 5], Q[7, 1] = torch.inf, -torch.inf, torch.nan
+    Q[8] = 0.0
+    x[1, 4] = torch.inf
+    x[2, 0], x[2, 1], x[2, 2] = top, 1.5 * 2.0 ** 119, 0.0
+    x[3, 2] = 2.0 ** 127
+    x[4, 7] = torch.nan
+    L = binding.DeviceLayer(P, Q, t["b"], t["W_gate"], t["W_up"], t["W_downT"])
+    tt = (x.double().cpu() @ P.double().cpu()).float().double()
+    assert tt[2, 0].isfinite() and tt[2, 0].to(torch.bfloat16).isinf() and tt[3, 3].isinf() and tt[3, 2].isfinite()
+    terms = tt[:, None, :] * Q.double().cpu()[None]
+    ref, size = terms.sum(-1) + t["b"].double().cpu(), terms.abs().sum(-1)
+    ok = ref.isfinite()
+    assert ref[1, 0] == torch.inf and ref[1, 1] == -torch.inf and ref[1, 8].isnan() and ref[2, 2].isfinite() and ok[0].sum() == D - 3
+    for flags in (0, binding.FLAG_ENGINE_VECTOR, binding.FLAG_ENGINE_MATRIX):
+        s = binding.predict(L.with_flags(flags), x)
+        mask = torch.zeros(D // 64, dtype=torch.int64, device="cuda")
+        binding.ffn_step(L.with_flags(flags), x, mask=mask)
+        assert torch.equal(mask, binding.compact(s)[0]), flags
+        s = s.cpu()
+        assert torch.equal(s.isnan(), ref.isnan()), flags
+        assert torch.equal(s[ref.isinf()].double(), ref[ref.isinf()]), flags
+        # two chains of fp32 additions of d and r terms, as above, against the sum of the terms' sizes
+        assert bool(((s.double() - ref).abs()[ok] <= 2e-5 * size[ok] + 1e-6).all()), flags
+
+
 @pytest.mark.parametrize("d,D,B", [(64, 64, 8), (192, 640, 5), (576, 4160, 8), (1088, 2112, 3), (1856, 1152, 8)])
 def test_rows_of_whole_lines(d, D, B):
     import torch
