@@ -57,9 +57,15 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t u)
 // score between the tail's ends (monotone in fp32 too), a counting pass gives the buckets' places, and inside a bucket (one
 // to three samples on the scores of a layer) a sample's rank is the number of smaller keys: the number of barriers does not
 // depend on the length.  A bucket of more than CAL_BUCKET_MAX samples (many equal scores, an outlier that leaves everybody
-// else in one bucket, an infinite score) sends the neuron to the network.
-// Every neuron through it, whole call at D = 11008, T = 2048, eta = 16: one outlier per neuron 393 us (network alone, 512
-// threads: 535), scores on a grid of quarters 376 (521), one score value 752 (732).
+// else in one bucket, an infinite score) sends the neuron to the network, whose 55 to 78 stages cost more than counting 256 keys
+// of a bucket does: whole call at D = 11008, eta = 16, limit 32 with twice the buckets / 32 / 256 / network for every neuron,
+// in us, T = 2048 and T = 4096:
+//   Gaussian                                   168 / 165 / 167 / 640       432 / 385 / 385 / 1960
+//   Student t, 4 degrees of freedom            231 / 287 / 191 / 643       626 / 958 / 472 / 1961
+//   Gaussian, token scale log-normal (0.6)     231 / 392 / 184 / 647       540 / 1140 / 446 / 1959
+//   one outlier at 20 times the spread         244 / 656 / 210 / 655       650 / 1897 / 527 / 1970
+//   one outlier at 10 times the spread         180 / 235 / 183 / 652       482 / 584 / 447 / 1969
+// Scores of a 90 %-sparse layer (139 us) with one huge outlier per neuron 362 us, on a grid of quarters 267, all equal 711.
 // Measured at D = 11008, T = 2048, eta = 16: network 450 us, buckets 131 us (512 threads, 64-bit reductions), 117 us with
 // the sorted tail in the keys' place (four blocks a compute unit instead of three), 91 us with 256 threads, reductions on
 // the scores alone and the ranks taken by tail position (660 -> 370 vector instructions a wave, half the waves); with 512
@@ -67,9 +73,12 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t u)
 // six, from memory instead of the cache 101 -> 92 us (D = 18944, T = 4096, eta = 1, whole call: 2915 -> 2144).
 // Scores and weights are read once and stay in registers, PER of each per thread (T <= PER * CAL_THREADS).
 // Dynamic LDS: calib_sort_lds().
-constexpr int CAL_BUCKET_MAX = 32;
+constexpr int CAL_BUCKET_MAX = 256;
+// As many as eight blocks' local memory has room for.  For T <= 512 no more, because clearing and adding up 1024 shows there
+// (0.5 to 1 us of 100); against 512 at T = 1000, D = 18944, outlier at 40 times the spread 249 -> 229 us, Student t, 3 degrees
+// of freedom 222 -> 208.
 template <int PER>
-constexpr int cal_buckets() { return PER <= 8 ? 512 : 1024; }
+constexpr int cal_buckets() { return PER == 2 || PER == 8 ? 512 : 1024; }
 
 // sort keys (n2 = T rounded up to a power of two), later the sorted tail (s, w) in their place; costs and their running
 // maxima; buckets.  19.5 KB at T = 2048, eta = 16: eight blocks a compute unit, as many as it has wave slots for.

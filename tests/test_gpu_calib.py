@@ -354,3 +354,27 @@ def test_both_widths_of_the_level_counters(env, D, T, eta):
     for sp in (1.0, 0.0, 0.8, 0.5, 0.99):
         _check(env, w, s, eta, binding.calib_need(sp, D, T))
     _check(env, w, s, eta, D * T + 1)
+
+
+@pytest.mark.parametrize("T,eta", [(400, 3), (1024, 16), (2048, 16), (4096, 5)])
+def test_scores_with_heavy_tails(env, T, eta):
+    """Scores whose bulk shares a few of the sort's buckets: buckets of one, of exactly 255, 256 and 257 samples (256 is the
+    most that is sorted inside a bucket), heavy tails, and tokens of very different scale."""
+    binding, torch, calib = env
+    rng = np.random.default_rng(T)
+    D = 12
+    w, s = _stats(rng, D, T, dead=(1,))
+    for i, df in zip(range(2, 5), (1, 3, 4)):
+        s[i] = s[i] / np.sqrt(rng.chisquare(df, T) / df)
+    for i in range(5, 8):
+        s[i] = s[i] * np.exp((0.6, 1.0, 2.0)[i - 5] * rng.standard_normal(T))
+    for i, m in zip(range(8, 11), (255, 256, 257)):              # m samples of one bucket in front of the evenly spread rest
+        s[i] = np.linspace(1.0, 2.0, T)
+        s[i, :m] = 1.0 + 1e-6 * rng.random(m)
+        s[i, 0] = 1.0
+        w[i, :] = rng.exponential(1.0, T)
+        s[i] = s[i][rng.permutation(T)]
+    s[11, ::2] *= 1e-4
+    s = s.astype(np.float32)
+    for sp in (0.3, 0.9, 0.99):
+        _check(env, w, s, eta, binding.calib_need(sp, D, T))
