@@ -84,9 +84,8 @@ enum {
      *  SVDP_FLAG_ENGINE_MATRIX: matrix cores wherever a kernel for them exists:
      *      - rows (gate, up, down over the list): taken 16 at a time as MFMA tiles straight
      *        from their place in the weight matrices (no gathered copy), bf16 x bf16 -> fp32
-     *        for gate and up, fp32 outer products for the down projection; needs bf16 storage,
-     *        d a multiple of 64 (any d where the default chooses them) and no
-     *        SVDP_FLAG_REVALIDATE;
+     *        for gate and up, fp32 outer products for the down projection; needs bf16 storage
+     *        and no SVDP_FLAG_REVALIDATE;
      *      - scores (t Q^T + b): bf16 MFMAs with t split into three bf16 terms (exact to fp32), or
      *        fp32 MFMAs for fp32 storage; below three tokens bf16 storage with r a multiple of 32,
      *        r <= 512.

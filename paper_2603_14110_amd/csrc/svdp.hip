@@ -224,11 +224,14 @@ RowsPlan plan_rows(const svdp_layer *L)
         const Engine engine = engine_of(L);
         // Rows alone, vector -> matrix, at 30 / 60 % of the rows, eight tokens (us): d x D = 512 x 2560 11.4 -> 12.2 / 13.2 ->
         // 12.6, 768 x 3072 13.4 -> 12.6 / 14.3 -> 13.1, 1024 x 4672 15.8 -> 13.8 / 19.5 -> 15.5, 2432 x 12864 30.1 -> 24.3 /
-        // 43.0 -> 35.6; below 2 M elements the launch more is not earned back.  At four tokens the vector kernel is ahead or
-        // level up to 3584 x 18944 (31.0 -> 31.4).  Rows that end inside a 128-byte line, whole step: d x D = 3128 x 12160, B = 8
-        // 78.6 -> 67.8, 2104 x 8064, B = 6 37.5 -> 30.9; asked for by the flag they stay on the vector units as ever.
+        // 43.0 -> 35.6; below 2 M elements the launch more is not earned back.  Rows that end inside a 128-byte line, whole
+        // step: d x D = 3128 x 12160, B = 8 78.6 -> 67.8, 2104 x 8064, B = 6 37.5 -> 30.9.
+        // Four tokens, whole step with the sum of the partial outputs, scores on the matrix cores either way, list of 0.33 to 0.4 /
+        // 0.55 to 0.6 of the rows, weights from memory: vector ahead or level.  512 x 2560 16.5 -> 18.8 / 17.8 -> 19.5,
+        // 1024 x 4672 20.6 -> 22.4 / 23.4 -> 24.9, 2432 x 12864 38.4 -> 38.8 / 46.9 -> 46.3, 3584 x 18944 57.2 -> 60.1 / 76.2 ->
+        // 77.2, 4096 x 11008 41.5 -> 42.4 / 53.1 -> 54.7; from the cache the same within 1 us.
         const bool want = engine == ENGINE_MATRIX || (engine == ENGINE_AUTO && NB >= 8 && (size_t)d * D >= ROWS_MATRIX_MIN);
-        if (want && (d % 64 == 0 || engine == ENGINE_AUTO)) {
+        if (want) {
             p.kind = ROWS_MATRIX;
             p.min_chunk = MF_ROWS;
             p.max_chunk = round_up(per > p.min_chunk ? per : p.min_chunk, MF_ROWS);

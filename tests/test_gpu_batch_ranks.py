@@ -105,7 +105,8 @@ def test_rows_of_whole_lines(d, D, B):
 
 @pytest.mark.parametrize("d,D,B", [(1032, 2112, 8), (1336, 1600, 5), (3128, 704, 8), (2104, 4224, 7), (8184, 320, 5)])
 def test_rows_with_a_partial_line(d, D, B):
-    """Layers of at least 2 M elements a matrix whose rows end inside a line: the default engine's rows."""
+    """Layers of at least 2 M elements a matrix whose rows end inside a line: the default engine's rows, which are the matrix
+    engine's (the same bits) and not the vector engine's (other sums)."""
     import torch
     import oracle
     from paper_2603_14110_amd import binding
@@ -113,12 +114,47 @@ def test_rows_with_a_partial_line(d, D, B):
     L, x = layer(torch, binding, d, D, 16, B, "bf16", d + D)
     f = {k: L.tensors[k].float().cpu().numpy() for k in ("W_gate", "W_up", "W_downT")}
     X = x.float().cpu().numpy()
-    idx = torch.zeros(D, dtype=torch.int32, device="cuda")
-    nnz = torch.zeros(1, dtype=torch.int32, device="cuda")
-    y = binding.ffn_step(L, x, idx=idx, nnz=nnz).cpu().numpy()
-    lst = idx[: nnz.item()].cpu().numpy()
-    parity.check_y(y, oracle.sparse_ffn(f["W_gate"], f["W_up"], f["W_downT"], X, lst), "bf16",
-                   slack=parity.fp32_forward_bound(f, X, lst))
-    yd = binding.dense_ffn(L, x).cpu().numpy()
-    parity.check_y(yd, oracle.dense_ffn(f["W_gate"], f["W_up"], f["W_downT"], X), "bf16",
-                   slack=parity.fp32_forward_bound(f, X, np.arange(D)))
+    for drelu in (0, binding.FLAG_DRELU):
+        idx = torch.zeros(D, dtype=torch.int32, device="cuda")
+        nnz = torch.zeros(1, dtype=torch.int32, device="cuda")
+        y = binding.ffn_step(L.with_flags(drelu), x, idx=idx, nnz=nnz)
+        lst = idx.cpu().numpy()[: nnz.item()]
+        parity.check_y(y.cpu().numpy(), oracle.sparse_ffn(f["W_gate"], f["W_up"], f["W_downT"], X, lst, drelu=bool(drelu)), "bf16",
+                       slack=parity.fp32_forward_bound(f, X, lst))
+        yd = binding.dense_ffn(L.with_flags(drelu), x)
+        parity.check_y(yd.cpu().numpy(), oracle.sparse_ffn(f["W_gate"], f["W_up"], f["W_downT"], X, np.arange(D), drelu=bool(drelu)),
+                       "bf16", slack=parity.fp32_forward_bound(f, X, np.arange(D)))
+        for engine, same in ((binding.FLAG_ENGINE_MATRIX, True), (binding.FLAG_ENGINE_VECTOR, False)):
+            assert torch.equal(binding.ffn_step(L.with_flags(drelu | engine), x), y) == same
+            assert torch.equal(binding.dense_ffn(L.with_flags(drelu | engine), x), yd) == same
+
+
+@pytest.mark.parametrize("d,D", [(8, 64), (56, 320), (120, 4160), (1032, 2112), (2104, 1088)])
+def test_lists_with_a_partial_line(d, D):
+    """Lists of the caller's own on the matrix cores, every batch size, rows that end inside a line: empty, one row, short and
+    long, unsorted, with repeated entries and with entries outside the layer (which contribute nothing)."""
+    import torch
+    import oracle
+    from paper_2603_14110_amd import binding
+
+    L, x = layer(torch, binding, d, D, 8, 8, "bf16", d + D)
+    f = {k: L.tensors[k].float().cpu().numpy() for k in ("W_gate", "W_up", "W_downT")}
+    X = x.float().cpu().numpy()
+    rng = np.random.default_rng(D)
+    bad = rng.permutation(D)[: D // 2].astype(np.int32)
+    bad[::5] = np.array([-1, D, D + 7, np.iinfo(np.int32).min, np.iinfo(np.int32).max], np.int32)[np.arange(bad[::5].size) % 5]
+    lists = [np.zeros(0, np.int32), np.array([D - 1], np.int32), np.arange(D, dtype=np.int32), np.arange(0, D, 7, dtype=np.int32),
+             rng.permutation(D).astype(np.int32), rng.integers(0, D, D).astype(np.int32), bad]
+    for B, drelu in ((1, 0), (2, 0), (3, binding.FLAG_DRELU), (4, 0), (5, binding.FLAG_DRELU), (8, 0)):
+        same = []
+        for lst in lists:
+            idx = torch.zeros(D, dtype=torch.int32, device="cuda")
+            idx[: lst.size] = torch.from_numpy(lst).cuda()
+            nnz = torch.tensor([lst.size], dtype=torch.int32, device="cuda")
+            y = binding.sparse_ffn(L.with_flags(drelu | binding.FLAG_ENGINE_MATRIX), x[:B], idx, nnz)
+            kept = lst[(lst >= 0) & (lst < D)]
+            parity.check_y(y.cpu().numpy(), oracle.sparse_ffn(f["W_gate"], f["W_up"], f["W_downT"], X[:B], kept, drelu=bool(drelu)),
+                           "bf16", slack=parity.fp32_forward_bound(f, X[:B], kept))
+            assert kept.size > 0 or not y.any()
+            same.append(torch.equal(y, binding.sparse_ffn(L.with_flags(drelu | binding.FLAG_ENGINE_VECTOR), x[:B], idx, nnz)))
+        assert d < 64 or not all(same)                          # other sums than the vector engine's

@@ -144,8 +144,8 @@ def test_matrix_engine_scores(env, shape):
 
 
 def test_engine_selection_and_determinism(env):
-    """No engine flag = matrix cores from 5 tokens up (batch capacity 8), vector units below; layers the matrix
-    kernel does not take (fp32 storage, d not a multiple of 512, re-validation) run on the vector kernel whatever
+    """No engine flag = rows on the matrix cores from 5 tokens up (batch capacity 8; from 2 M elements a matrix), vector units
+    below; layers the matrix row kernels do not take (fp32 storage, re-validation) run on the vector kernel whatever
     is asked for.  Seen through bit patterns: each engine is deterministic and the two differ in the
     last bits of y."""
     binding, torch, oracle = env
@@ -163,9 +163,17 @@ def test_engine_selection_and_determinism(env):
     # re-validation: vector row kernel under every setting (the score kernel still follows the flag,
     # which can only move scores within rounding of zero; the lists agree on this layer)
     assert torch.equal(run(MATRIX, 8, flags=binding.FLAG_REVALIDATE), run(VECTOR, 8, flags=binding.FLAG_REVALIDATE))
-    # d = 520: not a multiple of 512
+    # d = 520, rows that end inside a 128-byte line: the flag means the same
     c2 = RandomLayer(binding, torch, 12, 520, 4160, 16, 8)
-    assert torch.equal(binding.ffn_step(c2.dev.with_flags(MATRIX), c2.Xd), binding.ffn_step(c2.dev.with_flags(VECTOR), c2.Xd))
+    ym, yv, ya = (binding.ffn_step(c2.dev.with_flags(k), c2.Xd) for k in (MATRIX, VECTOR, AUTO))
+    assert torch.equal(ya, ym) and not torch.equal(ym, yv)
+    # fp32 storage: no row kernel on the matrix cores
+    t = c2.dev.tensors
+    c3 = binding.DeviceLayer(*(t[k].float() for k in ("P", "Q", "b", "W_gate", "W_up", "W_downT")))
+    idx = torch.arange(c2.D, dtype=torch.int32, device="cuda")
+    nnz = torch.tensor([c2.D], dtype=torch.int32, device="cuda")
+    y3 = [binding.sparse_ffn(c3.with_flags(k), c2.Xd.float(), idx, nnz).clone() for k in (MATRIX, VECTOR, AUTO)]
+    assert torch.equal(y3[0], y3[1]) and torch.equal(y3[0], y3[2])
 
 
 def test_two_host_threads_with_different_engines(env):
