@@ -101,11 +101,18 @@ def _check(st: int, what: str) -> None:
         raise SvdpError(f"{what}: {lib().svdp_status_string(st).decode()} (status {st})")
 
 
+# private to torch: a version without them gets its handles from torch.cuda.current_stream()
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
     # The handle behind torch.cuda.current_stream(), without the Stream object around it: that object costs 2.6 us a call, as
     # much as a kernel launch, and the host bounds every call on a small layer (step of d = 256, D = 1024: 15.4 -> 12.7 us, of
     # which 9.5 are the kernels).
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:

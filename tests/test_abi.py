@@ -264,6 +264,23 @@ def test_binding_fails_loudly_without_library(svdp, monkeypatch):
         svdp.lib()
 
 
+def test_stream_handle_without_torchs_private_functions(svdp, monkeypatch):
+    """The current stream's handle comes from two private functions of torch, and from its public interface where a version
+    lacks either of them."""
+    import types
+
+    import torch
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x70))
+    for missing in ("_raw_stream", "_current_device"):
+        with monkeypatch.context() as m:
+            m.setattr(svdp, "_raw_stream", lambda device: 0x100 + device)
+            m.setattr(svdp, "_current_device", lambda: 3)
+            assert svdp._stream() == 0x103
+            m.setattr(svdp, missing, None)
+            assert svdp._stream() == 0x70
+
+
 def test_bench_refuses_more_than_one_gpu():
     """One GPU only: `bench.py --gpus N` with N > 1 says so and exits without touching a device."""
     import subprocess
