@@ -79,7 +79,8 @@ enum {
      * Sec. 6 notes that batching lowers the sparsity the first can exploit.
      *  neither flag (default): per kernel and batch capacity, whichever was measured faster on
      *      MI355X: matrix cores for the scores from 3 tokens and for the rows from 5 tokens
-     *      (bf16 layers of at least 2 M elements a matrix), vector units below.
+     *      (bf16 layers of at least 2 M elements a matrix; over all rows above 1 M elements and 768
+     *      rows), vector units below.
      *  SVDP_FLAG_ENGINE_VECTOR: fp32 vector arithmetic everywhere (any dtype, batch, flags).
      *  SVDP_FLAG_ENGINE_MATRIX: matrix cores wherever a kernel for them exists:
      *      - rows (gate, up, down over the list): taken 16 at a time as MFMA tiles straight

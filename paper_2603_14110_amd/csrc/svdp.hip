@@ -205,8 +205,11 @@ inline bool split_fits(int d, int D, int NB)
            split_list_offset(d, D, NB) + (size_t)D * 4 <= (size_t)ROWS_BLOCKS * NB * d * 4;
 }
 
-constexpr size_t ROWS_MATRIX_MIN = 2 << 20;          // d * D from which the matrix engine's two row kernels are chosen
-template <typename W, int NB>
+// d * D from which the matrix engine's two row kernels are chosen over a list, and above which over all rows, if each block of
+// the vector kernel has more than three
+constexpr size_t ROWS_MATRIX_MIN = 2 << 20, ROWS_MATRIX_DENSE_MIN = 1 << 20;
+constexpr int ROWS_MATRIX_DENSE_ROWS = 3 * ROWS_BLOCKS;
+template <typename W, int NB, int MODE = ROWS_MASK>
 RowsPlan plan_rows(const svdp_layer *L)
 {
     const int d = L->d, D = L->D, G = ROWS_BLOCKS;
@@ -230,7 +233,13 @@ RowsPlan plan_rows(const svdp_layer *L)
         // 0.55 to 0.6 of the rows, weights from memory: vector ahead or level.  512 x 2560 16.5 -> 18.8 / 17.8 -> 19.5,
         // 1024 x 4672 20.6 -> 22.4 / 23.4 -> 24.9, 2432 x 12864 38.4 -> 38.8 / 46.9 -> 46.3, 3584 x 18944 57.2 -> 60.1 / 76.2 ->
         // 77.2, 4096 x 11008 41.5 -> 42.4 / 53.1 -> 54.7; from the cache the same within 1 us.
-        const bool want = engine == ENGINE_MATRIX || (engine == ENGINE_AUTO && NB >= 8 && (size_t)d * D >= ROWS_MATRIX_MIN);
+        // Over all rows, eight (five) tokens: 256 x 5120 17.9 -> 14.8 (18.0 -> 14.8), 512 x 4032 16.4 -> 13.7 (15.7 -> 13.7),
+        // 1000 x 1088 16.1 -> 12.3 (14.3 -> 12.2), 1024 x 1984 15.0 -> 13.1 (13.4 -> 13.0), 2048 x 960 17.6 -> 15.4 (15.0 -> 15.1);
+        // below: 1024 x 1024 13.7 -> 12.6 (12.0 -> 12.6), 512 x 1024 11.1 -> 11.7, 2048 x 640 14.8 -> 15.2 (12.9 -> 14.9), 3072 x 384 16.2 -> 18.4 (14.3 -> 18.0).
+        const size_t size = (size_t)d * D;
+        const bool large = size >= ROWS_MATRIX_MIN ||
+                           (MODE == ROWS_DENSE && size > ROWS_MATRIX_DENSE_MIN && D > ROWS_MATRIX_DENSE_ROWS);
+        const bool want = engine == ENGINE_MATRIX || (engine == ENGINE_AUTO && NB >= 8 && large);
         if (want) {
             p.kind = ROWS_MATRIX;
             p.min_chunk = MF_ROWS;
@@ -375,7 +384,7 @@ svdp_status launch_scores(const svdp_layer *L, const float *tpart, int nt, int B
 template <typename W, int NB, int MODE>
 bool prepare_rows(const svdp_layer *L)
 {
-    const RowsPlan p = plan_rows<W, NB>(L);
+    const RowsPlan p = plan_rows<W, NB, MODE>(L);
     if (p.kind == ROWS_SEQ) return grant_lds<k_rows_seq<W, NB, MODE>>(p.lds);
     if constexpr (std::is_same<W, bf16>::value) {
         if (p.kind == ROWS_MATRIX) return grant_lds<k_gate_up_mfma<NB, MODE>>(p.lds);
@@ -390,7 +399,7 @@ svdp_status launch_rows(const svdp_layer *L, const void *x, int B, const uint64_
                         const int32_t *nnz_in, int32_t *idx_out, int32_t *nnz_out, const Workspace &w, float *y,
                         hipStream_t st)
 {
-    const RowsPlan p = plan_rows<W, NB>(L);
+    const RowsPlan p = plan_rows<W, NB, MODE>(L);
     const int d = L->d, D = L->D;
     const W *Wg = static_cast<const W *>(L->W_gate), *Wu = static_cast<const W *>(L->W_up);
     const W *Wd = static_cast<const W *>(L->W_downT), *xs = static_cast<const W *>(x);

@@ -129,6 +129,30 @@ def test_rows_with_a_partial_line(d, D, B):
             assert torch.equal(binding.dense_ffn(L.with_flags(drelu | engine), x), yd) == same
 
 
+@pytest.mark.parametrize("d,D,dense,lists", [(512, 2560, True, False), (1024, 1088, True, False), (1024, 1024, False, False), (1000, 1088, True, False),
+                                             (2048, 832, True, False), (2048, 768, False, False), (1024, 960, False, False),
+                                             (4096, 512, True, True)])
+def test_size_from_which_rows_are_on_the_matrix_cores(d, D, dense, lists):
+    """The default engine at five and eight tokens, seen through bit patterns: over all rows above 1 M elements and 768 rows,
+    over a list from 2 M elements on."""
+    import torch
+    import oracle
+    from paper_2603_14110_amd import binding
+
+    L, x = layer(torch, binding, d, D, 16, 8, "bf16", d + D)
+    f = {k: L.tensors[k].float().cpu().numpy() for k in ("W_gate", "W_up", "W_downT")}
+    X = x.float().cpu().numpy()
+    M, V = L.with_flags(binding.FLAG_ENGINE_MATRIX), L.with_flags(binding.FLAG_ENGINE_VECTOR)
+    idx, nnz = torch.arange(D, dtype=torch.int32, device="cuda"), torch.tensor([D], dtype=torch.int32, device="cuda")
+    for B in (5, 8):
+        ref = oracle.dense_ffn(f["W_gate"], f["W_up"], f["W_downT"], X[:B])
+        slack = parity.fp32_forward_bound(f, X[:B], np.arange(D))
+        for call, matrix in ((lambda l: binding.dense_ffn(l, x[:B]), dense), (lambda l: binding.sparse_ffn(l, x[:B], idx, nnz), lists)):
+            y, ym, yv = call(L), call(M), call(V)
+            assert not torch.equal(ym, yv) and torch.equal(y, ym if matrix else yv)
+            parity.check_y(y.cpu().numpy(), ref, "bf16", slack=slack)
+
+
 @pytest.mark.parametrize("d,D", [(8, 64), (56, 320), (120, 4160), (1032, 2112), (2104, 1088)])
 def test_lists_with_a_partial_line(d, D):
     """Lists of the caller's own on the matrix cores, every batch size, rows that end inside a line: empty, one row, short and
