@@ -763,7 +763,9 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
     p += align_up(sizeof(SelectState));
     long long *hist = reinterpret_cast<long long *>(p);
     p += align_up((size_t)SEL_BINS * 8);
-    int32_t *lo = reinterpret_cast<int32_t *>(p);                // before the selection: dropped pairs at the start
+    int32_t *lo = reinterpret_cast<int32_t *>(p);
+    uint16_t *drop0 = reinterpret_cast<uint16_t *>(p);           // before the bounds: dropped pairs at the start
+    static_assert(CAL_MAX_T < 1 << 16, "drop0");
     p += align_up((size_t)D * 4);
     int32_t *up = reinterpret_cast<int32_t *>(p);
     int n2 = 1;
@@ -773,7 +775,7 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
         const size_t lds = calib_sort_lds<PER>(n2, MS);
         if (!grant_lds<k_calib_sort<PER>>(lds)) return SVDP_ERR_UNSUPPORTED;
         launch(k_calib_sort<PER>, dim3(D), dim3(CAL_THREADS), lds, st, w, s, T, n2, eta, MS, key, drop, tauc, k0,
-                           lo, kendall, reinterpret_cast<uint32_t *>(hist), SEL_BINS * 2, &work->readers, steps);
+                           drop0, kendall, reinterpret_cast<uint32_t *>(hist), SEL_BINS * 2, &work->readers, steps);
         return hip_status(hipSuccess);
     };
     svdp_status e = T <= 2 * CAL_THREADS ? sort(std::integral_constant<int, 2>{})
@@ -787,13 +789,13 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
     // (D T < 512 * 4096) fit 32 bits, and both lie in `hist`.
     auto select = [&](auto *first, auto *second) {
         using Bin = std::remove_pointer_t<decltype(first)>;
-        launch((k_select_hist<23, 8, -1, Bin>), dim3(hb + 1), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 0,
+        launch((k_select_hist<23, 8, -1, Bin>), dim3(hb), dim3(256), 0, st, key, drop, drop0, D, MS, (long long)need, 0,
                            work, second, first);
-        launch((k_select_hist<15, 8, 23, Bin>), dim3(hb), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 0, work,
+        launch((k_select_hist<15, 8, 23, Bin>), dim3(hb), dim3(256), 0, st, key, drop, drop0, D, MS, (long long)need, 0, work,
                            first, second);
-        launch((k_select_hist<7, 8, 15, Bin>), dim3(hb), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 1, work,
+        launch((k_select_hist<7, 8, 15, Bin>), dim3(hb), dim3(256), 0, st, key, drop, drop0, D, MS, (long long)need, 1, work,
                            second, first);
-        launch((k_select_hist<0, 7, 7, Bin>), dim3(hb), dim3(256), 0, st, key, drop, lo, D, MS, (long long)need, 2, work,
+        launch((k_select_hist<0, 7, 7, Bin>), dim3(hb), dim3(256), 0, st, key, drop, drop0, D, MS, (long long)need, 2, work,
                            first, second);
         launch(k_select_last<Bin>, dim3(1), dim3(64), 0, st, work, second);
     };

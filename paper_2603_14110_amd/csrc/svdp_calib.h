@@ -47,7 +47,7 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t u)
 //   drop [D][MS + 1] number of samples with s <= tau after 0, 1, 2, ... steps
 //   tauc [D][MS + 1] the threshold after 0, 1, 2, ... steps
 //   k0   [D]         the starting pointer (1-based count)
-//   drop0[D]         drop[.][0] once more, side by side
+//   drop0[D]         drop[.][0] once more, side by side (16 bits: T <= CAL_MAX_T)
 // Only the part of the order that the algorithm walks is sorted: everything below the first sample
 // with a positive weight (in the order by score, then sample index) is merely counted -- those
 // samples have zero weight and are dropped from the start -- and the rest, the "tail", typically a
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
                                                             int T, int n2max, int eta, int MS,
                                                             float *__restrict__ key, int32_t *__restrict__ drop,
                                                             float *__restrict__ tauc, int32_t *__restrict__ k0_out,
-                                                            int32_t *__restrict__ drop0, float *__restrict__ kendall,
+                                                            uint16_t *__restrict__ drop0, float *__restrict__ kendall,
                                                             uint32_t *__restrict__ clear0, int n_clear0,
                                                             uint32_t *__restrict__ clear1, int32_t *__restrict__ clear2)
 {
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calib_sort(const float *__restr
         }
         drop[(size_t)i * (MS + 1) + j] = dj;
         tauc[(size_t)i * (MS + 1) + j] = tj;
-        if (j == 0) drop0[i] = dj;
+        if (j == 0) drop0[i] = (uint16_t)dj;
     }
     if (tid == 0) k0_out[i] = k0;
     if (i == 0) {                                                  // what the selection counts in
@@ -466,12 +466,17 @@ __device__ __forceinline__ void select_add(uint32_t *at, long long v) { atomicAd
 // counts[digit] += gain over the steps whose key matches the prefix above this digit.  A thread takes SEL_RUN steps in a
 // row: a neuron's keys do not decrease, so they share few digits and most gains are added before they reach the (then
 // contended) counters.
-// FIRST: no digit is known; the launch's last block adds up drop0 instead, sets the start state and clears the other buffer.
+// FIRST: no digit is known.  Every block adds up drop0, 16 bits a neuron, while its first keys are on their way, and counts
+// nothing where the start meets the target already (a level below the share of zero weights); the first one sets the start
+// state and clears the other buffer.  Against one more block that adds up drop0 beside the counting, whole call in us, target
+// met: D = 18944, T = 1000, eta = 1 241 -> 159, D = 12544, T = 214, eta = 2 77.6 -> 64.3, D = 18944, T = 64, eta = 1 97 -> 78; steps
+// to take: D = 11008, T = 2048, eta = 16 148.2 -> 146.5, D = 6000, T = 800, eta = 1 142 -> 144.  (Every block a part of drop0, and no more
+// counting once all parts show it: 179, 78 and 99, and 149 and 147 with steps to take.)
 // Otherwise the digit before is worked out from `last` first, while the first keys are on their way.
 constexpr int SEL_RUN = 8;
 template <int SHIFT, int BITS, int LAST_SHIFT, typename Bin>
 __global__ __launch_bounds__(256) void k_select_hist(const float *__restrict__ key, const int32_t *__restrict__ drop,
-                                                     const int32_t *__restrict__ drop0, int D, int MS, long long need,
+                                                     const uint16_t *__restrict__ drop0, int D, int MS, long long need,
                                                      int which, SelectWork *__restrict__ work, Bin *__restrict__ last,
                                                      Bin *__restrict__ counts)
 {
@@ -481,20 +486,34 @@ __global__ __launch_bounds__(256) void k_select_hist(const float *__restrict__ k
     __shared__ SelectState now;
     __shared__ uint32_t arrived;
     const int tid = threadIdx.x;
-    int blocks = gridDim.x;
+    const int blocks = gridDim.x;
+    const size_t total = (size_t)D * MS, stride = (size_t)blocks * 256 * SEL_RUN;
+    size_t e0 = ((size_t)blockIdx.x * 256 + tid) * SEL_RUN;
+    uint32_t kb[SEL_RUN];
+    auto request = [&](size_t e) {
+#pragma unroll
+        for (int q = 0; q < SEL_RUN; ++q) kb[q] = e + q < total ? __float_as_uint(key[e + q]) : ~0u;
+    };
+    request(e0);                                // on their way while the digit before is worked out
+    lh[tid] = 0;
     if (FIRST) {
-        --blocks;
-        if ((int)blockIdx.x == blocks) {
-            long long c0 = 0;
-            constexpr int AHEAD = 16;
-            for (int i0 = tid; i0 < D; i0 += 256 * AHEAD) {
-                int32_t v[AHEAD];
+        const uint4 *v = reinterpret_cast<const uint4 *>(drop0);
+        const int nvec = D / 8;
+        constexpr int AHEAD = 8;
+        long long c0 = tid < D % 8 ? drop0[nvec * 8 + tid] : 0;
+        for (int g0 = tid; g0 < nvec; g0 += 256 * AHEAD) {
+            uint4 r[AHEAD];
+            uint32_t sum = 0u;
 #pragma unroll
-                for (int q = 0; q < AHEAD; ++q) v[q] = i0 + q * 256 < D ? drop0[i0 + q * 256] : 0;
+            for (int q = 0; q < AHEAD; ++q) r[q] = g0 + q * 256 < nvec ? v[g0 + q * 256] : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-                for (int q = 0; q < AHEAD; ++q) c0 += v[q];
-            }
-            c0 = block_sum_i64(c0, red);
+            for (int q = 0; q < AHEAD; ++q)
+                sum += (r[q].x & 0xffffu) + (r[q].x >> 16) + (r[q].y & 0xffffu) + (r[q].y >> 16) + (r[q].z & 0xffffu) +
+                       (r[q].z >> 16) + (r[q].w & 0xffffu) + (r[q].w >> 16);
+            c0 += sum;
+        }
+        c0 = block_sum_i64(c0, red);
+        if (blockIdx.x == 0) {
             last[tid] = 0;                      // the buffer of the second digit
             if (tid == 0) {
                 SelectState st;
@@ -505,18 +524,9 @@ __global__ __launch_bounds__(256) void k_select_hist(const float *__restrict__ k
                 st.at_start = c0 < need ? 0 : 1;
                 work->state[0] = st;
             }
-            return;
         }
+        if (c0 >= need) return;                 // in every block
     }
-    const size_t total = (size_t)D * MS, stride = (size_t)blocks * 256 * SEL_RUN;
-    size_t e0 = ((size_t)blockIdx.x * 256 + tid) * SEL_RUN;
-    uint32_t kb[SEL_RUN];
-    auto request = [&](size_t e) {
-#pragma unroll
-        for (int q = 0; q < SEL_RUN; ++q) kb[q] = e + q < total ? __float_as_uint(key[e + q]) : ~0u;
-    };
-    request(e0);                                // on their way while the digit before is worked out
-    lh[tid] = 0;
     if (!FIRST && tid < 64) {
         const SelectState st = select_pick<Bin>(work->state[which], last, LAST_SHIFT);
         if (tid == 0) {

@@ -378,3 +378,18 @@ def test_scores_with_heavy_tails(env, T, eta):
     s = s.astype(np.float32)
     for sp in (0.3, 0.9, 0.99):
         _check(env, w, s, eta, binding.calib_need(sp, D, T))
+
+
+@pytest.mark.parametrize("D,T,eta", [(3000, 400, 1), (257, 4096, 2), (20011, 54, 1)])
+def test_target_met_before_any_step(env, D, T, eta):
+    """Targets at, one below and one above the pairs that the start drops already, on more steps than one round of the first
+    digit's blocks takes; the call after one that stopped early finds nothing of it in the workspace."""
+    binding, torch, calib = env
+    assert D * -(-T // eta) > 256 * 256 * 8 or D < 512
+    rng = np.random.default_rng(D)
+    w, s = _stats(rng, D, T, dead=(0, D - 1))
+    start = calib.greedy_bias(w, s, 0, eta)
+    c0 = int((s <= -start["b"][:, None]).sum())
+    for need in (0, c0 - 1, c0, c0 + 1, c0 + 2000):
+        ref = _check(env, w, s, eta, need)
+        assert (ref["steps"] == 0) == (need <= c0)
