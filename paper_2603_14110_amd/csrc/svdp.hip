@@ -100,8 +100,8 @@ Workspace carve(void *base, int d, int D, int r, int NB)
 
 // Enqueues a kernel.  Straight to hipLaunchKernel: the <<<>>> form goes through a push and a pop of the launch
 // configuration besides (2.4 -> 2.25 us a launch of twenty arguments), and launches are what bounds small calls: a list of two
-// rows 9.7 -> 8.5 us, the step of d = 256, D = 1024 12.7 -> 11.6.  A refused launch is the last error, which
-// hip_status() reports.
+// rows 9.7 -> 8.5 us, the step of d = 256, D = 1024 12.7 -> 11.6 (10.5 to 12.5 by the host it runs on).  A refused launch is the
+// last error, which hip_status() reports.
 template <typename... P, typename... A>
 inline void launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t st, A &&...args)
 {

@@ -39,13 +39,20 @@ constexpr double EIG_PIECE = 8.0;           // largest degree of a piece of the 
 constexpr double EIG_SHIFT = 4e-13;         // of the first Cholesky QR pass (above k_chol_diag's bound of 1e-13)
 
 // Rows of the block for r wanted vectors: a quarter more (at least 32), so that the filter has a gap to work with, in
-// whole Jacobi strips; 0 where the Jacobi decomposition of all of G is the better way.  Whole call in ms, this / full, for a
-// mean of 0, 10, 1e4 times the spread, eigenvalues 10^(-6 i / r), exp(-i / d), all equal (handed over after one projection):
-//   d = 256, r = 64    3.9 / 3.5    6.6 / 3.5    4.1 / 3.2    3.1 / 8.7    4.2 / 3.4    5.0 / 3.1
-//   d = 512, r = 64    4.4 / 7.8    6.4 / 7.5    4.5 / 6.8    3.5 / 17     5.0 / 7.2    8.0 / 6.2
-//   d = 512, r = 200   8.1 / 7.5     13 / 7.4    8.9 / 6.8    7.3 / 17     8.9 / 7.3    9.9 / 6.1
-//   d = 1024, r = 400   17 / 18      28 / 18      19 / 16      14 / 37      19 / 17      21 / 13
-// so the largest block is about level on flat spectra and far ahead on decaying ones, and at n = 128 it loses on decaying ones (2.2 / 1.6).
+// whole Jacobi strips; 0 where the Jacobi decomposition of all of G is the better way.  Whole call in ms, this / full, for random
+// weights and tokens with a mean of 0, 10, 1e4 times their spread, weights with squared singular values 10^(-6 i / r), exp(-i / d),
+// 1 / (1 + i), and a gate matrix of 64 dominant directions with correlated tokens:
+//   d = 256, r = 64    3.8 / 3.8    5.2 / 3.5    4.2 / 3.1    3.3 / 8.8    3.9 / 3.4    5.4 / 3.7    4.0 / 4.5
+//   d = 512, r = 64    4.4 / 7.5    6.1 / 7.5    4.7 / 6.8    2.4 / 17     4.5 / 7.3    6.3 / 8.0    3.6 / 9.6
+//   d = 512, r = 200   8.3 / 7.5     12 / 7.4    8.9 / 6.8    6.5 / 17     8.2 / 7.3     16 / 7.9    8.8 / 9.6
+//   d = 1024, r = 256   12 / 18      20 / 18      13 / 16      12 / 37      12 / 17      20 / 19      11 / 24
+//   d = 1024, r = 400   18 / 18      31 / 18      19 / 16      13 / 37      18 / 17      31 / 19      20 / 24
+// The largest block (k = n / 2) is level on flat spectra, loses where a mean or a head of some ten to a hundred times the rest asks
+// for a second projection, and wins where the spectrum decays, on which the full decomposition takes all of its 24 sweeps: in
+// these, at most 2.0 times slower and up to 2.8 times faster, and which of the two is known after a projection, half of its
+// time.  At k = n / 3 it is behind on some (d = 384, r = 96 flat 6.2 / 5.5, 1 / (1 + i) 8.8 / 5.7), at n / 4 level or ahead on all.
+// At n = 128 it is behind on all but decaying spectra (r = 16: 2.0 / 1.8 flat, 2.8 / 1.8 with a mean of 10, 1.4 / 3.9 on
+// 10^(-6 i / r)).
 inline int eigtop_block(int n, int r)
 {
     const int k = round_up(r + std::max(32, r / 4), BJ_S);
@@ -54,12 +61,14 @@ inline int eigtop_block(int n, int r)
 
 // Rough times (us) of what the iteration and the full decomposition consist of, fitted to n = 256 .. 4096: a product of k
 // rows with G, one orthonormalisation, `sweeps` Jacobi sweeps over an m x m matrix.  The iteration goes on while what it
-// still needs is below the full decomposition's 14 sweeps (it takes 9 to 14; 9, d = 512, r = 200 and a mean of 10: 13.4 -> 19.1 ms,
-// handed over just before its end), and while it has not spent one and a half
-// times as much.  A limit on products alone (16 n rows) left out that at k = n / 2 the projections and orthonormalisations are
-// most of the time, and gave up blocks that were three products short:
-// whole call at d = 1024, r = 400, tokens with a mean of 10, 100, 1e4 times their spread 52, 46, 44 -> 33, 23, 22 ms (full
-// decomposition 29; eigenvalues exp(-i / d) 40 -> 25).
+// still needs is below the full decomposition's 14 sweeps (it takes 8 to 12 on flat spectra, 12 to 15 behind 64 dominant
+// directions, 24 on strongly decaying ones), and while it has not spent one and a half times as much.  Nine or eleven sweeps
+// there end it just before it is done: d = 512, r = 200 and a mean of 10: 11.8 -> 16.6 / 11.8 ms, 1 / (1 + i): 15.7 -> 17.1 / 20.7;
+// d = 1024, r = 400: 31 -> 44 / 44, 30 -> 40 / 45; no case gains.
+// Tried: handing over after the first projection where the pieces are short (a second one will be needed): d = 1024, r = 400 and
+// a mean of 10 31 -> 26, 1 / (1 + i) 30 -> 27, but d = 512, r = 128 and a mean of 10 9.7 -> 10.6, d = 256, r = 64 and a mean of 3
+// 4.0 -> 5.6.  A limit on products alone (16 n rows) left out that at k = n / 2 the projections and orthonormalisations are
+// most of the time, and gave up blocks that were three products short.
 inline double eig_product_us(int k, int n) { return 6.0 + 5e-8 * k * (double)n * n; }
 inline double eig_orthonormalize_us(int k) { return 40.0 + 0.8 * k; }
 inline double eig_jacobi_us(int m, int sweeps) { return sweeps * (m / BJ_B - 1) * (40.0 + 9e-6 * m * (double)m); }

@@ -325,7 +325,9 @@ constexpr int SCM_THREADS = 256;
 constexpr int SCM_KB = 16;          // column blocks of Q held in registers
 constexpr int SCM_NT = 4;           // partials of t requested together
 
-// a and b as hi + mid + lo each, two bf16 to a word.  WIDE: also where an element is infinite or NaN (then hi, with
+// a and b as hi + mid + lo each, two bf16 to a word.  Rounded by the packed conversion instead of
+// in integer arithmetic (step of bf16 d = 512, D = 2240, r = 24, four tokens 17.3 -> 16.6 us, d = 1024, D = 4096, r = 256, three
+// tokens 18.0 -> 17.5).  WIDE: also where an element is infinite or NaN (then hi, with
 // mid = lo = 0) or rounds past the largest bf16 (then hi is that).
 constexpr float BF16_MAX = 0x1.fep127f;
 template <bool WIDE>
