@@ -16,9 +16,9 @@
 // the wanted vectors together end below EIG_TOL (where they stop falling first: 5 EIG_TOL) of the SMALLEST wanted eigenvalue.
 // Against singular values worked out with 64-bit mantissas (d = 256, r = 40, tokens with a mean of 10 to 3e6 times their
 // spread; geometric spectra over up to twelve decades): within 4e-12 each, the product within 2e-9 of sigma_r.
-// Measured (bf16, whole call), full Jacobi -> this: d = 4096, r = 256: 467 -> 42 ms (56 products of 256 to 320 x 4096 x 4096 at
-// 0.16 to 0.22 ms, two projections of 11 Jacobi sweeps together, G once more); d = 1024, r = 64: 47 -> 4.3 ms;
-// d = 2560, r = 640: 183 -> 53 ms.  With b fixed between projections and pieces as long as the condition number allowed, the
+// Measured (bf16, 64 dominant directions, whole call), full Jacobi -> this: d = 4096, r = 256: 311 -> 39.5 ms (56 products of 256
+// to 320 x 4096 x 4096 at 0.16 to 0.22 ms, two projections, G once more); d = 1024, r = 64: 24 -> 2.9 ms; d = 2560, r = 640:
+// 105 -> 46 ms.  With b fixed between projections and pieces as long as the condition number allowed, the
 // first took three projections: b starts at 0.65 of where it ends, which costs three quarters of the filter's rate.  With
 // EIG_SETTLED = 1e-13 a projection more was needed at d = 512, r = 128 (9.1 against 6.2 ms): vectors that share a strip of the
 // projected matrix with the largest are left with that much.
