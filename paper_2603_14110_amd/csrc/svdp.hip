@@ -322,12 +322,12 @@ svdp_status launch_xP(const svdp_layer *L, const void *x, int B, float *tpart, i
     const size_t lds = xp_lds<W, NB>(L);
     if (glue != nullptr) {
         launch((k_xP<W, NB, true>), dim3(nt, ncs), dim3(XP_THREADS), lds, st, static_cast<const W *>(L->P),
-                           static_cast<const W *>(x), B, d, r, tpart, glue->y_prev, glue->shift, glue->eps,
-                           static_cast<W *>(glue->x_out));
+               static_cast<const W *>(x), B, d, r, tpart, glue->y_prev, glue->shift, glue->eps,
+               static_cast<W *>(glue->x_out));
     } else {
         launch((k_xP<W, NB, false>), dim3(nt, ncs), dim3(XP_THREADS), lds, st,
-                           static_cast<const W *>(L->P), static_cast<const W *>(x), B, d, r, tpart, nullptr, nullptr,
-                           0.f, nullptr);
+               static_cast<const W *>(L->P), static_cast<const W *>(x), B, d, r, tpart, nullptr, nullptr,
+               0.f, nullptr);
     }
     *nt_out = nt;
     return hip_status(hipSuccess);
@@ -368,14 +368,14 @@ svdp_status launch_scores(const svdp_layer *L, const float *tpart, int nt, int B
     const size_t lds = scores_lds<W, NB>(L);
     if (scores_on_matrix<W, NB>(L)) {
         launch((k_scores_mfma<W, NB>), dim3(L->D / SC_SLAB), dim3(SCM_THREADS), lds, st,
-                           static_cast<const W *>(L->Q), L->b, tpart, nt, B, L->D, L->r, s_out, mask_out);
+               static_cast<const W *>(L->Q), L->b, tpart, nt, B, L->D, L->r, s_out, mask_out);
         return hip_status(hipSuccess);
     }
     // block size: 512 threads for one or two tokens (short critical path), 256 for larger batches
     // (fewer wavefronts repeating the per-wave overhead); measured on the 7B and Mistral shapes
     with_scores_kernel<W, NB>(L, [&](auto k) {
         launch(decltype(k)::value, dim3(L->D / SC_SLAB), dim3(scores_threads<NB>()), lds, st,
-                           static_cast<const W *>(L->Q), L->b, tpart, nt, B, L->D, L->r, s_out, mask_out);
+               static_cast<const W *>(L->Q), L->b, tpart, nt, B, L->D, L->r, s_out, mask_out);
         return 0;
     });
     return hip_status(hipSuccess);
@@ -412,28 +412,28 @@ svdp_status launch_rows(const svdp_layer *L, const void *x, int B, const uint64_
             float *hbuf = reinterpret_cast<float *>(region + split_h_offset(d, NB));
             int32_t *lst = reinterpret_cast<int32_t *>(region + split_list_offset(d, D, NB));
             launch((k_gate_up_mfma<NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, xs, B,
-                               d, D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags,
-                               hbuf, lst);
+                   d, D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags,
+                   hbuf, lst);
             launch((k_down_slices<NB, MODE == ROWS_DENSE>), dim3((d + DS_SW - 1) / DS_SW, DOWN_RG), dim3(DS_THREADS), 0, st,
-                               Wd, lst, MODE == ROWS_DENSE ? nullptr : w.nnz, D, D, d, hbuf, DOWN_MIN_CHUNK, w.ypart);
+                   Wd, lst, MODE == ROWS_DENSE ? nullptr : w.nnz, D, D, d, hbuf, DOWN_MIN_CHUNK, w.ypart);
         }
     }
     if (matrix) {
         // launched above
     } else if (p.kind == ROWS_SEQ) {
         launch((k_rows_seq<W, NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, Wd, xs, B,
-                           d, D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags,
-                           w.ypart);
+               d, D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags,
+               w.ypart);
     } else {
         launch((k_rows<W, NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, Wd, xs, B, d,
-                           D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags, w.ypart);
+               D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags, w.ypart);
     }
     if (y != nullptr) {
         const int vpt = d / 4;
         const int blocks = B * ((vpt + RED_COLS - 1) / RED_COLS);
         launch(k_reduce_y, dim3(blocks), dim3(RED_COLS * RED_SEGS), 0, st, w.ypart,
-                           MODE == ROWS_DENSE ? nullptr : w.nnz, D, D, p.split ? DOWN_RG : ROWS_BLOCKS,
-                           p.split ? DOWN_MIN_CHUNK : p.min_chunk, NB, B, d, y);
+               MODE == ROWS_DENSE ? nullptr : w.nnz, D, D, p.split ? DOWN_RG : ROWS_BLOCKS,
+               p.split ? DOWN_MIN_CHUNK : p.min_chunk, NB, B, d, y);
     }
     return hip_status(hipSuccess);
 }
@@ -459,8 +459,8 @@ svdp_status launch_predict_small(const svdp_layer *L, const void *x, float *s, u
 {
     auto go = [&](auto lpr) {
         launch((k_predict_small<W, decltype(lpr)::value>), dim3(L->D / SC_SLAB), dim3(PS_THREADS),
-                           ps_lds<W>(L->d, L->r), st, static_cast<const W *>(L->P), static_cast<const W *>(L->Q), L->b,
-                           static_cast<const W *>(x), L->d, L->r, s, mask);
+               ps_lds<W>(L->d, L->r), st, static_cast<const W *>(L->P), static_cast<const W *>(L->Q), L->b,
+               static_cast<const W *>(x), L->d, L->r, s, mask);
         return hip_status(hipSuccess);
     };
     switch (scores_lpr_log2<W>(L)) {                  // r <= 32 PS_TILES: at most 32 column groups
@@ -699,10 +699,10 @@ svdp_status svdp_stack_glue(const void *x, const float *y, const float *shift, i
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (dtype == SVDP_F32)
         launch(k_stack_glue<float>, dim3(1), dim3(256), 0, st, static_cast<const float *>(x), y, shift,
-                           d, eps, static_cast<float *>(x_next));
+               d, eps, static_cast<float *>(x_next));
     else
         launch(k_stack_glue<bf16>, dim3(1), dim3(256), 0, st, static_cast<const bf16 *>(x), y, shift, d,
-                           eps, static_cast<bf16 *>(x_next));
+               eps, static_cast<bf16 *>(x_next));
     return hip_status(hipSuccess);
 }
 
@@ -775,7 +775,7 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
         const size_t lds = calib_sort_lds<PER>(n2, MS);
         if (!grant_lds<k_calib_sort<PER>>(lds)) return SVDP_ERR_UNSUPPORTED;
         launch(k_calib_sort<PER>, dim3(D), dim3(CAL_THREADS), lds, st, w, s, T, n2, eta, MS, key, drop, tauc, k0,
-                           drop0, kendall, reinterpret_cast<uint32_t *>(hist), SEL_BINS * 2, &work->readers, steps);
+               drop0, kendall, reinterpret_cast<uint32_t *>(hist), SEL_BINS * 2, &work->readers, steps);
         return hip_status(hipSuccess);
     };
     svdp_status e = T <= 2 * CAL_THREADS ? sort(std::integral_constant<int, 2>{})
@@ -790,13 +790,13 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
     auto select = [&](auto *first, auto *second) {
         using Bin = std::remove_pointer_t<decltype(first)>;
         launch((k_select_hist<23, 8, -1, Bin>), dim3(hb), dim3(256), 0, st, key, drop, drop0, D, MS, (long long)need, 0,
-                           work, second, first);
+               work, second, first);
         launch((k_select_hist<15, 8, 23, Bin>), dim3(hb), dim3(256), 0, st, key, drop, drop0, D, MS, (long long)need, 0, work,
-                           first, second);
+               first, second);
         launch((k_select_hist<7, 8, 15, Bin>), dim3(hb), dim3(256), 0, st, key, drop, drop0, D, MS, (long long)need, 1, work,
-                           second, first);
+               second, first);
         launch((k_select_hist<0, 7, 7, Bin>), dim3(hb), dim3(256), 0, st, key, drop, drop0, D, MS, (long long)need, 2, work,
-                           first, second);
+               first, second);
         launch(k_select_last<Bin>, dim3(1), dim3(64), 0, st, work, second);
     };
     static_assert(CAL_MAX_T <= 4096 && SEL_BINS * 8 <= 512 * 4, "see above");
@@ -811,7 +811,7 @@ svdp_status svdp_calib_bias(const float *w, const float *s, int32_t D, int32_t T
     const int chunk = (int)(((long long)D + 256 * SEL_BINS - 1) / (256 * SEL_BINS)) * 256, blocks = (D + chunk - 1) / chunk;
     launch(k_select_bounds, dim3(blocks), dim3(256), 0, st, key, drop, D, MS, chunk, state, lo, up, hist);
     launch(k_select_finish, dim3(blocks), dim3(256), 0, st, lo, up, drop, tauc, k0, D, T, eta, MS, chunk, state, hist,
-                       b, k, steps);
+           b, k, steps);
     return hip_status(hipSuccess);
 }
 
@@ -845,7 +845,7 @@ svdp_status svdp_calib_stats(const svdp_layer *layer, const void *X, int32_t T, 
 
     if (!grant_lds<k_gemm_wide>(GW_LDS)) return SVDP_ERR_UNSUPPORTED;
     launch(k_transpose16, dim3(tiles(r, 32), tiles(d, 32)), dim3(256), 0, st,
-                       static_cast<const uint16_t *>(layer->P), d, r, reinterpret_cast<uint16_t *>(Pt));
+           static_cast<const uint16_t *>(layer->P), d, r, reinterpret_cast<uint16_t *>(Pt));
     // t = X P, split into three terms.  Its tiles alone are few (32 at r = 256, T = 2048: 90 us on an eighth of the chip,
     // 16 + 5 us in eight parts), so they are cut along K into as many parts as fill it; the parts meet in s, which the
     // last launch overwrites.
@@ -856,11 +856,11 @@ svdp_status svdp_calib_stats(const svdp_layer *layer, const void *X, int32_t T, 
     const int nx = tiles(r, GM_BN), ny = tiles(T, GM_BM), norm_blocks = tiles(D, NORM_ROWS);
     if (nz > 1) {
         launch((k_gemm_nt<EPI_PLAIN>), dim3(nx * ny * nz + norm_blocks), dim3(GM_THREADS), 0, st, Xb, d, Pt, d, T, r, d,
-                           s, nullptr, r, kpart, nx, ny, nz, norm);
+               s, nullptr, r, kpart, nx, ny, nz, norm);
         launch(k_sum_split3, dim3(tiles(T * r, 256)), dim3(256), 0, st, s, nz, T, r, tp);
     } else {
         launch((k_gemm_nt<EPI_SPLIT3>), dim3(nx * ny + norm_blocks), dim3(GM_THREADS), 0, st, Xb, d, Pt, d, T, r, d,
-                           nullptr, tp, 3 * r, d, nx, ny, 1, norm);
+               nullptr, tp, 3 * r, d, nx, ny, 1, norm);
     }
     // w = (ReLU(W_gate X^T) * (W_up X^T))^2 * cn and s = Q t^T over the three terms
     const bf16 *Qb = static_cast<const bf16 *>(layer->Q), *tb = reinterpret_cast<const bf16 *>(tp);

@@ -36,7 +36,7 @@ template <typename TA, DgLayout LA, typename TB, DgLayout LB, int WM, int WN, in
                                          : (flags & DG_K_FROM_N) ? dim3(tm, tn, nz) : dim3(tn, tm, nz);
     if (nz > 1) {
         launch(kernel, grid, dim3(DG_THREADS), lds, st, A.p, A.ld, B.p, B.ld, scr.p, N, M, N, K, kpart, flags,
-                           DgEpilogue{});
+               DgEpilogue{});
         launch(k_dgemm_sum, grid1((size_t)M * N), dim3(256), 0, st, scr.p, nz, C, ldc, M, N, flags, ep);
     } else {
         launch(kernel, grid, dim3(DG_THREADS), lds, st, A.p, A.ld, B.p, B.ld, C, ldc, M, N, K, kpart, flags, ep);
