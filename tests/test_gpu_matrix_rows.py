@@ -112,7 +112,8 @@ def test_matrix_engine_arbitrary_lists(env, shape):
                 assert not y.any()
 
 
-# (d, D, r, B): ranks the score kernel on the matrix cores takes (multiples of 32 up to 512) and two it does not
+# (d, D, r, B): ranks the score kernel on the matrix cores takes below three tokens as well (multiples of 32 up to 512) and two
+# that it takes from three tokens on only
 SCORE_SHAPES = [(256, 1024, 32, 1), (512, 2048, 128, 8), (264, 640, 256, 5), (512, 4096, 320, 3), (128, 832, 512, 8),
                 (128, 256, 544, 4), (96, 192, 48, 2), (1024, 3072, 256, 7)]
 
