@@ -13,6 +13,10 @@ DEPS = [SRC, os.path.join(os.path.dirname(HERE), "include", "svdp.h")] + sorted(
 LIB = os.path.join(HERE, "libsvdp.so")
 # a matrix product that the device refused must not go unnoticed ([[nodiscard]])
 WARNINGS = ["-Wall", "-Wno-unused-function", "-Werror=unused-result"]
+# The first fourteen words of a kernel's arguments come in scalar registers with the launch (what the target has room for), instead
+# of by loads at the kernel's start that everything else waits for: 0.2 to 0.3 us a launch.  7B step 17.74 -> 16.93 us, eight
+# stacked layers 200.1 -> 189.8, ragged list 13.24 -> 12.86, greedy bias 145.8 -> 143.3.
+PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 PROBE_SRC = os.path.join(HERE, "csrc", "svdp_probe.hip")
 PROBE_LIB = os.path.join(HERE, "libsvdp_probe.so")
 
@@ -23,7 +27,7 @@ def hipcc_path() -> str:
 
 def _hipcc(src: str, out: str, verbose: bool) -> None:
     cmd = [hipcc_path(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", *WARNINGS, "-o", out, src]
+           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", *PRELOAD, *WARNINGS, "-o", out, src]
     if verbose:
         print(" ".join(cmd))
     subprocess.run(cmd, check=True)
