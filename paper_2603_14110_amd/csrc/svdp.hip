@@ -28,8 +28,6 @@ namespace {
 using namespace svdp;
 
 constexpr int XP_MAX_BLOCKS = 128;    // stage-1 row slabs of P (d <= 16384)
-constexpr int ROWS_BLOCKS = 256;      // row-kernel blocks: one chunk of the row list and one partial y each (128 to
-                                      // 512 were measured; 256 is best for every batch size)
 constexpr size_t ALIGN = 256;
 constexpr size_t LDS_DEFAULT = 64 * 1024;     // dynamic LDS a kernel may use without asking
 constexpr size_t LDS_MAX = 160 * 1024;        // LDS of one gfx950 compute unit
@@ -193,10 +191,8 @@ struct RowsPlan {
     bool split;         // gate/up kernel, then the down projection over column slices (k_down_slices)
 };
 
-// Split organisation: parts of the list per column slice, fewest rows of a part, and where its buffers lie
-// inside the workspace's partial-y region [ROWS_BLOCKS][NB][d]: the RG partial y's, then h [D][NB], then the list [D].
-constexpr int DOWN_RG = 8;
-constexpr int DOWN_MIN_CHUNK = 64;
+// Split organisation: where its buffers lie inside the workspace's partial-y region [ROWS_BLOCKS][NB][d]: the DOWN_RG partial
+// y's, then h [D][NB], then the list [D].
 inline size_t split_h_offset(int d, int NB) { return align_up((size_t)DOWN_RG * NB * d * 4); }
 inline size_t split_list_offset(int d, int D, int NB) { return split_h_offset(d, NB) + align_up((size_t)D * NB * 4); }
 inline bool split_fits(int d, int D, int NB)
@@ -373,9 +369,11 @@ svdp_status launch_scores(const svdp_layer *L, const float *tpart, int nt, int B
     }
     // block size: 512 threads for one or two tokens (short critical path), 256 for larger batches
     // (fewer wavefronts repeating the per-wave overhead); measured on the 7B and Mistral shapes
+    // threads per float4 column of t: no more than there are partials to add
+    const int npg = std::max(1, std::min(scores_threads<NB>() / (NB * L->r / 4), nt));
     with_scores_kernel<W, NB>(L, [&](auto k) {
         launch(decltype(k)::value, dim3(L->D / SC_SLAB), dim3(scores_threads<NB>()), lds, st,
-               static_cast<const W *>(L->Q), L->b, tpart, nt, B, L->D, L->r, s_out, mask_out);
+               static_cast<const W *>(L->Q), L->b, tpart, nt, npg, L->r, B, mask_out, s_out, L->D);
         return 0;
     });
     return hip_status(hipSuccess);
@@ -429,11 +427,11 @@ svdp_status launch_rows(const svdp_layer *L, const void *x, int B, const uint64_
                D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags, w.ypart);
     }
     if (y != nullptr) {
-        const int vpt = d / 4;
-        const int blocks = B * ((vpt + RED_COLS - 1) / RED_COLS);
-        launch(k_reduce_y, dim3(blocks), dim3(RED_COLS * RED_SEGS), 0, st, w.ypart,
-               MODE == ROWS_DENSE ? nullptr : w.nnz, D, D, p.split ? DOWN_RG : ROWS_BLOCKS,
-               p.split ? DOWN_MIN_CHUNK : p.min_chunk, NB, B, d, y);
+        // all rows: the number of partial outputs is known here
+        const int min_chunk = p.split ? DOWN_MIN_CHUNK : p.min_chunk, G = p.split ? DOWN_RG : ROWS_BLOCKS;
+        const int chunk = std::max(min_chunk, (D + G - 1) / G), parts = (D + chunk - 1) / chunk;
+        launch(k_reduce_y, dim3((d / 4 + RED_COLS - 1) / RED_COLS, B), dim3(RED_COLS * RED_SEGS), 0, st, w.ypart,
+               MODE == ROWS_DENSE ? nullptr : w.nnz, y, parts, NB, d);
     }
     return hip_status(hipSuccess);
 }

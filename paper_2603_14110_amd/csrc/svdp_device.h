@@ -58,6 +58,24 @@ __device__ __forceinline__ void load_vec(const bf16 *p, float (&v)[8])
     v[6] = __uint_as_float(q.w << 16); v[7] = __uint_as_float(q.w & 0xffff0000u);
 }
 
+// A range of memory with its length: 16-byte loads at or past `bytes` give zeros.  What a branch around a load would do, without
+// one: the compiler waits for every load that it finds inside a branch before the next one is requested (or at the join), so
+// that loads meant to be on their way together went one by one.  p and bytes are the same in all lanes of a wave; a 16-byte
+// vector lies inside or outside as a whole.
+constexpr uint32_t OUTSIDE = 0xfffffff0u;       // an offset past every range
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t range_of(const void *p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ uint4 load_range(__amdgpu_buffer_rsrc_t range, uint32_t at)
+{
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(range, at, 0, 0));
+}
+__device__ __forceinline__ float4 as_float4(const uint4 &q)
+{
+    return make_float4(__uint_as_float(q.x), __uint_as_float(q.y), __uint_as_float(q.z), __uint_as_float(q.w));
+}
+
 // Raw 16-byte load (issued early, widened later) and its widening to fp32.
 template <typename W>
 __device__ __forceinline__ uint4 load_raw(const W *p)
@@ -140,6 +158,19 @@ __device__ __forceinline__ int wave_inclusive_scan(int v)
     return s;
 }
 
+// v plus the value of the lane whose number differs by 16 (32): the swap of a register's odd and even rows (halves) with itself,
+// without the LDS round trip of a shuffle.
+__device__ __forceinline__ float add_xor16(float v)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_xor32(float v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Sum over aligned groups of 2^LOG2 consecutive lanes; every lane of a group
 // gets the group's sum.  Butterfly order, fixed.
 template <int LOG2>
@@ -149,8 +180,8 @@ __device__ __forceinline__ float group_sum(float v)
     if (LOG2 >= 2) v += dpp_move<0x4E>(v);
     if (LOG2 >= 3) v += dpp_move<0x141>(v);
     if (LOG2 >= 4) v += dpp_move<0x140>(v);
-    if (LOG2 >= 5) v += __shfl_xor(v, 16);
-    if (LOG2 >= 6) v += __shfl_xor(v, 32);
+    if (LOG2 >= 5) v = add_xor16(v);
+    if (LOG2 >= 6) v = add_xor32(v);
     return v;
 }
 

@@ -17,6 +17,10 @@ constexpr int ROWS_THREADS = 512;    // k_rows block
 constexpr int ROWS_WAVES = ROWS_THREADS / 64;
 constexpr int ROWS_UB = 4;           // row kernels: rows of W_downT fetched together (the LDS row capacity is padded to this)
 constexpr int SCAN_THREADS = 1024;   // k_compact_scan block
+constexpr int ROWS_BLOCKS = 256;     // row-kernel blocks: one chunk of the row list and one partial y each (128 to
+                                     // 512 were measured; 256 is best for every batch size)
+constexpr int SC_TL = 4;             // k_scores: partials of t that a thread requests together
+constexpr int SC_PG = 7;             // k_scores: sums of t read together
 constexpr int RED_COLS = 8;          // k_reduce_y: float4 columns per block (one 128-byte line per partial row)
 constexpr int RED_SEGS = 64;         // k_reduce_y: segments of the partial list per block
 
@@ -209,20 +213,21 @@ __global__ __launch_bounds__(256) void k_tsum(const float *__restrict__ tpart, i
 // neurons, then (optionally) the 64-bit mask word of the slab:
 // bit j = OR over tokens of [s > 0]   (eq. 2's H; the union over the batch).
 // A group of LPR = 2^LPR_LOG2 lanes owns every NGRP-th row of the slab; a lane
-// owns the column groups lig, lig+LPR, ... of its rows.  The rows' first column
-// groups are requested first; then t is assembled from the nt stage-1 partials
-// (threads split the partial list, all loads in flight, fixed combination
-// order through LDS), so the memory latencies overlap.
+// owns the column groups lig, lig+LPR, ... of its rows.
+// Bound: one trip to memory and the hand-overs behind it.  The nt stage-1 partials of t are requested first (npg threads per
+// column share them, SC_TL at a time and thread), then the rows' first column groups, so that t is put together (fixed order,
+// through LDS) while Q is on its way; the first SC_TL are added outside of the loop over further ones, because a wait inside
+// of it would be for Q as well.  7B step 18.1 -> 16.8 us with this and k_reduce_y's loads together, eight stacked layers 199.8 ->
+// 190.0 (loops of one load and one add each, two trips here and up to four there; sums in LDS read one by one).
 // SC_THREADS is 512 for one or two tokens (short critical path) and 256 for larger
 // batches (fewer wavefronts repeating the per-wave overhead).
 // Dynamic LDS: NB*r + NB*64 + max(SC_THREADS*4, NB*r) floats.
 // ---------------------------------------------------------------------------
 template <typename W, int NB, int LPR_LOG2, int SC_THREADS>
-__global__ __launch_bounds__(SC_THREADS) void k_scores(const W *__restrict__ Q,
+__global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 4))) void k_scores(const W *__restrict__ Q,
                                                        const float *__restrict__ bias,
-                                                       const float *__restrict__ tpart, int nt, int B,
-                                                       int D, int r, float *__restrict__ s_out,
-                                                       uint64_t *__restrict__ mask_out)
+                                                       const float *__restrict__ tpart, int nt, int npg, int r, int B,
+                                                       uint64_t *__restrict__ mask_out, float *__restrict__ s_out, int D)
 {
     constexpr int VEC = Elem<W>::VEC;
     constexpr int LPR = 1 << LPR_LOG2;              // lanes per row: 8, 16, 32 or 64
@@ -237,37 +242,70 @@ __global__ __launch_bounds__(SC_THREADS) void k_scores(const W *__restrict__ Q,
     const int lig = tid & (LPR - 1);
     const int grp = tid >> LPR_LOG2;
     const int cg = r / VEC;
-    const float my_bias = tid < SC_SLAB ? bias[i0 + tid] : 0.f;     // added after the row sums
 
-    // first column group of each of this group's rows
+    // t: thread (pg, cq) adds the partials pg, pg + npg, ... of its float4 column; npg > 1 only where one pass has room for all
+    const int ncq = NB * r / 4;
+    const __amdgpu_buffer_rsrc_t parts = range_of(tpart, (uint32_t)nt * ncq * 16);
+    uint4 tq[SC_TL];
+    int pg = 0, cq = tid;
+    if (npg > 1) {                     // tid / ncq, tid < 512
+        pg = (int)(((float)tid + 0.5f) * __builtin_amdgcn_rcpf((float)ncq));
+        cq = tid - pg * ncq;
+    }
+    auto request_t = [&](int k0) {
+#pragma unroll
+        for (int k = 0; k < SC_TL; ++k)
+            tq[k] = load_range(parts, pg < npg && cq < ncq ? (uint32_t)((pg + (k0 + k) * npg) * ncq + cq) * 16u : OUTSIDE);
+    };
+    auto add_t = [&](float4 s) {
+#pragma unroll
+        for (int k = 0; k < SC_TL; ++k) {
+            const float4 p = as_float4(tq[k]);
+            s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+        }
+        return s;
+    };
+    request_t(0);
+
+    // first column group of each of this group's rows, and the bias (added after the row sums)
     uint4 raw[RPG];
     const bool has_rows = NGRP <= SC_SLAB || grp < SC_SLAB;
     const W *qrow = Q + (size_t)(i0 + (has_rows ? grp : 0)) * r + (lig < cg ? lig : 0) * VEC;
 #pragma unroll
     for (int k = 0; k < RPG; ++k) raw[k] = load_raw(qrow + (size_t)k * NGRP * r);
+    const float my_bias = bias[i0 + (tid & (SC_SLAB - 1))];
+    __builtin_amdgcn_sched_barrier(0);
 
     {   // t = sum of the stage-1 partials
-        const int ncq = NB * r / 4;                        // float4 columns of t
-        const int npg = max(1, SC_THREADS / ncq);          // threads per column
-        const float4 *tp4 = reinterpret_cast<const float4 *>(tpart);
         float4 *tsp4 = reinterpret_cast<float4 *>(tsp);
-        for (int it = tid; it < ncq * npg; it += SC_THREADS) {
-            const int cq = it % ncq, pg = it / ncq;
-            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 8
-            for (int g = pg; g < nt; g += npg) {
-                const float4 p = tp4[(size_t)g * ncq + cq];
-                s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+        auto finish_t = [&](float4 s) {
+            for (int k0 = SC_TL; k0 * npg < nt; k0 += SC_TL) {
+                request_t(k0);
+                s = add_t(s);
             }
-            tsp4[pg * ncq + cq] = s;
+            if (pg < npg && cq < ncq) tsp4[pg * ncq + cq] = s;
+        };
+        finish_t(add_t(make_float4(0.f, 0.f, 0.f, 0.f)));          // apart from the loop: waits for its own loads only
+        if (npg == 1) {
+            for (int c0 = SC_THREADS; c0 < ncq; c0 += SC_THREADS) {
+                cq = c0 + tid;
+                request_t(0);
+                finish_t(add_t(make_float4(0.f, 0.f, 0.f, 0.f)));
+            }
         }
         __syncthreads();
         float4 *ts4 = reinterpret_cast<float4 *>(ts);
         for (int c = tid; c < ncq; c += SC_THREADS) {
             float4 s = tsp4[c];
-            for (int pg = 1; pg < npg; ++pg) {
-                const float4 p = tsp4[pg * ncq + c];
-                s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+            for (int q0 = 1; q0 < npg; q0 += SC_PG) {
+                float4 p[SC_PG];
+#pragma unroll
+                for (int k = 0; k < SC_PG; ++k) p[k] = tsp4[min(q0 + k, npg - 1) * ncq + c];
+#pragma unroll
+                for (int k = 0; k < SC_PG; ++k) {
+                    const bool in = q0 + k < npg;
+                    s.x += in ? p[k].x : 0.f; s.y += in ? p[k].y : 0.f; s.z += in ? p[k].z : 0.f; s.w += in ? p[k].w : 0.f;
+                }
             }
             ts4[c] = s;
         }
@@ -313,22 +351,17 @@ __global__ __launch_bounds__(SC_THREADS) void k_scores(const W *__restrict__ Q,
         }
     __syncthreads();
     if (tid < SC_SLAB) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b) sc[b * SC_SLAB + tid] += my_bias;
-    }
-    __syncthreads();
-
-    if (s_out != nullptr) {
-        for (int c = tid; c < NB * SC_SLAB; c += SC_THREADS) {
-            const int b = c / SC_SLAB, n = c % SC_SLAB;
-            if (b < B) s_out[(size_t)b * D + i0 + n] = sc[c];
-        }
-    }
-    if (mask_out != nullptr && tid < 64) {
         bool on = false;
-        for (int b = 0; b < B; ++b) on = on || (sc[b * SC_SLAB + tid] > 0.f);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const float v = sc[b * SC_SLAB + tid] + my_bias;
+            if (b < B) {
+                on = on || v > 0.f;
+                if (s_out != nullptr) s_out[(size_t)b * D + i0 + tid] = v;
+            }
+        }
         const uint64_t m = __ballot(on);
-        if (tid == 0) mask_out[blockIdx.x] = m;
+        if (mask_out != nullptr && tid == 0) mask_out[blockIdx.x] = m;
     }
 }
 
@@ -557,7 +590,7 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     const int hi = min(n, lo + chunk);
     const int cnt = hi - lo;
     if (blockIdx.x == 0 && tid == 0) {
-        if (MODE != ROWS_DENSE) *n_used = n;
+        if (MODE != ROWS_DENSE) *reinterpret_cast<int2 *>(n_used) = make_int2(n, active_blocks(n, chunk));
         if (MODE == ROWS_MASK && nnz_out != nullptr) *nnz_out = n;
     }
     if (cnt <= 0) return;
@@ -700,44 +733,40 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
 // the deterministic down-projection reduction, App. C).
 // A block owns RED_COLS float4 columns (one 128-byte line) of one token; the list
 // of partials is cut into RED_SEGS contiguous segments summed by different
-// threads (all loads in flight at once); the eight segments of a wave are then
+// threads (at most four partials each, requested together); the eight segments of a wave are then
 // combined with lane shifts, the eight waves through LDS.  The order depends
-// only on the number of partials.
+// only on the number of partials: used[1] where a list was used (the row kernels leave its length and that there), else `parts`.
+// Bound: two dependent trips, the number and the partials.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float seg8_sum(float v)
 {
     v += dpp_move<0x128>(v);        // row_ror:8  -> lanes l and l^8
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
+    return add_xor32(add_xor16(v));
 }
 
 __global__ __launch_bounds__(RED_COLS *RED_SEGS) void k_reduce_y(const float *__restrict__ ypart,
-                                                                 const int32_t *__restrict__ n_ptr, int n_fixed,
-                                                                 int D, int G, int min_chunk, int NB, int B, int d,
-                                                                 float *__restrict__ y)
+                                                                 const int32_t *__restrict__ used, float *__restrict__ y,
+                                                                 int parts, int NB, int d)
 {
     static_assert(RED_COLS == 8, "a wave holds 8 columns x 8 segments");
+    constexpr int PER = ROWS_BLOCKS / RED_SEGS;                    // most partials of a segment
     __shared__ float4 wred[RED_COLS * RED_SEGS / 64][RED_COLS];
-    int n = n_ptr != nullptr ? *n_ptr : n_fixed;
-    n = max(0, min(n, D));
-    const int gact = active_blocks(n, chunk_of(n, G, min_chunk));
-    const int vpt = d / 4;
-    const int bpt = (vpt + RED_COLS - 1) / RED_COLS;
-    const int b = blockIdx.x / bpt;
+    const int gact = used != nullptr ? used[1] : parts;
+    const int vpt = d / 4, b = blockIdx.y;
     const int c = threadIdx.x % RED_COLS, seg = threadIdx.x / RED_COLS;
-    const int v = (blockIdx.x % bpt) * RED_COLS + c;
+    const int v = blockIdx.x * RED_COLS + c;
     const int per = (gact + RED_SEGS - 1) / RED_SEGS;
-    const int g0 = seg * per, g1 = min(gact, g0 + per);
+    const int g0 = seg * per, g1 = v < vpt ? min(gact, g0 + per) : 0;
+    const __amdgpu_buffer_rsrc_t all = range_of(ypart, (uint32_t)(ROWS_BLOCKS * NB) * vpt * 16);
+    uint4 p[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        p[q] = load_range(all, g0 + q < g1 ? (uint32_t)(((g0 + q) * NB + b) * vpt + v) * 16u : OUTSIDE);
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (v < vpt) {
-        const float4 *src = reinterpret_cast<const float4 *>(ypart) + (size_t)b * vpt + v;
-        const size_t stride = (size_t)NB * vpt;
-#pragma unroll 4
-        for (int g = g0; g < g1; ++g) {
-            const float4 p = src[(size_t)g * stride];
-            s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
-        }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const float4 f = as_float4(p[q]);
+        s.x += f.x; s.y += f.y; s.z += f.z; s.w += f.w;
     }
     s.x = seg8_sum(s.x); s.y = seg8_sum(s.y); s.z = seg8_sum(s.z); s.w = seg8_sum(s.w);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -747,8 +776,8 @@ __global__ __launch_bounds__(RED_COLS *RED_SEGS) void k_reduce_y(const float *__
         float4 t = wred[0][c];
 #pragma unroll
         for (int q = 1; q < RED_COLS * RED_SEGS / 64; ++q) {
-            const float4 p = wred[q][c];
-            t.x += p.x; t.y += p.y; t.z += p.z; t.w += p.w;
+            const float4 w = wred[q][c];
+            t.x += w.x; t.y += w.y; t.z += w.z; t.w += w.w;
         }
         reinterpret_cast<float4 *>(y)[(size_t)b * vpt + v] = t;
     }

@@ -26,6 +26,8 @@ namespace svdp {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 constexpr int MF_ROWS = 16;      // list rows per tile
+constexpr int DOWN_RG = 8;       // k_down_slices: parts of the list per column slice (= partial outputs) ...
+constexpr int DOWN_MIN_CHUNK = 64;     // ... and fewest rows of a part
 constexpr int MF_UA = 4;         // 64-element steps fetched together
 
 __device__ __forceinline__ f32x4_t mfma_bf16(const uint4 &a, const uint4 &b, f32x4_t c)
@@ -75,7 +77,8 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
     const int hi = min(n, lo + chunk);
     const int cnt = hi - lo;
     if (blockIdx.x == 0 && tid == 0) {
-        if (MODE != ROWS_DENSE) *n_used = n;
+        if (MODE != ROWS_DENSE)
+            *reinterpret_cast<int2 *>(n_used) = make_int2(n, active_blocks(n, chunk_of(n, DOWN_RG, DOWN_MIN_CHUNK)));
         if (MODE == ROWS_MASK && nnz_out != nullptr) *nnz_out = n;
     }
     if (cnt <= 0) return;

@@ -60,7 +60,7 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     const int hi = min(n, lo + chunk);
     const int cnt = hi - lo;
     if (blockIdx.x == 0 && tid == 0) {
-        if (MODE != ROWS_DENSE) *n_used = n;
+        if (MODE != ROWS_DENSE) *reinterpret_cast<int2 *>(n_used) = make_int2(n, active_blocks(n, chunk));
         if (MODE == ROWS_MASK && nnz_out != nullptr) *nnz_out = n;
     }
     if (cnt <= 0) return;
