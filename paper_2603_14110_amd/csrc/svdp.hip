@@ -208,14 +208,13 @@ constexpr int ROWS_MATRIX_DENSE_ROWS = 3 * ROWS_BLOCKS;
 template <typename W, int NB, int MODE = ROWS_MASK>
 RowsPlan plan_rows(const svdp_layer *L)
 {
-    const int d = L->d, D = L->D, G = ROWS_BLOCKS;
-    const int per = (D + G - 1) / G;
+    const int d = L->d, D = L->D;
     RowsPlan p;
     p.split = false;
     if ((L->flags & SVDP_FLAG_REVALIDATE) != 0) {
         p.kind = ROWS_SEQ;
-        p.min_chunk = 4;
-        p.max_chunk = round_up(per > p.min_chunk ? per : p.min_chunk, ROWS_UB);
+        p.min_chunk = ROWS_MIN_CHUNK;
+        p.max_chunk = rows_max_chunk(D, p.min_chunk, ROWS_UB);
         p.lds = (size_t)NB * d * sizeof(W) + ((size_t)2 * NB * p.max_chunk + (size_t)3 * p.max_chunk) * 4;
         return p;
     }
@@ -239,7 +238,7 @@ RowsPlan plan_rows(const svdp_layer *L)
         if (want) {
             p.kind = ROWS_MATRIX;
             p.min_chunk = MF_ROWS;
-            p.max_chunk = round_up(per > p.min_chunk ? per : p.min_chunk, MF_ROWS);
+            p.max_chunk = rows_max_chunk(D, MF_ROWS, MF_ROWS);
             p.lds = (size_t)NB * round_up(d, 64) * 2 + ((size_t)ROWS_WAVES * p.max_chunk * 2 * NB + p.max_chunk) * 4;
             p.split = true;
             if (p.lds <= LDS_MAX && split_fits(d, D, NB)) return p;
@@ -247,8 +246,8 @@ RowsPlan plan_rows(const svdp_layer *L)
         }
     }
     p.kind = ROWS_VECTOR;
-    p.min_chunk = 4;
-    p.max_chunk = round_up(per > p.min_chunk ? per : p.min_chunk, ROWS_UB);
+    p.min_chunk = ROWS_MIN_CHUNK;
+    p.max_chunk = rows_max_chunk(D, p.min_chunk, ROWS_UB);
     p.lds = (size_t)NB * d * sizeof(W) + ((size_t)NB * p.max_chunk + p.max_chunk) * 4;
     return p;
 }
@@ -401,6 +400,8 @@ svdp_status launch_rows(const svdp_layer *L, const void *x, int B, const uint64_
     const int d = L->d, D = L->D;
     const W *Wg = static_cast<const W *>(L->W_gate), *Wu = static_cast<const W *>(L->W_up);
     const W *Wd = static_cast<const W *>(L->W_downT), *xs = static_cast<const W *>(x);
+    const void *list = MODE == ROWS_MASK ? static_cast<const void *>(mask) : idx_in;
+    const int dB = d | B << 16;                 // d <= 16384: the kernels' arguments that come in registers are few
     bool matrix = false;
     if constexpr (std::is_same<W, bf16>::value) {
         matrix = p.kind == ROWS_MATRIX;
@@ -409,9 +410,8 @@ svdp_status launch_rows(const svdp_layer *L, const void *x, int B, const uint64_
             char *region = reinterpret_cast<char *>(w.ypart);
             float *hbuf = reinterpret_cast<float *>(region + split_h_offset(d, NB));
             int32_t *lst = reinterpret_cast<int32_t *>(region + split_list_offset(d, D, NB));
-            launch((k_gate_up_mfma<NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, xs, B,
-                   d, D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags,
-                   hbuf, lst);
+            launch((k_gate_up_mfma<NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, xs, list, Wg, Wu, nnz_in, dB,
+                   D, L->flags, idx_out, nnz_out, w.nnz, hbuf, lst);
             launch((k_down_slices<NB, MODE == ROWS_DENSE>), dim3((d + DS_SW - 1) / DS_SW, DOWN_RG), dim3(DS_THREADS), 0, st,
                    Wd, lst, MODE == ROWS_DENSE ? nullptr : w.nnz, D, D, d, hbuf, DOWN_MIN_CHUNK, w.ypart);
         }
@@ -419,12 +419,11 @@ svdp_status launch_rows(const svdp_layer *L, const void *x, int B, const uint64_
     if (matrix) {
         // launched above
     } else if (p.kind == ROWS_SEQ) {
-        launch((k_rows_seq<W, NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, Wd, xs, B,
-               d, D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags,
-               w.ypart);
+        launch((k_rows_seq<W, NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, xs, list, Wg, Wu, Wd, nnz_in, dB, D,
+               L->flags, idx_out, nnz_out, w.nnz, w.ypart);
     } else {
-        launch((k_rows<W, NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, Wg, Wu, Wd, xs, B, d,
-               D, mask, idx_in, nnz_in, idx_out, nnz_out, w.nnz, p.max_chunk, p.min_chunk, L->flags, w.ypart);
+        launch((k_rows<W, NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, xs, list, Wg, Wu, Wd, nnz_in, dB, D,
+               L->flags, idx_out, nnz_out, w.nnz, w.ypart);
     }
     if (y != nullptr) {
         // all rows: the number of partial outputs is known here

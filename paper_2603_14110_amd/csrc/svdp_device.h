@@ -71,6 +71,10 @@ __device__ __forceinline__ uint4 load_range(__amdgpu_buffer_rsrc_t range, uint32
 {
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(range, at, 0, 0));
 }
+__device__ __forceinline__ uint64_t load_range_8(__amdgpu_buffer_rsrc_t range, uint32_t at)
+{
+    return __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(range, at, 0, 0));
+}
 __device__ __forceinline__ float4 as_float4(const uint4 &q)
 {
     return make_float4(__uint_as_float(q.x), __uint_as_float(q.y), __uint_as_float(q.z), __uint_as_float(q.w));

@@ -434,6 +434,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_compact_scan(const uint64_t *_
 //                nonzero, without a separate launch) and extracts its own
 //                part of the ascending list; when idx_out / nnz_out are given
 //                each block also writes its part of the list there.
+// `list` is idx_in or mask; dB = d | B << 16 (arguments beyond the first fourteen words are not there at the start).
 // The list of n rows is cut into gridDim.x contiguous chunks; block g handles
 // chunk g:
 //   phase A: one wave per row: g = W_gate[i].x, u = W_up[i].x (wave reduction),
@@ -441,8 +442,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_compact_scan(const uint64_t *_
 //   phase B: every thread owns 16-byte column groups of the output and adds
 //            h * W_downT[i][cols] over the chunk in list order -> ypart[g].
 //            The first rows of W_downT are requested before phase A starts.
-// Blocks with an empty chunk write nothing; block 0 records n for k_reduce_y.
-// max_chunk (the LDS row capacity) is a multiple of ROWS_UB.
+// Blocks with an empty chunk write no partial y; block 0 records n and the number of partials for k_reduce_y.
+// The LDS row capacity is a multiple of ROWS_UB.
 // Dynamic LDS: NB*d storage elements (x as stored), NB*max_chunk floats, max_chunk ints.
 // ---------------------------------------------------------------------------
 enum RowsMode { ROWS_DENSE = 0, ROWS_LIST = 1, ROWS_MASK = 2 };
@@ -454,6 +455,13 @@ enum RowsMode { ROWS_DENSE = 0, ROWS_LIST = 1, ROWS_MASK = 2 };
 // eight, measured; four costs the step nothing, because the sum of the partials gains what the
 // row kernel loses, and halves the partial-y traffic of short lists.)
 __device__ __forceinline__ int chunk_of(int n, int G, int min_chunk) { return max(min_chunk, (n + G - 1) / G); }
+constexpr int ROWS_MIN_CHUNK = 4;   // of k_rows and k_rows_seq
+// LDS row capacity of a block of a row kernel: its share of all D rows, in whole groups.
+__host__ __device__ constexpr int rows_max_chunk(int D, int min_chunk, int group)
+{
+    const int per = (D + ROWS_BLOCKS - 1) / ROWS_BLOCKS, most = per > min_chunk ? per : min_chunk;
+    return (most + group - 1) / group * group;
+}
 // Blocks that get rows (= partial y's written).
 __device__ __forceinline__ int active_blocks(int n, int chunk) { return n > 0 ? (n + chunk - 1) / chunk : 0; }
 
@@ -461,28 +469,38 @@ __device__ __forceinline__ int active_blocks(int n, int chunk) { return n > 0 ? 
 // by itself (lane l owns the wpl consecutive words starting at l*wpl), so no block-wide
 // step is needed; lane_first is the list position of the lane's first set bit.  The
 // lane's first ROWS_WREG words stay in registers (held[]) for rows_list_from_mask.
-constexpr int ROWS_WREG = 4;        // covers D <= 16384
+constexpr int ROWS_WREG = 8;        // covers D <= 32768; the second half is only asked for where D > 16384
 template <int MODE>
-__device__ __forceinline__ int rows_list_length(int D, const uint64_t *__restrict__ mask,
-                                                const int32_t *__restrict__ nnz_in, int lane, int &lane_first,
-                                                int &wpl, uint64_t (&held)[ROWS_WREG])
+__device__ __forceinline__ void rows_request_mask(int D, const void *__restrict__ list, int lane, int &wpl,
+                                                  uint64_t (&held)[ROWS_WREG])
 {
-    lane_first = 0;
-    wpl = 0;
-    if (MODE == ROWS_DENSE) return D;
-    if (MODE == ROWS_LIST) return max(0, min(*nnz_in, D));
     const int nwords = D / 64;
     wpl = (nwords + 63) / 64;
+#pragma unroll
+    for (int j = 0; j < ROWS_WREG; ++j) held[j] = 0ull;
+    if (MODE != ROWS_MASK) return;
+    const __amdgpu_buffer_rsrc_t words = range_of(list, (uint32_t)nwords * 8);
+#pragma unroll
+    for (int j = 0; j < ROWS_WREG / 2; ++j) held[j] = load_range_8(words, j < wpl ? (uint32_t)(lane * wpl + j) * 8u : OUTSIDE);
+    if (wpl > ROWS_WREG / 2) {
+#pragma unroll
+        for (int j = ROWS_WREG / 2; j < ROWS_WREG; ++j)
+            held[j] = load_range_8(words, j < wpl ? (uint32_t)(lane * wpl + j) * 8u : OUTSIDE);
+    }
+}
+template <int MODE>
+__device__ __forceinline__ int rows_list_length(int D, const void *__restrict__ list, const int32_t *__restrict__ nnz_in,
+                                                int lane, int wpl, const uint64_t (&held)[ROWS_WREG], int &lane_first)
+{
+    lane_first = 0;
+    if (MODE == ROWS_DENSE) return D;
+    if (MODE == ROWS_LIST) return max(0, min(*nnz_in, D));
     int c = 0;
 #pragma unroll
-    for (int j = 0; j < ROWS_WREG; ++j) {
-        const int k = lane * wpl + j;
-        held[j] = (j < wpl && k < nwords) ? mask[k] : 0ull;
-        c += __popcll(held[j]);
-    }
+    for (int j = 0; j < ROWS_WREG; ++j) c += __popcll(held[j]);
     for (int j = ROWS_WREG; j < wpl; ++j) {
         const int k = lane * wpl + j;
-        if (k < nwords) c += __popcll(mask[k]);
+        if (k < D / 64) c += __popcll(static_cast<const uint64_t *>(list)[k]);
     }
     const int inc = wave_inclusive_scan(c);
     lane_first = inc - c;
@@ -512,7 +530,7 @@ __device__ __forceinline__ void rows_list_word(uint64_t w, int j, int wpl, int l
     }
     p += pc;
 }
-__device__ __forceinline__ void rows_list_from_mask(int D, const uint64_t *__restrict__ mask, int lane,
+__device__ __forceinline__ void rows_list_from_mask(int D, const void *__restrict__ list, int lane,
                                                     int lane_first, int wpl, const uint64_t (&held)[ROWS_WREG], int lo,
                                                     int hi, int *lidx)
 {
@@ -523,7 +541,7 @@ __device__ __forceinline__ void rows_list_from_mask(int D, const uint64_t *__res
         if (j < wpl) rows_list_word(held[j], j, wpl, lane, p, lo, hi, lidx);
     for (int j = ROWS_WREG; j < wpl; ++j) {
         const int k = lane * wpl + j;
-        rows_list_word(k < nwords ? mask[k] : 0ull, j, wpl, lane, p, lo, hi, lidx);
+        rows_list_word(k < nwords ? static_cast<const uint64_t *>(list)[k] : 0ull, j, wpl, lane, p, lo, hi, lidx);
     }
 }
 
@@ -531,158 +549,195 @@ __device__ __forceinline__ void rows_list_from_mask(int D, const uint64_t *__res
 // [0, D) become -1 and are skipped by every row kernel: they contribute nothing), from the mask
 // words (wave 0), or the block's own range of all rows.  Ends with a block barrier.
 template <int MODE>
-__device__ __forceinline__ void rows_block_list(int D, const uint64_t *__restrict__ mask,
-                                                const int32_t *__restrict__ idx_in, int lane_first, int wpl,
+__device__ __forceinline__ void rows_block_list(int D, const void *__restrict__ list, int lane_first, int wpl,
                                                 const uint64_t (&held)[ROWS_WREG], int lo, int hi, int *lidx)
 {
     const int tid = threadIdx.x, cnt = hi - lo;
     if (MODE == ROWS_LIST) {
         for (int q = tid; q < cnt; q += blockDim.x) {
-            const int i = idx_in[lo + q];
+            const int i = static_cast<const int32_t *>(list)[lo + q];
             lidx[q] = (unsigned)i < (unsigned)D ? i : -1;
         }
     } else if (MODE == ROWS_MASK) {
-        if (tid < 64) rows_list_from_mask(D, mask, tid, lane_first, wpl, held, lo, hi, lidx);
+        if (tid < 64) rows_list_from_mask(D, list, tid, lane_first, wpl, held, lo, hi, lidx);
     } else {
         for (int q = tid; q < cnt; q += blockDim.x) lidx[q] = lo + q;
     }
     __syncthreads();
 }
 
-template <typename W, int NB, int MODE>
-__global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_rows(
-    const W *__restrict__ Wg, const W *__restrict__ Wu, const W *__restrict__ WdT, const W *__restrict__ x, int B,
-    int d, int D, const uint64_t *__restrict__ mask, const int32_t *__restrict__ idx_in,
-    const int32_t *__restrict__ nnz_in, int32_t *__restrict__ idx_out, int32_t *__restrict__ nnz_out,
-    int32_t *__restrict__ n_used, int max_chunk, int min_chunk, uint32_t flags, float *__restrict__ ypart)
+// x [B][d] as stored into xraw [NB][nvec] (zeros beyond B), in two halves: the first ROWS_XV vectors of a thread are
+// requested behind whatever the caller asked for before and stored once that has been used; rows longer than that follow in a loop.
+constexpr int ROWS_XV = 2;
+template <typename W, int NB>
+__device__ __forceinline__ void rows_request_x(const W *__restrict__ x, int B, int d, int v0, uint4 (&xv)[ROWS_XV][NB])
 {
     constexpr int VEC = Elem<W>::VEC;
-    constexpr int UA = NB <= 2 ? 8 : 4;     // 16-byte loads in flight per matrix in phase A
+    const __amdgpu_buffer_rsrc_t tokens = range_of(x, (uint32_t)(B * d) * sizeof(W));
+#pragma unroll
+    for (int k = 0; k < ROWS_XV; ++k)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int v = v0 + threadIdx.x + k * ROWS_THREADS;
+            xv[k][b] = load_range(tokens, v * VEC < d ? (uint32_t)(b * d + v * VEC) * sizeof(W) : OUTSIDE);
+        }
+}
+
+// Bound: for a short list, the trips: mask and x, the rows, the partial outputs' way out; for a long one the stream.  So each phase
+// asks for everything it will need before it waits: the first rows of W_downT before phase A, a row's vectors of both
+// matrices at once and the next row's before this one's sums are taken, two groups of W_downT rows in turn.  (The requests stand outside
+// of branches, as ranges that end where the row does: a branch there made the compiler wait for each.)
+// Against loads in branches, two of them waited for one by one and the rest of a row in two trips: dense FFN of 5120 x 13824
+// 82.0 -> 76.7 us, step of 3584 x 18944, four tokens (33 % of the rows) 54.9 -> 51.6, ragged list of 1507 rows 12.4 -> 11.9, eight
+// stacked 7B layers 190.0 -> 183.
+template <typename W, int NB, int MODE>
+__global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(2, 4))) void k_rows(
+    const W *__restrict__ x, const void *__restrict__ list, const W *__restrict__ Wg, const W *__restrict__ Wu,
+    const W *__restrict__ WdT, const int32_t *__restrict__ nnz_in, int dB, int D, uint32_t flags, int32_t *__restrict__ idx_out,
+    int32_t *__restrict__ nnz_out, int32_t *__restrict__ n_used, float *__restrict__ ypart)
+{
+    constexpr int VEC = Elem<W>::VEC;
+    constexpr int UA = 8;                   // 16-byte loads in flight per matrix in phase A
     constexpr int UB = ROWS_UB;             // rows of W_downT per group in phase B
     extern __shared__ uint4 smem16[];
-    const int nvec = d / VEC;
+    const int d = dB & 0xffff, B = NB == 1 ? 1 : dB >> 16;
+    const int nvec = d / VEC, max_chunk = rows_max_chunk(D, ROWS_MIN_CHUNK, UB);
     uint4 *xraw = smem16;                                        // [NB][nvec] x in storage form
     float *hs = reinterpret_cast<float *>(xraw + NB * nvec);     // [NB][max_chunk]
     int *lidx = reinterpret_cast<int *>(hs + NB * max_chunk);    // [max_chunk]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int G = gridDim.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // ---- request x (as stored, no conversion; rows of a batch beyond B are zero).  The first
-    // vector of every token stays in registers until the list is known, so that the request
-    // for the mask words below is in flight together with it ----
-    uint4 xfirst[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-        xfirst[b] = (b < B && tid < nvec) ? load_raw(x + (size_t)b * d + (size_t)tid * VEC) : make_uint4(0u, 0u, 0u, 0u);
-
-    // ---- the list: n, this block's chunk [lo, hi) ----
+    // ---- request the mask words, then x ----
     int lane_first, wpl;
     uint64_t held[ROWS_WREG];
-    const int n = rows_list_length<MODE>(D, mask, nnz_in, lane, lane_first, wpl, held);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        if (tid < nvec) xraw[b * nvec + tid] = xfirst[b];
-        for (int v = tid + ROWS_THREADS; v < nvec; v += ROWS_THREADS)
-            xraw[b * nvec + v] = b < B ? load_raw(x + (size_t)b * d + (size_t)v * VEC) : make_uint4(0u, 0u, 0u, 0u);
-    }
-    const int chunk = chunk_of(n, G, min_chunk);
+    rows_request_mask<MODE>(D, list, lane, wpl, held);
+    uint4 xv[ROWS_XV][NB];
+    rows_request_x<W, NB>(x, B, d, 0, xv);
+
+    // ---- the list: n, this block's chunk [lo, hi) ----
+    const int n = rows_list_length<MODE>(D, list, nnz_in, lane, wpl, held, lane_first);
+    const int chunk = chunk_of(n, ROWS_BLOCKS, ROWS_MIN_CHUNK);
     const int lo = min(n, (int)blockIdx.x * chunk);
     const int hi = min(n, lo + chunk);
     const int cnt = hi - lo;
-    if (blockIdx.x == 0 && tid == 0) {
-        if (MODE != ROWS_DENSE) *reinterpret_cast<int2 *>(n_used) = make_int2(n, active_blocks(n, chunk));
-        if (MODE == ROWS_MASK && nnz_out != nullptr) *nnz_out = n;
+    // written at the kernel's end: a wait for loads waits for the stores in front of them too
+    auto store_list = [&] {
+        if (blockIdx.x == 0 && tid == 0) {
+            if (MODE != ROWS_DENSE) *reinterpret_cast<int2 *>(n_used) = make_int2(n, active_blocks(n, chunk));
+            if (MODE == ROWS_MASK && nnz_out != nullptr) *nnz_out = n;
+        }
+        if (MODE == ROWS_MASK && idx_out != nullptr)
+            for (int q = tid; q < cnt; q += ROWS_THREADS) idx_out[lo + q] = lidx[q];
+    };
+    if (cnt <= 0) {
+        store_list();
+        return;
     }
-    if (cnt <= 0) return;
 
-    // h of the positions past the chunk's end (phase B works in whole groups of UB rows)
-    const int ngroups = (cnt + UB - 1) / UB;
-    for (int i = cnt + tid; i < ngroups * UB; i += ROWS_THREADS)
+    for (int v0 = 0; v0 < nvec; v0 += ROWS_XV * ROWS_THREADS) {
+        if (v0 != 0) rows_request_x<W, NB>(x, B, d, v0, xv);
 #pragma unroll
-        for (int b = 0; b < NB; ++b) hs[b * max_chunk + i] = 0.f;
-    rows_block_list<MODE>(D, mask, idx_in, lane_first, wpl, held, lo, hi, lidx);
-    if (MODE == ROWS_MASK && idx_out != nullptr)
-        for (int q = tid; q < cnt; q += ROWS_THREADS) idx_out[lo + q] = lidx[q];
+        for (int k = 0; k < ROWS_XV; ++k)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const int v = v0 + tid + k * ROWS_THREADS;
+                if (v < nvec) xraw[b * nvec + v] = xv[k][b];
+            }
+    }
+    // h of the positions past the chunk's end (phase B works in whole groups of UB rows)
+    __shared__ __align__(16) float h_none[UB];
+    if (tid < UB) h_none[tid] = 0.f;
+    const int ngroups = (cnt + UB - 1) / UB;
+    if (tid < ngroups * UB - cnt) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) hs[b * max_chunk + cnt + tid] = 0.f;
+    }
+    rows_block_list<MODE>(D, list, lane_first, wpl, held, lo, hi, lidx);
 
     const bool drelu = (flags & 1u) != 0;
-    // row q of the chunk, or -1 (past the end; a rejected entry of the caller's list)
-    auto row_of = [&](int q) -> int { return q < cnt ? (MODE == ROWS_DENSE ? lo + q : lidx[q]) : -1; };
-    auto down_piece = [&](int q, const W *colp) -> uint4 {      // the same branch for every thread of the block
-        const int row = row_of(q);
-        uint4 piece = make_uint4(0u, 0u, 0u, 0u);
-        if (row >= 0) piece = load_raw(colp + (size_t)row * d);
-        return piece;
+    const uint32_t row_bytes = (uint32_t)d * sizeof(W);
+    // row i of a matrix; nothing at all where i < 0 (past the end; a rejected entry of the caller's list)
+    auto row_range = [&](const W *M, int i) { return range_of(M + (size_t)max(i, 0) * d, i >= 0 ? row_bytes : 0u); };
+    // rows UB g .. UB g + UB - 1 of the chunk, at byte `at` of each; zeros past the end
+    auto fetch = [&](int g, uint32_t at, uint4 (&piece)[UB]) {
+        static_assert(UB == 4, "one 16-byte read of the list");
+        int row[UB];
+        if (MODE == ROWS_DENSE) {
+#pragma unroll
+            for (int k = 0; k < UB; ++k) row[k] = lo + g * UB + k;
+        } else {
+            const int4 r4 = *reinterpret_cast<const int4 *>(lidx + min(g, ngroups - 1) * UB);
+            row[0] = __builtin_amdgcn_readfirstlane(r4.x);
+            row[1] = __builtin_amdgcn_readfirstlane(r4.y);
+            row[2] = __builtin_amdgcn_readfirstlane(r4.z);
+            row[3] = __builtin_amdgcn_readfirstlane(r4.w);
+        }
+#pragma unroll
+        for (int k = 0; k < UB; ++k) piece[k] = load_range(row_range(WdT, g * UB + k < cnt ? row[k] : -1), at);
     };
-
     // ---- request the first group of W_downT rows for this thread's first column group ----
-    uint4 cur[UB];
-    if (tid < nvec) {
-#pragma unroll
-        for (int k = 0; k < UB; ++k) cur[k] = down_piece(k, WdT + (size_t)tid * VEC);
-    }
+    uint4 pa[UB], pb[UB];
+    fetch(0, (uint32_t)tid * 16u, pa);
 
-    // ---- phase A: one wave per row; the row's 16-byte vectors are fetched UA at a time per
-    // matrix and lane (the whole row at once when d <= 64*UA*VEC) ----
-    for (int q = wave; q < cnt; q += ROWS_WAVES) {
-        const int row = row_of(q);
-        float ag[NB], au[NB];
+    // ---- phase A: one wave per row, 64 UA vectors of both matrices at a time ----
+    uint4 rg[UA], ru[UA];
+    auto request = [&](int q, int vb) {
+        const int row = __builtin_amdgcn_readfirstlane(MODE == ROWS_DENSE ? lo + q : lidx[q]);
+        const __amdgpu_buffer_rsrc_t g = row_range(Wg, row), u = row_range(Wu, row);
+        const uint32_t at = (uint32_t)(vb + lane) * 16u;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) ag[b] = au[b] = 0.f;
-        if (row >= 0) {
-            const W *g = Wg + (size_t)row * d;
-            const W *u = Wu + (size_t)row * d;
-            // whole batches of UA vectors per matrix and lane, then one batch with a ragged end
-            int vb = 0;
-            for (; vb + 64 * UA <= nvec; vb += 64 * UA) {
-                uint4 rg[UA], ru[UA];
+        for (int k = 0; k < UA / 2; ++k) {
+            rg[k] = load_range(g, at + k * 1024);
+            ru[k] = load_range(u, at + k * 1024);
+        }
+        if (vb + UA / 2 * 64 < nvec) {
 #pragma unroll
-                for (int k = 0; k < UA; ++k) {
-                    rg[k] = load_raw(g + (size_t)(vb + k * 64 + lane) * VEC);
-                    ru[k] = load_raw(u + (size_t)(vb + k * 64 + lane) * VEC);
-                }
-#pragma unroll
-                for (int k = 0; k < UA; ++k) {
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) {
-                        const uint4 xv = xraw[b * nvec + vb + k * 64 + lane];
-                        ag[b] = dot_raw(rg[k], xv, ag[b], (const W *)nullptr);
-                        au[b] = dot_raw(ru[k], xv, au[b], (const W *)nullptr);
-                    }
-                }
-            }
-            if (vb < nvec) {
-                uint4 rg[UA], ru[UA];
-#pragma unroll
-                for (int k = 0; k < UA; ++k) {
-                    const int v = vb + k * 64 + lane;
-                    rg[k] = ru[k] = make_uint4(0u, 0u, 0u, 0u);
-                    if (v < nvec) {
-                        rg[k] = load_raw(g + (size_t)v * VEC);
-                        ru[k] = load_raw(u + (size_t)v * VEC);
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < UA; ++k) {
-                    const int v = min(vb + k * 64 + lane, nvec - 1);      // a zero weight vector meets any x
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) {
-                        const uint4 xv = xraw[b * nvec + v];
-                        ag[b] = dot_raw(rg[k], xv, ag[b], (const W *)nullptr);
-                        au[b] = dot_raw(ru[k], xv, au[b], (const W *)nullptr);
-                    }
-                }
+            for (int k = UA / 2; k < UA; ++k) {
+                rg[k] = load_range(g, at + k * 1024);
+                ru[k] = load_range(u, at + k * 1024);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (wave < cnt) request(wave, 0);
+    float ag[NB], au[NB];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const float gs = wave_sum(ag[b]);
-            const float us = wave_sum(au[b]);
-            if (lane == 0) {
-                const float gp = fmaxf(gs, 0.f);
-                const float uu = drelu ? fmaxf(us, 0.f) : us;
-                hs[b * max_chunk + q] = row >= 0 ? gp * uu : 0.f;
+    for (int b = 0; b < NB; ++b) ag[b] = au[b] = 0.f;
+    for (int q = wave, vb = 0; q < cnt;) {
+        auto half = [&](int k0) {
+#pragma unroll
+            for (int k = k0; k < k0 + UA / 2; ++k) {
+                const int v = min(vb + k * 64 + lane, nvec - 1);          // a zero weight vector meets any x
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const uint4 xq = xraw[b * nvec + v];
+                    ag[b] = dot_raw(rg[k], xq, ag[b], (const W *)nullptr);
+                    au[b] = dot_raw(ru[k], xq, au[b], (const W *)nullptr);
+                }
+            }
+        };
+        half(0);
+        if (vb + UA / 2 * 64 < nvec) half(UA / 2);
+        const bool whole = vb + UA * 64 >= nvec;                     // the row is done
+        const int nq = whole ? q + ROWS_WAVES : q, nvb = whole ? 0 : vb + UA * 64;
+        if (nq < cnt) request(nq, nvb);
+        if (whole) {
+            const bool valid = MODE != ROWS_LIST || lidx[q] >= 0;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const float gs = wave_sum(ag[b]);
+                const float us = wave_sum(au[b]);
+                if (lane == 0) {
+                    const float gp = fmaxf(gs, 0.f);
+                    const float uu = drelu ? fmaxf(us, 0.f) : us;
+                    hs[b * max_chunk + q] = valid ? gp * uu : 0.f;
+                }
+                ag[b] = au[b] = 0.f;
             }
         }
+        q = nq;
+        vb = nvb;
     }
     __syncthreads();
 
@@ -693,30 +748,36 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int e = 0; e < VEC; ++e) acc[b][e] = 0.f;
-        const W *colp = WdT + (size_t)v * VEC;
-        if (v != tid) {
+        const uint32_t at = (uint32_t)v * 16u;
+        auto add = [&](int g, const uint4 (&piece)[UB]) {
+            float h[NB][UB];
 #pragma unroll
-            for (int k = 0; k < UB; ++k) cur[k] = down_piece(k, colp);
-        }
-        for (int gq = 0; gq < ngroups; ++gq) {
-            uint4 nxt[UB];
-            if (gq + 1 < ngroups) {
-#pragma unroll
-                for (int k = 0; k < UB; ++k) nxt[k] = down_piece((gq + 1) * UB + k, colp);
+            for (int b = 0; b < NB; ++b) {
+                const float4 h4 = *reinterpret_cast<const float4 *>(g < ngroups ? hs + b * max_chunk + g * UB : h_none);
+                h[b][0] = h4.x; h[b][1] = h4.y; h[b][2] = h4.z; h[b][3] = h4.w;
             }
 #pragma unroll
             for (int k = 0; k < UB; ++k) {
                 float w[VEC];
-                widen(cur[k], w, (const W *)nullptr);
+                widen(piece[k], w, (const W *)nullptr);
 #pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    const float h = hs[b * max_chunk + gq * UB + k];
+                for (int b = 0; b < NB; ++b)
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) acc[b][e] = fmaf(h, w[e], acc[b][e]);
-                }
+                    for (int e = 0; e < VEC; ++e) acc[b][e] = fmaf(h[b][k], w[e], acc[b][e]);
             }
-#pragma unroll
-            for (int k = 0; k < UB; ++k) cur[k] = nxt[k];
+        };
+        if (v != tid) fetch(0, at, pa);
+        if (ngroups == 1) {
+            add(0, pa);
+        } else {
+            for (int g = 0; g < ngroups; g += 2) {          // a group past the end adds zeros: a test would draw its loads in
+                fetch(g + 1, at, pb);
+                __builtin_amdgcn_sched_barrier(0);
+                add(g, pa);
+                fetch(g + 2, at, pa);
+                __builtin_amdgcn_sched_barrier(0);
+                add(g + 1, pb);
+            }
         }
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
@@ -726,6 +787,7 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
                 out[e4] = make_float4(acc[b][4 * e4], acc[b][4 * e4 + 1], acc[b][4 * e4 + 2], acc[b][4 * e4 + 3]);
         }
     }
+    store_list();
 }
 
 // ---------------------------------------------------------------------------

@@ -38,11 +38,13 @@ __device__ __forceinline__ f32x4_t mfma_bf16(const uint4 &a, const uint4 &b, f32
 
 template <int NB, int MODE>
 __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
-    const bf16 *__restrict__ Wg, const bf16 *__restrict__ Wu, const bf16 *__restrict__ x, int B, int d, int D,
-    const uint64_t *__restrict__ mask, const int32_t *__restrict__ idx_in, const int32_t *__restrict__ nnz_in,
-    int32_t *__restrict__ idx_out, int32_t *__restrict__ nnz_out, int32_t *__restrict__ n_used, int max_chunk,
-    int min_chunk, uint32_t flags, float *__restrict__ hbuf, int32_t *__restrict__ lst)
+    const bf16 *__restrict__ x, const void *__restrict__ list, const bf16 *__restrict__ Wg, const bf16 *__restrict__ Wu,
+    const int32_t *__restrict__ nnz_in, int dB, int D, uint32_t flags, int32_t *__restrict__ idx_out,
+    int32_t *__restrict__ nnz_out, int32_t *__restrict__ n_used, float *__restrict__ hbuf, int32_t *__restrict__ lst)
 {
+    const int d = dB & 0xffff, B = dB >> 16;
+    const int max_chunk = rows_max_chunk(D, MF_ROWS, MF_ROWS);
+    constexpr int min_chunk = MF_ROWS;
     static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8, "token slots are addressed with a mask");
     extern __shared__ uint4 smem16[];
     const int nvec = d / 8;                                        // 16-byte vectors per token
@@ -52,7 +54,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
     int *lidx = reinterpret_cast<int *>(part + (size_t)ROWS_WAVES * max_chunk * 2 * NB);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lm = lane & 15, lq = lane >> 4;
-    const int G = gridDim.x;
+    constexpr int G = ROWS_BLOCKS;
 
     // ---- request x; the vector of element 8c..8c+7 goes where the lane that needs it as an
     // operand will read it: step c/8, instruction (c/4)%2, lane quarter c%4, token ----
@@ -64,7 +66,8 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
 
     int lane_first, wpl;
     uint64_t held[ROWS_WREG];
-    const int n = rows_list_length<MODE>(D, mask, nnz_in, lane, lane_first, wpl, held);
+    rows_request_mask<MODE>(D, list, lane, wpl, held);
+    const int n = rows_list_length<MODE>(D, list, nnz_in, lane, wpl, held, lane_first);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         if (tid < nvec) xs[xslot(tid, b)] = xfirst[b];
@@ -83,7 +86,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
     }
     if (cnt <= 0) return;
 
-    rows_block_list<MODE>(D, mask, idx_in, lane_first, wpl, held, lo, hi, lidx);
+    rows_block_list<MODE>(D, list, lane_first, wpl, held, lo, hi, lidx);
     if (MODE == ROWS_MASK && idx_out != nullptr)
         for (int q = tid; q < cnt; q += ROWS_THREADS) idx_out[lo + q] = lidx[q];
     if (MODE != ROWS_DENSE)

@@ -22,11 +22,13 @@ namespace svdp {
 
 template <typename W, int NB, int MODE>
 __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_rows_seq(
-    const W *__restrict__ Wg, const W *__restrict__ Wu, const W *__restrict__ WdT, const W *__restrict__ x, int B,
-    int d, int D, const uint64_t *__restrict__ mask, const int32_t *__restrict__ idx_in,
-    const int32_t *__restrict__ nnz_in, int32_t *__restrict__ idx_out, int32_t *__restrict__ nnz_out,
-    int32_t *__restrict__ n_used, int max_chunk, int min_chunk, uint32_t flags, float *__restrict__ ypart)
+    const W *__restrict__ x, const void *__restrict__ list, const W *__restrict__ Wg, const W *__restrict__ Wu,
+    const W *__restrict__ WdT, const int32_t *__restrict__ nnz_in, int dB, int D, uint32_t flags, int32_t *__restrict__ idx_out,
+    int32_t *__restrict__ nnz_out, int32_t *__restrict__ n_used, float *__restrict__ ypart)
 {
+    const int d = dB & 0xffff, B = dB >> 16;
+    const int max_chunk = rows_max_chunk(D, ROWS_MIN_CHUNK, ROWS_UB);
+    constexpr int min_chunk = ROWS_MIN_CHUNK;
     constexpr int VEC = Elem<W>::VEC;
     constexpr int UG = NB <= 2 ? 8 : 4;     // 16-byte loads of one matrix in flight per lane in phase G
     constexpr int UB = 4;                   // rows of W_downT per group in phase B
@@ -40,7 +42,7 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     int *srow = lidx + max_chunk;                                // [max_chunk] alive flags in phase G, then the survivors' rows
     int *spos = srow + max_chunk;                                // [max_chunk] list positions of the survivors
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int G = gridDim.x;
+    constexpr int G = ROWS_BLOCKS;
 
     uint4 xfirst[NB];
 #pragma unroll
@@ -48,7 +50,8 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
         xfirst[b] = (b < B && tid < nvec) ? load_raw(x + (size_t)b * d + (size_t)tid * VEC) : make_uint4(0u, 0u, 0u, 0u);
     int lane_first, wpl;
     uint64_t held[ROWS_WREG];
-    const int n = rows_list_length<MODE>(D, mask, nnz_in, lane, lane_first, wpl, held);
+    rows_request_mask<MODE>(D, list, lane, wpl, held);
+    const int n = rows_list_length<MODE>(D, list, nnz_in, lane, wpl, held, lane_first);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         if (tid < nvec) xraw[b * nvec + tid] = xfirst[b];
@@ -65,7 +68,7 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     }
     if (cnt <= 0) return;
 
-    rows_block_list<MODE>(D, mask, idx_in, lane_first, wpl, held, lo, hi, lidx);
+    rows_block_list<MODE>(D, list, lane_first, wpl, held, lo, hi, lidx);
     if (MODE == ROWS_MASK && idx_out != nullptr)
         for (int q = tid; q < cnt; q += ROWS_THREADS) idx_out[lo + q] = lidx[q];
     const bool drelu = (flags & 1u) != 0;
