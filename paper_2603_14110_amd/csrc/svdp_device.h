@@ -67,9 +67,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t range_of(const void *p, uint32
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
 }
+// STREAM: the line is not kept for another read (the cache hint `nt`).
+template <bool STREAM = false>
 __device__ __forceinline__ uint4 load_range(__amdgpu_buffer_rsrc_t range, uint32_t at)
 {
-    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(range, at, 0, 0));
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(range, at, 0, STREAM ? 2 : 0));
 }
 __device__ __forceinline__ uint64_t load_range_8(__amdgpu_buffer_rsrc_t range, uint32_t at)
 {

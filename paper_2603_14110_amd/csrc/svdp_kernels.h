@@ -7,6 +7,8 @@
 
 #include "svdp_device.h"
 
+#include <type_traits>
+
 namespace svdp {
 
 constexpr int XP_THREADS = 256;      // k_xP block
@@ -566,6 +568,13 @@ __device__ __forceinline__ void rows_block_list(int D, const void *__restrict__ 
     __syncthreads();
 }
 
+// Whether the rows of a list are read past the caches: lists of 64 MB and more, which twice the L2s would not hold.  Rows alone, read
+// as usual -> past them, in us, weights from memory / the same layer again and again: d = 4096, one token, 37 MB 12.8 -> 13.7 /
+// 11.8 -> 11.7, 74 MB 19.4 -> 18.8 / 17.3 -> 17.0, 147 MB 31.9 -> 29.0 / 26.5 -> 27.0, 246 MB 47.8 -> 42.7 / 40.1 -> 41.2, 352 MB 64.0 ->
+// 58.0 / 63.2 -> 55.7; d = 2824, two tokens, 51 MB 18.2 -> 18.8 / 16.0 -> 17.1.  What they leave in the caches is the predictor: a whole
+// step of 3584 x 18944, four tokens, 33 % of the rows 51.6 -> 44.9.
+__device__ __forceinline__ bool streams(int n, int d, int bytes) { return (float)n * (float)(3 * d * bytes) >= 64e6f; }
+
 // x [B][d] as stored into xraw [NB][nvec] (zeros beyond B), in two halves: the first ROWS_XV vectors of a thread are
 // requested behind whatever the caller asked for before and stored once that has been used; rows longer than that follow in a loop.
 constexpr int ROWS_XV = 2;
@@ -659,134 +668,139 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(2,
     const uint32_t row_bytes = (uint32_t)d * sizeof(W);
     // row i of a matrix; nothing at all where i < 0 (past the end; a rejected entry of the caller's list)
     auto row_range = [&](const W *M, int i) { return range_of(M + (size_t)max(i, 0) * d, i >= 0 ? row_bytes : 0u); };
-    // rows UB g .. UB g + UB - 1 of the chunk, at byte `at` of each; zeros past the end
-    auto fetch = [&](int g, uint32_t at, uint4 (&piece)[UB]) {
-        static_assert(UB == 4, "one 16-byte read of the list");
-        int row[UB];
-        if (MODE == ROWS_DENSE) {
+    auto work = [&](auto stream) {
+        constexpr bool STREAM = decltype(stream)::value;
+        // rows UB g .. UB g + UB - 1 of the chunk, at byte `at` of each; zeros past the end
+        auto fetch = [&](int g, uint32_t at, uint4 (&piece)[UB]) {
+            static_assert(UB == 4, "one 16-byte read of the list");
+            int row[UB];
+            if (MODE == ROWS_DENSE) {
 #pragma unroll
-            for (int k = 0; k < UB; ++k) row[k] = lo + g * UB + k;
-        } else {
-            const int4 r4 = *reinterpret_cast<const int4 *>(lidx + min(g, ngroups - 1) * UB);
-            row[0] = __builtin_amdgcn_readfirstlane(r4.x);
-            row[1] = __builtin_amdgcn_readfirstlane(r4.y);
-            row[2] = __builtin_amdgcn_readfirstlane(r4.z);
-            row[3] = __builtin_amdgcn_readfirstlane(r4.w);
-        }
-#pragma unroll
-        for (int k = 0; k < UB; ++k) piece[k] = load_range(row_range(WdT, g * UB + k < cnt ? row[k] : -1), at);
-    };
-    // ---- request the first group of W_downT rows for this thread's first column group ----
-    uint4 pa[UB], pb[UB];
-    fetch(0, (uint32_t)tid * 16u, pa);
-
-    // ---- phase A: one wave per row, 64 UA vectors of both matrices at a time ----
-    uint4 rg[UA], ru[UA];
-    auto request = [&](int q, int vb) {
-        const int row = __builtin_amdgcn_readfirstlane(MODE == ROWS_DENSE ? lo + q : lidx[q]);
-        const __amdgpu_buffer_rsrc_t g = row_range(Wg, row), u = row_range(Wu, row);
-        const uint32_t at = (uint32_t)(vb + lane) * 16u;
-#pragma unroll
-        for (int k = 0; k < UA / 2; ++k) {
-            rg[k] = load_range(g, at + k * 1024);
-            ru[k] = load_range(u, at + k * 1024);
-        }
-        if (vb + UA / 2 * 64 < nvec) {
-#pragma unroll
-            for (int k = UA / 2; k < UA; ++k) {
-                rg[k] = load_range(g, at + k * 1024);
-                ru[k] = load_range(u, at + k * 1024);
+                for (int k = 0; k < UB; ++k) row[k] = lo + g * UB + k;
+            } else {
+                const int4 r4 = *reinterpret_cast<const int4 *>(lidx + min(g, ngroups - 1) * UB);
+                row[0] = __builtin_amdgcn_readfirstlane(r4.x);
+                row[1] = __builtin_amdgcn_readfirstlane(r4.y);
+                row[2] = __builtin_amdgcn_readfirstlane(r4.z);
+                row[3] = __builtin_amdgcn_readfirstlane(r4.w);
             }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    if (wave < cnt) request(wave, 0);
-    float ag[NB], au[NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) ag[b] = au[b] = 0.f;
-    for (int q = wave, vb = 0; q < cnt;) {
-        auto half = [&](int k0) {
+            for (int k = 0; k < UB; ++k) piece[k] = load_range<STREAM>(row_range(WdT, g * UB + k < cnt ? row[k] : -1), at);
+        };
+        // ---- request the first group of W_downT rows for this thread's first column group ----
+        uint4 pa[UB], pb[UB];
+        fetch(0, (uint32_t)tid * 16u, pa);
+
+        // ---- phase A: one wave per row, 64 UA vectors of both matrices at a time ----
+        uint4 rg[UA], ru[UA];
+        auto request = [&](int q, int vb) {
+            const int row = __builtin_amdgcn_readfirstlane(MODE == ROWS_DENSE ? lo + q : lidx[q]);
+            const __amdgpu_buffer_rsrc_t g = row_range(Wg, row), u = row_range(Wu, row);
+            const uint32_t at = (uint32_t)(vb + lane) * 16u;
 #pragma unroll
-            for (int k = k0; k < k0 + UA / 2; ++k) {
-                const int v = min(vb + k * 64 + lane, nvec - 1);          // a zero weight vector meets any x
+            for (int k = 0; k < UA / 2; ++k) {
+                rg[k] = load_range<STREAM>(g, at + k * 1024);
+                ru[k] = load_range<STREAM>(u, at + k * 1024);
+            }
+            if (vb + UA / 2 * 64 < nvec) {
+#pragma unroll
+                for (int k = UA / 2; k < UA; ++k) {
+                    rg[k] = load_range<STREAM>(g, at + k * 1024);
+                    ru[k] = load_range<STREAM>(u, at + k * 1024);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if (wave < cnt) request(wave, 0);
+        float ag[NB], au[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) ag[b] = au[b] = 0.f;
+        for (int q = wave, vb = 0; q < cnt;) {
+            auto half = [&](int k0) {
+#pragma unroll
+                for (int k = k0; k < k0 + UA / 2; ++k) {
+                    const int v = min(vb + k * 64 + lane, nvec - 1);          // a zero weight vector meets any x
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        const uint4 xq = xraw[b * nvec + v];
+                        ag[b] = dot_raw(rg[k], xq, ag[b], (const W *)nullptr);
+                        au[b] = dot_raw(ru[k], xq, au[b], (const W *)nullptr);
+                    }
+                }
+            };
+            half(0);
+            if (vb + UA / 2 * 64 < nvec) half(UA / 2);
+            const bool whole = vb + UA * 64 >= nvec;                     // the row is done
+            const int nq = whole ? q + ROWS_WAVES : q, nvb = whole ? 0 : vb + UA * 64;
+            if (nq < cnt) request(nq, nvb);
+            if (whole) {
+                const bool valid = MODE != ROWS_LIST || lidx[q] >= 0;
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const uint4 xq = xraw[b * nvec + v];
-                    ag[b] = dot_raw(rg[k], xq, ag[b], (const W *)nullptr);
-                    au[b] = dot_raw(ru[k], xq, au[b], (const W *)nullptr);
+                    const float gs = wave_sum(ag[b]);
+                    const float us = wave_sum(au[b]);
+                    if (lane == 0) {
+                        const float gp = fmaxf(gs, 0.f);
+                        const float uu = drelu ? fmaxf(us, 0.f) : us;
+                        hs[b * max_chunk + q] = valid ? gp * uu : 0.f;
+                    }
+                    ag[b] = au[b] = 0.f;
                 }
             }
-        };
-        half(0);
-        if (vb + UA / 2 * 64 < nvec) half(UA / 2);
-        const bool whole = vb + UA * 64 >= nvec;                     // the row is done
-        const int nq = whole ? q + ROWS_WAVES : q, nvb = whole ? 0 : vb + UA * 64;
-        if (nq < cnt) request(nq, nvb);
-        if (whole) {
-            const bool valid = MODE != ROWS_LIST || lidx[q] >= 0;
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const float gs = wave_sum(ag[b]);
-                const float us = wave_sum(au[b]);
-                if (lane == 0) {
-                    const float gp = fmaxf(gs, 0.f);
-                    const float uu = drelu ? fmaxf(us, 0.f) : us;
-                    hs[b * max_chunk + q] = valid ? gp * uu : 0.f;
-                }
-                ag[b] = au[b] = 0.f;
-            }
+            q = nq;
+            vb = nvb;
         }
-        q = nq;
-        vb = nvb;
-    }
-    __syncthreads();
+        __syncthreads();
 
-    // ---- phase B: every thread owns 16-byte column groups of the output ----
-    for (int v = tid; v < nvec; v += ROWS_THREADS) {
-        float acc[NB][VEC];
+        // ---- phase B: every thread owns 16-byte column groups of the output ----
+        for (int v = tid; v < nvec; v += ROWS_THREADS) {
+            float acc[NB][VEC];
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+            for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) acc[b][e] = 0.f;
-        const uint32_t at = (uint32_t)v * 16u;
-        auto add = [&](int g, const uint4 (&piece)[UB]) {
-            float h[NB][UB];
+                for (int e = 0; e < VEC; ++e) acc[b][e] = 0.f;
+            const uint32_t at = (uint32_t)v * 16u;
+            auto add = [&](int g, const uint4 (&piece)[UB]) {
+                float h[NB][UB];
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const float4 h4 = *reinterpret_cast<const float4 *>(g < ngroups ? hs + b * max_chunk + g * UB : h_none);
+                    h[b][0] = h4.x; h[b][1] = h4.y; h[b][2] = h4.z; h[b][3] = h4.w;
+                }
+#pragma unroll
+                for (int k = 0; k < UB; ++k) {
+                    float w[VEC];
+                    widen(piece[k], w, (const W *)nullptr);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) acc[b][e] = fmaf(h[b][k], w[e], acc[b][e]);
+                }
+            };
+            if (v != tid) fetch(0, at, pa);
+            if (ngroups == 1) {
+                add(0, pa);
+            } else {
+                for (int g = 0; g < ngroups; g += 2) {          // a group past the end adds zeros: a test would draw its loads in
+                    fetch(g + 1, at, pb);
+                    __builtin_amdgcn_sched_barrier(0);
+                    add(g, pa);
+                    fetch(g + 2, at, pa);
+                    __builtin_amdgcn_sched_barrier(0);
+                    add(g + 1, pb);
+                }
+            }
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                const float4 h4 = *reinterpret_cast<const float4 *>(g < ngroups ? hs + b * max_chunk + g * UB : h_none);
-                h[b][0] = h4.x; h[b][1] = h4.y; h[b][2] = h4.z; h[b][3] = h4.w;
-            }
+                float4 *out = reinterpret_cast<float4 *>(ypart + ((size_t)blockIdx.x * NB + b) * d + (size_t)v * VEC);
 #pragma unroll
-            for (int k = 0; k < UB; ++k) {
-                float w[VEC];
-                widen(piece[k], w, (const W *)nullptr);
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) acc[b][e] = fmaf(h[b][k], w[e], acc[b][e]);
-            }
-        };
-        if (v != tid) fetch(0, at, pa);
-        if (ngroups == 1) {
-            add(0, pa);
-        } else {
-            for (int g = 0; g < ngroups; g += 2) {          // a group past the end adds zeros: a test would draw its loads in
-                fetch(g + 1, at, pb);
-                __builtin_amdgcn_sched_barrier(0);
-                add(g, pa);
-                fetch(g + 2, at, pa);
-                __builtin_amdgcn_sched_barrier(0);
-                add(g + 1, pb);
+                for (int e4 = 0; e4 < VEC / 4; ++e4)
+                    out[e4] = make_float4(acc[b][4 * e4], acc[b][4 * e4 + 1], acc[b][4 * e4 + 2], acc[b][4 * e4 + 3]);
             }
         }
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            float4 *out = reinterpret_cast<float4 *>(ypart + ((size_t)blockIdx.x * NB + b) * d + (size_t)v * VEC);
-#pragma unroll
-            for (int e4 = 0; e4 < VEC / 4; ++e4)
-                out[e4] = make_float4(acc[b][4 * e4], acc[b][4 * e4 + 1], acc[b][4 * e4 + 2], acc[b][4 * e4 + 3]);
-        }
-    }
+    };
+    if (streams(n, d, (int)sizeof(W))) work(std::true_type{});
+    else work(std::false_type{});
     store_list();
 }
 
