@@ -239,7 +239,7 @@ RowsPlan plan_rows(const svdp_layer *L)
             p.kind = ROWS_MATRIX;
             p.min_chunk = MF_ROWS;
             p.max_chunk = rows_max_chunk(D, MF_ROWS, MF_ROWS);
-            p.lds = (size_t)NB * round_up(d, 64) * 2 + ((size_t)ROWS_WAVES * p.max_chunk * 2 * NB + p.max_chunk) * 4;
+            p.lds = (size_t)NB * mf_x_stride(d) * 16 + ((size_t)ROWS_WAVES * p.max_chunk * 2 * NB + p.max_chunk) * 4;
             p.split = true;
             if (p.lds <= LDS_MAX && split_fits(d, D, NB)) return p;
             p.split = false;
@@ -413,7 +413,7 @@ svdp_status launch_rows(const svdp_layer *L, const void *x, int B, const uint64_
             launch((k_gate_up_mfma<NB, MODE>), dim3(ROWS_BLOCKS), dim3(ROWS_THREADS), p.lds, st, xs, list, Wg, Wu, nnz_in, dB,
                    D, L->flags, idx_out, nnz_out, w.nnz, hbuf, lst);
             launch((k_down_slices<NB, MODE == ROWS_DENSE>), dim3((d + DS_SW - 1) / DS_SW, DOWN_RG), dim3(DS_THREADS), 0, st,
-                   Wd, lst, MODE == ROWS_DENSE ? nullptr : w.nnz, D, D, d, hbuf, DOWN_MIN_CHUNK, w.ypart);
+                   Wd, lst, MODE == ROWS_DENSE ? nullptr : w.nnz, D, d, hbuf, w.ypart);
         }
     }
     if (matrix) {

@@ -88,6 +88,13 @@ __device__ __forceinline__ uint4 load_raw(const W *p)
 {
     return *reinterpret_cast<const uint4 *>(p);
 }
+template <bool STREAM, typename W>
+__device__ __forceinline__ uint4 load_raw_hint(const W *p)
+{
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    if (!STREAM) return load_raw(p);
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p)));
+}
 __device__ __forceinline__ void widen(const uint4 &q, float (&v)[4], const float *)
 {
     v[0] = __uint_as_float(q.x); v[1] = __uint_as_float(q.y);

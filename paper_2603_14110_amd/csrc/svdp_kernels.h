@@ -575,16 +575,16 @@ __device__ __forceinline__ void rows_block_list(int D, const void *__restrict__ 
 // step of 3584 x 18944, four tokens, 33 % of the rows 51.6 -> 44.9.
 __device__ __forceinline__ bool streams(int n, int d, int bytes) { return (float)n * (float)(3 * d * bytes) >= 64e6f; }
 
-// x [B][d] as stored into xraw [NB][nvec] (zeros beyond B), in two halves: the first ROWS_XV vectors of a thread are
+// x [B][d] as stored into xraw [NB][nvec] (zeros beyond B), in two halves: the first XV vectors of a thread are
 // requested behind whatever the caller asked for before and stored once that has been used; rows longer than that follow in a loop.
 constexpr int ROWS_XV = 2;
-template <typename W, int NB>
-__device__ __forceinline__ void rows_request_x(const W *__restrict__ x, int B, int d, int v0, uint4 (&xv)[ROWS_XV][NB])
+template <typename W, int NB, int XV>
+__device__ __forceinline__ void rows_request_x(const W *__restrict__ x, int B, int d, int v0, uint4 (&xv)[XV][NB])
 {
     constexpr int VEC = Elem<W>::VEC;
     const __amdgpu_buffer_rsrc_t tokens = range_of(x, (uint32_t)(B * d) * sizeof(W));
 #pragma unroll
-    for (int k = 0; k < ROWS_XV; ++k)
+    for (int k = 0; k < XV; ++k)
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const int v = v0 + threadIdx.x + k * ROWS_THREADS;

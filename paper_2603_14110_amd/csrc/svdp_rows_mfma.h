@@ -8,14 +8,18 @@
 //            chunk of the list written to memory (h [list position][NB], and the checked list).  Tiles of 16
 //            list rows x 64 elements of d; four lanes fetch 64 contiguous bytes of one row per load, two
 //            loads cover 128 bytes and feed two v_mfma_f32_16x16x32_bf16 per matrix, whose other operand is
-//            x in LDS, stored in operand order.  The eight waves of the block split d between them; their
+//            x in LDS.  The eight waves of the block split d between them; their
 //            16x16 partial tiles meet in LDS and are added in wave order.
 //   k_down_slices   y[token][col] = sum over the list of h * W_downT[row][col], by blocks that own a
 //            128-byte column slice and one of eight parts of the list (see there).
 // Products of bf16 values are exact in fp32 and every sum has a fixed order.
+// Both are bound by the stream (4.4 and 3.5 TB/s with the launches, 5 and more without) and the trips before it: mask and x, the
+// rows; the list's length, its part of the list, the rows.  So every phase's requests stand together and outside of branches, one group of
+// steps is under way while another is multiplied, and lists of 64 MB and more are read past the caches (streams()).  Step of 4096 x
+// 14336, eight tokens (57 % of the rows) 63.2 -> 60.4 us, its first pass 123 -> 95; gate/up alone 29.7 -> 28.0, slices 20.7 -> 17.5.
 // A row's last, partial step (d no multiple of 64) is a step of its own, with zeros past the end on both sides.
 // Requirements checked by the host: NB <= 8.
-// Dynamic LDS of k_gate_up_mfma: NB * (d rounded up to 64) * 2 bytes (x) + ROWS_WAVES*max_chunk*2*NB floats (partial tiles) +
+// Dynamic LDS of k_gate_up_mfma: NB * mf_x_stride(d) * 16 bytes (x) + ROWS_WAVES*max_chunk*2*NB floats (partial tiles) +
 // max_chunk ints (list); max_chunk % 16 == 0.
 #pragma once
 
@@ -29,6 +33,9 @@ constexpr int MF_ROWS = 16;      // list rows per tile
 constexpr int DOWN_RG = 8;       // k_down_slices: parts of the list per column slice (= partial outputs) ...
 constexpr int DOWN_MIN_CHUNK = 64;     // ... and fewest rows of a part
 constexpr int MF_UA = 4;         // 64-element steps fetched together
+// 16-byte vectors from one token's x to the next in LDS: the four vectors that eight tokens' lanes read at once, and the
+// consecutive ones that a wave writes, lie in different banks
+__host__ __device__ constexpr int mf_x_stride(int d) { return (d + 63) / 64 * 8 + 4; }
 
 __device__ __forceinline__ f32x4_t mfma_bf16(const uint4 &a, const uint4 &b, f32x4_t c)
 {
@@ -47,50 +54,51 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
     constexpr int min_chunk = MF_ROWS;
     static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8, "token slots are addressed with a mask");
     extern __shared__ uint4 smem16[];
-    const int nvec = d / 8;                                        // 16-byte vectors per token
     const int full = d / 64, nsteps = (d + 63) / 64;               // 64-element steps per row: whole ones, all
-    uint4 *xs = smem16;                                            // [nsteps][2][4][NB], operand order
-    float *part = reinterpret_cast<float *>(xs + NB * nsteps * 8); // [ROWS_WAVES][tiles][2][16][NB]
+    const int stride = mf_x_stride(d);
+    uint4 *xs = smem16;                                            // [NB][stride]
+    float *part = reinterpret_cast<float *>(xs + NB * stride);     // [ROWS_WAVES][tiles][2][16][NB]
     int *lidx = reinterpret_cast<int *>(part + (size_t)ROWS_WAVES * max_chunk * 2 * NB);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lm = lane & 15, lq = lane >> 4;
     constexpr int G = ROWS_BLOCKS;
 
-    // ---- request x; the vector of element 8c..8c+7 goes where the lane that needs it as an
-    // operand will read it: step c/8, instruction (c/4)%2, lane quarter c%4, token ----
-    auto xslot = [&](int c, int b) -> int { return (((c >> 3) * 2 + ((c >> 2) & 1)) * 4 + (c & 3)) * NB + b; };
-    uint4 xfirst[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-        xfirst[b] = (b < B && tid < nvec) ? load_raw(x + (size_t)b * d + (size_t)tid * 8) : make_uint4(0u, 0u, 0u, 0u);
-
+    // ---- request the mask words, then x ----
     int lane_first, wpl;
     uint64_t held[ROWS_WREG];
     rows_request_mask<MODE>(D, list, lane, wpl, held);
+    uint4 xv[1][NB];
+    rows_request_x<bf16, NB>(x, B, d, 0, xv);
     const int n = rows_list_length<MODE>(D, list, nnz_in, lane, wpl, held, lane_first);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        if (tid < nvec) xs[xslot(tid, b)] = xfirst[b];
-        for (int c = tid + ROWS_THREADS; c < nvec; c += ROWS_THREADS)
-            xs[xslot(c, b)] = b < B ? load_raw(x + (size_t)b * d + (size_t)c * 8) : make_uint4(0u, 0u, 0u, 0u);
-        if (nvec + tid < nsteps * 8) xs[xslot(nvec + tid, b)] = make_uint4(0u, 0u, 0u, 0u);      // at most seven
-    }
     const int chunk = chunk_of(n, G, min_chunk);
     const int lo = min(n, (int)blockIdx.x * chunk);
     const int hi = min(n, lo + chunk);
     const int cnt = hi - lo;
-    if (blockIdx.x == 0 && tid == 0) {
+    // written at the kernel's end: a wait for loads waits for the stores in front of them too
+    auto store_list = [&] {
+        if (blockIdx.x == 0 && tid == 0) {
+            if (MODE != ROWS_DENSE)
+                *reinterpret_cast<int2 *>(n_used) = make_int2(n, active_blocks(n, chunk_of(n, DOWN_RG, DOWN_MIN_CHUNK)));
+            if (MODE == ROWS_MASK && nnz_out != nullptr) *nnz_out = n;
+        }
         if (MODE != ROWS_DENSE)
-            *reinterpret_cast<int2 *>(n_used) = make_int2(n, active_blocks(n, chunk_of(n, DOWN_RG, DOWN_MIN_CHUNK)));
-        if (MODE == ROWS_MASK && nnz_out != nullptr) *nnz_out = n;
+            for (int q = tid; q < cnt; q += ROWS_THREADS) {
+                lst[lo + q] = lidx[q];
+                if (MODE == ROWS_MASK && idx_out != nullptr) idx_out[lo + q] = lidx[q];
+            }
+    };
+    if (cnt <= 0) {
+        store_list();
+        return;
     }
-    if (cnt <= 0) return;
-
+    for (int v0 = 0; v0 < nsteps * 8; v0 += ROWS_THREADS) {        // zeros past the row's end
+        if (v0 != 0) rows_request_x<bf16, NB>(x, B, d, v0, xv);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            if (v0 + tid < nsteps * 8) xs[b * stride + v0 + tid] = xv[0][b];
+    }
     rows_block_list<MODE>(D, list, lane_first, wpl, held, lo, hi, lidx);
-    if (MODE == ROWS_MASK && idx_out != nullptr)
-        for (int q = tid; q < cnt; q += ROWS_THREADS) idx_out[lo + q] = lidx[q];
-    if (MODE != ROWS_DENSE)
-        for (int q = tid; q < cnt; q += ROWS_THREADS) lst[lo + q] = lidx[q];
 
     const bool drelu = (flags & 1u) != 0;
     // rows past the end of the chunk repeat its last row, and a rejected entry of the caller's list
@@ -101,52 +109,26 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
     };
     const int ntile = (cnt + MF_ROWS - 1) / MF_ROWS;
 
-    // ---- this wave's share of d is the steps [first, last) ----
-    const int uwave = __builtin_amdgcn_readfirstlane(wave);         // the tests of the loop below stay scalar
-    const int first = uwave * nsteps / ROWS_WAVES, end = (uwave + 1) * nsteps / ROWS_WAVES, last = min(end, full);
+    // ---- this wave's share of d is the steps [first, last); MF_UA of them are under way while as many are multiplied ----
+    const int first = wave * nsteps / ROWS_WAVES, end = (wave + 1) * nsteps / ROWS_WAVES, last = min(end, full);
     const int tb = lm & (NB - 1);                                   // token slot read as the x operand
-    for (int t = 0; t < ntile; ++t) {
-        const size_t row = row_of(t * MF_ROWS + lm);
-        const bf16 *pg = Wg + row * d + lq * 8;
-        const bf16 *pu = Wu + row * d + lq * 8;
-        f32x4_t ag = {0.f, 0.f, 0.f, 0.f}, au = {0.f, 0.f, 0.f, 0.f};
-        for (int s0 = first; s0 < last; s0 += MF_UA) {
-            uint4 g0[MF_UA], g1[MF_UA], u0[MF_UA], u1[MF_UA];
-#pragma unroll
-            for (int k = 0; k < MF_UA; ++k) {
-                if (s0 + k < last) {
-                    g0[k] = load_raw(pg + (size_t)(s0 + k) * 64);
-                    g1[k] = load_raw(pg + (size_t)(s0 + k) * 64 + 32);
-                    u0[k] = load_raw(pu + (size_t)(s0 + k) * 64);
-                    u1[k] = load_raw(pu + (size_t)(s0 + k) * 64 + 32);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < MF_UA; ++k) {
-                if (s0 + k < last) {
-                    const int s = s0 + k;
-                    const uint4 xa = xs[((s * 2 + 0) * 4 + lq) * NB + tb];
-                    const uint4 xb = xs[((s * 2 + 1) * 4 + lq) * NB + tb];
-                    ag = mfma_bf16(g0[k], xa, ag);
-                    au = mfma_bf16(u0[k], xa, au);
-                    ag = mfma_bf16(g1[k], xb, ag);
-                    au = mfma_bf16(u1[k], xb, au);
-                }
-            }
-        }
+    const uint4 *xt = xs + tb * stride + lq;
+    f32x4_t ag = {0.f, 0.f, 0.f, 0.f}, au = {0.f, 0.f, 0.f, 0.f};
+    // the tile's last products, and its partial sums: the lane holds rows 4*lq .. 4*lq+3 of the tile for token lm
+    auto finish_tile = [&](int t) {
         if (end > full) {                        // the last wave: the partial step
+            const size_t row = row_of(t * MF_ROWS + lm);
+            const bf16 *pg = Wg + row * d + (size_t)full * 64 + lq * 8, *pu = Wu + row * d + (size_t)full * 64 + lq * 8;
             const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
             const int col = full * 64 + lq * 8;
-            const uint4 g0 = col < d ? load_raw(pg + (size_t)full * 64) : zero, u0 = col < d ? load_raw(pu + (size_t)full * 64) : zero;
-            const uint4 g1 = col + 32 < d ? load_raw(pg + (size_t)full * 64 + 32) : zero,
-                        u1 = col + 32 < d ? load_raw(pu + (size_t)full * 64 + 32) : zero;
-            const uint4 xa = xs[((full * 2 + 0) * 4 + lq) * NB + tb], xb = xs[((full * 2 + 1) * 4 + lq) * NB + tb];
+            const uint4 g0 = col < d ? load_raw(pg) : zero, u0 = col < d ? load_raw(pu) : zero;
+            const uint4 g1 = col + 32 < d ? load_raw(pg + 32) : zero, u1 = col + 32 < d ? load_raw(pu + 32) : zero;
+            const uint4 xa = xt[full * 8], xb = xt[full * 8 + 4];
             ag = mfma_bf16(g0, xa, ag);
             au = mfma_bf16(u0, xa, au);
             ag = mfma_bf16(g1, xb, ag);
             au = mfma_bf16(u1, xb, au);
         }
-        // the lane holds rows 4*lq .. 4*lq+3 of the tile for token lm
         if (lm < NB) {
             float *pt = part + ((size_t)(wave * ntile + t) * 2) * MF_ROWS * NB;
 #pragma unroll
@@ -155,6 +137,76 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
                 pt[MF_ROWS * NB + (lq * 4 + i) * NB + lm] = au[i];
             }
         }
+        ag = au = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    };
+    struct Group {
+        uint4 g0[MF_UA], g1[MF_UA], u0[MF_UA], u1[MF_UA];
+    };
+    auto work = [&](auto stream) {
+        constexpr bool STREAM = decltype(stream)::value;
+        // steps s0 .. s0 + MF_UA - 1 of tile t.  Past the wave's last step that one again, past the last tile the matrices' first
+        // line: nothing is asked for in a branch, after which every load would have to be awaited at once.
+        auto request = [&](int t, int s0, Group &w) {
+            const bool beyond = t >= ntile;
+            const size_t row = beyond ? 0 : row_of(t * MF_ROWS + lm);
+            const bf16 *pg = Wg + row * d + lq * 8, *pu = Wu + row * d + lq * 8;
+#pragma unroll
+            for (int k = 0; k < MF_UA; ++k) {
+                const size_t at = beyond ? 0 : (size_t)min(s0 + k, last - 1) * 64;
+                w.g0[k] = load_raw_hint<STREAM>(pg + at);
+                w.g1[k] = load_raw_hint<STREAM>(pg + at + 32);
+                w.u0[k] = load_raw_hint<STREAM>(pu + at);
+                w.u1[k] = load_raw_hint<STREAM>(pu + at + 32);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        // (no test around a product: the loads of a step left out would still be awaited before the next request)
+        auto consume = [&](int s0, Group &w) {
+            if (s0 + MF_UA > last) {
+#pragma unroll
+                for (int k = 1; k < MF_UA; ++k)
+                    if (s0 + k >= last) w.g0[k] = w.g1[k] = w.u0[k] = w.u1[k] = make_uint4(0u, 0u, 0u, 0u);
+            }
+#pragma unroll
+            for (int k = 0; k < MF_UA; ++k) {
+                const int s = min(s0 + k, last - 1) * 8;
+                const uint4 xa = xt[s], xb = xt[s + 4];
+                ag = mfma_bf16(w.g0[k], xa, ag);
+                au = mfma_bf16(w.u0[k], xa, au);
+                ag = mfma_bf16(w.g1[k], xb, ag);
+                au = mfma_bf16(w.u1[k], xb, au);
+            }
+        };
+        Group wa, wb;
+        int t = 0, s0 = first, tn = 0, sn = first;                   // the group multiplied, the group requested
+        auto advance = [&](int &tt, int &ss) {
+            ss += MF_UA;
+            if (ss >= last) {
+                ss = first;
+                ++tt;
+            }
+        };
+        auto turn = [&](Group &now, Group &next) {
+            advance(tn, sn);
+            request(tn, sn, next);
+            consume(s0, now);
+            if (s0 + MF_UA >= last) finish_tile(t);
+            advance(t, s0);
+        };
+        request(tn, sn, wa);
+        while (true) {
+            turn(wa, wb);
+            if (t >= ntile) break;
+            turn(wb, wa);
+            if (t >= ntile) break;
+        }
+    };
+    if (first >= last) {
+        for (int t = 0; t < ntile; ++t) finish_tile(t);
+    } else if (streams(n, d, 2)) {
+        work(std::true_type{});
+    } else {
+        work(std::false_type{});
     }
     __syncthreads();
     // partial tiles of the waves, added in wave order -> h[list position][token]
@@ -174,6 +226,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
         }
         hbuf[(size_t)(lo + q) * NB + b] = h;
     }
+    store_list();
 }
 
 // ---------------------------------------------------------------------------
@@ -197,32 +250,47 @@ constexpr int DS_LPR = 8;            // lanes per row: 16 bytes each, one 128-by
 constexpr int DS_SW = DS_LPR * 8;    // columns of a slice
 
 template <int NB, bool DENSE>
-__global__ __launch_bounds__(DS_THREADS) void k_down_slices(const bf16 *__restrict__ WdT,
+__global__ __launch_bounds__(DS_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_down_slices(const bf16 *__restrict__ WdT,
                                                             const int32_t *__restrict__ lst,
-                                                            const int32_t *__restrict__ n_ptr, int n_fixed, int D, int d,
-                                                            const float *__restrict__ hbuf, int min_chunk,
-                                                            float *__restrict__ ypart)
+                                                            const int32_t *__restrict__ n_ptr, int D, int d,
+                                                            const float *__restrict__ hbuf, float *__restrict__ ypart)
 {
     constexpr int LPR = DS_LPR, SW = DS_SW;
     constexpr int RPW = 64 / LPR;                // rows per wave load
     constexpr int RSETS = RPW / 2;               // row-lane sets of a wave left after the lane shift below
-    __shared__ int lidx[DENSE ? 1 : DS_MAX_CHUNK];
+    __shared__ int4 list4[DENSE ? 1 : DS_MAX_CHUNK / 4 + 1];
     __shared__ float red[DS_WAVES * RSETS * NB * SW];         // [DS_WAVES * RSETS][NB][SW]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cg = lane % LPR, sub = lane / LPR;
-    const int slice = blockIdx.x, rg = blockIdx.y, RG = gridDim.y;
-    int n = n_ptr != nullptr ? *n_ptr : n_fixed;
+    const int slice = blockIdx.x, rg = blockIdx.y;
+    int n = n_ptr != nullptr ? *n_ptr : D;
     n = max(0, min(n, D));
-    const int chunk = chunk_of(n, RG, min_chunk);
+    const int chunk = chunk_of(n, DOWN_RG, DOWN_MIN_CHUNK);
     const int lo = min(n, rg * chunk), hi = min(n, lo + chunk), cnt = hi - lo;
     if (cnt <= 0) return;
+    // the part of the list, in whole 16-byte vectors (D is a multiple of four): at most five a thread, one trip for all
+    const int lo4 = lo / 4, off = lo % 4;
     if (!DENSE) {
-        for (int q = tid; q < cnt; q += DS_THREADS) lidx[q] = lst[lo + q];
+        constexpr int LV = DS_MAX_CHUNK / 4 / DS_THREADS;
+        const __amdgpu_buffer_rsrc_t entries = range_of(lst, (uint32_t)D * 4);
+        const int n4 = (hi + 3) / 4 - lo4;
+        uint4 e[LV + 1];
+#pragma unroll
+        for (int k = 0; k <= LV; ++k) {
+            const int v = tid + k * DS_THREADS;
+            e[k] = load_range(entries, v < n4 ? (uint32_t)(lo4 + v) * 16u : OUTSIDE);
+        }
+#pragma unroll
+        for (int k = 0; k <= LV; ++k) {
+            const int v = tid + k * DS_THREADS;
+            if (v < n4) list4[v] = __builtin_bit_cast(int4, e[k]);
+        }
         __syncthreads();
     }
-    const bf16 *colp = WdT + (size_t)slice * SW + (size_t)cg * 8;
+    const int *lidx = reinterpret_cast<const int *>(list4) + off;
     const int ngroups = (cnt + RPW - 1) / RPW;
     const bool colok = slice * SW + cg * 8 < d;
+    const bf16 *colp = WdT + (size_t)slice * SW + (size_t)(colok ? cg : 0) * 8;
 
     // v_mfma_f32_4x4x1_16b: sixteen independent 4 x 4 outer products; the four lanes of a block work on the same
     // row, lane j of the block supplies h of token 4 tg + j and its own column's weight, and keeps the four tokens'
@@ -235,49 +303,62 @@ __global__ __launch_bounds__(DS_THREADS) void k_down_slices(const bf16 *__restri
         for (int e = 0; e < 8; ++e) acc[g][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     // group g of the chunk = its rows RPW g .. RPW g + RPW - 1; this wave takes the groups wave, wave + DS_WAVES, ...
-    auto fetch = [&](int g0, uint4 (&wv)[DS_UB], float (&hv)[DS_UB][TG]) {
-#pragma unroll
-        for (int k = 0; k < DS_UB; ++k) {
-            const int q = (g0 + k * DS_WAVES) * RPW + sub;
-            wv[k] = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-            for (int g = 0; g < TG; ++g) hv[k][g] = 0.f;
-            if (q < cnt) {
-                const int row = DENSE ? lo + q : lidx[q];
-                if (row >= 0) {                                    // a rejected entry of the caller's list: h is zero
-                    if (colok) wv[k] = load_raw(colp + (size_t)row * d);     // h is read for the lane's neighbours all the same
-                    const float *hp = hbuf + (size_t)(lo + q) * NB;
-#pragma unroll
-                    for (int g = 0; g < TG; ++g)
-                        if (g * 4 + (lane & 3) < NB) hv[k][g] = hp[g * 4 + (lane & 3)];
-                }
-            }
-        }
+    // Requested without branches (each load inside of one is waited for): positions past the end and rejected entries of the
+    // caller's list read another row, whose weights are then replaced by zeros (h is zero already, but a weight may be infinite).
+    const __amdgpu_buffer_rsrc_t hpart = range_of(hbuf, (uint32_t)hi * NB * 4);
+    const uint32_t my_token = (lane & 3) < NB ? (uint32_t)(lane & 3) * 4u : OUTSIDE;
+    struct Group {
+        uint4 w[DS_UB];
+        float h[DS_UB][TG];
+        bool in[DS_UB];
     };
-    auto consume = [&](const uint4 (&wv)[DS_UB], const float (&hv)[DS_UB][TG]) {
+    auto work = [&](auto stream) {
+        constexpr bool STREAM = decltype(stream)::value;
+        auto fetch = [&](int g0, Group &p) {
+            int row[DS_UB];
 #pragma unroll
-        for (int k = 0; k < DS_UB; ++k) {
-            float w[8];
-            widen(wv[k], w, (const bf16 *)nullptr);
+            for (int k = 0; k < DS_UB; ++k) {
+                const int q = (g0 + k * DS_WAVES) * RPW + sub;
+                row[k] = DENSE ? lo + min(q, cnt - 1) : lidx[min(q, cnt - 1)];
+                p.in[k] = colok && q < cnt && row[k] >= 0;
+            }
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int k = 0; k < DS_UB; ++k) {
+                const int q = (g0 + k * DS_WAVES) * RPW + sub;
+                p.w[k] = load_raw_hint<STREAM>(colp + (size_t)max(row[k], 0) * d);
+                const uint32_t at = NB < 4 && my_token == OUTSIDE ? OUTSIDE : (uint32_t)((lo + q) * NB) * 4u + my_token;
 #pragma unroll
                 for (int g = 0; g < TG; ++g)
-                    acc[g][e] = __builtin_amdgcn_mfma_f32_4x4x1f32(hv[k][g], w[e], acc[g][e], 0, 0, 0);
+                    p.h[k][g] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(hpart, at, g * 16, 0));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto consume = [&](const Group &p) {
+#pragma unroll
+            for (int k = 0; k < DS_UB; ++k) {
+                float w[8];
+                const uint4 in = make_uint4(p.in[k] ? p.w[k].x : 0u, p.in[k] ? p.w[k].y : 0u, p.in[k] ? p.w[k].z : 0u, p.in[k] ? p.w[k].w : 0u);
+                widen(in, w, (const bf16 *)nullptr);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int g = 0; g < TG; ++g)
+                        acc[g][e] = __builtin_amdgcn_mfma_f32_4x4x1f32(p.h[k][g], w[e], acc[g][e], 0, 0, 0);
+            }
+        };
+        Group pa, pb;
+        constexpr int STEP = DS_WAVES * DS_UB;
+        if (wave < ngroups) fetch(wave, pa);
+        for (int g0 = wave; g0 < ngroups; g0 += 2 * STEP) {
+            fetch(g0 + STEP, pb);                // past the end: the last row again, not counted
+            consume(pa);
+            if (g0 + STEP >= ngroups) break;
+            fetch(g0 + 2 * STEP, pa);
+            consume(pb);
         }
     };
-    {
-        uint4 wa[DS_UB], wb[DS_UB];
-        float ha[DS_UB][TG], hb[DS_UB][TG];
-        constexpr int STEP = DS_WAVES * DS_UB;
-        fetch(wave, wa, ha);
-        for (int g0 = wave; g0 < ngroups; g0 += 2 * STEP) {
-            fetch(g0 + STEP, wb, hb);            // past the end: nothing is requested
-            consume(wa, ha);
-            fetch(g0 + 2 * STEP, wa, ha);
-            consume(wb, hb);
-        }
-    }
+    if (streams(n, d, 2)) work(std::true_type{});
+    else work(std::false_type{});
     // row lanes l and l ^ 8 first (a lane shift), then the four remaining sets of a wave and the waves through
     // LDS, in order
 #pragma unroll

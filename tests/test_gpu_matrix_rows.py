@@ -252,3 +252,21 @@ def test_matrix_engine_under_graph_replay(env):
             for k in outs:
                 assert torch.equal(outs[k], ref[k]), (rnd, k)
             binding.ffn_step(c.dev, c.Xd[:3])                       # eager work between replays
+
+
+@pytest.mark.parametrize("d,n", [(2048, 5208), (2048, 5209), (2056, 5189), (4104, 2600)])
+def test_lists_read_past_the_caches(env, d, n):
+    """Lists on both sides of 64 MB (3 n d values of two bytes), from where rows are requested with another cache hint; whole
+    and partial steps of a row, both engines."""
+    binding, torch, oracle = env
+    D = (n + 127) // 64 * 64
+    c = RandomLayer(binding, torch, d + n, d, D, 16, 8)
+    lst = np.random.default_rng(n).permutation(D)[:n].astype(np.int32)
+    idx = torch.zeros(D, dtype=torch.int32, device="cuda")
+    idx[:n] = torch.from_numpy(lst).cuda()
+    nnz = torch.tensor([n], dtype=torch.int32, device="cuda")
+    for engine, batches in ((binding.FLAG_ENGINE_MATRIX, (8,)), (binding.FLAG_ENGINE_VECTOR, (1, 3))):
+        for B in batches:
+            y = binding.sparse_ffn(c.dev.with_flags(engine), c.Xd[:B], idx, nnz).cpu().numpy()
+            y_ref = oracle.sparse_ffn(c.f["W_gate"], c.f["W_up"], c.f["W_downT"], c.X[:B], lst)
+            parity.check_y(y, y_ref, "bf16", slack=parity.fp32_forward_bound(c.f, c.X[:B], lst))
