@@ -348,11 +348,23 @@ auto with_scores_kernel(const svdp_layer *L, F &&f)
     }
 }
 
+// column blocks of Q that a wave of the matrix score kernel holds: no more requests than there are columns, nearly
+template <typename W, int NB, typename F>
+auto with_matrix_scores_kernel(const svdp_layer *L, F &&f)
+{
+    const int nkb = (L->r + scm_block<W>() - 1) / scm_block<W>();
+    if (nkb <= SCM_KB / 4)
+        return f(std::integral_constant<decltype(&k_scores_mfma<W, NB, SCM_KB / 4>), &k_scores_mfma<W, NB, SCM_KB / 4>>{});
+    if (nkb <= SCM_KB / 2)
+        return f(std::integral_constant<decltype(&k_scores_mfma<W, NB, SCM_KB / 2>), &k_scores_mfma<W, NB, SCM_KB / 2>>{});
+    return f(std::integral_constant<decltype(&k_scores_mfma<W, NB, SCM_KB>), &k_scores_mfma<W, NB, SCM_KB>>{});
+}
+
 template <typename W, int NB>
 bool prepare_scores(const svdp_layer *L)
 {
     const size_t lds = scores_lds<W, NB>(L);
-    if (scores_on_matrix<W, NB>(L)) return grant_lds<k_scores_mfma<W, NB>>(lds);
+    if (scores_on_matrix<W, NB>(L)) return with_matrix_scores_kernel<W, NB>(L, [&](auto k) { return grant_lds<decltype(k)::value>(lds); });
     return with_scores_kernel<W, NB>(L, [&](auto k) { return grant_lds<decltype(k)::value>(lds); });
 }
 
@@ -362,8 +374,11 @@ svdp_status launch_scores(const svdp_layer *L, const float *tpart, int nt, int B
 {
     const size_t lds = scores_lds<W, NB>(L);
     if (scores_on_matrix<W, NB>(L)) {
-        launch((k_scores_mfma<W, NB>), dim3(L->D / SC_SLAB), dim3(SCM_THREADS), lds, st,
-               static_cast<const W *>(L->Q), L->b, tpart, nt, B, L->D, L->r, s_out, mask_out);
+        with_matrix_scores_kernel<W, NB>(L, [&](auto k) {
+            launch(decltype(k)::value, dim3(L->D / SC_SLAB), dim3(SCM_THREADS), lds, st, static_cast<const W *>(L->Q), L->b,
+                   tpart, nt, L->r, B, mask_out, s_out, L->D);
+            return 0;
+        });
         return hip_status(hipSuccess);
     }
     // block size: 512 threads for one or two tokens (short critical path), 256 for larger batches

@@ -389,7 +389,7 @@ __global__ __launch_bounds__(DS_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
 // Predictor stage 2 on the matrix cores: s_i = t . Q[i,:] + b_i for a slab of
 // 64 neurons and up to eight tokens, and the slab's mask word (eq. 2).  One
 // wave per 16 rows of Q; a lane fetches 16 bytes of one row per column block (four lanes: 64
-// contiguous bytes; SCM_KB blocks are requested before t is touched).  t is the sum of the nt
+// contiguous bytes; KB blocks are requested behind the partials of t).  t is the sum of the nt
 // stage-1 partials and lies in LDS in operand order:
 //   fp32: as it is, v_mfma_f32_16x16x4_f32;
 //   bf16: split into three bf16 terms hi + mid + lo = t exactly to 24 bits, so that bf16
@@ -403,14 +403,17 @@ __global__ __launch_bounds__(DS_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
 // six lane exchanges per row and token (and k_tsum before it: 2 to 4.6 us).  Step with three and more tokens, vector kernel
 // -> this one, in us: fp32 d = 464, D = 2176, r = 192, three tokens 22.7 -> 17.7 (scores 10.2 -> 5.1); fp32 d = 1720, D = 8064,
 // r = 464, six tokens 52.4 -> 41.0 (20.7 -> 11.2); bf16 d = 512, D = 2240, r = 24, four tokens 22.0 -> 17.9.
+// All partials of t (up to SCM_NT) are requested at once and in front of Q, as ranges: in groups of four behind Q each group's wait
+// was for Q as well.  KB, the blocks of Q held, is the smallest of three that takes the whole row (a request past the row is not free).
+// Step of 4096 x 14336, r = 256, eight tokens 63.1 -> 62.0 / 60.5 -> 59.7 us (two boxes), of 3584 x 18944, r = 512, four tokens level.
 // Tried on it: two waves per 16 rows with half of the columns each, and sixteen partials requested at once (r = 192: 4.8 ->
 // 5.5; r = 512: 11.5 -> 11.5), the blocks of two slabs in one (the same), column blocks in another order per wave (0.4 slower),
 // the compiler's own unrolling of the partials' loop (eight tokens, r = 256: 6.7 -> 9.2).
 // Dynamic LDS: scm_lds bytes.
 // ---------------------------------------------------------------------------
 constexpr int SCM_THREADS = 256;
-constexpr int SCM_KB = 16;          // column blocks of Q held in registers
-constexpr int SCM_NT = 4;           // partials of t requested together
+constexpr int SCM_KB = 16;          // most column blocks of Q held in registers
+constexpr int SCM_NT = 16;          // partials of t requested together
 
 // a and b as hi + mid + lo each, two bf16 to a word.  Rounded by the packed conversion instead of
 // in integer arithmetic (step of bf16 d = 512, D = 2240, r = 24, four tokens 17.3 -> 16.6 us, d = 1024, D = 4096, r = 256, three
@@ -452,75 +455,72 @@ size_t scm_lds(int NB, int r)
     return scm_terms<W>() * nkb * 4 * NB * 16;
 }
 
-template <typename W, int NB>
-__global__ __launch_bounds__(SCM_THREADS) void k_scores_mfma(const W *__restrict__ Q, const float *__restrict__ bias,
-                                                             const float *__restrict__ tpart, int nt, int B, int D,
-                                                             int r, float *__restrict__ s_out,
-                                                             uint64_t *__restrict__ mask_out)
+template <typename W, int NB, int KB>
+__global__ __launch_bounds__(SCM_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_scores_mfma(
+    const W *__restrict__ Q, const float *__restrict__ bias, const float *__restrict__ tpart, int nt, int r, int B,
+    uint64_t *__restrict__ mask_out, float *__restrict__ s_out, int D)
 {
     static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8, "token slots are addressed with a mask");
     constexpr int VEC = Elem<W>::VEC, CB = scm_block<W>(), TERMS = scm_terms<W>();
     extern __shared__ uint4 smem16[];
     __shared__ uint32_t word16[SCM_THREADS / 64];
     uint4 *ops = smem16;                                            // [TERMS][nkb * 4 column groups][NB]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lm = lane & 15, lq = lane >> 4;
     const int i0 = blockIdx.x * SC_SLAB + wave * 16;
     const int nkb = (r + CB - 1) / CB;
 
-    uint4 q[SCM_KB];
-    const W *qrow = Q + (size_t)(i0 + lm) * r + lq * VEC;
-    const int nfull = r / CB;
-    const bool in_tail = nfull * CB + lq * VEC < r;                 // this lane's columns of the last, partial block exist
+    // partials p0 .. p0 + SCM_NT - 1 of t for slot u = (token b, columns VEC g .. VEC g + VEC - 1); zeros past the last
+    const int ngr = r / VEC, slots = nkb * 4, all = NB * slots;
+    const __amdgpu_buffer_rsrc_t parts = range_of(tpart, (uint32_t)(nt * NB * r) * 4);
+    uint4 v[SCM_NT][VEC / 4];
+    auto request_t = [&](int u, int p0) {
+        const int b = u / slots, g = u - b * slots;
+        const uint32_t at = u < all && g < ngr ? (uint32_t)((p0 * NB + b) * r + g * VEC) * 4u : 1u << 31;      // past the range with all k
+#pragma unroll
+        for (int k = 0; k < SCM_NT; ++k)
+#pragma unroll
+            for (int h = 0; h < VEC / 4; ++h)
+                v[k][h] = load_range(parts, at + (uint32_t)(k * NB * r + 4 * h) * 4u);
+    };
+    request_t(tid, 0);
+
+    uint4 q[KB];
+    const __amdgpu_buffer_rsrc_t qrows = range_of(Q + (size_t)i0 * r, (uint32_t)(16 * r) * sizeof(W));
     auto request_q = [&](int kb0) {
 #pragma unroll
-        for (int k = 0; k < SCM_KB; ++k) {
-            const int kb = kb0 + k;
-            if (kb < nfull) {
-                q[k] = load_raw(qrow + (size_t)kb * CB);
-            } else if (kb < nkb) {
-                q[k] = make_uint4(0u, 0u, 0u, 0u);
-                if (in_tail) q[k] = load_raw(qrow + (size_t)kb * CB);
-            }
+        for (int k = 0; k < KB; ++k) {
+            const int col = (kb0 + k) * CB + lq * VEC;
+            q[k] = load_range(qrows, col < r ? (uint32_t)(lm * r + col) * sizeof(W) : OUTSIDE);
         }
     };
     request_q(0);
     float bs[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) bs[i] = bias[i0 + lq * 4 + i];
+    __builtin_amdgcn_sched_barrier(0);
 
-    // t for (token b, columns VEC g .. VEC g + VEC - 1): sum of the partials in order, then its operands
-    const int ngr = r / VEC, slots = nkb * 4;
-    for (int u = tid; u < NB * slots; u += SCM_THREADS) {
-        const int b = u / slots, g = u % slots;
+    // t of a slot: sum of its partials in order, then its operands
+    auto finish_t = [&](int u) {
+        const int b = u / slots, g = u - b * slots;
         float t[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) t[e] = 0.f;
-        if (g < ngr) {
-            const float4 *tp = reinterpret_cast<const float4 *>(tpart + (size_t)b * r + (size_t)g * VEC);
-            const size_t stride4 = (size_t)NB * r / 4;
-            int p = 0;
-            for (; p + SCM_NT <= nt; p += SCM_NT) {                 // requested together: one trip for SCM_NT partials
-                float4 v[SCM_NT][VEC / 4];
+        auto add = [&] {
 #pragma unroll
-                for (int k = 0; k < SCM_NT; ++k)
-#pragma unroll
-                    for (int h = 0; h < VEC / 4; ++h) v[k][h] = tp[(size_t)(p + k) * stride4 + h];
-#pragma unroll
-                for (int k = 0; k < SCM_NT; ++k)
-#pragma unroll
-                    for (int h = 0; h < VEC / 4; ++h) {
-                        t[4 * h] += v[k][h].x; t[4 * h + 1] += v[k][h].y; t[4 * h + 2] += v[k][h].z; t[4 * h + 3] += v[k][h].w;
-                    }
-            }
-            for (; p < nt; ++p) {
+            for (int k = 0; k < SCM_NT; ++k)
 #pragma unroll
                 for (int h = 0; h < VEC / 4; ++h) {
-                    const float4 v = tp[(size_t)p * stride4 + h];
-                    t[4 * h] += v.x; t[4 * h + 1] += v.y; t[4 * h + 2] += v.z; t[4 * h + 3] += v.w;
+                    const float4 p = as_float4(v[k][h]);
+                    t[4 * h] += p.x; t[4 * h + 1] += p.y; t[4 * h + 2] += p.z; t[4 * h + 3] += p.w;
                 }
-            }
+        };
+        add();                                   // apart from the loop: waits for its own loads only, not for Q
+        for (int p0 = SCM_NT; p0 < nt; p0 += SCM_NT) {
+            request_t(u, p0);
+            add();
         }
+        if (u >= all) return;
         uint4 *op = ops + (size_t)g * NB + b;
         if constexpr (TERMS == 1) {
             *op = make_uint4(__float_as_uint(t[0]), __float_as_uint(t[1]), __float_as_uint(t[2]), __float_as_uint(t[3]));
@@ -539,15 +539,20 @@ __global__ __launch_bounds__(SCM_THREADS) void k_scores_mfma(const W *__restrict
 #pragma unroll
             for (int p = 0; p < 3; ++p) op[(size_t)p * slots * NB] = make_uint4(pl[p][0], pl[p][1], pl[p][2], pl[p][3]);
         }
+    };
+    finish_t(tid);
+    for (int u = tid + SCM_THREADS; u - tid < all; u += SCM_THREADS) {
+        request_t(u, 0);
+        finish_t(u);
     }
     __syncthreads();
 
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
     const uint4 *op0 = ops + (size_t)lq * NB + (lm & (NB - 1));
-    for (int kb0 = 0; kb0 < nkb; kb0 += SCM_KB) {
+    for (int kb0 = 0; kb0 < nkb; kb0 += KB) {
         if (kb0 > 0) request_q(kb0);
 #pragma unroll
-        for (int k = 0; k < SCM_KB; ++k) {
+        for (int k = 0; k < KB; ++k) {
             if (kb0 + k < nkb) {
                 const uint4 *op = op0 + (size_t)(kb0 + k) * 4 * NB;
                 if constexpr (TERMS == 1) {

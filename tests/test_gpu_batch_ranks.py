@@ -182,3 +182,12 @@ def test_lists_with_a_partial_line(d, D):
             assert kept.size > 0 or not y.any()
             same.append(torch.equal(y, binding.sparse_ffn(L.with_flags(drelu | binding.FLAG_ENGINE_VECTOR), x[:B], idx, nnz)))
         assert d < 64 or not all(same)                          # other sums than the vector engine's
+
+
+@pytest.mark.parametrize("d,D,r,B,dt", [(4096, 128, 128, 8, "bf16"), (4104, 64, 136, 5, "bf16"), (264, 64, 256, 8, "bf16"), (8200, 64, 264, 8, "bf16"),
+                                         (4352, 64, 512, 3, "bf16"), (512, 64, 520, 4, "bf16"), (4100, 64, 64, 8, "f32"), (256, 64, 68, 3, "f32"),
+                                         (128, 64, 132, 8, "f32"), (64, 64, 260, 4, "f32")])
+def test_scores_at_the_edges_of_what_a_wave_holds(d, D, r, B, dt):
+    """Ranks on both sides of 4, 8 and 16 column blocks held at once; 1 to 33 partials of t, on both sides of the 16 requested at
+    once; more and fewer slots of t than threads.  The bound of test_scores_of_every_rank."""
+    test_scores_of_every_rank(d, D, r, B, dt)
