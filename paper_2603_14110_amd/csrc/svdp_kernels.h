@@ -487,7 +487,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_compact_scan(const uint64_t *_
 //            The first rows of W_downT are requested before phase A starts.
 // Blocks with an empty chunk write no partial y; block 0 records n and the number of partials for k_reduce_y.
 // The LDS row capacity is a multiple of ROWS_UB.
-// Dynamic LDS: NB*d storage elements (x as stored), NB*max_chunk floats, max_chunk ints.
+// Dynamic LDS: NB*d storage elements (x as stored), NB*max_chunk floats, max_chunk ints, up to all of a compute unit's: no static LDS.
 // ---------------------------------------------------------------------------
 enum RowsMode { ROWS_DENSE = 0, ROWS_LIST = 1, ROWS_MASK = 2 };
 
@@ -696,8 +696,6 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(2,
             }
     }
     // h of the positions past the chunk's end (phase B works in whole groups of UB rows)
-    __shared__ __align__(16) float h_none[UB];
-    if (tid < UB) h_none[tid] = 0.f;
     const int ngroups = (cnt + UB - 1) / UB;
     if (tid < ngroups * UB - cnt) {
 #pragma unroll
@@ -805,8 +803,9 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(2,
                 float h[NB][UB];
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const float4 h4 = *reinterpret_cast<const float4 *>(g < ngroups ? hs + b * max_chunk + g * UB : h_none);
-                    h[b][0] = h4.x; h[b][1] = h4.y; h[b][2] = h4.z; h[b][3] = h4.w;
+                    const float4 h4 = *reinterpret_cast<const float4 *>(hs + b * max_chunk + min(g, ngroups - 1) * UB);
+                    const bool in = g < ngroups;
+                    h[b][0] = in ? h4.x : 0.f; h[b][1] = in ? h4.y : 0.f; h[b][2] = in ? h4.z : 0.f; h[b][3] = in ? h4.w : 0.f;
                 }
 #pragma unroll
                 for (int k = 0; k < UB; ++k) {

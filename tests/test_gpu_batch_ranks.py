@@ -191,3 +191,22 @@ def test_scores_at_the_edges_of_what_a_wave_holds(d, D, r, B, dt):
     """Ranks on both sides of 4, 8 and 16 column blocks held at once; 1 to 33 partials of t, on both sides of the 16 requested at
     once; more and fewer slots of t than threads.  The bound of test_scores_of_every_rank."""
     test_scores_of_every_rank(d, D, r, B, dt)
+
+
+@pytest.mark.parametrize("d,dt", [(10168, "bf16"), (5084, "f32")])
+def test_rows_that_take_a_compute_units_whole_lds(d, dt):
+    """Eight tokens and 32 rows a block: 8 d values and 9 x 32 words are 160 KB to the byte."""
+    import torch
+    from paper_2603_14110_amd import binding
+
+    D, B, n = 8192, 8, 1000
+    L, x = layer(torch, binding, d, D, 16, B, dt, d)
+    assert 8 * d * L.tensors["W_gate"].element_size() + 9 * 4 * (D // 256) == 160 * 1024
+    idx = torch.arange(0, D, device="cuda", dtype=torch.int32)
+    idx[:n] = idx[5::8][:n].clone()
+    y = binding.sparse_ffn(L, x, idx, torch.tensor([n], dtype=torch.int32, device="cuda"))
+    rows = idx[:n].long()
+    Wg, Wu, Wd = (L.tensors[k][rows].double() for k in ("W_gate", "W_up", "W_downT"))
+    ref = ((x.double() @ Wg.T).clamp(min=0) * (x.double() @ Wu.T)) @ Wd
+    # chains of d and of n fp32 additions, as for the scores above
+    assert float((y.double() - ref).abs().max()) <= 2e-5 * float(ref.abs().max())
