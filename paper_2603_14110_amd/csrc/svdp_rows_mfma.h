@@ -14,8 +14,8 @@
 //            128-byte column slice and one of eight parts of the list (see there).
 // Products of bf16 values are exact in fp32 and every sum has a fixed order.
 // Both are bound by the stream (4.4 and 3.5 TB/s with the launches, 5 and more without) and the trips before it: mask and x, the
-// rows; the list's length, its part of the list, the rows.  So every phase's requests stand together and outside of branches, one group of
-// steps is under way while another is multiplied, and lists of 64 MB and more are read past the caches (streams()).  Step of 4096 x
+// rows; the list's length, its part of the list, the rows.  So every phase's requests stand together and outside of branches, one step
+// (one group of rows) is under way while another is multiplied, and lists of 64 MB and more are read past the caches (streams()).  Step of 4096 x
 // 14336, eight tokens (57 % of the rows) 63.2 -> 60.4 us, its first pass 123 -> 95; gate/up alone 29.7 -> 28.0, slices 20.7 -> 17.5.
 // A row's last, partial step (d no multiple of 64) is a step of its own, with zeros past the end on both sides.
 // Requirements checked by the host: NB <= 8.
@@ -32,7 +32,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 constexpr int MF_ROWS = 16;      // list rows per tile
 constexpr int DOWN_RG = 8;       // k_down_slices: parts of the list per column slice (= partial outputs) ...
 constexpr int DOWN_MIN_CHUNK = 64;     // ... and fewest rows of a part
-constexpr int MF_UA = 4;         // 64-element steps fetched together
 // 16-byte vectors from one token's x to the next in LDS: the four vectors that eight tokens' lanes read at once, and the
 // consecutive ones that a wave writes, lie in different banks
 __host__ __device__ constexpr int mf_x_stride(int d) { return (d + 63) / 64 * 8 + 4; }
@@ -109,7 +108,12 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
     };
     const int ntile = (cnt + MF_ROWS - 1) / MF_ROWS;
 
-    // ---- this wave's share of d is the steps [first, last); MF_UA of them are under way while as many are multiplied ----
+    // ---- this wave's share of d is the steps [first, last); one is under way while another is multiplied ----
+    // (Groups of several steps have to take the last group's place for steps that the wave does not have: weights of zero do not
+    // do that, since zero times an infinite x is NaN, and requests for them are not free.  Groups of four -> single steps, eight tokens,
+    // a list, weights from memory / the same layer again and again, us: d = 512, n = 2000 15.0 -> 12.9 / 13.4 -> 10.8 (d = 520), d = 1024, n = 1843
+    // 15.7 -> 13.2 / 14.3 -> 11.8, d = 2560, n = 1920 20.8 -> 17.4 / 19.9 -> 16.6, d = 4096, n = 3072 23.9 -> 23.3 / 23.5 -> 22.9, d = 6144, n =
+    // 4608 46.4 -> 46.9 / 41.5 -> 42.7, n = 11059 90.6 -> 90.0 / 89.5 -> 88.5, d = 8192 level.)
     const int first = wave * nsteps / ROWS_WAVES, end = (wave + 1) * nsteps / ROWS_WAVES, last = min(end, full);
     const int tb = lm & (NB - 1);                                   // token slot read as the x operand
     const uint4 *xt = xs + tb * stride + lq;
@@ -139,59 +143,40 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
         }
         ag = au = f32x4_t{0.f, 0.f, 0.f, 0.f};
     };
-    struct Group {
-        uint4 g0[MF_UA], g1[MF_UA], u0[MF_UA], u1[MF_UA];
+    struct Step {
+        uint4 g0, g1, u0, u1;
     };
     auto work = [&](auto stream) {
         constexpr bool STREAM = decltype(stream)::value;
-        // steps s0 .. s0 + MF_UA - 1 of tile t.  Past the wave's last step that one again, past the last tile the matrices' first
-        // line: nothing is asked for in a branch, after which every load would have to be awaited at once.
-        auto request = [&](int t, int s0, Group &w) {
+        // step s of tile t; past the last tile the matrices' first line: nothing is asked for in a branch, after which every load
+        // would have to be awaited at once
+        auto request = [&](int t, int s, Step &w) {
             const bool beyond = t >= ntile;
-            const size_t row = beyond ? 0 : row_of(t * MF_ROWS + lm);
-            const bf16 *pg = Wg + row * d + lq * 8, *pu = Wu + row * d + lq * 8;
-#pragma unroll
-            for (int k = 0; k < MF_UA; ++k) {
-                const size_t at = beyond ? 0 : (size_t)min(s0 + k, last - 1) * 64;
-                w.g0[k] = load_raw_hint<STREAM>(pg + at);
-                w.g1[k] = load_raw_hint<STREAM>(pg + at + 32);
-                w.u0[k] = load_raw_hint<STREAM>(pu + at);
-                w.u1[k] = load_raw_hint<STREAM>(pu + at + 32);
-            }
+            const size_t row = beyond ? 0 : row_of(t * MF_ROWS + lm), at = row * d + (beyond ? 0 : (size_t)s * 64) + lq * 8;
+            w.g0 = load_raw_hint<STREAM>(Wg + at);
+            w.g1 = load_raw_hint<STREAM>(Wg + at + 32);
+            w.u0 = load_raw_hint<STREAM>(Wu + at);
+            w.u1 = load_raw_hint<STREAM>(Wu + at + 32);
             __builtin_amdgcn_sched_barrier(0);
         };
-        // (no test around a product: the loads of a step left out would still be awaited before the next request)
-        auto consume = [&](int s0, Group &w) {
-            if (s0 + MF_UA > last) {
-#pragma unroll
-                for (int k = 1; k < MF_UA; ++k)
-                    if (s0 + k >= last) w.g0[k] = w.g1[k] = w.u0[k] = w.u1[k] = make_uint4(0u, 0u, 0u, 0u);
-            }
-#pragma unroll
-            for (int k = 0; k < MF_UA; ++k) {
-                const int s = min(s0 + k, last - 1) * 8;
-                const uint4 xa = xt[s], xb = xt[s + 4];
-                ag = mfma_bf16(w.g0[k], xa, ag);
-                au = mfma_bf16(w.u0[k], xa, au);
-                ag = mfma_bf16(w.g1[k], xb, ag);
-                au = mfma_bf16(w.u1[k], xb, au);
-            }
-        };
-        Group wa, wb;
-        int t = 0, s0 = first, tn = 0, sn = first;                   // the group multiplied, the group requested
+        Step wa, wb;
+        int t = 0, s = first, tn = 0, sn = first;                    // the step multiplied, the step requested
         auto advance = [&](int &tt, int &ss) {
-            ss += MF_UA;
-            if (ss >= last) {
+            if (++ss >= last) {
                 ss = first;
                 ++tt;
             }
         };
-        auto turn = [&](Group &now, Group &next) {
+        auto turn = [&](const Step &now, Step &next) {
             advance(tn, sn);
             request(tn, sn, next);
-            consume(s0, now);
-            if (s0 + MF_UA >= last) finish_tile(t);
-            advance(t, s0);
+            const uint4 xa = xt[s * 8], xb = xt[s * 8 + 4];
+            ag = mfma_bf16(now.g0, xa, ag);
+            au = mfma_bf16(now.u0, xa, au);
+            ag = mfma_bf16(now.g1, xb, ag);
+            au = mfma_bf16(now.u1, xb, au);
+            if (s + 1 >= last) finish_tile(t);
+            advance(t, s);
         };
         request(tn, sn, wa);
         while (true) {

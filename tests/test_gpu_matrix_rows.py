@@ -270,3 +270,51 @@ def test_lists_read_past_the_caches(env, d, n):
             y = binding.sparse_ffn(c.dev.with_flags(engine), c.Xd[:B], idx, nnz).cpu().numpy()
             y_ref = oracle.sparse_ffn(c.f["W_gate"], c.f["W_up"], c.f["W_downT"], c.X[:B], lst)
             parity.check_y(y, y_ref, "bf16", slack=parity.fp32_forward_bound(c.f, c.X[:B], lst))
+
+
+def upward_layer(torch, binding, d, D, B, seed, dtype="bf16"):
+    """A layer whose gate, up and down weights are all positive: h and y of an infinite token have its sign."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    T = torch.float32 if dtype == "f32" else torch.bfloat16
+    mk = lambda *s: (torch.randn(*s, device="cuda", generator=g) / d ** 0.5).to(T)
+    up = lambda: mk(D, d).abs().clamp(min=2.0 ** -20)
+    L = binding.DeviceLayer(mk(d, 16), mk(D, 16), torch.ones(D, device="cuda"), up(), up(), up())
+    return L, torch.randn(B, d, device="cuda", generator=g).to(T)
+
+
+def check_not_finite(torch, binding, L, x, flags, places):
+    """Token 1 with an infinite element, token 6 with a NaN one, at each of the places: y of token 1 is infinite, as its sums are; the
+    gate and up products of token 6 are NaN, of which ReLU makes zero (so y is NaN unless the up branch is rectified as well); the other
+    tokens keep their bits."""
+    D, n = L.tensors["W_gate"].shape[0], 300
+    dev = L.with_flags(flags)
+    idx = torch.arange(1, D + 1, device="cuda", dtype=torch.int32) % D
+    nnz = torch.tensor([n], dtype=torch.int32, device="cuda")
+    calls = (lambda z: binding.sparse_ffn(dev, z, idx, nnz), lambda z: binding.dense_ffn(dev, z))
+    plain = [c(x) for c in calls]
+    rest = [b for b in range(x.shape[0]) if b not in (1, 6)]
+    for place in places:
+        z = x.clone()
+        z[1, place], z[6, place] = torch.inf, torch.nan
+        for c, ref in zip(calls, plain):
+            y = c(z)
+            assert torch.equal(y[rest], ref[rest]), place
+            assert (y[1] == torch.inf).all(), place
+            assert (y[6] == 0).all() if flags & binding.FLAG_DRELU else y[6].isnan().all(), place
+        mask = torch.zeros(D // 64, dtype=torch.int64, device="cuda")
+        assert (binding.ffn_step(dev, z, mask=mask)[1] == torch.inf).all() and mask.any(), place
+
+
+# d / 512 steps of 64 elements a wave: 1, 2, 3, 5, 7 and 8; rows that end in a partial step; fewer steps than waves
+@pytest.mark.parametrize("d", [512, 1024, 1536, 2560, 3584, 4096, 2824, 520, 448, 72])
+@pytest.mark.parametrize("drelu", [False, True])
+def test_tokens_that_are_not_finite(d, drelu):
+    """The last element of each wave's share of a row, and the row's first and last ones."""
+    import torch
+    from paper_2603_14110_amd import binding
+
+    L, x = upward_layer(torch, binding, d, 640, 8, d)
+    ends = [64 * ((w + 1) * ((d + 63) // 64) // 8) for w in range(8)]
+    check_not_finite(torch, binding, L, x, binding.FLAG_ENGINE_MATRIX | (binding.FLAG_DRELU if drelu else 0),
+                     sorted({min(e, d) - 1 for e in ends if e} | {0, d - 9, d - 1}))
