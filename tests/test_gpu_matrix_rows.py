@@ -273,37 +273,36 @@ def test_lists_read_past_the_caches(env, d, n):
 
 
 def upward_layer(torch, binding, d, D, B, seed, dtype="bf16"):
-    """A layer whose gate, up and down weights are all positive: h and y of an infinite token have its sign."""
+    """A layer whose weights are all positive: scores, h and y of an infinite token have its sign."""
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
     T = torch.float32 if dtype == "f32" else torch.bfloat16
     mk = lambda *s: (torch.randn(*s, device="cuda", generator=g) / d ** 0.5).to(T)
-    up = lambda: mk(D, d).abs().clamp(min=2.0 ** -20)
-    L = binding.DeviceLayer(mk(d, 16), mk(D, 16), torch.ones(D, device="cuda"), up(), up(), up())
+    up = lambda *s: mk(*s).abs().clamp(min=2.0 ** -20)
+    L = binding.DeviceLayer(up(d, 16), up(D, 16), torch.ones(D, device="cuda"), up(D, d), up(D, d), up(D, d))
     return L, torch.randn(B, d, device="cuda", generator=g).to(T)
 
 
 def check_not_finite(torch, binding, L, x, flags, places):
-    """Token 1 with an infinite element, token 6 with a NaN one, at each of the places: y of token 1 is infinite, as its sums are; the
-    gate and up products of token 6 are NaN, of which ReLU makes zero (so y is NaN unless the up branch is rectified as well); the other
-    tokens keep their bits."""
-    D, n = L.tensors["W_gate"].shape[0], 300
+    """The first token with an infinite element, the last one of several with a NaN one, at each of the places: y of the first is
+    infinite, as its sums are; the gate and up products of the last are NaN, of which ReLU makes zero (so y is NaN unless the up branch is
+    rectified as well); the other tokens keep their bits."""
+    D, n, B = L.tensors["W_gate"].shape[0], 300, x.shape[0]
     dev = L.with_flags(flags)
     idx = torch.arange(1, D + 1, device="cuda", dtype=torch.int32) % D
     nnz = torch.tensor([n], dtype=torch.int32, device="cuda")
     calls = (lambda z: binding.sparse_ffn(dev, z, idx, nnz), lambda z: binding.dense_ffn(dev, z))
     plain = [c(x) for c in calls]
-    rest = [b for b in range(x.shape[0]) if b not in (1, 6)]
     for place in places:
         z = x.clone()
-        z[1, place], z[6, place] = torch.inf, torch.nan
+        z[B - 1, place], z[0, place] = torch.nan, torch.inf
         for c, ref in zip(calls, plain):
             y = c(z)
-            assert torch.equal(y[rest], ref[rest]), place
-            assert (y[1] == torch.inf).all(), place
-            assert (y[6] == 0).all() if flags & binding.FLAG_DRELU else y[6].isnan().all(), place
+            assert torch.equal(y[1:B - 1], ref[1:B - 1]), place
+            assert (y[0] == torch.inf).all(), place
+            assert B == 1 or ((y[B - 1] == 0).all() if flags & binding.FLAG_DRELU else y[B - 1].isnan().all()), place
         mask = torch.zeros(D // 64, dtype=torch.int64, device="cuda")
-        assert (binding.ffn_step(dev, z, mask=mask)[1] == torch.inf).all() and mask.any(), place
+        assert (binding.ffn_step(dev, z, mask=mask)[0] == torch.inf).all() and mask.any(), place
 
 
 # d / 512 steps of 64 elements a wave: 1, 2, 3, 5, 7 and 8; rows that end in a partial step; fewer steps than waves
@@ -318,3 +317,18 @@ def test_tokens_that_are_not_finite(d, drelu):
     ends = [64 * ((w + 1) * ((d + 63) // 64) // 8) for w in range(8)]
     check_not_finite(torch, binding, L, x, binding.FLAG_ENGINE_MATRIX | (binding.FLAG_DRELU if drelu else 0),
                      sorted({min(e, d) - 1 for e in ends if e} | {0, d - 9, d - 1}))
+
+
+# 16-byte vectors of a row: fewer than a wave's lanes, a few more, half of what a wave asks for at once and a few more, all of that and a
+# few more
+@pytest.mark.parametrize("vectors", [9, 64, 65, 255, 256, 257, 320, 448, 513, 1100])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B", [1, 2, 4, 8])
+def test_tokens_that_are_not_finite_on_the_vector_units(vectors, dtype, B):
+    import torch
+    from paper_2603_14110_amd import binding
+
+    d = vectors * (8 if dtype == "bf16" else 4)
+    L, x = upward_layer(torch, binding, d, 640, B, d, dtype)
+    for flags in (0, binding.FLAG_DRELU, binding.FLAG_REVALIDATE):
+        check_not_finite(torch, binding, L, x, binding.FLAG_ENGINE_VECTOR | flags, (0, d // 2, d - 1))
