@@ -609,12 +609,19 @@ __device__ __forceinline__ void rows_block_list(int D, const void *__restrict__ 
     __syncthreads();
 }
 
-// Whether the rows of a list are read past the caches: lists of 64 MB and more, which twice the L2s would not hold.  Rows alone, read
-// as usual -> past them, in us, weights from memory / the same layer again and again: d = 4096, one token, 37 MB 12.8 -> 13.7 /
-// 11.8 -> 11.7, 74 MB 19.4 -> 18.8 / 17.3 -> 17.0, 147 MB 31.9 -> 29.0 / 26.5 -> 27.0, 246 MB 47.8 -> 42.7 / 40.1 -> 41.2, 352 MB 64.0 ->
-// 58.0 / 63.2 -> 55.7; d = 2824, two tokens, 51 MB 18.2 -> 18.8 / 16.0 -> 17.1.  What they leave in the caches is the predictor: a whole
-// step of 3584 x 18944, four tokens, 33 % of the rows 51.6 -> 44.9.
-__device__ __forceinline__ bool streams(int n, int d, int bytes) { return (float)n * (float)(3 * d * bytes) >= 64e6f; }
+// Whether the rows of a list are read past the caches.  One or two tokens: lists of 64 MB and more, which twice the L2s would not hold;
+// more: of 256 MB, which the memory-side cache would not.  k_rows, read as usual -> past the caches, in us, weights from memory / the same layer
+// again and again: d = 2560, one token, 80 MB 19.7 -> 18.6 / 17.0 -> 16.5, 144 MB 29.9 -> 27.1 / 25.4 -> 25.6, 240 MB 46.5 -> 41.4 / 38.1 -> 39.8,
+// 352 MB 63.7 -> 56.6 / 59.0 -> 55.8; four tokens, d = 4096, 80 MB 25.8 -> 26.4 / 23.3 -> 26.1, 144 MB 35.4 -> 34.3 / 30.5 -> 34.2, 240 MB 51.6 ->
+// 47.5 / 44.4 -> 46.9, 288 MB 60.1 -> 54.8 / 52.2 -> 54.6, 352 MB 70.5 -> 64.0 / 67.4 -> 64.1 (from 64 MB on, four tokens would be slower again
+// and again than with loads in branches).
+// k_down_slices' part, eight tokens: d = 4096, 240 MB 56.4 -> 55.1 / 49.9 -> 51.5, 288 MB 64.0 -> 62.3 / 57.4 -> 58.7, 352 MB 75.8 -> 73.7 / 73.1 -> 69.4; d =
+// 8192, 500 MB 120 -> 106 both ways.  k_gate_up_mfma always reads as usual: it fetches a line in two halves (d = 3584, 172 MB 43.4 ->
+// 45.2 / 39.5 -> 44.2, 352 MB 74.6 -> 78.9 / 67.1 -> 78.3).  k_rows_seq as well: not measured otherwise.
+__device__ __forceinline__ bool streams(int tokens, int n, int d, int bytes)
+{
+    return (float)n * (float)(3 * d * bytes) >= (tokens <= 2 ? 64e6f : 256e6f);
+}
 
 // x [B][d] as stored into xraw [NB][nvec] (zeros beyond B), in two halves: the first XV vectors of a thread are
 // requested behind whatever the caller asked for before and stored once that has been used; rows longer than that follow in a loop.
@@ -846,7 +853,7 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(2,
             }
         }
     };
-    if (streams(n, d, (int)sizeof(W))) work(std::true_type{});
+    if (streams(NB, n, d, (int)sizeof(W))) work(std::true_type{});
     else work(std::false_type{});
     store_list();
 }

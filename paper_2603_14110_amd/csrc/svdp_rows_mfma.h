@@ -15,7 +15,7 @@
 // Products of bf16 values are exact in fp32 and every sum has a fixed order.
 // Both are bound by the stream (4.4 and 3.5 TB/s with the launches, 5 and more without) and the trips before it: mask and x, the
 // rows; the list's length, its part of the list, the rows.  So every phase's requests stand together and outside of branches, one step
-// (one group of rows) is under way while another is multiplied, and lists of 64 MB and more are read past the caches (streams()).  Step of 4096 x
+// (one group of rows) is under way while another is multiplied.  Step of 4096 x
 // 14336, eight tokens (57 % of the rows) 63.2 -> 60.4 us, its first pass 123 -> 95; gate/up alone 29.7 -> 28.0, slices 20.7 -> 17.5.
 // A row's last, partial step (d no multiple of 64) is a step of its own, with zeros past the end on both sides.
 // Requirements checked by the host: NB <= 8.
@@ -146,17 +146,18 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
     struct Step {
         uint4 g0, g1, u0, u1;
     };
-    auto work = [&](auto stream) {
-        constexpr bool STREAM = decltype(stream)::value;
+    if (first >= last) {
+        for (int t = 0; t < ntile; ++t) finish_tile(t);
+    } else {
         // step s of tile t; past the last tile the matrices' first line: nothing is asked for in a branch, after which every load
         // would have to be awaited at once
         auto request = [&](int t, int s, Step &w) {
             const bool beyond = t >= ntile;
             const size_t row = beyond ? 0 : row_of(t * MF_ROWS + lm), at = row * d + (beyond ? 0 : (size_t)s * 64) + lq * 8;
-            w.g0 = load_raw_hint<STREAM>(Wg + at);
-            w.g1 = load_raw_hint<STREAM>(Wg + at + 32);
-            w.u0 = load_raw_hint<STREAM>(Wu + at);
-            w.u1 = load_raw_hint<STREAM>(Wu + at + 32);
+            w.g0 = load_raw(Wg + at);
+            w.g1 = load_raw(Wg + at + 32);
+            w.u0 = load_raw(Wu + at);
+            w.u1 = load_raw(Wu + at + 32);
             __builtin_amdgcn_sched_barrier(0);
         };
         Step wa, wb;
@@ -185,13 +186,6 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
             turn(wb, wa);
             if (t >= ntile) break;
         }
-    };
-    if (first >= last) {
-        for (int t = 0; t < ntile; ++t) finish_tile(t);
-    } else if (streams(n, d, 2)) {
-        work(std::true_type{});
-    } else {
-        work(std::false_type{});
     }
     __syncthreads();
     // partial tiles of the waves, added in wave order -> h[list position][token]
@@ -342,7 +336,7 @@ __global__ __launch_bounds__(DS_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
             consume(pb);
         }
     };
-    if (streams(n, d, 2)) work(std::true_type{});
+    if (streams(8, n, d, 2)) work(std::true_type{});            // whatever NB: on the engine's own choice it is 8
     else work(std::false_type{});
     // row lanes l and l ^ 8 first (a lane shift), then the four remaining sets of a wave and the waves through
     // LDS, in order

@@ -210,3 +210,24 @@ def test_rows_that_take_a_compute_units_whole_lds(d, dt):
     ref = ((x.double() @ Wg.T).clamp(min=0) * (x.double() @ Wu.T)) @ Wd
     # chains of d and of n fp32 additions, as for the scores above
     assert float((y.double() - ref).abs().max()) <= 2e-5 * float(ref.abs().max())
+
+
+# 3 n d values on both sides of 64 MB (one and two tokens) and of 256 MB (more of them), where rows are requested with another cache hint
+@pytest.mark.parametrize("d,dt,B,n", [(2048, "f32", 1, 2604), (2048, "f32", 2, 2605), (2052, "f32", 1, 2600), (2048, "f32", 3, 10416), (2048, "f32", 8, 10417),
+                                       (4096, "bf16", 3, 10417), (4096, "bf16", 8, 10416), (4096, "bf16", 8, 10417), (4104, "bf16", 5, 10400)])
+def test_long_lists(d, dt, B, n):
+    import torch
+    from paper_2603_14110_amd import binding
+
+    es = 4 if dt == "f32" else 2
+    limit = 64e6 if B <= 2 else 256e6
+    assert abs(3 * n * d * es - limit) <= 0.002 * limit
+    L, x = layer(torch, binding, d, (n + 127) // 64 * 64, 16, B, dt, n)
+    D = L.tensors["W_gate"].shape[0]
+    idx = torch.randperm(D, device="cuda", generator=torch.Generator(device="cuda").manual_seed(n)).to(torch.int32)
+    y = binding.sparse_ffn(L, x, idx, torch.tensor([n], dtype=torch.int32, device="cuda"))
+    rows = idx[:n].long()
+    Wg, Wu, Wd = (L.tensors[k][rows].double() for k in ("W_gate", "W_up", "W_downT"))
+    ref = ((x.double() @ Wg.T).clamp(min=0) * (x.double() @ Wu.T)) @ Wd
+    # chains of d and of n fp32 additions, as for the scores above
+    assert float((y.double() - ref).abs().max()) <= 2e-5 * float(ref.abs().max())
