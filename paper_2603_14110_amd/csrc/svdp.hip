@@ -152,6 +152,8 @@ inline Engine engine_of(const svdp_layer *L)
                                                 : (L->flags & SVDP_FLAG_ENGINE_MATRIX) ? ENGINE_MATRIX : ENGINE_AUTO;
 }
 
+inline int xp_slabs(int d) { return (d + XP_ROWS - 1) / XP_ROWS; }        // partials of t; <= XP_MAX_BLOCKS since d <= 16384
+
 template <typename W, int NB>
 size_t xp_lds(const svdp_layer *)
 {
@@ -312,7 +314,7 @@ svdp_status launch_xP(const svdp_layer *L, const void *x, int B, float *tpart, i
                       const GlueArgs *glue)
 {
     const int d = L->d, r = L->r;
-    const int nt = (d + XP_ROWS - 1) / XP_ROWS;           // <= XP_MAX_BLOCKS since d <= 16384
+    const int nt = xp_slabs(d);
     const int ncs = (r + XP_COLS - 1) / XP_COLS;
     const size_t lds = xp_lds<W, NB>(L);
     if (glue != nullptr) {
@@ -348,16 +350,27 @@ auto with_scores_kernel(const svdp_layer *L, F &&f)
     }
 }
 
-// column blocks of Q that a wave of the matrix score kernel holds: no more requests than there are columns, nearly
+// The matrix score kernel for a layer: column blocks of Q that a wave holds and partials of t that a thread requests together, both
+// nearly as many as there are, since a request for what is not there is not free.
 template <typename W, int NB, typename F>
 auto with_matrix_scores_kernel(const svdp_layer *L, F &&f)
 {
-    const int nkb = (L->r + scm_block<W>() - 1) / scm_block<W>();
-    if (nkb <= SCM_KB / 4)
-        return f(std::integral_constant<decltype(&k_scores_mfma<W, NB, SCM_KB / 4>), &k_scores_mfma<W, NB, SCM_KB / 4>>{});
-    if (nkb <= SCM_KB / 2)
-        return f(std::integral_constant<decltype(&k_scores_mfma<W, NB, SCM_KB / 2>), &k_scores_mfma<W, NB, SCM_KB / 2>>{});
-    return f(std::integral_constant<decltype(&k_scores_mfma<W, NB, SCM_KB>), &k_scores_mfma<W, NB, SCM_KB>>{});
+    const int nkb = (L->r + scm_block<W>() - 1) / scm_block<W>(), nt = xp_slabs(L->d);
+    auto of = [&](auto kb, auto parts) {
+        constexpr auto k = &k_scores_mfma<W, NB, decltype(kb)::value, decltype(parts)::value>;
+        return f(std::integral_constant<decltype(k), k>{});
+    };
+    auto with_parts = [&](auto kb) {
+        if constexpr (NB >= 4) {               // one and two tokens come here only on the caller's wish
+            if (nt <= SCM_NT / 4) return of(kb, std::integral_constant<int, SCM_NT / 4>{});
+            if ((nt - 1) % SCM_NT < SCM_NT / 2) return of(kb, std::integral_constant<int, SCM_NT / 2>{});
+        }
+        return of(kb, std::integral_constant<int, SCM_NT>{});
+    };
+    if (nkb <= SCM_KB / 4) return with_parts(std::integral_constant<int, SCM_KB / 4>{});
+    if (nkb <= SCM_KB / 2) return with_parts(std::integral_constant<int, SCM_KB / 2>{});
+    if (nkb <= SCM_KB * 3 / 4) return with_parts(std::integral_constant<int, SCM_KB * 3 / 4>{});
+    return with_parts(std::integral_constant<int, SCM_KB>{});
 }
 
 template <typename W, int NB>
@@ -462,7 +475,7 @@ bool tsum_needed(const svdp_layer *L)
 template <typename W>
 bool predict_small(const svdp_layer *L)
 {
-    const int tiles = ((L->d + XP_ROWS - 1) / XP_ROWS) * ((L->r + XP_COLS - 1) / XP_COLS);
+    const int tiles = xp_slabs(L->d) * ((L->r + XP_COLS - 1) / XP_COLS);
     return tiles <= PS_TILES && !scores_on_matrix<W, 1>(L);
 }
 

@@ -382,17 +382,19 @@ __global__ __launch_bounds__(DS_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
 // six lane exchanges per row and token (and k_tsum before it: 2 to 4.6 us).  Step with three and more tokens, vector kernel
 // -> this one, in us: fp32 d = 464, D = 2176, r = 192, three tokens 22.7 -> 17.7 (scores 10.2 -> 5.1); fp32 d = 1720, D = 8064,
 // r = 464, six tokens 52.4 -> 41.0 (20.7 -> 11.2); bf16 d = 512, D = 2240, r = 24, four tokens 22.0 -> 17.9.
-// All partials of t (up to SCM_NT) are requested at once and in front of Q, as ranges: in groups of four behind Q each group's wait
-// was for Q as well.  KB, the blocks of Q held, is the smallest of three that takes the whole row (a request past the row is not free).
+// Partials of t are requested NT at a time and in front of Q, as ranges: in groups of four behind Q each group's wait was for Q as well.
+// A request past the last partial or the row's end is not free, so NT (4, 8, 16) and KB (4, 8, 12, 16) follow what there is.  t = x P and scores,
+// NT = 16 and KB = 4, 8, 16 -> this, us: 256 x 1024, r = 32, four tokens 5.8 -> 5.0, 1024 x 4096, r = 256, eight tokens 7.8 -> 6.9, 2048 x 8192, r =
+// 384, eight tokens 10.2 -> 9.1, 5120 x 13824, r = 320, eight tokens (20 partials, three times eight instead of twice sixteen) 12.4 -> 11.3.
 // Step of 4096 x 14336, r = 256, eight tokens 63.1 -> 62.0 / 60.5 -> 59.7 us (two boxes), of 3584 x 18944, r = 512, four tokens level.
-// Tried on it: two waves per 16 rows with half of the columns each, and sixteen partials requested at once (r = 192: 4.8 ->
-// 5.5; r = 512: 11.5 -> 11.5), the blocks of two slabs in one (the same), column blocks in another order per wave (0.4 slower),
+// Tried on it: two waves per 16 rows with half of the columns each, the blocks of two slabs in one (the same), column blocks in another
+// order per wave (0.4 slower),
 // the compiler's own unrolling of the partials' loop (eight tokens, r = 256: 6.7 -> 9.2).
 // Dynamic LDS: scm_lds bytes.
 // ---------------------------------------------------------------------------
 constexpr int SCM_THREADS = 256;
 constexpr int SCM_KB = 16;          // most column blocks of Q held in registers
-constexpr int SCM_NT = 16;          // partials of t requested together
+constexpr int SCM_NT = 16;          // most partials of t requested together
 
 // a and b as hi + mid + lo each, two bf16 to a word.  Rounded by the packed conversion instead of
 // in integer arithmetic (step of bf16 d = 512, D = 2240, r = 24, four tokens 17.3 -> 16.6 us, d = 1024, D = 4096, r = 256, three
@@ -434,7 +436,7 @@ size_t scm_lds(int NB, int r)
     return scm_terms<W>() * nkb * 4 * NB * 16;
 }
 
-template <typename W, int NB, int KB>
+template <typename W, int NB, int KB, int NT>
 __global__ __launch_bounds__(SCM_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_scores_mfma(
     const W *__restrict__ Q, const float *__restrict__ bias, const float *__restrict__ tpart, int nt, int r, int B,
     uint64_t *__restrict__ mask_out, float *__restrict__ s_out, int D)
@@ -449,15 +451,15 @@ __global__ __launch_bounds__(SCM_THREADS) __attribute__((amdgpu_waves_per_eu(2))
     const int i0 = blockIdx.x * SC_SLAB + wave * 16;
     const int nkb = (r + CB - 1) / CB;
 
-    // partials p0 .. p0 + SCM_NT - 1 of t for slot u = (token b, columns VEC g .. VEC g + VEC - 1); zeros past the last
+    // partials p0 .. p0 + NT - 1 of t for slot u = (token b, columns VEC g .. VEC g + VEC - 1); zeros past the last
     const int ngr = r / VEC, slots = nkb * 4, all = NB * slots;
     const __amdgpu_buffer_rsrc_t parts = range_of(tpart, (uint32_t)(nt * NB * r) * 4);
-    uint4 v[SCM_NT][VEC / 4];
+    uint4 v[NT][VEC / 4];
     auto request_t = [&](int u, int p0) {
         const int b = u / slots, g = u - b * slots;
         const uint32_t at = u < all && g < ngr ? (uint32_t)((p0 * NB + b) * r + g * VEC) * 4u : 1u << 31;      // past the range with all k
 #pragma unroll
-        for (int k = 0; k < SCM_NT; ++k)
+        for (int k = 0; k < NT; ++k)
 #pragma unroll
             for (int h = 0; h < VEC / 4; ++h)
                 v[k][h] = load_range(parts, at + (uint32_t)(k * NB * r + 4 * h) * 4u);
@@ -487,7 +489,7 @@ __global__ __launch_bounds__(SCM_THREADS) __attribute__((amdgpu_waves_per_eu(2))
         for (int e = 0; e < VEC; ++e) t[e] = 0.f;
         auto add = [&] {
 #pragma unroll
-            for (int k = 0; k < SCM_NT; ++k)
+            for (int k = 0; k < NT; ++k)
 #pragma unroll
                 for (int h = 0; h < VEC / 4; ++h) {
                     const float4 p = as_float4(v[k][h]);
@@ -495,7 +497,7 @@ __global__ __launch_bounds__(SCM_THREADS) __attribute__((amdgpu_waves_per_eu(2))
                 }
         };
         add();                                   // apart from the loop: waits for its own loads only, not for Q
-        for (int p0 = SCM_NT; p0 < nt; p0 += SCM_NT) {
+        for (int p0 = NT; p0 < nt; p0 += NT) {
             request_t(u, p0);
             add();
         }

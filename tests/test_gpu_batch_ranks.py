@@ -186,10 +186,12 @@ def test_lists_with_a_partial_line(d, D):
 
 @pytest.mark.parametrize("d,D,r,B,dt", [(4096, 128, 128, 8, "bf16"), (4104, 64, 136, 5, "bf16"), (264, 64, 256, 8, "bf16"), (8200, 64, 264, 8, "bf16"),
                                          (4352, 64, 512, 3, "bf16"), (512, 64, 520, 4, "bf16"), (4100, 64, 64, 8, "f32"), (256, 64, 68, 3, "f32"),
-                                         (128, 64, 132, 8, "f32"), (64, 64, 260, 4, "f32")])
+                                         (128, 64, 132, 8, "f32"), (64, 64, 260, 4, "f32"),
+                                         (1024, 64, 384, 8, "bf16"), (1032, 64, 392, 4, "bf16"), (2048, 64, 192, 5, "f32"), (2052, 64, 196, 8, "f32"),
+                                         (6144, 64, 96, 8, "bf16"), (6152, 64, 352, 3, "bf16"), (16384, 64, 128, 4, "bf16")])
 def test_scores_at_the_edges_of_what_a_wave_holds(d, D, r, B, dt):
-    """Ranks on both sides of 4, 8 and 16 column blocks held at once; 1 to 33 partials of t, on both sides of the 16 requested at
-    once; more and fewer slots of t than threads.  The bound of test_scores_of_every_rank."""
+    """Ranks on both sides of 4, 8, 12 and 16 column blocks held at once; 1 to 64 partials of t, on both sides of the 4, 8 and 16
+    requested at once; more and fewer slots of t than threads.  The bound of test_scores_of_every_rank."""
     test_scores_of_every_rank(d, D, r, B, dt)
 
 
@@ -210,6 +212,13 @@ def test_rows_that_take_a_compute_units_whole_lds(d, dt):
     ref = ((x.double() @ Wg.T).clamp(min=0) * (x.double() @ Wu.T)) @ Wd
     # chains of d and of n fp32 additions, as for the scores above
     assert float((y.double() - ref).abs().max()) <= 2e-5 * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("d,D,r,B,dt", [(5120, 128, 512, 1, "bf16"), (4096, 128, 512, 2, "bf16"), (4104, 64, 520, 2, "bf16"), (5124, 64, 512, 1, "f32"),
+                                         (16384, 64, 1024, 2, "bf16"), (2048, 64, 2048, 1, "f32")])
+def test_scores_with_partials_left_for_a_loop(d, D, r, B, dt):
+    """One and two tokens, more partials of t than the threads of a column request at the start; more columns than threads."""
+    test_scores_of_every_rank(d, D, r, B, dt)
 
 
 # 3 n d values on both sides of 64 MB (one and two tokens) and of 256 MB (more of them), where rows are requested with another cache hint
