@@ -6,14 +6,14 @@
 //   phase G: one wave per listed row: g = W_gate[i].x for every token; only if
 //            some token has g > 0 (a wave-uniform test) the row of W_up is
 //            fetched and h = ReLU(g)*u formed; other rows end here;
-//   then     wave 0 compacts the surviving rows of the chunk (ballot + popcount),
-//            and their h and indices are packed;
+//   then     the surviving rows of the chunk are counted and compacted (ballot +
+//            popcount), and their h and indices are packed;
 //   phase B: as in k_rows, over the survivors only, so rows of W_downT whose
 //            gate was <= 0 for every token are never read.
 // Dropped terms are exact zeros, so y has the values of the parallel pipeline.
 // Bytes read per listed row: d*w for the gate, 2*d*w more only if it survives.
 // Dynamic LDS: NB*d storage elements (x) + 2*NB*max_chunk floats (h, packed h)
-// + 3*max_chunk ints (list, flags / packed rows, survivor positions).
+// + 3*max_chunk ints (list, flags / packed rows, survivor positions), up to all of a compute unit's: no static LDS.
 #pragma once
 
 #include "svdp_kernels.h"
@@ -33,7 +33,6 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     constexpr int UG = NB <= 2 ? 8 : 4;     // 16-byte loads of one matrix in flight per lane in phase G
     constexpr int UB = 4;                   // rows of W_downT per group in phase B
     extern __shared__ uint4 smem16[];
-    __shared__ int ns_shared;
     const int nvec = d / VEC;
     uint4 *xraw = smem16;                                        // [NB][nvec] x in storage form
     float *hs = reinterpret_cast<float *>(xraw + NB * nvec);     // [NB][max_chunk] by list position
@@ -153,20 +152,17 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     }
     __syncthreads();
 
-    // ---- survivors of the chunk, in list order ----
-    if (wave == 0) {
-        int run = 0;
-        for (int base = 0; base < cnt; base += 64) {
-            const int q = base + lane;
-            const bool on = q < cnt && srow[q] != 0;
-            const uint64_t bal = __ballot(on);
-            if (on) spos[run + __popcll(bal & ((1ull << lane) - 1ull))] = q;
-            run += __popcll(bal);
-        }
-        if (lane == 0) ns_shared = run;
+    // ---- survivors of the chunk, in list order: every wave counts them (no word of LDS for the number: the dynamic part may fill all
+    // of a compute unit's), the first one notes their positions ----
+    int ns = 0;
+    for (int base = 0; base < cnt; base += 64) {
+        const int q = base + lane;
+        const bool on = q < cnt && srow[q] != 0;
+        const uint64_t bal = __ballot(on);
+        if (on && wave == 0) spos[ns + __popcll(bal & ((1ull << lane) - 1ull))] = q;
+        ns += __popcll(bal);
     }
     __syncthreads();
-    const int ns = ns_shared;
     const int ngroups = (ns + UB - 1) / UB;
     const int padded = ngroups * UB;
     // pack h and rows of the survivors; the last group is padded with repeats of the last row and h = 0

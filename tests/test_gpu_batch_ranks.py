@@ -214,6 +214,32 @@ def test_rows_that_take_a_compute_units_whole_lds(d, dt):
     assert float((y.double() - ref).abs().max()) <= 2e-5 * float(ref.abs().max())
 
 
+# B d values, and B + 1 words a row of a block's share (sequential: 2 B + 3), are 160 KB to the byte
+@pytest.mark.parametrize("flag,B,d,D,dt", [("", 8, 10168, 8192, "bf16"), ("", 3, 10220, 4096, "f32"), ("sequential", 8, 10088, 8192, "bf16"),
+                                             ("sequential", 8, 5044, 8192, "f32"), ("sequential", 3, 10196, 4096, "f32")])
+def test_whole_lds_and_every_row(flag, B, d, D, dt):
+    import torch
+    from paper_2603_14110_amd import binding
+
+    nb, es = 8 if B > 4 else 4, 4 if dt == "f32" else 2
+    assert nb * d * es + (2 * nb + 3 if flag else nb + 1) * (D // 256) * 4 == 160 * 1024
+    L, x = layer(torch, binding, d, D, 16, B, dt, d)
+    dev = L.with_flags(binding.FLAG_REVALIDATE if flag else binding.FLAG_ENGINE_VECTOR)
+    t = L.tensors
+    g, u = x.double() @ t["W_gate"].double().T, x.double() @ t["W_up"].double().T
+    h = g.clamp(min=0) * u
+    idx = torch.arange(D, device="cuda", dtype=torch.int32)
+    y = binding.sparse_ffn(dev, x, idx, torch.tensor([D], dtype=torch.int32, device="cuda"))
+    mask = torch.zeros(D // 64, dtype=torch.int64, device="cuda")
+    kept, nnz = torch.zeros(D, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    y2 = binding.ffn_step(dev, x, mask=mask, idx=kept, nnz=nnz)
+    rows = kept[:int(nnz)].long()
+    assert 0 < rows.numel() < D
+    for out, ref in ((y, h @ t["W_downT"].double()), (y2, h[:, rows] @ t["W_downT"][rows].double()), (binding.dense_ffn(dev, x), h @ t["W_downT"].double())):
+        # chains of d and of D fp32 additions, as for the scores above
+        assert float((out.double() - ref).abs().max()) <= 2e-5 * float(ref.abs().max())
+
+
 @pytest.mark.parametrize("d,D,r,B,dt", [(5120, 128, 512, 1, "bf16"), (4096, 128, 512, 2, "bf16"), (4104, 64, 520, 2, "bf16"), (5124, 64, 512, 1, "f32"),
                                          (16384, 64, 1024, 2, "bf16"), (2048, 64, 2048, 1, "f32")])
 def test_scores_with_partials_left_for_a_loop(d, D, r, B, dt):
