@@ -30,7 +30,6 @@ using namespace svdp;
 constexpr int XP_MAX_BLOCKS = 128;    // stage-1 row slabs of P (d <= 16384)
 constexpr size_t ALIGN = 256;
 constexpr size_t LDS_DEFAULT = 64 * 1024;     // dynamic LDS a kernel may use without asking
-constexpr size_t LDS_MAX = 160 * 1024;        // LDS of one gfx950 compute unit
 constexpr int MAX_DEVICES = 64;
 
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
@@ -241,7 +240,7 @@ RowsPlan plan_rows(const svdp_layer *L)
             p.kind = ROWS_MATRIX;
             p.min_chunk = MF_ROWS;
             p.max_chunk = rows_max_chunk(D, MF_ROWS, MF_ROWS);
-            p.lds = (size_t)NB * mf_x_stride(d) * 16 + ((size_t)ROWS_WAVES * p.max_chunk * 2 * NB + p.max_chunk) * 4;
+            p.lds = mf_lds(d, D, NB);
             p.split = true;
             if (p.lds <= LDS_MAX && split_fits(d, D, NB)) return p;
             p.split = false;

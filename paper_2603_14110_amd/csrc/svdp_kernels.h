@@ -11,6 +11,7 @@
 
 namespace svdp {
 
+constexpr size_t LDS_MAX = 160 * 1024;    // bytes of LDS of one gfx950 compute unit
 constexpr int XP_THREADS = 256;      // k_xP block
 constexpr int XP_ROWS = 256;         // rows of P per k_xP block
 constexpr int XP_COLS = 32;          // columns of P per k_xP block

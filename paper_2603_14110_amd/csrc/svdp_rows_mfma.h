@@ -19,7 +19,7 @@
 // 14336, eight tokens (57 % of the rows) 63.2 -> 60.4 us, its first pass 123 -> 95; gate/up alone 29.7 -> 28.0, slices 20.7 -> 17.5.
 // A row's last, partial step (d no multiple of 64) is a step of its own, with zeros past the end on both sides.
 // Requirements checked by the host: NB <= 8.
-// Dynamic LDS of k_gate_up_mfma: NB * mf_x_stride(d) * 16 bytes (x) + ROWS_WAVES*max_chunk*2*NB floats (partial tiles) +
+// Dynamic LDS of k_gate_up_mfma: NB * mf_x_stride * 16 bytes (x) + ROWS_WAVES*max_chunk*2*NB floats (partial tiles) +
 // max_chunk ints (list); max_chunk % 16 == 0.
 #pragma once
 
@@ -32,9 +32,20 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 constexpr int MF_ROWS = 16;      // list rows per tile
 constexpr int DOWN_RG = 8;       // k_down_slices: parts of the list per column slice (= partial outputs) ...
 constexpr int DOWN_MIN_CHUNK = 64;     // ... and fewest rows of a part
-// 16-byte vectors from one token's x to the next in LDS: the four vectors that eight tokens' lanes read at once, and the
-// consecutive ones that a wave writes, lie in different banks
-__host__ __device__ constexpr int mf_x_stride(int d) { return (d + 63) / 64 * 8 + 4; }
+// LDS of k_gate_up_mfma behind x: partial tiles and the list.
+__host__ __device__ constexpr size_t mf_rest_bytes(int D, int NB)
+{
+    return (size_t)(ROWS_WAVES * 2 * NB + 1) * rows_max_chunk(D, MF_ROWS, MF_ROWS) * 4;
+}
+// 16-byte vectors from one token's x to the next in LDS: with four more than there are, the four vectors that eight tokens' lanes read at
+// once, and the consecutive ones that a wave writes, lie in different banks.  Without them where the layer leaves no room (four tokens,
+// d > 16256, D > 28672).
+__host__ __device__ constexpr int mf_x_stride(int d, int D, int NB)
+{
+    const int vectors = (d + 63) / 64 * 8;
+    return NB * (vectors + 4) * 16 + mf_rest_bytes(D, NB) <= LDS_MAX ? vectors + 4 : vectors;
+}
+__host__ __device__ constexpr size_t mf_lds(int d, int D, int NB) { return (size_t)(NB * mf_x_stride(d, D, NB) * 16) + mf_rest_bytes(D, NB); }
 
 __device__ __forceinline__ f32x4_t mfma_bf16(const uint4 &a, const uint4 &b, f32x4_t c)
 {
@@ -54,7 +65,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gate_up_mfma(
     static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8, "token slots are addressed with a mask");
     extern __shared__ uint4 smem16[];
     const int full = d / 64, nsteps = (d + 63) / 64;               // 64-element steps per row: whole ones, all
-    const int stride = mf_x_stride(d);
+    const int stride = mf_x_stride(d, D, NB);
     uint4 *xs = smem16;                                            // [NB][stride]
     float *part = reinterpret_cast<float *>(xs + NB * stride);     // [ROWS_WAVES][tiles][2][16][NB]
     int *lidx = reinterpret_cast<int *>(part + (size_t)ROWS_WAVES * max_chunk * 2 * NB);

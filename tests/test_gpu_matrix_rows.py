@@ -272,6 +272,28 @@ def test_lists_read_past_the_caches(env, d, n):
             parity.check_y(y, y_ref, "bf16", slack=parity.fp32_forward_bound(c.f, c.X[:B], lst))
 
 
+@pytest.mark.parametrize("d,D", [(16256, 28736), (16264, 28736), (16320, 28672)])
+def test_matrix_rows_that_leave_no_room_between_tokens(d, D):
+    """Four tokens' x beside 128 rows a block: on both sides of where the gaps between the tokens no longer fit, the matrix engine takes
+    the layer (other sums than the vector engine's) and is right."""
+    import torch
+    from paper_2603_14110_amd import binding
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    mk = lambda *s: (torch.randn(*s, device="cuda", generator=g, dtype=torch.bfloat16) / d ** 0.5)
+    L = binding.DeviceLayer(mk(d, 8), mk(D, 8), torch.zeros(D, device="cuda"), mk(D, d), mk(D, d), mk(D, d))
+    x = torch.randn(3, d, device="cuda", generator=g).to(torch.bfloat16)
+    idx, n = torch.randperm(D, device="cuda", generator=g).to(torch.int32), 700
+    nnz = torch.tensor([n], dtype=torch.int32, device="cuda")
+    y = binding.sparse_ffn(L.with_flags(binding.FLAG_ENGINE_MATRIX), x, idx, nnz)
+    assert not torch.equal(y, binding.sparse_ffn(L.with_flags(binding.FLAG_ENGINE_VECTOR), x, idx, nnz))
+    Wg, Wu, Wd = (L.tensors[k][idx[:n].long()].double() for k in ("W_gate", "W_up", "W_downT"))
+    ref = ((x.double() @ Wg.T).clamp(min=0) * (x.double() @ Wu.T)) @ Wd
+    # chains of d and of n fp32 additions: |error| <= (d + n) 2^-24 sum |terms|; far inside the bound used for such lists elsewhere
+    assert float((y.double() - ref).abs().max()) <= 2e-5 * float(ref.abs().max())
+
+
 def upward_layer(torch, binding, d, D, B, seed, dtype="bf16"):
     """A layer whose weights are all positive: scores, h and y of an infinite token have its sign."""
     g = torch.Generator(device="cuda")
