@@ -8,8 +8,8 @@ import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "csrc", "svdp.hip")
-# every file the translation unit includes: the library is rebuilt when any of them is newer
-DEPS = [SRC, os.path.join(os.path.dirname(HERE), "include", "svdp.h")] + sorted(glob.glob(os.path.join(HERE, "csrc", "*.h")))
+# every file the translation unit includes, and this one with the compiler's options: the library is rebuilt when any of them is newer
+DEPS = [os.path.abspath(__file__), SRC, os.path.join(os.path.dirname(HERE), "include", "svdp.h")] + sorted(glob.glob(os.path.join(HERE, "csrc", "*.h")))
 LIB = os.path.join(HERE, "libsvdp.so")
 # a matrix product that the device refused must not go unnoticed ([[nodiscard]])
 WARNINGS = ["-Wall", "-Wno-unused-function", "-Werror=unused-result"]
@@ -19,6 +19,7 @@ WARNINGS = ["-Wall", "-Wno-unused-function", "-Werror=unused-result"]
 PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 PROBE_SRC = os.path.join(HERE, "csrc", "svdp_probe.hip")
 PROBE_LIB = os.path.join(HERE, "libsvdp_probe.so")
+PROBE_DEPS = [os.path.abspath(__file__), PROBE_SRC, os.path.join(os.path.dirname(HERE), "include", "svdp_probe.h")]
 
 
 def hipcc_path() -> str:
@@ -43,8 +44,7 @@ def build_lib(force: bool = True, verbose: bool = False) -> str:
 
 def build_probe(force: bool = True, verbose: bool = False) -> str:
     """Compile the benchmark's measurement helpers (include/svdp_probe.h)."""
-    deps = [PROBE_SRC, os.path.join(os.path.dirname(HERE), "include", "svdp_probe.h")]
-    if not force and os.path.exists(PROBE_LIB) and all(os.path.getmtime(PROBE_LIB) >= os.path.getmtime(p) for p in deps):
+    if not force and os.path.exists(PROBE_LIB) and all(os.path.getmtime(PROBE_LIB) >= os.path.getmtime(p) for p in PROBE_DEPS):
         return PROBE_LIB
     _hipcc(PROBE_SRC, PROBE_LIB, verbose)
     return PROBE_LIB

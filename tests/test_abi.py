@@ -57,6 +57,25 @@ def test_probe_library_exports_what_its_header_declares():
     assert L.svdp_probe_chase(None, 4, 4, 0x1000, None) == 1
 
 
+@pytest.mark.parametrize("which", ["lib", "probe"])
+def test_a_library_older_than_its_compile_line_is_built_again(which, monkeypatch):
+    """Not only the sources: build.py holds the compiler's options."""
+    from paper_2603_14110_amd import build
+
+    own, lib = os.path.abspath(build.__file__), build.LIB if which == "lib" else build.PROBE_LIB
+    make = build.build_lib if which == "lib" else build.build_probe
+    times, built = {}, []
+    monkeypatch.setattr(build.os.path, "exists", lambda p: True)
+    monkeypatch.setattr(build.os.path, "getmtime", lambda p: times.get(p, 1.0))
+    monkeypatch.setattr(build, "_hipcc", lambda src, out, verbose: built.append(out))
+    times.update({lib: 2.0, own: 2.0})
+    make(force=False)
+    assert not built
+    times[own] = 3.0
+    make(force=False)
+    assert built == [lib]
+
+
 def test_bench_sample_is_stratified_and_seeded():
     """The timed subsample of bench.py: fixed for a given K, without repeats, and its mean density follows the
     stream's within half a percentage point from 20 steps up, on a skewed density distribution."""
