@@ -165,7 +165,7 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     __syncthreads();
     const int ngroups = (ns + UB - 1) / UB;
     const int padded = ngroups * UB;
-    // pack h and rows of the survivors; the last group is padded with repeats of the last row and h = 0
+    // pack h and rows of the survivors; the last group is padded with repeats of the last row, which are requested and left out
     for (int j = tid; j < padded; j += ROWS_THREADS) {
         const int q = spos[min(j, ns - 1)];
         srow[j] = lidx[q];
@@ -195,6 +195,7 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
             }
 #pragma unroll
             for (int k = 0; k < UB; ++k) {
+                if (k > 0 && gq * UB + k >= ns) break;           // no h of zero times a weight that may be infinite
                 float w[VEC];
                 widen(cur[k], w, (const W *)nullptr);
 #pragma unroll

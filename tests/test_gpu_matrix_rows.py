@@ -354,3 +354,31 @@ def test_tokens_that_are_not_finite_on_the_vector_units(vectors, dtype, B):
     L, x = upward_layer(torch, binding, d, 640, B, d, dtype)
     for flags in (0, binding.FLAG_DRELU, binding.FLAG_REVALIDATE):
         check_not_finite(torch, binding, L, x, binding.FLAG_ENGINE_VECTOR | flags, (0, d // 2, d - 1))
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 512), ("f32", 1004)])
+def test_weights_that_are_not_finite(dtype, d):
+    """Infinite and NaN weights of the down projection, in the last listed row among others: y is infinite, or NaN, in those columns and
+    nowhere else, whatever the last group of rows lacks."""
+    import torch
+    from paper_2603_14110_amd import binding
+
+    D = 640
+    L, x = upward_layer(torch, binding, d, D, 8, d, dtype)
+    x = x.abs()                                                    # every h is positive
+    t = L.tensors
+    Wd = t["W_downT"].clone()
+    idx = torch.arange(D - 1, -1, -1, device="cuda", dtype=torch.int32)
+    for n in (1, 2, 3, 4, 5, 254, 257, 639):
+        W = Wd.clone()
+        last = int(idx[n - 1])
+        W[last, 3], W[last, d - 1], W[int(idx[0]), 7] = torch.inf, torch.nan, torch.inf
+        layer = binding.DeviceLayer(t["P"], t["Q"], t["b"], t["W_gate"], t["W_up"], W)
+        want = torch.zeros(d, device="cuda")
+        want[3] = want[7] = torch.inf
+        want[d - 1] = torch.nan
+        nnz = torch.tensor([n], dtype=torch.int32, device="cuda")
+        for flags in (binding.FLAG_ENGINE_VECTOR, binding.FLAG_REVALIDATE, binding.FLAG_ENGINE_MATRIX):
+            for B in (1, 2, 4, 8):
+                y = binding.sparse_ffn(layer.with_flags(flags), x[:B], idx, nnz)
+                assert (y.isnan() == want.isnan()).all() and ((y == torch.inf) == (want == torch.inf)).all(), (n, flags, B)
