@@ -610,18 +610,19 @@ __device__ __forceinline__ void rows_block_list(int D, const void *__restrict__ 
     __syncthreads();
 }
 
-// Whether the rows of a list are read past the caches.  One or two tokens: lists of 64 MB and more, which twice the L2s would not hold;
-// more: of 256 MB, which the memory-side cache would not.  k_rows, read as usual -> past the caches, in us, weights from memory / the same layer
-// again and again: d = 2560, one token, 80 MB 19.7 -> 18.6 / 17.0 -> 16.5, 144 MB 29.9 -> 27.1 / 25.4 -> 25.6, 240 MB 46.5 -> 41.4 / 38.1 -> 39.8,
-// 352 MB 63.7 -> 56.6 / 59.0 -> 55.8; four tokens, d = 4096, 80 MB 25.8 -> 26.4 / 23.3 -> 26.1, 144 MB 35.4 -> 34.3 / 30.5 -> 34.2, 240 MB 51.6 ->
-// 47.5 / 44.4 -> 46.9, 288 MB 60.1 -> 54.8 / 52.2 -> 54.6, 352 MB 70.5 -> 64.0 / 67.4 -> 64.1 (from 64 MB on, four tokens would be slower again
-// and again than with loads in branches).
-// k_down_slices' part, eight tokens: d = 4096, 240 MB 56.4 -> 55.1 / 49.9 -> 51.5, 288 MB 64.0 -> 62.3 / 57.4 -> 58.7, 352 MB 75.8 -> 73.7 / 73.1 -> 69.4; d =
-// 8192, 500 MB 120 -> 106 both ways.  k_gate_up_mfma always reads as usual: it fetches a line in two halves (d = 3584, 172 MB 43.4 ->
-// 45.2 / 39.5 -> 44.2, 352 MB 74.6 -> 78.9 / 67.1 -> 78.3).  k_rows_seq as well: not measured otherwise.
+// Whether the rows of a list are read past the caches: from 64 MB on with one or two tokens, from 100 MB on with more.  Gains where the
+// weights come from memory, as in a model of many layers, loses where one layer's are called again and again and fit the memory-side
+// cache.  Read as usual -> past the caches, us, from memory (1.5 GB of listed rows in turn) / the same layer: k_rows, d = 2560, one token,
+// 64 MB 18.2 -> 16.7, 144 MB 30.4 -> 28.0 / 25.4 -> 25.6, 256 MB 48.5 -> 44.0; d = 4096, two tokens, 80 MB 22.1 -> 21.7 / 19.1 -> 19.9, 144 MB 31.5 ->
+// 29.9 / 26.6 -> 28.2; four tokens, 64 MB 23.0 -> 24.1, 80 MB 26.4 -> 26.4 / 23.3 -> 26.1, 112 MB 30.8 -> 30.4 / 27.0 -> 30.4, 144 MB 36.0 -> 34.2 /
+// 30.5 -> 34.2, 256 MB 54.9 -> 50.4, 320 MB 65.8 -> 59.4.  What they leave in the caches is the predictor: whole step, four tokens, 105 MB
+// of 4096 x 14336 38.2 -> 36.1 / 33.7 -> 36.2, 134 MB of 3584 x 18944 48.1 -> 45.8 / 43.0 -> 45.2.
+// k_down_slices, both row kernels of eight tokens: d = 4096, 48 MB 22.4 -> 22.4, 112 MB 34.6 -> 34.1 / 30.8 -> 31.9, 200 MB 47.7 -> 47.0, 320 MB 71.7 ->
+// 69.8; d = 2560, 144 MB 43.2 -> 42.7.  k_gate_up_mfma always reads as usual, since it fetches a line in two halves: the same two, past the caches
+// in both, 25.1, 35.3, 49.3 and 73.5.  k_rows_seq as well: not measured otherwise.
 __device__ __forceinline__ bool streams(int tokens, int n, int d, int bytes)
 {
-    return (float)n * (float)(3 * d * bytes) >= (tokens <= 2 ? 64e6f : 256e6f);
+    return (float)n * (float)(3 * d * bytes) >= (tokens <= 2 ? 64e6f : 100e6f);
 }
 
 // x [B][d] as stored into xraw [NB][nvec] (zeros beyond B), in two halves: the first XV vectors of a thread are

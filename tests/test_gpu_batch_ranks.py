@@ -247,15 +247,15 @@ def test_scores_with_partials_left_for_a_loop(d, D, r, B, dt):
     test_scores_of_every_rank(d, D, r, B, dt)
 
 
-# 3 n d values on both sides of 64 MB (one and two tokens) and of 256 MB (more of them), where rows are requested with another cache hint
-@pytest.mark.parametrize("d,dt,B,n", [(2048, "f32", 1, 2604), (2048, "f32", 2, 2605), (2052, "f32", 1, 2600), (2048, "f32", 3, 10416), (2048, "f32", 8, 10417),
-                                       (4096, "bf16", 3, 10417), (4096, "bf16", 8, 10416), (4096, "bf16", 8, 10417), (4104, "bf16", 5, 10400)])
+# 3 n d values on both sides of 64 MB (one and two tokens) and of 100 MB (more of them), where rows are requested with another cache hint
+@pytest.mark.parametrize("d,dt,B,n", [(2048, "f32", 1, 2604), (2048, "f32", 2, 2605), (2052, "f32", 1, 2600), (2048, "f32", 3, 4069), (2048, "f32", 8, 4070),
+                                       (4096, "bf16", 3, 4070), (4096, "bf16", 8, 4069), (4096, "bf16", 8, 4070), (4104, "bf16", 5, 4062)])
 def test_long_lists(d, dt, B, n):
     import torch
     from paper_2603_14110_amd import binding
 
     es = 4 if dt == "f32" else 2
-    limit = 64e6 if B <= 2 else 256e6
+    limit = 64e6 if B <= 2 else 100e6
     assert abs(3 * n * d * es - limit) <= 0.002 * limit
     L, x = layer(torch, binding, d, (n + 127) // 64 * 64, 16, B, dt, n)
     D = L.tensors["W_gate"].shape[0]
