@@ -202,3 +202,28 @@ def test_real_stack_specs_teacher_forced(oracle):
         assert 0.0 < np.mean(dens) < 0.6, (sp.sparsity, dens)
         del dev
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("d,dtype", [(4096, "bf16"), (4104, "bf16"), (5120, "bf16"), (8200, "bf16"), (2048, "f32"), (2052, "f32"), (4100, "f32")])
+def test_glued_rows_longer_than_what_is_requested_first(d, dtype):
+    """512 vectors of a token are requested at the start, the rest in a loop (512 to 1025 here): x_out, mask and y have the bits of
+    svdp_stack_glue and svdp_ffn_step, y_prev and shift at any 4-byte address."""
+    import torch
+    from paper_2603_14110_amd import binding
+
+    D, r = 256, 40
+    T = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(d)
+    mk = lambda *s: (torch.randn(*s, device="cuda", generator=g) / s[-1] ** 0.5).to(T)
+    L = binding.DeviceLayer(mk(d, r), mk(D, r), torch.randn(D, device="cuda", generator=g), mk(D, d), mk(D, d), mk(D, d))
+    for B in (1, 2, 3, 8):
+        xp = torch.randn(B, d, device="cuda", generator=g).to(T)
+        for off in (0, 1):
+            yp = torch.randn(B * d + 1, device="cuda", generator=g)[off:off + B * d].view(B, d)
+            shift = torch.randn(d + 1, device="cuda", generator=g)[off:off + d]
+            x_ref = torch.stack([binding.stack_glue(xp[b], yp[b].clone(), shift.clone()) for b in range(B)])
+            m1, m2 = (torch.zeros(D // 64, dtype=torch.int64, device="cuda") for _ in range(2))
+            y_ref = binding.ffn_step(L.with_flags(binding.FLAG_ENGINE_VECTOR), x_ref, mask=m1)
+            x_out = torch.zeros_like(xp)
+            y = binding.ffn_step_glued(L.with_flags(binding.FLAG_ENGINE_VECTOR), xp, yp, shift, x_out, mask=m2)
+            assert torch.equal(x_out, x_ref) and torch.equal(m1, m2) and torch.equal(y, y_ref) and m1.any(), (B, off)
