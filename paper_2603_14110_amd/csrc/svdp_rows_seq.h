@@ -165,7 +165,7 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     __syncthreads();
     const int ngroups = (ns + UB - 1) / UB;
     const int padded = ngroups * UB;
-    // pack h and rows of the survivors; the last group is padded with repeats of the last row, which are requested and left out
+    // pack h and rows of the survivors; the last group is padded with repeats of the last row and h = 0, their weights cleared below
     for (int j = tid; j < padded; j += ROWS_THREADS) {
         const int q = spos[min(j, ns - 1)];
         srow[j] = lidx[q];
@@ -193,9 +193,13 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(4)
 #pragma unroll
                 for (int k = 0; k < UB; ++k) nxt[k] = load_raw(colp + (size_t)srow[(gq + 1) * UB + k] * d);
             }
+            if (ns - gq * UB < UB) {                             // h of zero times a weight that may be infinite would be NaN
+#pragma unroll
+                for (int k = 1; k < UB; ++k)
+                    if (gq * UB + k >= ns) cur[k] = make_uint4(0u, 0u, 0u, 0u);
+            }
 #pragma unroll
             for (int k = 0; k < UB; ++k) {
-                if (k > 0 && gq * UB + k >= ns) break;           // no h of zero times a weight that may be infinite
                 float w[VEC];
                 widen(cur[k], w, (const W *)nullptr);
 #pragma unroll
