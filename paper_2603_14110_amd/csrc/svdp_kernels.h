@@ -716,8 +716,8 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(2,
     const uint32_t row_bytes = (uint32_t)d * sizeof(W);
     // row i of a matrix; nothing at all where i < 0 (past the end; a rejected entry of the caller's list)
     auto row_range = [&](const W *M, int i) { return range_of(M + (size_t)max(i, 0) * d, i >= 0 ? row_bytes : 0u); };
-    auto work = [&](auto stream) {
-        constexpr bool STREAM = decltype(stream)::value;
+    auto work = [&](auto stream, auto ragged) {
+        constexpr bool STREAM = decltype(stream)::value, RAGGED = decltype(ragged)::value;
         // rows UB g .. UB g + UB - 1 of the chunk, at byte `at` of each; zeros past the end
         auto fetch = [&](int g, uint32_t at, uint4 (&piece)[UB]) {
             static_assert(UB == 4, "one 16-byte read of the list");
@@ -764,23 +764,42 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
         for (int b = 0; b < NB; ++b) ag[b] = au[b] = 0.f;
         for (int q = wave, vb = 0; q < cnt;) {
-            // Lanes past the row's end take no part: their weights of zero would make NaN of an infinite x.  One token: x cleared, for
-            // more: a branch (the step of 7B 15.92 -> 16.00 us, with a branch 16.23; 2560 x 7680, four tokens, 1500 rows 15.23 -> 14.87,
-            // with x cleared 15.76).
+            // Lanes past the row's end take no part: their weights of zero would make NaN of an infinite x.  One and two tokens: halves that
+            // lie in the row as a whole have no test, in the others x is read in front of it (a read behind each test is awaited by
+            // itself).  Against x cleared in every product (one token) or a test around each (two): eight stacked 7B layers 178.5 ->
+            // 177.5 us, list of 1507 rows of 2824 12.09 -> 12.02, dense 5120 x 13824 68.9 -> 69.0.  More tokens: the products are
+            // longer than the reads; the split as above 47.6 -> 48.0 (3584 x 18944, four tokens).
             auto half = [&](int k0) {
+                auto product = [&](int k, int b, const uint4 &xq) {
+                    ag[b] = dot_raw(rg[k], xq, ag[b], (const W *)nullptr);
+                    au[b] = dot_raw(ru[k], xq, au[b], (const W *)nullptr);
+                };
+                const int v0 = vb + k0 * 64 + lane;
+                if (!RAGGED || (NB <= 2 && vb + (k0 + UA / 2) * 64 <= nvec)) {
 #pragma unroll
-                for (int k = k0; k < k0 + UA / 2; ++k) {
-                    const int v = vb + k * 64 + lane;
-                    if (NB == 1 || v < nvec) {
-                        const uint32_t keep = NB > 1 || v < nvec ? ~0u : 0u;
+                    for (int k = 0; k < UA / 2; ++k)
 #pragma unroll
-                        for (int b = 0; b < NB; ++b) {
-                            const uint4 xq = xraw[b * nvec + (NB > 1 ? v : min(v, nvec - 1))];
-                            const uint4 xk = make_uint4(xq.x & keep, xq.y & keep, xq.z & keep, xq.w & keep);
-                            ag[b] = dot_raw(rg[k], xk, ag[b], (const W *)nullptr);
-                            au[b] = dot_raw(ru[k], xk, au[b], (const W *)nullptr);
+                        for (int b = 0; b < NB; ++b) product(k0 + k, b, xraw[b * nvec + v0 + k * 64]);
+                } else if (NB <= 2) {
+                    uint4 xq[UA / 2][NB];
+#pragma unroll
+                    for (int k = 0; k < UA / 2; ++k)
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) xq[k][b] = xraw[b * nvec + min(v0 + k * 64, nvec - 1)];
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int k = 0; k < UA / 2; ++k)
+                        if (v0 + k * 64 < nvec) {
+#pragma unroll
+                            for (int b = 0; b < NB; ++b) product(k0 + k, b, xq[k][b]);
                         }
-                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < UA / 2; ++k)
+                        if (v0 + k * 64 < nvec) {
+#pragma unroll
+                            for (int b = 0; b < NB; ++b) product(k0 + k, b, xraw[b * nvec + v0 + k * 64]);
+                        }
                 }
             };
             half(0);
@@ -855,8 +874,14 @@ __global__ __launch_bounds__(ROWS_THREADS) __attribute__((amdgpu_waves_per_eu(2,
             }
         }
     };
-    if (streams(NB, n, d, (int)sizeof(W))) work(std::true_type{});
-    else work(std::false_type{});
+    auto work_rows = [&](auto stream) {
+        if constexpr (NB <= 2) {
+            if (nvec % (UA / 2 * 64) == 0) return work(stream, std::false_type{});
+        }
+        work(stream, std::true_type{});
+    };
+    if (streams(NB, n, d, (int)sizeof(W))) work_rows(std::true_type{});
+    else work_rows(std::false_type{});
     store_list();
 }
 
