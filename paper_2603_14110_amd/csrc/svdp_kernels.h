@@ -27,10 +27,10 @@ constexpr int SC_PG = 7;             // k_scores: sums of t read together
 constexpr int RED_COLS = 8;          // k_reduce_y: float4 columns per block (one 128-byte line per partial row)
 constexpr int RED_SEGS = 64;         // k_reduce_y: segments of the partial list per block
 
-// Sum over j < d of (x[j] + y[j])^2 by a block of 256 threads in a fixed order (a thread takes the
-// 16-byte vectors t, t + 256, ... of x in ascending order, then the lanes of a wave, then the four
-// waves): the mean square of the stacked benchmark's glue.  Every thread gets the total.
-// part: 4 floats of shared memory.  d is a multiple of the vector length.
+// Sum of a value over a block of 256 threads in a fixed order (the lanes of a wave, then the four waves); every thread gets it.
+// The glue's sum of (x[j] + y[j])^2 ends here, in k_xP and in k_stack_glue.  What the threads bring is the same in both, so that the
+// two give the same bits: a thread takes the 16-byte vectors t, t + 256, ... of x in ascending order, of each vector the elements in
+// ascending order, with one fmaf(v, v, sum) each.  part: 4 floats of shared memory.
 __device__ __forceinline__ float glue_block_total(float ss, float *part)
 {
     const int tid = threadIdx.x;
@@ -51,13 +51,13 @@ __device__ __forceinline__ float glue_block_total(float ss, float *part)
 // Dynamic LDS: NB*XP_ROWS + NSUB*(NB*XP_COLS + 1) + PARTS*NB*XP_COLS floats.
 // ---------------------------------------------------------------------------
 // With GLUE the token is not given but made here: x = RMSNorm(x_prev + y_prev) + shift rounded to
-// the storage type, the stacked benchmark's glue (k_stack_glue forms the mean square with the same
-// function, so the two give the same bits).  Every block forms the norm itself from the d sums of x_prev
+// the storage type, the stacked benchmark's glue (the order of the mean square's sum is k_stack_glue's,
+// see glue_block_total, so the two give the same bits).  Every block forms the norm itself from the d sums of x_prev
 // and y_prev (a few KB from L2) instead of waiting for one more launch; the blocks of the first
 // column tile also write x to x_out for the row kernel.
 // Bound: the trips.  Everything is asked for at the start, in the order of its use, so that the norm and x are there while P (from
 // memory) is on its way; with P asked for first, every wait was for it, and the tile's own x and y came one trip after
-// the sum.  With GLUE 5.05 -> 3.73 us at d = 4096, r = 256; eight stacked 7B layers 177.6 -> 168.0; without GLUE level.
+// the sum.  With GLUE 5.05 -> 3.73 us at d = 4096, r = 256; eight stacked 7B layers 181.7 -> 172.0; without GLUE level.
 template <typename W, int NB, bool GLUE>
 __global__ __launch_bounds__(XP_THREADS) void k_xP(const W *__restrict__ P, const W *__restrict__ x,
                                                    int B, int d, int r, float *__restrict__ tpart,
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(XP_THREADS) void k_xP(const W *__restrict__ P, cons
     __shared__ float gpart[4];
     float inv[NB];
     if (GLUE) {
-        static_assert(XP_THREADS == 256, "a thread takes the vectors t, t + 256, ... of x, as k_stack_glue does");
+        static_assert(XP_THREADS == 256, "a thread takes the vectors t, t + 256, ... of x, as in k_stack_glue");
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             inv[b] = 0.f;
@@ -619,7 +619,8 @@ __device__ __forceinline__ void rows_block_list(int D, const void *__restrict__ 
 // of 4096 x 14336 38.2 -> 36.1 / 33.7 -> 36.2, 134 MB of 3584 x 18944 48.1 -> 45.8 / 43.0 -> 45.2.
 // k_down_slices, both row kernels of eight tokens: d = 4096, 48 MB 22.4 -> 22.4, 112 MB 34.6 -> 34.1 / 30.8 -> 31.9, 200 MB 47.7 -> 47.0, 320 MB 71.7 ->
 // 69.8; d = 2560, 144 MB 43.2 -> 42.7.  k_gate_up_mfma always reads as usual, since it fetches a line in two halves: the same two, past the caches
-// in both, 25.1, 35.3, 49.3 and 73.5.  k_rows_seq as well: not measured otherwise.
+// in both, 25.1, 35.3, 49.3 and 73.5 (only the first pass after a layer's weights have been written gains from it: step of 4096 x 14336, eight
+// tokens 98 -> 83, later ones 64 -> 69: what is read as usual has to wait for written lines to leave the caches).  k_rows_seq as well: not measured otherwise.
 __device__ __forceinline__ bool streams(int tokens, int n, int d, int bytes)
 {
     return (float)n * (float)(3 * d * bytes) >= (tokens <= 2 ? 64e6f : 100e6f);
@@ -952,8 +953,8 @@ __global__ __launch_bounds__(256) void k_stack_glue(const W *x, const float *__r
     constexpr int KEEP = 4;                            // vectors of x + y a thread keeps in registers
     __shared__ float part[4];
     const int tid = threadIdx.x, nvec = d / VEC;
-    // one trip to memory for x, y and the shift of the thread's first KEEP vectors; the sum of squares
-    // in a thread takes the vectors t, t + 256, ... of x, as k_stack_glue does (the thread's vectors ascending, their elements ascending)
+    // one trip to memory for x, y and the shift of the thread's first KEEP vectors; the sum of squares in the order that
+    // glue_block_total states
     float v[KEEP][VEC], sh[KEEP][VEC];
 #pragma unroll
     for (int k = 0; k < KEEP; ++k) {
