@@ -13,10 +13,11 @@
 //   k_down_slices   y[token][col] = sum over the list of h * W_downT[row][col], by blocks that own a
 //            128-byte column slice and one of eight parts of the list (see there).
 // Products of bf16 values are exact in fp32 and every sum has a fixed order.
-// Both are bound by the stream (4.4 and 3.5 TB/s with the launches, 5 and more without) and the trips before it: mask and x, the
-// rows; the list's length, its part of the list, the rows.  So every phase's requests stand together and outside of branches, one step
-// (one group of rows) is under way while another is multiplied.  Step of 4096 x
-// 14336, eight tokens (57 % of the rows) 63.2 -> 60.4 us, its first pass 123 -> 95; gate/up alone 29.7 -> 28.0, slices 20.7 -> 17.5.
+// Both are bound by the stream and the trips before it: mask and x, the rows; the list's length, its part of the list, the rows.
+// 4096 x 14336, eight tokens, 8077 rows on average, weights from memory, launch included: gate/up 132 MB in 27.6 us (4.8 TB/s), slices
+// 66 MB in 18.1 us (3.7 TB/s).  So every phase's requests stand together and outside of branches, one step (one group of rows) is under
+// way while another is multiplied.  Step of this shape, three layers in turn, with loads in branches in all its kernels -> now: 69.1 ->
+// 62.2 us.
 // A row's last, partial step (d no multiple of 64) is a step of its own, with zeros past the end on both sides.
 // Requirements checked by the host: NB <= 8.
 // Dynamic LDS of k_gate_up_mfma: NB * mf_x_stride * 16 bytes (x) + ROWS_WAVES*max_chunk*2*NB floats (partial tiles) +
