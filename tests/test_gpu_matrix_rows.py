@@ -256,8 +256,9 @@ def test_matrix_engine_under_graph_replay(env):
 
 @pytest.mark.parametrize("d,n", [(2048, 5208), (2048, 5209), (2056, 5189), (4104, 2600)])
 def test_lists_read_past_the_caches(env, d, n):
-    """Lists on both sides of 64 MB (3 n d values of two bytes), from where rows are requested with another cache hint; whole
-    and partial steps of a row, both engines."""
+    """Lists on both sides of 64 MB (3 n d values of two bytes), from where the vector engine requests the rows of one token with another
+    cache hint (three tokens and more, and the matrix engine's column slices: from 100 MB, test_long_lists of test_gpu_batch_ranks.py); whole and
+    partial steps of a row, both engines."""
     binding, torch, oracle = env
     D = (n + 127) // 64 * 64
     c = RandomLayer(binding, torch, d + n, d, D, 16, 8)
